@@ -337,10 +337,10 @@ struct Workspace {
     int next_async = 0;  // slot for the next asynchronous frame
     FrameSlot& fs() { return slot[active]; }
     DevBuf work;            // blend work counters (evaluations, contributions)
-    // JPEG encoder: per-interval bit buffers (all zero between calls),
-    // per-interval bit counts and output lengths, code tables, length
-    DevBuf jpeg_bits, jpeg_seg_bits, jpeg_seg_len, jpeg_huff, jpeg_len;
-    HostPinned jpeg_len_host;
+    // JPEG encoder: per-interval bit buffers, byte counts and output lengths,
+    // the constant tables (uploaded once), the streams' lengths
+    DevBuf jpeg_bits, jpeg_seg_bytes, jpeg_seg_len, jpeg_tables;
+    HostPinned jpeg_len;
     hipEvent_t ev[7] = {};  // stage boundaries when stage timing is on
     EventTimer ktimer;      // per-launch events when kernel timing is on
     uint32_t rec_cap = 0, dup_cap = 0, tile_cap = 0;
@@ -1510,8 +1510,8 @@ struct JpegJob {
     uint64_t bytes;
 };
 void check_jpeg_args(int width, int height, int quality);
-// Encodes the jobs one after another on `st` with the workspace's scratch
-// buffers, then waits for the stream and fills in the lengths.
+// Encodes the jobs on `st` with the workspace's scratch buffers, then waits
+// for the stream and fills in the lengths.
 void jpeg_encode_jobs(tigas_context* ctx, Workspace& ws, hipStream_t st, JpegJob* jobs, int n);
 
 struct tigas_server {
@@ -1784,16 +1784,8 @@ int64_t submit_locked(tigas_server* sv, const tigas_request* r, double arrival) 
 
 namespace {
 
-// ITU-T T.81 Annex K: quantisation tables (Tables K.1, K.2, row-major) and
-// Huffman tables (K.3 to K.6: code counts per length 1..16, then symbols).
-const uint8_t kQLuma[64] = {16, 11, 10, 16, 24,  40,  51,  61,  12, 12, 14, 19, 26,  58,  60,  55,
-                            14, 13, 16, 24, 40,  57,  69,  56,  14, 17, 22, 29, 51,  87,  80,  62,
-                            18, 22, 37, 56, 68,  109, 103, 77,  24, 35, 55, 64, 81,  104, 113, 92,
-                            49, 64, 78, 87, 103, 121, 120, 101, 72, 92, 95, 98, 112, 100, 103, 99};
-const uint8_t kQChroma[64] = {17, 18, 24, 47, 99, 99, 99, 99, 18, 21, 26, 66, 99, 99, 99, 99,
-                              24, 26, 56, 99, 99, 99, 99, 99, 47, 66, 99, 99, 99, 99, 99, 99,
-                              99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99,
-                              99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99};
+// ITU-T T.81 Annex K: Huffman tables (K.3 to K.6: code counts per length
+// 1..16, then symbols).
 struct HuffSpec {
     uint8_t counts[16];
     uint8_t syms[162];
@@ -1833,13 +1825,6 @@ int huff_count(const HuffSpec& h) {
     return n;
 }
 
-// Quality scaling of a base table: 5000/q below 50, else 200 - 2q percent,
-// rounded, within 1..255 (8-bit tables).
-void scaled_qtable(const uint8_t* base, int quality, uint8_t* out) {
-    const long s = quality < 50 ? 5000 / quality : 200 - 2 * quality;
-    for (int i = 0; i < 64; ++i) out[i] = (uint8_t)std::min(255L, std::max(1L, ((long)base[i] * s + 50) / 100));
-}
-
 // Row-major index of each zig-zag scan position.
 void zigzag_order(int* zz) {
     int i = 0;
@@ -1861,16 +1846,16 @@ void huff_codes(const HuffSpec& h, uint32_t* out) {
     }
 }
 
-// SOI, JFIF APP0, DQT, SOF0 (4:4:4), DHT, DRI (JPEG_SEG_MCUS MCUs), SOS.
-std::vector<uint8_t> jpeg_header(int W, int H, const uint8_t* ql, const uint8_t* qc) {
+// SOI, JFIF APP0, DQT, SOF0 (4:4:4), DHT, DRI (JPEG_SEG_MCUS MCUs), SOS; the
+// quantisation tables and the frame size are filled in per frame by
+// k_jpeg_pack.
+std::vector<uint8_t> jpeg_header() {
     std::vector<uint8_t> h;
     auto b = [&](unsigned v) { h.push_back((uint8_t)v); };
     auto w16 = [&](unsigned v) {
         b(v >> 8);
         b(v & 0xff);
     };
-    int zz[64];
-    zigzag_order(zz);
     w16(0xFFD8);
     w16(0xFFE0);
     w16(16);
@@ -1879,14 +1864,14 @@ std::vector<uint8_t> jpeg_header(int W, int H, const uint8_t* ql, const uint8_t*
     w16(0xFFDB);
     w16(2 + 2 * 65);
     b(0);
-    for (int i = 0; i < 64; ++i) b(ql[zz[i]]);
+    for (int i = 0; i < 64; ++i) b(0);  // at JPEG_HDR_QLUMA
     b(1);
-    for (int i = 0; i < 64; ++i) b(qc[zz[i]]);
+    for (int i = 0; i < 64; ++i) b(0);  // at JPEG_HDR_QCHROMA
     w16(0xFFC0);
     w16(17);
     b(8);
-    w16((unsigned)H);
-    w16((unsigned)W);
+    w16(0);  // height, at JPEG_HDR_SIZE
+    w16(0);  // width
     b(3);
     for (int c = 0; c < 3; ++c) {
         b(c + 1);
@@ -1931,69 +1916,115 @@ void check_jpeg_args(int width, int height, int quality) {
     if (quality < 1 || quality > 100) fail(TIGAS_E_INVALID, "jpeg: quality must be 1..100");
 }
 
+namespace {
+
+// What every frame's encoding reads, in one device buffer: the Huffman codes,
+// the zig-zag order and the header template.
+struct JpegTables {
+    uint32_t huff[4 * 256];
+    uint8_t zigzag[64];
+    uint8_t header[704];
+};
+
+const JpegTables& jpeg_tables(uint32_t* header_len) {
+    static const std::pair<JpegTables, uint32_t> t = [] {
+        JpegTables x{};
+        for (int k = 0; k < 4; ++k) huff_codes(kHuff[k], x.huff + 256 * k);
+        int zz[64];
+        zigzag_order(zz);
+        for (int i = 0; i < 64; ++i) x.zigzag[i] = (uint8_t)zz[i];
+        const std::vector<uint8_t> h = jpeg_header();
+        if (h.size() > sizeof x.header) fail(TIGAS_E_DEVICE, "jpeg: header template exceeds its table");
+        std::copy(h.begin(), h.end(), x.header);
+        return std::make_pair(x, (uint32_t)h.size());
+    }();
+    *header_len = t.second;
+    return t.first;
+}
+
+// M[k][n] = c(k)/2 cos((2n+1) k pi/16), rounded once from FP64.
+const float* jpeg_dct() {
+    static const std::vector<float> m = [] {
+        std::vector<float> d(64);
+        for (int k = 0; k < 8; ++k)
+            for (int i = 0; i < 8; ++i) {
+                const double ck = k == 0 ? std::sqrt(0.5) : 1.0;
+                d[k * 8 + i] = (float)(0.5 * ck * std::cos((2 * i + 1) * k * 3.14159265358979323846 / 16.0));
+            }
+        return d;
+    }();
+    return m.data();
+}
+
+// Intervals a group of jobs may hold besides its first job: bounds the
+// groups' bit buffers (25 KB per interval at worst) to about 100 MB.
+constexpr uint32_t kJpegGroupSegs = 4096;
+
+}  // namespace
+
 void jpeg_encode_jobs(tigas_context* ctx, Workspace& ws, hipStream_t st, JpegJob* jobs, int n) {
     if (n <= 0) return;
     const uint32_t seg_words = (uint32_t)((3 * JPEG_SEG_MCUS * (size_t)kBlockMaxBits + 31) / 32 + 1);
-    int max_seg = 1;
-    for (int i = 0; i < n; ++i) {
-        const int64_t n_mcu = (int64_t)((jobs[i].width + 7) / 8) * ((jobs[i].height + 7) / 8);
-        max_seg = std::max(max_seg, (int)((n_mcu + JPEG_SEG_MCUS - 1) / JPEG_SEG_MCUS));
+    auto job_mcus = [&](const JpegJob& j) {
+        return (uint32_t)((j.width + 7) / 8) * (uint32_t)((j.height + 7) / 8);
+    };
+    auto job_segs = [&](const JpegJob& j) { return (job_mcus(j) + JPEG_SEG_MCUS - 1) / JPEG_SEG_MCUS; };
+    // consecutive jobs share a pair of launches: [first, last) per group
+    std::vector<std::pair<int, int>> groups;
+    uint32_t max_segs = 1;
+    for (int i = 0; i < n;) {
+        int e = i;
+        uint32_t segs = 0;
+        while (e < n && e - i < JPEG_MAX_JOBS && (e == i || segs + job_segs(jobs[e]) <= kJpegGroupSegs))
+            segs += job_segs(jobs[e++]);
+        groups.emplace_back(i, e);
+        max_segs = std::max(max_segs, segs);
+        i = e;
     }
-    if (ws.jpeg_bits.ensure((size_t)max_seg * seg_words * 4)) HIPCHK(hipMemset(ws.jpeg_bits.p, 0, ws.jpeg_bits.bytes));
-    ws.jpeg_seg_bits.ensure((size_t)max_seg * 4);
-    ws.jpeg_seg_len.ensure((size_t)max_seg * 4);
-    ws.jpeg_huff.ensure(4 * 256 * 4);
-    ws.jpeg_len.ensure((size_t)n * 8);
-    ws.jpeg_len_host.ensure((size_t)n * 8);
-    uint32_t codes[4 * 256];
-    for (int t = 0; t < 4; ++t) huff_codes(kHuff[t], codes + 256 * t);
-    HIPCHK(hipMemcpyAsync(ws.jpeg_huff.p, codes, sizeof codes, hipMemcpyHostToDevice, st));
-    float dct[64];
-    for (int k = 0; k < 8; ++k)
-        for (int m = 0; m < 8; ++m) {  // rounded once from FP64
-            const double ck = k == 0 ? std::sqrt(0.5) : 1.0;
-            dct[k * 8 + m] = (float)(0.5 * ck * std::cos((2 * m + 1) * k * 3.14159265358979323846 / 16.0));
+    uint32_t header_len = 0;
+    const JpegTables& tables = jpeg_tables(&header_len);
+    if (ws.jpeg_tables.ensure(sizeof(JpegTables))) {
+        const hipError_t e = hipMemcpy(ws.jpeg_tables.p, &tables, sizeof(JpegTables), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {  // not filled: not kept
+            (void)hipFree(ws.jpeg_tables.p);
+            ws.jpeg_tables.p = nullptr;
+            ws.jpeg_tables.bytes = 0;
+            HIPCHK(e);
         }
+    }
+    ws.jpeg_bits.ensure((size_t)max_segs * seg_words * 4);
+    ws.jpeg_seg_bytes.ensure((size_t)max_segs * 4);
+    ws.jpeg_seg_len.ensure((size_t)max_segs * 4);
+    ws.jpeg_len.ensure((size_t)n * 8, /*coherent=*/true);
     const bool kprof = ctx->profile_kernels.load();
     if (kprof) ws.ktimer.reset();
     TimerScope ts(kprof ? &ws.ktimer : nullptr);
-    std::vector<std::vector<uint8_t>> hdrs(n);  // alive until the stream has finished
-    for (int i = 0; i < n; ++i) {
-        const JpegJob& j = jobs[i];
-        JpegArgs a{};
-        a.rgb = j.rgb;
-        a.width = j.width;
-        a.height = j.height;
-        a.w8 = (j.width + 7) / 8;
-        a.h8 = (j.height + 7) / 8;
-        a.n_mcu = (int64_t)a.w8 * a.h8;
-        a.nseg = (int)((a.n_mcu + JPEG_SEG_MCUS - 1) / JPEG_SEG_MCUS);
-        a.seg_words = seg_words;
-        uint8_t ql[64], qc[64];
-        scaled_qtable(kQLuma, j.quality, ql);
-        scaled_qtable(kQChroma, j.quality, qc);
-        for (int k = 0; k < 64; ++k) {
-            a.rq_luma[k] = 1.0f / (float)ql[k];
-            a.rq_chroma[k] = 1.0f / (float)qc[k];
-            a.dct[k] = dct[k];
+    const JpegTables* dev = ws.jpeg_tables.as<JpegTables>();
+    JpegBatch a{};
+    a.seg_words = seg_words;
+    a.header_len = header_len;
+    std::copy(jpeg_dct(), jpeg_dct() + 64, a.dct);
+    a.huff = dev->huff;
+    a.header = dev->header;
+    a.zigzag = dev->zigzag;
+    a.bits = ws.jpeg_bits.as<uint32_t>();
+    a.seg_bytes = ws.jpeg_seg_bytes.as<uint32_t>();
+    a.seg_len = ws.jpeg_seg_len.as<uint32_t>();
+    for (const auto& g : groups) {  // one after another on the stream: they share the scratch buffers
+        uint32_t segs = 0;
+        a.njobs = g.second - g.first;
+        for (int k = 0; k < a.njobs; ++k) {
+            const JpegJob& j = jobs[g.first + k];
+            a.job[k] = {j.rgb, j.out, j.capacity, ws.jpeg_len.as<uint64_t>() + g.first + k, j.width, j.height,
+                        (j.width + 7) / 8, j.quality, job_mcus(j), job_segs(j), segs};
+            segs += a.job[k].nseg;
         }
-        hdrs[i] = jpeg_header(j.width, j.height, ql, qc);
-        HIPCHK(hipMemcpyAsync(j.out, hdrs[i].data(), std::min(hdrs[i].size(), j.capacity), hipMemcpyHostToDevice, st));
-        a.huff = ws.jpeg_huff.as<uint32_t>();
-        a.bits = ws.jpeg_bits.as<uint32_t>();
-        a.seg_bits = ws.jpeg_seg_bits.as<uint32_t>();
-        a.seg_len = ws.jpeg_seg_len.as<uint32_t>();
-        a.out = j.out;
-        a.capacity = j.capacity;
-        a.header_len = hdrs[i].size();
-        a.out_len = ws.jpeg_len.as<uint64_t>() + i;
-        launch_jpeg(a, st);  // jobs run one after another on the stream and share the scratch buffers
+        launch_jpeg(a, segs, st);
     }
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(ws.jpeg_len_host.p, ws.jpeg_len.p, (size_t)n * 8, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+    wait_stream(st);
     if (kprof) record_kernel_times(ctx, ws);
-    for (int i = 0; i < n; ++i) std::memcpy(&jobs[i].bytes, (const uint8_t*)ws.jpeg_len_host.p + 8 * i, 8);
+    for (int i = 0; i < n; ++i) std::memcpy(&jobs[i].bytes, (const uint8_t*)ws.jpeg_len.p + 8 * i, 8);
 }
 
 // Latency ABR controller state (tigas_abr_*): the throughput samples of the

@@ -188,29 +188,57 @@ void launch_bin(const uint32_t* sorted_rec, const uint32_t* sorted_packed, const
                 uint32_t cap, int tiles_x, int tiles_y, uint32_t* hist, uint32_t* gsum, uint32_t* round_cnt,
                 uint32_t* round_off, uint2* ranges, Counters* host_cnt, const PreOut& o, const ViewParams* views_dev,
                 uint32_t* val_out, uint32_t* tile_out, uint32_t* depth_out, uint32_t* order, hipStream_t st);
-// Baseline JPEG of an RGB8 frame: one workgroup per restart interval of
-// JPEG_SEG_MCUS MCUs; the header is written by the host.
-constexpr int JPEG_THREADS = 128;
-constexpr int JPEG_SEG_MCUS = 40;  // 120 blocks: one thread each
-struct JpegArgs {
+// Baseline JPEGs of RGB8 frames: one workgroup per restart interval of
+// JPEG_SEG_MCUS MCUs, the intervals of up to JPEG_MAX_JOBS frames in one pair
+// of launches.
+constexpr int JPEG_SEG_MCUS = 40;
+constexpr int JPEG_SEG_THREADS = 512;
+constexpr int JPEG_PACK_THREADS = 256;
+constexpr int JPEG_MAX_JOBS = 16;
+// Annex K base tables (Tables K.1, K.2), row-major, and their scaling by
+// quality: 5000/q below 50, else 200 - 2q percent, rounded, within 1..255.
+#define JPEG_QLUMA                                                                                            \
+    {                                                                                                         \
+        16, 11, 10, 16, 24, 40, 51, 61, 12, 12, 14, 19, 26, 58, 60, 55, 14, 13, 16, 24, 40, 57, 69, 56, 14,   \
+            17, 22, 29, 51, 87, 80, 62, 18, 22, 37, 56, 68, 109, 103, 77, 24, 35, 55, 64, 81, 104, 113, 92,   \
+            49, 64, 78, 87, 103, 121, 120, 101, 72, 92, 95, 98, 112, 100, 103, 99                             \
+    }
+#define JPEG_QCHROMA                                                                                          \
+    {                                                                                                         \
+        17, 18, 24, 47, 99, 99, 99, 99, 18, 21, 26, 66, 99, 99, 99, 99, 24, 26, 56, 99, 99, 99, 99, 99, 47,   \
+            66, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99,   \
+            99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99, 99                                        \
+    }
+__host__ __device__ constexpr int jpeg_quant_step(int base, int quality) {
+    const int s = quality < 50 ? 5000 / quality : 200 - 2 * quality;
+    const int q = (base * s + 50) / 100;
+    return q < 1 ? 1 : q > 255 ? 255 : q;
+}
+// Header bytes that differ between frames: the two quantisation tables, then
+// height and width (two bytes each).
+constexpr uint32_t JPEG_HDR_QLUMA = 25, JPEG_HDR_QCHROMA = 90, JPEG_HDR_SIZE = 159;
+struct JpegJobArgs {
     const uint8_t* rgb;  // H x W x 3, row-major
-    int width, height, w8, h8;
-    int64_t n_mcu;  // w8 h8
-    int nseg;       // restart intervals
-    float dct[64];        // M[k][n] = c(k)/2 cos((2n+1) k pi/16), FP32
-    float rq_luma[64];    // 1/Q, row-major
-    float rq_chroma[64];
-    const uint32_t* huff;  // [4][256] length << 16 | code: DC luma, AC luma, DC chroma, AC chroma
-    uint32_t* bits;        // [nseg][seg_words] entropy-coded bits of each interval (all zero between calls)
-    uint32_t seg_words;
-    uint32_t* seg_bits;  // [nseg] bits of each interval
-    uint32_t* seg_len;   // [nseg] output bytes of each interval (stuffing and marker included)
     uint8_t* out;
     uint64_t capacity;
-    uint64_t header_len;
-    uint64_t* out_len;  // total length (written by the last interval)
+    uint64_t* out_len;   // total length (written by the last interval)
+    int width, height, w8, quality;
+    uint32_t n_mcu, nseg;  // 8x8 pixel blocks, restart intervals
+    uint32_t seg_base;     // intervals of the jobs before this one
 };
-void launch_jpeg(const JpegArgs& a, hipStream_t st);
+struct JpegBatch {
+    JpegJobArgs job[JPEG_MAX_JOBS];
+    int njobs;
+    uint32_t seg_words, header_len;
+    float dct[64];          // M[k][n] = c(k)/2 cos((2n+1) k pi/16), FP32
+    const uint32_t* huff;   // [4][256] length << 16 | code: DC luma, AC luma, DC chroma, AC chroma
+    const uint8_t* header;  // header template
+    const uint8_t* zigzag;  // row-major index of each scan position
+    uint32_t* bits;         // [intervals][seg_words] entropy-coded bits, padded with ones
+    uint32_t* seg_bytes;    // [intervals] bytes before stuffing
+    uint32_t* seg_len;      // [intervals] output bytes (stuffing and marker included)
+};
+void launch_jpeg(const JpegBatch& a, uint32_t nseg, hipStream_t st);
 void launch_blend(const ViewParams* views_dev, int nviews, uint32_t n_tiles, const uint2* ranges,
                   const uint32_t* vals, const PreOut& o, uint32_t nrec, int tile_w, int tile_h, int batch_depth,
                   int ppl, unsigned long long* work, uint32_t* queue, int persistent_blocks, bool cull,

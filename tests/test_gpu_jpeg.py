@@ -53,6 +53,69 @@ def test_stream_equals_oracle(ctx, size, q):
     assert got == want
 
 
+@pytest.mark.parametrize("mcus", [39, 40, 41, 79, 81])
+def test_interval_edges(ctx, mcus):
+    # one restart interval is 40 MCUs: the last one short, full, and a single
+    # MCU over, with the last column of pixels inside a block
+    img = _image(7, mcus * 8 - 3, seed=mcus)
+    _say("jpeg interval", mcus)
+    for q in (35, 90):
+        assert ctx.jpeg_bytes(_gpu(img), q) == oj.encode(img, q)
+
+
+@pytest.mark.parametrize("kind", ["noise", "two_level", "sparse", "flat"])
+def test_interval_bit_counts(ctx, kind):
+    # from one code per block to intervals of more bits than one window of
+    # the bit stream holds (65536); single high-frequency values follow runs of
+    # zeros of every length
+    rng = np.random.default_rng(17)
+    H, W = 24, 328
+    if kind == "noise":
+        img = rng.integers(0, 256, (H, W, 3)).astype(np.uint8)
+    elif kind == "two_level":
+        img = (rng.integers(0, 2, (H, W, 3)) * 255).astype(np.uint8)
+    elif kind == "flat":
+        img = np.full((H, W, 3), 77, np.uint8)
+    else:
+        y, x = np.mgrid[0:H, 0:W]
+        u, v = (x // 8) % 8, (x // 64 + y // 8) % 8  # one DCT basis function per block
+        img = 128 + 60 * np.cos((2 * (x % 8) + 1) * u * np.pi / 16) * np.cos((2 * (y % 8) + 1) * v * np.pi / 16)
+        img = np.repeat(np.rint(img)[:, :, None], 3, 2).astype(np.uint8)
+    for q in (10, 90, 100):
+        _say("jpeg bits", kind, q)
+        want = oj.encode(img, q)
+        if kind == "two_level" and q == 100:
+            assert len(want) > 3 * 65536 // 8
+        assert ctx.jpeg_bytes(_gpu(img), q) == want
+
+
+def test_many_payloads_in_one_batch(ctx):
+    # more payloads than one pair of launches takes, of different sizes and
+    # qualities: each is its own frame's stream
+    scene, poses, _, _, _ = synth.c1_single_view()
+    s = ctx.load_scene(scene)
+    k = synth.fov_intrinsics(200, 120)
+    frames, outs, reqs = [], [], []
+    with tigas.Server(ctx, slots=1) as sv:
+        for i in range(37):
+            sc = (0.25, 0.5, 0.75, 1.0)[i % 4]
+            ow, oh = tigas.output_size(200, 120, sc)
+            frames.append(torch.empty((oh, ow, 3), dtype=torch.uint8, device="cuda"))
+            outs.append(torch.zeros(1 << 16, dtype=torch.uint8, device="cuda"))
+            reqs.append(tigas.request_c(s, poses[0], k, 200, 120, frames[i], client=i, res_scale=sc,
+                                        jpeg_quality=10 + 2 * i, jpeg_out=outs[i]))
+        for r in reqs:
+            sv.submit(r)
+        sv.drain()
+        done = {c["id"]: c for c in sv.poll()}
+    assert max(c["batch_size"] for c in done.values()) > 16
+    for i in range(37):
+        want = oj.encode(frames[i].cpu().numpy(), 10 + 2 * i)
+        assert done[i]["status"] == 0 and done[i]["jpeg_bytes"] == len(want)
+        assert bytes(outs[i][:len(want)].cpu().numpy()) == want
+    s.free()
+
+
 def test_wide_frames_and_repeated_calls(ctx):
     # wide frames (intervals wrap across MCU rows), then a smaller frame on the
     # same buffers, then the large one again: the interval bit buffers must
