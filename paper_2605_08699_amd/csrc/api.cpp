@@ -202,6 +202,8 @@ struct Plan {
     std::vector<ViewParams> views;
     std::vector<Group> groups;
     uint32_t nrec = 0, n_tiles = 0;
+    uint32_t seg_len = 0, nseg = 0, nchunks = 0;  // bucketed depth sort (set_buckets)
+    uint64_t row_words = 0;
     TileCfg tc{16, 16, 64, 1};
     bool persistent = false;  // blend as a persistent kernel over a tile work queue
     bool allow_graph = true;  // capture/replay (off for one-off shapes such as serving batches)
@@ -296,8 +298,8 @@ struct FrameMem {
     uint32_t* ext[2] = {nullptr, nullptr};
     uint32_t* hist = nullptr;      // digit counts per sort segment
     uint32_t* hist_tot = nullptr;  // per-digit totals
-    uint32_t* zr = nullptr;        // three-pass depth sort: key range and per-segment ranges
-    uint32_t* segmm = nullptr;     //   (null: the four-pass depth sort only)
+    BucketMem bk{};                // bucketed depth sort
+    bool flag_wide = true;         // flag frames too deep for it (the caller renders them again)
     uint32_t* queue = nullptr;
     uint2* ranges = nullptr;
     uint32_t* order = nullptr;     // the blend's dispatch order of the tiles
@@ -324,7 +326,9 @@ struct Workspace {
     DevBuf counters;
     // per duplicate (also holds the visible Gaussians during the depth passes)
     DevBuf key[2], val[2], ext[2];
-    DevBuf hist, queue, sortrange;
+    DevBuf hist, queue;
+    DevBuf vmask, sample;        // per 64 records
+    DevBuf bkt_rows, bkt_small;  // bucketed depth sort: counts, everything else
     // emission-order copies for the inspection entry point
     DevBuf dbg_key, dbg_val, dbg_ext;
     // per tile / per view
@@ -362,9 +366,7 @@ struct Workspace {
             m.ext[i] = ext[i].as<uint32_t>();
         }
         m.hist = hist.as<uint32_t>();
-        m.hist_tot = m.hist + (size_t)512 * SORT_MAX_BLOCKS;
-        m.zr = sortrange.as<uint32_t>();
-        m.segmm = m.zr + 2;
+        m.hist_tot = m.hist + (size_t)256 * SORT_MAX_BLOCKS;
         m.queue = queue.as<uint32_t>();
         m.ranges = ranges.as<uint2>();
         m.order = reinterpret_cast<uint32_t*>(m.ranges + tile_cap);  // after the ranges, in the same buffer
@@ -390,6 +392,8 @@ struct Workspace {
         o.blk_vis = blk_vis.as<uint32_t>();
         o.blk_fb = blk_fb.as<uint32_t>();
         o.blk_view = blk_view.as<uint32_t>();
+        o.vmask = vmask.as<unsigned long long>();
+        o.sample = sample.as<uint32_t>();
         o.fb_list = fb_list.as<uint2>();
         o.chunk_vis = chunk_vis.as<uint32_t>();
         o.chunk_dup = chunk_dup.as<unsigned long long>();
@@ -412,6 +416,8 @@ struct Workspace {
         const size_t nb = r / K1_THREADS + 1;
         for (DevBuf* b : {&blk_sum, &blk_vis, &blk_fb, &blk_view, &blk_off, &blk_sum2, &blk_off2}) grow(*b, nb * 4);
         grow(fb_list, r * 8);
+        grow(vmask, r / 64 * 8);
+        grow(sample, r / 64 * 4);
         const size_t nch = nb / SCAN_CHUNK + 2;
         for (DevBuf* b : {&chunk_vis, &chunk_fb, &chunk_dups}) grow(*b, nch * 4);
         grow(chunk_dup, nch * 8);
@@ -425,8 +431,7 @@ struct Workspace {
             grow(val[i], (size_t)cap * 4);
             grow(ext[i], (size_t)cap * 4);
         }
-        grow(hist, ((size_t)512 * SORT_MAX_BLOCKS + 512) * 4);  // counts per (digit, segment), then digit totals
-        grow(sortrange, (size_t)(2 + 2 * SORT_MAX_BLOCKS) * 4);
+        grow(hist, ((size_t)256 * SORT_MAX_BLOCKS + 256) * 4);  // counts per (digit, segment), then digit totals
         grow(queue, 8 * 4);                                  // blend band queues
         dup_cap = cap;
     }
@@ -626,13 +631,7 @@ ViewParams make_view(const tigas_scene* sc, const tigas_pose* pose, const tigas_
 size_t frame_bytes(const ViewParams& v) { return (size_t)v.width * v.height * 3 * (v.fmt == 1 ? 4 : 1); }
 
 // Depth digits of the (tile | depth) key: positive FP32 bit patterns, bit 31 clear.
-const SortPass kDepthPasses[4] = {{0, 8, -1}, {8, 8, -1}, {16, 8, -1}, {24, 7, -1}};
-// Three passes of 9-bit digits of the key less the frame's smallest key, for
-// frames whose visible keys span less than 2^27 (depths within about 16
-// octaves); a wider frame is flagged by the first pass's scan, skipped by the
-// later passes and rendered again with kDepthPasses.
-const SortPass kDepthPasses3[3] = {{0, 9, 0}, {9, 9, 1}, {18, 9, 2}};
-
+const SortPass kDepthPasses[4] = {{0, 8}, {8, 8}, {16, 8}, {24, 7}};
 // The fewest passes of at most 8 bits, with the bits spread evenly over them
 // (e.g. 12 bits as 6 + 6): fewer digits per pass give longer runs of equal
 // digits per chunk, so the scatter writes whole cache lines more often.
@@ -643,7 +642,7 @@ std::vector<SortPass> tile_passes(uint32_t n_tiles) {
     int sh = 0;
     for (int i = 0; i < np; ++i) {
         const int b = (tb - sh + (np - i) - 1) / (np - i);
-        p.push_back({sh, b, -1});
+        p.push_back({sh, b});
         sh += b;
     }
     return p;
@@ -671,6 +670,55 @@ void set_tiles(Plan& plan, const TileCfg& tc) {
         v.tile_base = plan.n_tiles;
         plan.n_tiles += (uint32_t)(v.tiles_x * v.tiles_y);
     }
+}
+
+// Lays out the bucketed depth sort of a plan: each view's records in segments
+// of seg_len, a whole number of rounds of a workgroup (about 512 segments
+// over the plan, what the chip holds at once: a workgroup's counts cost a row
+// of the view's buckets however few records it has), and a power of two of
+// buckets, about BUCKET_RECORDS records each.
+void set_buckets(Plan& plan) {
+    plan.seg_len = std::min<uint32_t>(65536, std::max<uint32_t>(4096, round_up((uint64_t)plan.nrec / 500 + 1, 1024)));
+    plan.nseg = plan.nchunks = 0;
+    plan.row_words = 0;
+    for (const Group& g : plan.groups)
+        for (int k = 0; k < g.nviews; ++k) {
+            ViewParams& v = plan.views[g.first_view + k];
+            v.rec_base = g.rec_base + (uint32_t)k * g.n_pad;
+            v.n_pad = g.n_pad;
+            v.seg_base = plan.nseg;
+            v.nseg = (g.n_pad + plan.seg_len - 1) / plan.seg_len;
+            v.bkt_base = plan.nchunks * COL_CHUNK;
+            v.nbkt = g.n_pad ? 1 : 0;
+            while (v.nbkt && v.nbkt < BUCKET_MAX && v.nbkt * 2 <= g.n_pad / BUCKET_RECORDS) v.nbkt *= 2;
+            v.row_base = plan.row_words;
+            plan.nseg += v.nseg;
+            plan.nchunks += (v.nbkt + COL_CHUNK - 1) / COL_CHUNK;
+            plan.row_words += (uint64_t)v.nseg * v.nbkt;
+        }
+}
+
+// Lays the bucketed depth sort's scratch, except the element array, out from
+// `rows` and `small` (null: only the sizes).
+BucketMem carve_buckets(const Plan& plan, void* rows, void* small, size_t* rows_bytes, size_t* small_bytes) {
+    BucketMem b{};
+    b.rows = static_cast<uint32_t*>(rows);
+    *rows_bytes = std::max<size_t>(plan.row_words, 1) * 4;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        char* p = small ? static_cast<char*>(small) + off : nullptr;
+        off += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    const size_t nb = (size_t)plan.nchunks * COL_CHUNK;
+    b.vc = reinterpret_cast<ViewCount*>(take(plan.views.size() * sizeof(ViewCount)));
+    b.start_in = reinterpret_cast<uint32_t*>(take(nb * 4));
+    b.tot = reinterpret_cast<uint32_t*>(take(nb * 4));
+    b.chunk = reinterpret_cast<uint32_t*>(take((size_t)plan.nchunks * 4));
+    b.cdf = reinterpret_cast<uint32_t*>(take(plan.views.size() * BUCKET_CDF_WORDS * 4));
+    b.segmm = reinterpret_cast<uint32_t*>(take((size_t)plan.nseg * 8));
+    *small_bytes = std::max<size_t>(off, 256);
+    return b;
 }
 
 // Everything about a plan that a captured graph depends on, except the view
@@ -710,7 +758,19 @@ void ensure_bin(Workspace& ws, const Plan& plan) {
                           bin_emit_groups(ws.dup_cap, plan.nrec)) * 4);
 }
 
-void prepare(Workspace& ws, const Plan& plan, bool debug) {
+// The plan's frame memory in the workspace's active slot.
+FrameMem frame_mem(Workspace& ws, const Plan& plan) {
+    FrameMem m = ws.mem();
+    size_t rb, sb;
+    m.bk = carve_buckets(plan, ws.bkt_rows.p, ws.bkt_small.p, &rb, &sb);
+    // 16 bytes for each visible record: the duplicate buffers hold at least
+    // four words per record
+    m.bk.elem = ws.key[0].as<uint4>();
+    return m;
+}
+
+void prepare(Workspace& ws, Plan& plan, bool debug) {
+    set_buckets(plan);
     if (ws.counters.ensure(sizeof(Counters))) {
         // the FP64-list count is cleared by each frame after use; start at zero
         HIPCHK(hipMemset(ws.counters.p, 0, sizeof(Counters)));
@@ -724,6 +784,12 @@ void prepare(Workspace& ws, const Plan& plan, bool debug) {
     uint64_t est = std::max<uint64_t>((uint64_t)ws.last_D + ws.last_D / 4, (uint64_t)plan.nrec * 4);
     est = std::max<uint64_t>(est, 1u << 20);
     ws.ensure_dups((uint32_t)std::min<uint64_t>(est, 0xfff00000ull));
+    {
+        size_t rb, sb;
+        (void)carve_buckets(plan, nullptr, nullptr, &rb, &sb);
+        ws.grow(ws.bkt_rows, rb);
+        ws.grow(ws.bkt_small, sb);
+    }
     ensure_bin(ws, plan);
     if (debug) {
         const size_t bytes = (size_t)ws.dup_cap * 4;
@@ -736,14 +802,15 @@ void prepare(Workspace& ws, const Plan& plan, bool debug) {
 // Enqueue the whole launch sequence of a plan on ws.stream (no allocation, no
 // host synchronisation: capturable).  Returns the index of the sort buffer
 // that holds the sorted lists.
-//   preprocess -> scan visible -> compact -> depth passes (visible Gaussians)
-//   -> duplicate in depth order -> tile passes (duplicates) -> ranges -> blend
+//   preprocess -> depth order of the visible Gaussians (buckets; or scan
+//   visible -> compact -> radix passes) -> tile placement (counting; or
+//   duplicate in depth order -> tile passes -> ranges) -> blend
 // Per-context switches that change the launch sequence (not its results).
 struct LaunchOptions {
     bool cull = true;         // blend: per-block threshold culling of list entries
     bool bin = true;          // single view: tile digit placed by counting (else radix passes over the duplicates)
     bool cull_tiles = false;  // duplicates only for tiles the Gaussian can reach (radix passes then)
-    bool depth3 = true;       // three-pass depth sort (when the rectangles pack and the buffers are there)
+    bool buckets = true;      // bucketed depth sort when the rectangles pack (else four radix passes)
 };
 
 // Whether every view's tile rectangles fit the packed one-word form.
@@ -789,8 +856,6 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     zl.n[0] = 8;
     zl.p[1] = reinterpret_cast<uint32_t*>(m.ranges);
     zl.n[1] = 2 * plan.n_tiles;
-    launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
-    mark(2);
     SortBuffers sb;
     for (int i = 0; i < 2; ++i) {
         sb.key[i] = m.key[i];
@@ -799,19 +864,23 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     }
     sb.hist = m.hist;
     sb.dtot = m.hist_tot;
-    sb.zr = m.zr;
-    sb.segmm = m.segmm;
-    // depth digits, on the visible Gaussians (record order in, depth order
-    // out); the tile rectangles travel packed with them when every view has
-    // at most 256 x 256 tiles, else the last pass gathers them.  Three 9-bit
-    // passes when the rectangles pack (a frame whose keys turn out to span
-    // too much is flagged and redone with four), else four 8-bit passes.
+    // depth order of the visible Gaussians (each view's in the bucketed form,
+    // all views' together in the radix one: a tile is one view's, so its list
+    // is the same); the tile rectangles travel packed with them when every
+    // view has at most 256 x 256 tiles, else the last radix pass gathers them
     const bool packed = packed_rects(plan);
-    const bool depth3 = opt.depth3 && packed && m.zr;
-    launch_compact(o, nblk, m.blk_off, sb.key[0], sb.val[0], packed ? sb.ext[0] : nullptr, vdev, st);
-    const int cv = launch_sort(sb, depth3 ? kDepthPasses3 : kDepthPasses, depth3 ? 3 : 4, /*which=*/1, m.dup_cap,
-                               sort_blocks(plan.nrec), 0, packed, cnt, packed ? nullptr : o.rect,
-                               packed ? nullptr : o.srect, st);
+    int cv = 0;
+    if (opt.buckets && packed) {
+        mark(2);
+        launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl, m.flag_wide,
+                           sb.val[0], sb.ext[0], st);
+    } else {
+        launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
+        mark(2);
+        launch_compact(o, nblk, m.blk_off, sb.key[0], sb.val[0], packed ? sb.ext[0] : nullptr, vdev, st);
+        cv = launch_sort(sb, kDepthPasses, 4, /*which=*/1, m.dup_cap, sort_blocks(plan.nrec), 0, packed, cnt,
+                         packed ? nullptr : o.rect, packed ? nullptr : o.srect, st);
+    }
     const int cd = cv ^ 1;
     const bool bin = use_bin(plan, opt);
     if (!bin && opt.cull_tiles && packed) {
@@ -883,17 +952,17 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
     opt.cull = ctx->blend_cull.load();
     opt.bin = ctx->tile_bin.load();
     opt.cull_tiles = ctx->tile_cull.load();
-    opt.depth3 = !ctx->depth4.load();
+    opt.buckets = !ctx->depth4.load();
     const bool kprof = ctx->profile_kernels.load();
     const bool graph = ctx->use_graphs.load() && plan.allow_graph && !debug && !work && !prof && !kprof;
     if (kprof) {
         ws.ktimer.reset();
         TimerScope ts(&ws.ktimer);
-        return enqueue(ws.mem(), plan, debug, prof, work, pblocks, opt);
+        return enqueue(frame_mem(ws, plan), plan, debug, prof, work, pblocks, opt);
     }
-    if (!graph) return enqueue(ws.mem(), plan, debug, prof, work, pblocks, opt);
+    if (!graph) return enqueue(frame_mem(ws, plan), plan, debug, prof, work, pblocks, opt);
     const std::string key = shape_key(plan, true) + (opt.cull ? "c1" : "c0") + (opt.bin ? "b1" : "b0") + (opt.cull_tiles ? "t1" : "t0") +
-                            (opt.depth3 ? "d3" : "d4") + (ws.active ? "f1" : "f0");
+                            (opt.buckets ? "d3" : "d4") + (ws.active ? "f1" : "f0");
     GraphEntry& g = ws.graphs[key];
     if (!g.exec || g.gen != ws.gen) {
         if (g.exec) HIPCHK(hipGraphExecDestroy(g.exec));
@@ -906,7 +975,7 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
         HIPCHK(hipStreamBeginCapture(ws.stream, hipStreamCaptureModeThreadLocal));
         int cur = 0;
         try {
-            cur = enqueue(ws.mem(), plan, debug, prof, work, pblocks, opt);
+            cur = enqueue(frame_mem(ws, plan), plan, debug, prof, work, pblocks, opt);
         } catch (...) {
             (void)hipStreamEndCapture(ws.stream, &graph_t);
             if (graph_t) (void)hipGraphDestroy(graph_t);
@@ -941,14 +1010,14 @@ void wait_stream(hipStream_t st) {
 // duplicates overflowed the buffers (it then emitted nothing) is rendered
 // again (synchronously) with larger buffers; returns the counters of the
 // final attempt.
-Counters settle_frame(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug, bool prof,
+Counters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool debug, bool prof,
                       unsigned long long* work, int& cur, int& rerenders) {
     Counters c;
     std::memcpy(&c, ws.fs().host_counters.p, sizeof(c));
     rerenders = 0;
     if (c.overflow) {
-        // bit 1: the visible depth keys span too much for the three-pass
-        // sort: four passes from now on; bit 0: more duplicates than the
+        // bit 1: the visible depth keys span too much for the bucketed
+        // sort: four radix passes from now on; bit 0: more duplicates than the
         // buffers hold: grow them
         if (c.overflow & 2u) ctx->depth4.store(true);
         if (c.overflow & 1u) {
@@ -1064,7 +1133,7 @@ void finish_all_async(tigas_context* ctx, Workspace& ws) {
 
 // Runs the plan to completion (synchronous) from slot 0, after any
 // asynchronous frames of the workspace.
-int run_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug, unsigned long long* work = nullptr) {
+int run_plan(tigas_context* ctx, Workspace& ws, Plan& plan, bool debug, unsigned long long* work = nullptr) {
     finish_all_async(ctx, ws);
     ws.active = 0;
     prepare(ws, plan, debug);
@@ -1337,7 +1406,8 @@ struct Carver {
 
 // Lays out a single-view launch sequence of nrec records and n_tiles tiles
 // in the scratch array; the duplicate buffers take what is left.
-FrameMem carve_scratch(void* scratch_dev, uint32_t nrec, uint32_t n_tiles, Counters* cnt_out, hipStream_t st) {
+FrameMem carve_scratch(void* scratch_dev, const Plan& plan, Counters* cnt_out, hipStream_t st) {
+    const uint32_t nrec = plan.nrec, n_tiles = plan.n_tiles;
     Carver c{static_cast<char*>(scratch_dev), (size_t)TIGAS_NOALLOC_SCRATCH_BYTES};
     FrameMem m;
     m.stream = st;
@@ -1373,9 +1443,21 @@ FrameMem carve_scratch(void* scratch_dev, uint32_t nrec, uint32_t n_tiles, Count
     // the first-round table sized for the largest duplicate capacity below
     m.bin_gsum = c.take<uint32_t>(((size_t)(BIN_GROUPS + 2) * n_tiles + BIN_TILES_MAX / 256 +
                                    ((size_t)nrec + BIN_BLOCK - 1) / BIN_BLOCK + 1 + bin_emit_groups(16u << 20, nrec)) * 4);
-    // sort passes over at most 16M keys use at most 1024 segments
-    m.hist = c.take<uint32_t>((size_t)256 * 1024 * 4);
+    // sort passes over at most 16M keys use at most 1024 segments; the
+    // bucketed sort, which runs instead of them, has its scratch in the same place
+    size_t rows_bytes, small_bytes;
+    (void)carve_buckets(plan, nullptr, nullptr, &rows_bytes, &small_bytes);
+    rows_bytes = (rows_bytes + 255) / 256 * 256;
+    const size_t mask_bytes = ((size_t)nrec / 64 * 8 + 255) / 256 * 256;
+    const size_t bkt_bytes = rows_bytes + small_bytes + mask_bytes + (size_t)nrec / 64 * 4;
+    char* hist = c.take<char>(std::max((size_t)256 * 1024 * 4, bkt_bytes));
+    m.hist = reinterpret_cast<uint32_t*>(hist);
     m.hist_tot = c.take<uint32_t>((size_t)512 * 4);
+    m.bk = carve_buckets(plan, hist, hist + rows_bytes, &rows_bytes, &small_bytes);
+    rows_bytes = (rows_bytes + 255) / 256 * 256;
+    o.vmask = reinterpret_cast<unsigned long long*>(hist + rows_bytes + small_bytes);
+    o.sample = reinterpret_cast<uint32_t*>(hist + rows_bytes + small_bytes + mask_bytes);
+    m.flag_wide = false;  // no second attempt here
     // six duplicate arrays of dup_cap words (keys, values, extra; two each)
     const size_t left = c.cap > c.off + 6 * 256 ? c.cap - c.off - 6 * 256 : 0;
     const uint64_t dup_cap = std::min<uint64_t>(left / 24 / 256 * 256, 16u << 20);
@@ -1383,11 +1465,11 @@ FrameMem carve_scratch(void* scratch_dev, uint32_t nrec, uint32_t n_tiles, Count
         fail(TIGAS_E_INVALID, "scene too large for the allocation-free render: its records and the duplicate "
                               "buffers need more than the " + std::to_string(TIGAS_NOALLOC_SCRATCH_BYTES >> 20) +
                                   " MiB scratch array");
-    for (int i = 0; i < 2; ++i) {
-        m.key[i] = c.take<uint32_t>(dup_cap * 4);
-        m.val[i] = c.take<uint32_t>(dup_cap * 4);
-        m.ext[i] = c.take<uint32_t>(dup_cap * 4);
-    }
+    // (whole multiples of 256 bytes: the first four, contiguous, also hold the
+    // bucketed sort's 16-byte elements)
+    for (uint32_t** p : {&m.key[0], &m.key[1], &m.val[1], &m.ext[1], &m.val[0], &m.ext[0]})
+        *p = c.take<uint32_t>(dup_cap * 4);
+    m.bk.elem = reinterpret_cast<uint4*>(m.key[0]);
     if (c.off > c.cap) fail(TIGAS_E_DEVICE, "scratch layout exceeds the array");
     m.dup_cap = (uint32_t)dup_cap;
     return m;
@@ -1412,9 +1494,10 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     if (!out->data || out->capacity < frame_bytes(v)) fail(TIGAS_E_BUFFER, "output frame buffer too small");
     v.out_ptr = (uint64_t)(uintptr_t)out->data;
     set_tiles(plan, tile_cfg(q));  // as requested, else 16x16 tiles: no autotuner here
+    set_buckets(plan);
     const hipStream_t st = pick_stream(ctx, hip_stream);
     const FrameMem m =
-        carve_scratch(scratch_dev, plan.nrec, plan.n_tiles, reinterpret_cast<Counters*>(counters), st);
+        carve_scratch(scratch_dev, plan, reinterpret_cast<Counters*>(counters), st);
     // the previous call's counters stay in the array: start this frame from zero
     launch_fill_u32(reinterpret_cast<uint32_t*>(m.cnt), sizeof(Counters) / 4, 0u, st);
     LaunchOptions opt;

@@ -18,6 +18,16 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 1;
 constexpr int SCAN_CHUNK = SCAN_THREADS * SCAN_ITEMS;  // counts per workgroup of the chunked scans
 constexpr int MAX_SORT_PASSES = 8;
+// Bucketed depth sort: buckets per view (one per BUCKET_RECORDS records, a
+// power of two), the samples that place their boundaries, the bins of the
+// samples' distribution, and the elements a workgroup sorts at once.
+constexpr int BUCKET_RECORDS = 1024;
+constexpr int BUCKET_MAX = 4096;
+constexpr int BUCKET_SAMPLES = 16384;
+constexpr int BUCKET_BINS = 2048;
+constexpr int BUCKET_CDF_WORDS = BUCKET_BINS + 8;  // cumulative counts, smallest and largest sample, shift, scale
+constexpr int BUCKET_SORT_CAP = 4096;
+constexpr int COL_CHUNK = 32;  // columns per workgroup of a column scan
 // Binned tile digit (single view): Gaussians per histogram block (eight
 // rounds of 256), work per emission workgroup (entries, with each round of
 // 256 Gaussians also counting BIN_ROUND_COST), groups of blocks for the
@@ -61,6 +71,13 @@ struct ViewParams {
     float bg[3];
     uint64_t out_ptr;    // device address of this view's frame
     SceneView scene;     // the scene this view renders
+    // bucketed depth sort: the view's records, its segments of them, its
+    // buckets (numbered from a multiple of COL_CHUNK) and the words of its
+    // (segment x bucket) counts before them
+    uint32_t rec_base, n_pad;
+    uint32_t seg_base, nseg;
+    uint32_t bkt_base, nbkt;
+    uint64_t row_base;
 };
 
 struct Counters {
@@ -95,6 +112,8 @@ struct PreOut {
     uint32_t* blk_vis;  // per block: records that touch a tile
     uint32_t* blk_fb;   // per block: FP64 fallbacks
     uint32_t* blk_view; // per block: view index
+    unsigned long long* vmask;  // per 64 records: which touch a tile
+    uint32_t* sample;           // per 64 records: the depth key of one that does (all ones: none)
     uint32_t* chunk_vis;            // per SCAN_CHUNK block counts: visible records,
     unsigned long long* chunk_dup;  // duplicates,
     uint32_t* chunk_fb;             // FP64 fallbacks,
@@ -109,10 +128,28 @@ struct SortBuffers {
     uint32_t* key[2];
     uint32_t* val[2];
     uint32_t* ext[2];
-    uint32_t* hist;    // [512][segments] digit counts per segment (then each digit's offsets)
-    uint32_t* dtot;    // [512] per-digit totals
-    uint32_t* zr;      // 2 words: smallest and largest visible depth key (three-pass depth sort)
-    uint32_t* segmm;   // [segments][2]: each segment's smallest and largest key
+    uint32_t* hist;    // [256][segments] digit counts per segment (then each digit's offsets)
+    uint32_t* dtot;    // [256] per-digit totals
+};
+
+// Per-view totals of the preprocess.
+struct ViewCount {
+    unsigned long long dups;
+    uint32_t visible, fallbacks;
+    uint32_t start;  // visible records of the views before
+    uint32_t pad;
+};
+
+// Scratch of the bucketed depth sort (all views of a launch sequence).
+struct BucketMem {
+    uint4* elem;         // [visible] (depth key, record, packed rectangle, -) in bucket order
+    uint32_t* rows;      // per view [segments][buckets]: counts, then exclusive prefixes over segments
+    uint32_t* start_in;  // per bucket: records of the buckets before it in its chunk of COL_CHUNK
+    uint32_t* tot;       // per bucket: records
+    uint32_t* chunk;     // per chunk of COL_CHUNK buckets: records
+    uint32_t* cdf;       // per view: BUCKET_CDF_WORDS
+    uint32_t* segmm;     // [segments][2]: smallest and largest key
+    ViewCount* vc;       // per view
 };
 
 // Arrays cleared (as u32 words) by the first kernel after preprocess.
@@ -124,8 +161,7 @@ struct ZeroList {
 
 struct SortPass {
     int shift;
-    int bits;   // <= 8, or 9 for the passes of the three-pass depth sort
-    int adapt;  // -1: a fixed digit of the key; 0..2: pass of the three-pass depth sort
+    int bits;   // <= 8
 };
 
 // ---- launchers (kernels.hip) ----
@@ -159,6 +195,18 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
                              uint32_t* blk_cnt, uint32_t* blk_off, Counters* cnt, const ViewParams* views_dev,
                              int tile_w, int tile_h, uint32_t* tile_out, uint32_t* val_out, uint32_t* depth_out,
                              hipStream_t st);
+// Bucketed depth sort of every view's visible records: val / ext receive the
+// record ids and packed tile rectangles view by view in depth order, equal
+// depths in record order (views of at most 256 x 256 tiles).  The same
+// launches set the frame's counters, clear zl and recompute, in FP64, the
+// conic of every Gaussian preprocess listed as near-singular.  flag_wide: a
+// frame whose depth keys span 2^27 or more sets overflow bit 1 and is left
+// unsorted (the caller renders it again with the four-pass radix sort).
+// seg_len: records per segment; nseg, nchunks: segments and bucket chunks of
+// all views.
+void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
+                        uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
+                        bool flag_wide, uint32_t* val, uint32_t* ext, hipStream_t st);
 // Runs LSD passes over the count selected by `which` (0 duplicates, 1 visible)
 // starting in buffer `start`; returns the buffer index holding the result.
 // With `rect_src`, the last pass also writes rect_src[value] to rect_dst in

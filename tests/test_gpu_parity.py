@@ -157,6 +157,70 @@ def test_frame_just_shallow_enough_keeps_three_passes(ctx):
     gc.check_tiles(dbg, 16, 16)
 
 
+def _depth_scene(kind, n):
+    """n small Gaussians in view whose depths are spread in a way that the
+    buckets of the depth sort meet in different forms."""
+    rng = np.random.default_rng(n)
+    if kind == "spread":
+        z = rng.uniform(1.0, 9.0, n)
+    elif kind == "equal":
+        z = np.full(n, 4.0)
+    elif kind == "two":
+        z = np.where(rng.random(n) < 0.5, 3.0, 5.0)
+    elif kind == "lattice":
+        z = 2.0 + rng.integers(0, 40, n) * 0.125
+    elif kind == "thin":  # a thin slab and one far Gaussian
+        z = 5.0 + rng.normal(0.0, 1e-4, n)
+        z[n // 2] = 900.0
+    else:  # steps: half of them at one depth, the rest spread
+        z = np.where(rng.random(n) < 0.5, 4.0, rng.uniform(1.0, 9.0, n))
+    means = np.column_stack([rng.uniform(-0.3, 0.3, n) * z, rng.uniform(-0.2, 0.2, n) * z, z])
+    ls = np.repeat(np.log(0.004 * z)[:, None], 3, axis=1)
+    return make_scene(means, ls, None, rng.normal(0.0, 1.0, n), rng.uniform(0.0, 1.0, (n, 3)))
+
+
+@pytest.mark.parametrize("kind,n", [("spread", n) for n in (1, 63, 65, 257, 2047, 2049, 4096, 4097, 8193, 70_001)] +
+                         [(k, n) for k in ("equal", "two", "lattice", "thin", "steps") for n in (3000, 60_000)])
+def test_depth_buckets_give_the_stable_order(ctx, kind, n):
+    """Segments and buckets of every fill, equal depths (more than a bucket's
+    workgroup holds at once, too) and a depth range that one far Gaussian
+    stretches: the lists of the plain 64-bit key sort, and the frame of the
+    four-pass radix sort."""
+    scene = _depth_scene(kind, n)
+    W, H = 160, 112
+    k = intr(150.0, W / 2, H / 2)
+    s = ctx.load_scene(scene)
+    _say("depth buckets", kind, n)
+    dbg = ctx.render_debug(s, eye_pose(), k, W, H, tile=(16, 16))
+    assert ctx.stats()["rerenders"] == 0 and dbg["n_dup"] > 0
+    gc.check_tiles(dbg, 16, 16)
+    ctx.set_depth_passes(4)
+    try:
+        ref = ctx.render(s, eye_pose(), k, W, H, fmt="f32", tile=(16, 16))
+    finally:
+        ctx.set_depth_passes(3)
+    np.testing.assert_array_equal(dbg["image"], ref)
+    s.free()
+
+
+def test_depth_buckets_of_several_views_and_a_culled_one(ctx):
+    """Views of scenes of different sizes, one of which shows nothing, in one
+    sequence: each frame is the view's own."""
+    scenes = [ctx.load_scene(_depth_scene("spread", n)) for n in (70_000, 300, 5000)]
+    poses = [eye_pose(), eye_pose(), synth.Pose(np.eye(3, dtype=np.float32), np.array([0, 0, 500.0], np.float32)),
+             eye_pose()]
+    which = [scenes[0], scenes[1], scenes[0], scenes[2]]
+    sizes = [(160, 112), (64, 48), (160, 112), (33, 200)]
+    ks = [intr(150.0, w / 2, h / 2) for w, h in sizes]
+    got = ctx.render_batch(which, poses, ks, [w for w, _ in sizes], [h for _, h in sizes], fmt="f32", tile=(16, 16),
+                           batch_depth=64)
+    for s, p, k, (w, h), img in zip(which, poses, ks, sizes, got):
+        np.testing.assert_array_equal(img, ctx.render(s, p, k, w, h, fmt="f32", tile=(16, 16)))
+    assert not got[2].any()
+    for s in scenes:
+        s.free()
+
+
 @pytest.mark.parametrize("tile", [(16, 16), (8, 8), (16, 32), (32, 16)])
 def test_culled_tile_lists_bit_exact_and_frames_unchanged(ctx, c1, tile):
     """Tighter tile culling: the lists equal the reference less exactly the
