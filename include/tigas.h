@@ -250,12 +250,14 @@ tigas_status tigas_profile_stages(tigas_context* ctx, int enable);
  * replayed (default on; environment TIGAS_GRAPHS=0 turns it off at context
  * creation).  This switches it for the context. */
 tigas_status tigas_set_graphs(tigas_context* ctx, int enable);
-/* Single-view renders place the tile digit of the (tile | depth) keys by
- * counting (per-block tile histograms of the depth-ordered Gaussians, then
- * each entry written straight to its sorted position) when the view's tile
- * grid has at most 8192 tiles; otherwise, and when this is switched off
- * (environment TIGAS_TILE_BIN=0 at context creation), by radix passes over the
- * emitted duplicates.  The sorted lists are identical either way. */
+/* Renders place the tile digit of the (tile | depth) keys by counting (tile
+ * counts of runs of the depth-ordered Gaussians, then each entry written
+ * straight to its sorted position) when every view's grid has at most 256
+ * lists each way; otherwise, and when this is switched off (environment
+ * TIGAS_TILE_BIN=0 at context creation), by radix passes over the emitted
+ * duplicates.  With counting, neighbouring tiles of large frames share one
+ * list (a power of two of them; inspection shows the tiles' own lists).
+ * Frames, and the order of each tile's entries, are identical either way. */
 tigas_status tigas_set_tile_binning(tigas_context* ctx, int enable);
 /* Tighter tile culling: a (Gaussian, tile) entry of the tile lists is
  * emitted only when the Gaussian's exponent can reach the skip threshold at
@@ -264,7 +266,7 @@ tigas_status tigas_set_tile_binning(tigas_context* ctx, int enable);
  * every tile of its bounding rectangle.  Fewer entries to sort and stage;
  * frames are identical (a dropped entry is one every pixel of its tile would
  * skip).  Off by default (environment TIGAS_TILE_CULL=1 at context creation
- * turns it on); while on, single views use the radix tile passes, since the
+ * turns it on); while on, renders use the radix tile passes, since the
  * counting placement needs whole rectangles. */
 tigas_status tigas_set_tile_culling(tigas_context* ctx, int enable);
 /* Depth order of the visible Gaussians (the depth digits of the sort keys,

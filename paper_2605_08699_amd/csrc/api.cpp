@@ -167,12 +167,12 @@ uint16_t f32_to_f16(float f) {
 
 }  // namespace
 
-static_assert(sizeof(tigas_frame_counters) == sizeof(Counters), "public counters mirror the device counters");
-static_assert(offsetof(tigas_frame_counters, duplicates) == offsetof(Counters, D) &&
-                  offsetof(tigas_frame_counters, visible) == offsetof(Counters, visible) &&
-                  offsetof(tigas_frame_counters, fallbacks) == offsetof(Counters, fallbacks) &&
-                  offsetof(tigas_frame_counters, overflow) == offsetof(Counters, overflow),
-              "public counters mirror the device counters");
+static_assert(sizeof(tigas_frame_counters) == sizeof(FrameCounters), "public counters mirror the frame's counters");
+static_assert(offsetof(tigas_frame_counters, duplicates) == offsetof(FrameCounters, D) &&
+                  offsetof(tigas_frame_counters, visible) == offsetof(FrameCounters, visible) &&
+                  offsetof(tigas_frame_counters, fallbacks) == offsetof(FrameCounters, fallbacks) &&
+                  offsetof(tigas_frame_counters, overflow) == offsetof(FrameCounters, overflow),
+              "public counters mirror the frame's counters");
 
 // Scratch array of the allocation-free render (see render_noalloc): one copy
 // per device, held until the process ends.
@@ -201,9 +201,12 @@ struct Group {
 struct Plan {
     std::vector<ViewParams> views;
     std::vector<Group> groups;
-    uint32_t nrec = 0, n_tiles = 0;
+    uint32_t nrec = 0;
+    uint32_t n_tiles = 0;   // tile lists; the tiles the blend is launched over, and those of the frames
+    uint32_t n_blend = 0, n_frame_tiles = 0;
     uint32_t seg_len = 0, nseg = 0, nchunks = 0;  // bucketed depth sort (set_buckets)
     uint64_t row_words = 0;
+    uint32_t nunits = 0, tchunks = 0, max_tiles = 0;  // tile placement (set_tiles)
     TileCfg tc{16, 16, 64, 1};
     bool persistent = false;  // blend as a persistent kernel over a tile work queue
     bool allow_graph = true;  // capture/replay (off for one-off shapes such as serving batches)
@@ -292,7 +295,7 @@ struct FrameMem {
                                       // null: a single view uploaded as a kernel argument
     PreOut pre{};
     Counters* cnt = nullptr;
-    Counters* cnt_out = nullptr;  // receives the final counters (pinned host memory or device memory)
+    FrameCounters* cnt_out = nullptr;  // receives the final counters (pinned host memory or device memory)
     uint32_t* key[2] = {nullptr, nullptr};
     uint32_t* val[2] = {nullptr, nullptr};
     uint32_t* ext[2] = {nullptr, nullptr};
@@ -303,8 +306,7 @@ struct FrameMem {
     uint32_t* queue = nullptr;
     uint2* ranges = nullptr;
     uint32_t* order = nullptr;     // the blend's dispatch order of the tiles
-    uint32_t* bin_hist = nullptr;  // binned tile digit: block histograms, group starts
-    uint32_t* bin_gsum = nullptr;
+    TileMem tm{};                  // tile placement by counting
     uint32_t* blk_off = nullptr;
     uint32_t* blk_sum2 = nullptr;
     uint32_t* blk_off2 = nullptr;
@@ -320,7 +322,7 @@ struct Workspace {
     std::mutex mu;  // one launch sequence at a time per workspace
     // per record
     DevBuf recs, rect, srect, zkey;
-    DevBuf blk_sum, blk_vis, blk_fb, blk_view, blk_off, blk_sum2, blk_off2;
+    DevBuf blk_sum, blk_vis, blk_fb, blk_tiles, blk_view, blk_off, blk_sum2, blk_off2;
     DevBuf fb_list;  // near-singular Gaussians for the FP64 conic kernel
     DevBuf chunk_vis, chunk_dup, chunk_fb, chunk_dups;  // totals per chunk of block counts
     DevBuf counters;
@@ -333,7 +335,7 @@ struct Workspace {
     DevBuf dbg_key, dbg_val, dbg_ext;
     // per tile / per view
     DevBuf ranges;
-    DevBuf bin_hist, bin_gsum;
+    DevBuf tile_rows, tile_small;  // tile placement: counts, everything else
     DevBuf frame_staging;
     static constexpr int NSLOT = 2;
     FrameSlot slot[NSLOT];
@@ -359,7 +361,7 @@ struct Workspace {
         m.views_src = fs().host_views.p;
         m.pre = pre();
         m.cnt = counters.as<Counters>();
-        m.cnt_out = fs().host_counters.as<Counters>();
+        m.cnt_out = fs().host_counters.as<FrameCounters>();
         for (int i = 0; i < 2; ++i) {
             m.key[i] = key[i].as<uint32_t>();
             m.val[i] = val[i].as<uint32_t>();
@@ -370,8 +372,6 @@ struct Workspace {
         m.queue = queue.as<uint32_t>();
         m.ranges = ranges.as<uint2>();
         m.order = reinterpret_cast<uint32_t*>(m.ranges + tile_cap);  // after the ranges, in the same buffer
-        m.bin_hist = bin_hist.as<uint32_t>();
-        m.bin_gsum = bin_gsum.as<uint32_t>();
         m.blk_off = blk_off.as<uint32_t>();
         m.blk_sum2 = blk_sum2.as<uint32_t>();
         m.blk_off2 = blk_off2.as<uint32_t>();
@@ -391,6 +391,7 @@ struct Workspace {
         o.blk_sum = blk_sum.as<uint32_t>();
         o.blk_vis = blk_vis.as<uint32_t>();
         o.blk_fb = blk_fb.as<uint32_t>();
+        o.blk_tiles = blk_tiles.as<uint32_t>();
         o.blk_view = blk_view.as<uint32_t>();
         o.vmask = vmask.as<unsigned long long>();
         o.sample = sample.as<uint32_t>();
@@ -414,7 +415,7 @@ struct Workspace {
         grow(srect, r * 8);
         grow(zkey, r * 4);
         const size_t nb = r / K1_THREADS + 1;
-        for (DevBuf* b : {&blk_sum, &blk_vis, &blk_fb, &blk_view, &blk_off, &blk_sum2, &blk_off2}) grow(*b, nb * 4);
+        for (DevBuf* b : {&blk_sum, &blk_vis, &blk_fb, &blk_tiles, &blk_view, &blk_off, &blk_sum2, &blk_off2}) grow(*b, nb * 4);
         grow(fb_list, r * 8);
         grow(vmask, r / 64 * 8);
         grow(sample, r / 64 * 4);
@@ -483,7 +484,7 @@ struct tigas_context {
     std::map<std::string, std::pair<int64_t, double>> kernel_ms;  // name -> (launches, total ms)
     std::atomic<bool> use_graphs{true};
     std::atomic<bool> blend_cull{true};     // blend: per-block threshold culling
-    std::atomic<bool> tile_bin{true};       // single view: tile digit placed by counting
+    std::atomic<bool> tile_bin{true};       // tile digit placed by counting
     std::atomic<bool> tile_cull{false};     // duplicates only for tiles each Gaussian can reach
     std::atomic<bool> depth4{false};        // four-pass depth sort (requested, or after a frame too deep for three)
     double stage_ms[6] = {0, 0, 0, 0, 0, 0};
@@ -509,7 +510,7 @@ struct tigas_context {
         if (!p) {
             p.reset(new Workspace());
             p->stream = s;
-            for (FrameSlot& f : p->slot) f.host_counters.ensure(sizeof(Counters), /*coherent=*/true);
+            for (FrameSlot& f : p->slot) f.host_counters.ensure(sizeof(FrameCounters), /*coherent=*/true);
             if (p->counters.ensure(sizeof(Counters))) HIPCHK(hipMemset(p->counters.p, 0, sizeof(Counters)));
         }
         return *p;
@@ -657,19 +658,60 @@ int sort_blocks(uint64_t n) {
     return (int)std::min<uint64_t>(cap, std::max<uint64_t>(1, n / 4096));
 }
 
-// Tile layout of a plan for a tile configuration (tile ids are global:
-// view tile offset + row-major local id).
-void set_tiles(Plan& plan, const TileCfg& tc) {
-    plan.tc = tc;
-    plan.n_tiles = 0;
-    for (ViewParams& v : plan.views) {
-        v.tile_w = tc.tw;
-        v.tile_h = tc.th;
-        v.tiles_x = (v.width + tc.tw - 1) / tc.tw;
-        v.tiles_y = (v.height + tc.th - 1) / tc.th;
-        v.tile_base = plan.n_tiles;
-        plan.n_tiles += (uint32_t)(v.tiles_x * v.tiles_y);
+// Tiles that share a list, as powers of two across and down: lists of about
+// the same number however large the frame, so that the entries of the lists,
+// which cost the placement, stay in proportion to what a block of the blend
+// reads of its list.  All kernels of a frame at 1, 2, 4 and 8 tiles of 16x32
+// per list: 1M/720p (1840 tiles) 224 / 225 / 228 / 233 us; 3M/1080p (4080) 467 /
+// 454 / 434 / 443 us; 3M/4K (16320) 898 / 789 / 755 / 741 us; a batch of 32
+// views at 1080p 7.99 / 7.57 / 7.68 / 8.24 ms; 20k/256x256 (128) 108 / 109 /
+// 115 / 129 us.  Tall lists of an even doubling: 32x64 instead of 64x32 costs
+// the counting 2 us less at 3M/1080p.  Frames are the same.
+void list_scale(ViewParams& v, const TileCfg& tc) {
+    v.lx = v.ly = 0;
+    auto lists = [&] {
+        const int64_t w = (int64_t)tc.tw << v.lx, h = (int64_t)tc.th << v.ly;
+        return ((v.width + w - 1) / w) * ((v.height + h - 1) / h);
+    };
+    while (lists() > 1024 && v.lx + v.ly < 4) {
+        if (tc.tw << v.lx < tc.th << v.ly) ++v.lx;
+        else ++v.ly;
     }
+}
+
+// Tile layout of a plan for a tile configuration (list ids are global: view
+// list offset + row-major local id).  shared: lists of several tiles (only
+// for the placement by counting, and not for inspection, which shows the
+// tiles' own lists).
+void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
+    plan.tc = tc;
+    plan.n_tiles = plan.n_blend = plan.n_frame_tiles = plan.tchunks = plan.max_tiles = 0;
+    for (ViewParams& v : plan.views) {
+        v.lx = v.ly = 0;
+        if (shared) list_scale(v, tc);
+        v.tw_log = ceil_log2((uint64_t)tc.tw);
+        v.th_log = ceil_log2((uint64_t)tc.th);
+        const int lw = tc.tw << v.lx, lh = tc.th << v.ly;
+        v.tiles_x = (v.width + lw - 1) / lw;
+        v.tiles_y = (v.height + lh - 1) / lh;
+        v.tile_base = plan.n_tiles;
+        v.btile_base = plan.n_blend;
+        v.tchunk_base = plan.tchunks;
+        const uint32_t n = (uint32_t)(v.tiles_x * v.tiles_y);
+        plan.n_tiles += n;
+        plan.n_blend += n << (v.lx + v.ly);
+        plan.n_frame_tiles += (uint32_t)(((v.width + tc.tw - 1) / tc.tw) * ((v.height + tc.th - 1) / tc.th));
+        plan.tchunks += (n + TILE_CHUNK - 1) / TILE_CHUNK;
+        plan.max_tiles = std::max(plan.max_tiles, n);
+        if (shared && (v.tiles_x > 256 || v.tiles_y > 256)) {  // too many even so: not placed by counting
+            set_tiles(plan, tc, false);
+            return;
+        }
+    }
+    // units of the tile placement: each has a row of the largest view's tiles
+    // (at most 256 MB of them), and costs a pass over it
+    const uint64_t want = std::min<uint64_t>(TILE_UNITS_MAX, (uint64_t)TILE_UNITS * plan.views.size());
+    plan.nunits = (uint32_t)std::max<uint64_t>(256, std::min<uint64_t>(want, (64u << 20) / std::max(plan.max_tiles, 1u)));
 }
 
 // Lays out the bucketed depth sort of a plan: each view's records in segments
@@ -714,6 +756,8 @@ BucketMem carve_buckets(const Plan& plan, void* rows, void* small, size_t* rows_
     b.vc = reinterpret_cast<ViewCount*>(take(plan.views.size() * sizeof(ViewCount)));
     b.start_in = reinterpret_cast<uint32_t*>(take(nb * 4));
     b.tot = reinterpret_cast<uint32_t*>(take(nb * 4));
+    b.cost = reinterpret_cast<uint32_t*>(take(nb * 4));
+    b.ccost = reinterpret_cast<unsigned long long*>(take((size_t)plan.nchunks * 8));
     b.chunk = reinterpret_cast<uint32_t*>(take((size_t)plan.nchunks * 4));
     b.cdf = reinterpret_cast<uint32_t*>(take(plan.views.size() * BUCKET_CDF_WORDS * 4));
     b.segmm = reinterpret_cast<uint32_t*>(take((size_t)plan.nseg * 8));
@@ -748,14 +792,27 @@ std::string shape_key(const Plan& plan, bool with_tiles) {
     return k;
 }
 
-// Buffers of the binned tile digit for a single-view plan (they depend on the
-// duplicate capacity too: call again after it grows).
-void ensure_bin(Workspace& ws, const Plan& plan) {
-    if (plan.views.size() != 1 || !bin_fits(plan.views[0].tiles_x, plan.views[0].tiles_y)) return;
-    const size_t nbc = std::max<size_t>(1, (plan.nrec + BIN_BLOCK - 1) / BIN_BLOCK);
-    ws.grow(ws.bin_hist, nbc * plan.n_tiles * 4);
-    ws.grow(ws.bin_gsum, ((size_t)(BIN_GROUPS + 2) * plan.n_tiles + BIN_TILES_MAX / 256 + nbc +
-                          bin_emit_groups(ws.dup_cap, plan.nrec)) * 4);
+// Lays the tile placement's scratch out from `rows` and `small` (null: only
+// the sizes).
+TileMem carve_tiles(const Plan& plan, void* rows, void* small, size_t* rows_bytes, size_t* small_bytes) {
+    TileMem m{};
+    m.nunits = plan.nunits;
+    m.stride = std::max(plan.max_tiles, 1u);
+    m.rows = static_cast<uint32_t*>(rows);
+    const size_t units = (size_t)plan.nunits + plan.views.size();
+    *rows_bytes = units * m.stride * 4;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        char* p = small ? static_cast<char*>(small) + off : nullptr;
+        off += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    m.urange = reinterpret_cast<uint2*>(take(units * 8));
+    m.start_in = reinterpret_cast<uint32_t*>(take((size_t)plan.n_tiles * 4));
+    m.tot = reinterpret_cast<uint32_t*>(take((size_t)plan.n_tiles * 4));
+    m.chunk = reinterpret_cast<uint32_t*>(take((size_t)plan.tchunks * 4));
+    *small_bytes = std::max<size_t>(off, 256);
+    return m;
 }
 
 // The plan's frame memory in the workspace's active slot.
@@ -766,6 +823,7 @@ FrameMem frame_mem(Workspace& ws, const Plan& plan) {
     // 16 bytes for each visible record: the duplicate buffers hold at least
     // four words per record
     m.bk.elem = ws.key[0].as<uint4>();
+    m.tm = carve_tiles(plan, ws.tile_rows.p, ws.tile_small.p, &rb, &sb);
     return m;
 }
 
@@ -789,8 +847,10 @@ void prepare(Workspace& ws, Plan& plan, bool debug) {
         (void)carve_buckets(plan, nullptr, nullptr, &rb, &sb);
         ws.grow(ws.bkt_rows, rb);
         ws.grow(ws.bkt_small, sb);
+        (void)carve_tiles(plan, nullptr, nullptr, &rb, &sb);
+        ws.grow(ws.tile_rows, rb);
+        ws.grow(ws.tile_small, sb);
     }
-    ensure_bin(ws, plan);
     if (debug) {
         const size_t bytes = (size_t)ws.dup_cap * 4;
         ws.dbg_key.ensure(bytes);
@@ -808,7 +868,7 @@ void prepare(Workspace& ws, Plan& plan, bool debug) {
 // Per-context switches that change the launch sequence (not its results).
 struct LaunchOptions {
     bool cull = true;         // blend: per-block threshold culling of list entries
-    bool bin = true;          // single view: tile digit placed by counting (else radix passes over the duplicates)
+    bool bin = true;          // tile digit placed by counting (else radix passes over the duplicates)
     bool cull_tiles = false;  // duplicates only for tiles the Gaussian can reach (radix passes then)
     bool buckets = true;      // bucketed depth sort when the rectangles pack (else four radix passes)
 };
@@ -822,9 +882,7 @@ bool packed_rects(const Plan& plan) {
 
 // Whether the plan's tile digit is placed by counting.
 bool use_bin(const Plan& plan, const LaunchOptions& opt) {
-    return opt.bin && !(opt.cull_tiles && packed_rects(plan)) && plan.views.size() == 1 &&
-           plan.views[0].tiles_x <= 256 && plan.views[0].tiles_y <= 256 &&
-           bin_fits(plan.views[0].tiles_x, plan.views[0].tiles_y);
+    return opt.bin && !opt.cull_tiles && packed_rects(plan) && (opt.buckets || plan.views.size() == 1);
 }
 
 int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned long long* work, int pblocks,
@@ -856,6 +914,8 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     zl.n[0] = 8;
     zl.p[1] = reinterpret_cast<uint32_t*>(m.ranges);
     zl.n[1] = 2 * plan.n_tiles;
+    zl.p[2] = reinterpret_cast<uint32_t*>(m.bk.ccost);
+    zl.n[2] = 2 * plan.nchunks;
     SortBuffers sb;
     for (int i = 0; i < 2; ++i) {
         sb.key[i] = m.key[i];
@@ -873,7 +933,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     if (opt.buckets && packed) {
         mark(2);
         launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl, m.flag_wide,
-                           sb.val[0], sb.ext[0], st);
+                           plan.nunits, sb.val[0], sb.ext[0], st);
     } else {
         launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
         mark(2);
@@ -902,10 +962,9 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     int cur = cd;
     if (bin) {
         // tile digit by counting, straight from the depth-ordered Gaussians
-        const ViewParams& v = plan.views[0];
-        launch_bin(sb.val[cv], sb.ext[cv], cnt, plan.nrec, m.dup_cap, v.tiles_x, v.tiles_y, m.bin_hist, m.bin_gsum,
-                   m.blk_sum2, m.blk_off2, m.ranges, m.cnt_out, o, vdev, sb.val[cd], debug ? sb.key[cd] : nullptr,
-                   debug ? sb.ext[cd] : nullptr, m.order, st);
+        launch_tiles(m.tm, m.bk, vdev, plan.views.data(), nv, cnt, !opt.buckets, plan.tchunks, sb.val[cv], sb.ext[cv],
+                     m.ranges, plan.persistent || nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
+                     debug ? sb.key[cd] : nullptr, debug ? sb.ext[cd] : nullptr, o.zkey, st);
         mark(4);
         mark(5);
     } else {
@@ -918,7 +977,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         if (!plan.persistent) launch_tile_order(m.ranges, plan.n_tiles, m.order, st);
         mark(5);
     }
-    launch_blend(vdev, nv, plan.n_tiles, m.ranges, sb.val[cur], o, plan.nrec, plan.tc.tw, plan.tc.th, plan.tc.bd,
+    launch_blend(vdev, nv, plan.n_blend, m.ranges, sb.val[cur], o, plan.nrec, plan.tc.tw, plan.tc.th, plan.tc.bd,
                  plan.tc.ppl, work, plan.persistent ? m.queue : nullptr, pblocks, opt.cull,
                  plan.persistent ? nullptr : m.order, st);
     mark(6);
@@ -926,10 +985,16 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     return cur;
 }
 
+// Whether the tiles of a plan of the context may share lists.
+bool share_lists(tigas_context* ctx, const Plan& plan) {
+    return ctx->tile_bin.load() && !ctx->tile_cull.load() && (!ctx->depth4.load() || plan.views.size() == 1);
+}
+
 bool plan_binned(tigas_context* ctx, const Plan& plan) {
     LaunchOptions opt;
     opt.bin = ctx->tile_bin.load();
     opt.cull_tiles = ctx->tile_cull.load();
+    opt.buckets = !ctx->depth4.load();
     return use_bin(plan, opt);
 }
 
@@ -1010,21 +1075,24 @@ void wait_stream(hipStream_t st) {
 // duplicates overflowed the buffers (it then emitted nothing) is rendered
 // again (synchronously) with larger buffers; returns the counters of the
 // final attempt.
-Counters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool debug, bool prof,
+FrameCounters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool debug, bool prof,
                       unsigned long long* work, int& cur, int& rerenders) {
-    Counters c;
+    FrameCounters c;
     std::memcpy(&c, ws.fs().host_counters.p, sizeof(c));
     rerenders = 0;
     if (c.overflow) {
         // bit 1: the visible depth keys span too much for the bucketed
         // sort: four radix passes from now on; bit 0: more duplicates than the
         // buffers hold: grow them
-        if (c.overflow & 2u) ctx->depth4.store(true);
+        if (c.overflow & 2u) {
+            ctx->depth4.store(true);
+            set_tiles(plan, plan.tc, !debug && share_lists(ctx, plan));
+            prepare(ws, plan, debug);
+        }
         if (c.overflow & 1u) {
             const uint64_t want = (uint64_t)c.D + c.D / 4 + 1024;
             if (want > 0xfff00000ull) fail(TIGAS_E_OOM, "duplicate count exceeds the 32-bit index range");
             ws.ensure_dups((uint32_t)want);
-            ensure_bin(ws, plan);
         }
         if (debug) prepare(ws, plan, debug);
         if (work) HIPCHK(hipMemsetAsync(work, 0, 16, ws.stream));
@@ -1038,12 +1106,12 @@ Counters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool debug,
     return c;
 }
 
-tigas_stats frame_stats(const Plan& plan, const Counters& c, int rerenders, bool binned, int depth_passes) {
+tigas_stats frame_stats(const Plan& plan, const FrameCounters& c, int rerenders, bool binned, int depth_passes) {
     tigas_stats st{};
     st.visible = c.visible;
     st.duplicates = c.D;
     st.fallbacks = c.fallbacks;
-    st.tiles = plan.n_tiles;
+    st.tiles = plan.n_frame_tiles;
     st.sort_passes = depth_passes + (binned ? 1 : (int64_t)tile_passes(plan.n_tiles).size());
     st.rerenders = rerenders;
     st.tile_w = plan.tc.tw;
@@ -1108,7 +1176,7 @@ void finish_async(tigas_context* ctx, Workspace& ws, int si) {
         HIPCHK(hipEventElapsedTime(&d.gpu_ms, f.t0, f.t1));
         ws.active = si;
         int cur = f.cur, rerenders = 0;
-        const Counters c = settle_frame(ctx, ws, f.plan, false, false, nullptr, cur, rerenders);
+        const FrameCounters c = settle_frame(ctx, ws, f.plan, false, false, nullptr, cur, rerenders);
         d.stats = frame_stats(f.plan, c, rerenders, plan_binned(ctx, f.plan), depth_passes(ctx, f.plan));
         record_stats(ctx, ws, d.stats, false);
     } catch (const Error& e) {
@@ -1141,7 +1209,7 @@ int run_plan(tigas_context* ctx, Workspace& ws, Plan& plan, bool debug, unsigned
     int cur = launch_plan(ctx, ws, plan, debug, prof, work);
     wait_stream(ws.stream);
     int rerenders = 0;
-    const Counters c = settle_frame(ctx, ws, plan, debug, prof, work, cur, rerenders);
+    const FrameCounters c = settle_frame(ctx, ws, plan, debug, prof, work, cur, rerenders);
     record_stats(ctx, ws, frame_stats(plan, c, rerenders, plan_binned(ctx, plan), depth_passes(ctx, plan)), prof);
     return cur;
 }
@@ -1187,7 +1255,7 @@ TileCfg autotune(tigas_context* ctx, Workspace& ws, Plan& plan) {
     TileCfg best = kTileCandidates[2];
     double best_ms = 1e30;
     for (const TileCfg& tc : kTileCandidates) {
-        set_tiles(plan, tc);
+        set_tiles(plan, tc, share_lists(ctx, plan));
         run_plan(ctx, ws, plan, false);  // capture + warm
         run_plan(ctx, ws, plan, false);
         double ts[7];
@@ -1261,7 +1329,7 @@ void render_views(tigas_context* ctx, Workspace& ws, Plan& plan, const tigas_qua
         if (q && q->batch_depth != 0) tc.bd = req.bd;
         if (q && q->pixels_per_lane != 0 && tc.th >= 16) tc.ppl = req.ppl;
     }
-    set_tiles(plan, tc);
+    set_tiles(plan, tc, !dbg && share_lists(ctx, plan));
     unsigned long long* work = nullptr;
     if (work_out) {
         ws.work.ensure(16);
@@ -1320,7 +1388,7 @@ void render_submit(tigas_scene* scene, const tigas_pose* pose, const tigas_intri
         if (q && q->batch_depth != 0) tc.bd = req.bd;
         if (q && q->pixels_per_lane != 0 && tc.th >= 16) tc.ppl = req.ppl;
     }
-    set_tiles(plan, tc);
+    set_tiles(plan, tc, share_lists(ctx, plan));
     const int si = ws.next_async;
     FrameSlot& f = ws.slot[si];
     if (f.pending) finish_async(ctx, ws, si);  // two frames in flight at most
@@ -1406,7 +1474,7 @@ struct Carver {
 
 // Lays out a single-view launch sequence of nrec records and n_tiles tiles
 // in the scratch array; the duplicate buffers take what is left.
-FrameMem carve_scratch(void* scratch_dev, const Plan& plan, Counters* cnt_out, hipStream_t st) {
+FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_out, hipStream_t st) {
     const uint32_t nrec = plan.nrec, n_tiles = plan.n_tiles;
     Carver c{static_cast<char*>(scratch_dev), (size_t)TIGAS_NOALLOC_SCRATCH_BYTES};
     FrameMem m;
@@ -1414,7 +1482,7 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, Counters* cnt_out, h
     m.views = c.take<ViewParams>(sizeof(ViewParams));
     m.views_src = nullptr;  // the view is stored by a kernel
     m.cnt = c.take<Counters>(sizeof(Counters));
-    m.cnt_out = cnt_out ? cnt_out : c.take<Counters>(sizeof(Counters));
+    m.cnt_out = cnt_out ? cnt_out : c.take<FrameCounters>(sizeof(FrameCounters));
     m.queue = c.take<uint32_t>(8 * 4);
     PreOut& o = m.pre;
     o.rec = c.take<Rec>((size_t)nrec * sizeof(Rec));
@@ -1427,6 +1495,7 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, Counters* cnt_out, h
     o.blk_sum = c.take<uint32_t>(nb * 4);
     o.blk_vis = c.take<uint32_t>(nb * 4);
     o.blk_fb = c.take<uint32_t>(nb * 4);
+    o.blk_tiles = reinterpret_cast<uint32_t*>(o.srect);  // written by the last radix pass only, long after
     o.blk_view = c.take<uint32_t>(nb * 4);
     m.blk_off = c.take<uint32_t>(nb * 4);
     m.blk_sum2 = c.take<uint32_t>(nb * 4);
@@ -1439,10 +1508,11 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, Counters* cnt_out, h
     o.cnt = m.cnt;
     m.ranges = c.take<uint2>((size_t)std::max<uint32_t>(n_tiles, 1) * 8);
     m.order = c.take<uint32_t>((size_t)std::max<uint32_t>(n_tiles, 1) * 4);
-    m.bin_hist = c.take<uint32_t>(((size_t)nrec + BIN_BLOCK - 1) / BIN_BLOCK * n_tiles * 4);
-    // the first-round table sized for the largest duplicate capacity below
-    m.bin_gsum = c.take<uint32_t>(((size_t)(BIN_GROUPS + 2) * n_tiles + BIN_TILES_MAX / 256 +
-                                   ((size_t)nrec + BIN_BLOCK - 1) / BIN_BLOCK + 1 + bin_emit_groups(16u << 20, nrec)) * 4);
+    size_t tr, ts;
+    (void)carve_tiles(plan, nullptr, nullptr, &tr, &ts);
+    char* tile_rows = c.take<char>(tr);
+    char* tile_small = c.take<char>(ts);
+    m.tm = carve_tiles(plan, tile_rows, tile_small, &tr, &ts);
     // sort passes over at most 16M keys use at most 1024 segments; the
     // bucketed sort, which runs instead of them, has its scratch in the same place
     size_t rows_bytes, small_bytes;
@@ -1493,11 +1563,14 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     out->out_h = v.height;
     if (!out->data || out->capacity < frame_bytes(v)) fail(TIGAS_E_BUFFER, "output frame buffer too small");
     v.out_ptr = (uint64_t)(uintptr_t)out->data;
-    set_tiles(plan, tile_cfg(q));  // as requested, else 16x16 tiles: no autotuner here
+    // as requested, else 16x16 tiles: no autotuner here
+    set_tiles(plan, tile_cfg(q), ctx->tile_bin.load() && !ctx->tile_cull.load());
     set_buckets(plan);
+    // fewer units than with a workspace: their rows come out of the array
+    plan.nunits = std::min<uint32_t>(plan.nunits, (plan.nrec + 2047) / 2048 + 20);
     const hipStream_t st = pick_stream(ctx, hip_stream);
     const FrameMem m =
-        carve_scratch(scratch_dev, plan, reinterpret_cast<Counters*>(counters), st);
+        carve_scratch(scratch_dev, plan, reinterpret_cast<FrameCounters*>(counters), st);
     // the previous call's counters stay in the array: start this frame from zero
     launch_fill_u32(reinterpret_cast<uint32_t*>(m.cnt), sizeof(Counters) / 4, 0u, st);
     LaunchOptions opt;
@@ -1508,7 +1581,7 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
 }
 
 void debug_copy(Workspace& ws, const Plan& plan, int cur, int64_t n, uint32_t n_pad, tigas_debug_out* dbg) {
-    Counters c;
+    FrameCounters c;
     std::memcpy(&c, ws.fs().host_counters.p, sizeof(c));
     dbg->n_dup = c.D;
     dbg->n_tiles = plan.n_tiles;

@@ -23,10 +23,10 @@
 //                  the same, keeping only the tiles where the Gaussian can
 //                  reach the skip threshold at some pixel (count, then emit)
 //   k_ranges       [start, end) of every tile in the sorted list
-//   k_bin_*        single views: the tile digit placed by counting instead
-//                  (per-block tile histograms from 2D difference grids, their
-//                  prefixes, then every (Gaussian, tile) entry written straight
-//                  to its sorted position; the ranges are the tile starts)
+//   k_tile_*       the tile digit placed by counting instead (per-unit tile
+//                  counts from 2D difference grids, their prefixes, then
+//                  every (Gaussian, tile) entry written straight to its sorted
+//                  position; the ranges are the tile starts)
 //   k_blend        front-to-back compositing, one wave64 per 8x8 pixel block,
 //                  Gaussians staged per wave in LDS, per-wave early exit
 //
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
         // FP32 order key (also the near-plane test)
         const float z32 = __builtin_fmaf(v.V[6], mx, __builtin_fmaf(v.V[7], my, __builtin_fmaf(v.V[8], mz, v.tz_key)));
         bool vis = ok && z32 > NEAR_Z;
-        uint32_t touched = 0, fb = 0;
+        uint32_t touched = 0, tiles = 0, fb = 0;  // lists and tiles met, FP64 fallback
         float4 r0 = {0, 0, 0, 0}, r1 = {0, 0, 0, 0}, r2 = {0, 0, 0, 0};
         uint2 bb = {0u, 0u}, tr = {0u, 0u};
         if (vis) {
@@ -430,8 +430,14 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
                 const int x0 = max((int)ceilf(xl), 0), x1 = min((int)floorf(xr), v.width - 1);
                 const int y0 = max((int)ceilf(yl), 0), y1 = min((int)floorf(yr), v.height - 1);
                 if (x0 <= x1 && y0 <= y1) {
-                    const int tx0 = x0 / v.tile_w, tx1 = x1 / v.tile_w;
-                    const int ty0 = y0 / v.tile_h, ty1 = y1 / v.tile_h;
+                    int tx0 = x0 >> v.tw_log, tx1 = x1 >> v.tw_log;
+                    int ty0 = y0 >> v.th_log, ty1 = y1 >> v.th_log;
+                    tiles = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
+                    // the lists' rectangle
+                    tx0 >>= v.lx;
+                    tx1 >>= v.lx;
+                    ty0 >>= v.ly;
+                    ty1 >>= v.ly;
                     touched = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
                     bb = make_uint2((uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)x1 | ((uint32_t)y1 << 16));
                     tr = make_uint2((uint32_t)tx0 | ((uint32_t)ty0 << 16),
@@ -458,7 +464,7 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
                 const bool fin = ((sh_fin >> v.sh_degree) & 1u) && __builtin_isfinite(rgb[0]) &&
                                  __builtin_isfinite(rgb[1]) && __builtin_isfinite(rgb[2]);
                 if (!fin) {
-                    touched = 0;
+                    touched = tiles = 0;
                     fb = 0;
                     tr = make_uint2(0u, 0u);
                 }
@@ -508,7 +514,7 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
         }
         // per-block counts: wave sums, then one barrier (LDS slots alternate
         // between views so the next view cannot overwrite unread sums)
-        const uint32_t s0 = wave_sum(touched), s1 = wave_sum(touched ? 1u : 0u), s2 = wave_sum(touched ? fb : 0u);
+        const uint32_t s0 = wave_sum(touched), s1 = wave_sum(touched ? 1u + (fb << 16) : 0u), s2 = wave_sum(tiles);
         const int wv = threadIdx.x >> 6;
         if ((threadIdx.x & 63) == 0) {
             red[vi & 1][wv][0] = s0;
@@ -526,8 +532,9 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
             }
             const uint32_t blk = rec / K1_THREADS;
             o.blk_sum[blk] = t0;
-            o.blk_vis[blk] = t1;
-            o.blk_fb[blk] = t2;
+            o.blk_vis[blk] = t1 & 0xffffu;
+            o.blk_fb[blk] = t1 >> 16;
+            o.blk_tiles[blk] = t2;
             o.blk_view[blk] = view_base + (uint32_t)vi;
         }
     }
@@ -679,6 +686,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_visible(const uint32_t* _
         F = block_sum_u64(F, red64);
         if (threadIdx.x == 0) {
             cnt->D = D > 0xffffffffull ? 0xffffffffu : (uint32_t)D;
+            cnt->pairs = cnt->D;  // one tile per list
             cnt->visible = (uint32_t)V;
             cnt->fallbacks = (uint32_t)F;
             cnt->overflow = D > (uint64_t)cap ? 1u : 0u;
@@ -710,7 +718,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_dups(const uint32_t* __re
         uint64_t D = 0;
         for (int c = (int)threadIdx.x; c < nchunks; c += SCAN_THREADS) D += tot[c];
         D = block_sum_u64(D, red64);
-        if (threadIdx.x == 0 && !cnt->overflow) cnt->D = (uint32_t)min(D, 0xffffffffull);
+        if (threadIdx.x == 0 && !cnt->overflow) cnt->D = cnt->pairs = (uint32_t)min(D, 0xffffffffull);
     }
 }
 
@@ -1116,8 +1124,9 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
     if (blockIdx.x >= nseg) {  // a view's totals
         const int vi = (int)(blockIdx.x - nseg);
         const uint32_t k0 = views[vi].rec_base / K1_THREADS, n = views[vi].n_pad / K1_THREADS;
-        uint64_t d = 0, vis = 0, fb = 0;
+        uint64_t d = 0, vis = 0, fb = 0, tl = 0;
         for (uint32_t i = t; i < n; i += NT) {
+            tl += o.blk_tiles[k0 + i];
             d += o.blk_sum[k0 + i];
             vis += o.blk_vis[k0 + i];
             fb += o.blk_fb[k0 + i];
@@ -1125,7 +1134,9 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
         d = block_sum_u64(d, red64);
         vis = block_sum_u64(vis, red64);
         fb = block_sum_u64(fb, red64);
+        tl = block_sum_u64(tl, red64);
         if (t == 0) {
+            b.vc[vi].tiles = tl;
             b.vc[vi].dups = d;
             b.vc[vi].visible = (uint32_t)vis;
             b.vc[vi].fallbacks = (uint32_t)fb;
@@ -1236,57 +1247,74 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
     for (uint32_t i = t; i < nbkt; i += NT) row[i] = hist[i];
 }
 
-// Exclusive prefixes down the columns of a row-major nrows x ncols array, in
-// place, for the COL_CHUNK columns from c0 on, by 1024 threads: 32 groups of
-// consecutive rows, a lane per column (128-byte row pieces).  Per column its
-// total (tot) and the totals of the chunk's columns before it (start_in), and
-// the chunk's total.
-__device__ __forceinline__ void column_scan(uint32_t* a, uint32_t nrows, uint32_t ncols, uint32_t c0,
+// Exclusive prefixes down the columns of a row-major nrows x ncols array
+// (rows `stride` words apart), in place, for the CW columns from c0 on, by
+// 1024 threads: 1024 / CW groups of consecutive rows, a lane per column, the
+// first U rows of a group kept in registers (all loads in flight at once, and
+// usually all there are); a wave then scans the groups of a column or two.
+// Per column its total (tot) and the totals of the chunk's columns before it
+// (start_in), and the chunk's total.
+template <uint32_t CW, uint32_t U>
+__device__ __forceinline__ void column_scan(uint32_t* a, uint32_t nrows, uint32_t stride, uint32_t ncols, uint32_t c0,
                                             uint32_t* __restrict__ start_in, uint32_t* __restrict__ tot,
                                             uint32_t* __restrict__ chunk, uint32_t* lds) {
-    static_assert(COL_CHUNK == 32, "32 columns x 32 row groups");
-    const uint32_t c = threadIdx.x & 31u, g = threadIdx.x >> 5;
+    constexpr uint32_t G = 1024 / CW, ROW = CW + 1;
+    static_assert((CW == 16 && G == 64) || (CW == 32 && G == 32), "a wave scans the groups of one column or two");
+    const uint32_t c = threadIdx.x % CW, g = threadIdx.x / CW;
     const bool in = c0 + c < ncols;
-    const uint32_t per = (nrows + 31u) / 32u, b0 = min(nrows, g * per), b1 = min(nrows, b0 + per);
+    const uint32_t per = (nrows + G - 1u) / G, b0 = min(nrows, g * per), b1 = in ? min(nrows, b0 + per) : b0;
     uint32_t* p = a + c0 + c;
-    constexpr uint32_t U = 8;
-    uint32_t sum = 0;
-    if (in)
-        for (uint32_t r = b0; r < b1; r += U) {
-            uint32_t x[U];
+    uint32_t x[U], sum = 0;
 #pragma unroll
-            for (uint32_t k = 0; k < U; ++k) x[k] = r + k < b1 ? p[(size_t)(r + k) * ncols] : 0u;
+    for (uint32_t k = 0; k < U; ++k) x[k] = b0 + k < b1 ? p[(size_t)(b0 + k) * stride] : 0u;
 #pragma unroll
-            for (uint32_t k = 0; k < U; ++k) sum += x[k];
+    for (uint32_t k = 0; k < U; ++k) sum += x[k];
+    for (uint32_t r = b0 + U; r < b1; ++r) sum += p[(size_t)r * stride];
+    lds[g * ROW + c] = sum;
+    __syncthreads();
+    {
+        const uint32_t l = threadIdx.x & 63u, w = threadIdx.x >> 6;
+        const uint32_t col = G == 64 ? w : 2 * w + (l >> 5), row = l % G;
+        const uint32_t v = lds[row * ROW + col];
+        uint32_t incl = wave_incl_scan(v);
+        if (G == 32) {
+            const uint32_t low = readlane(incl, 31);
+            incl -= l >= 32u ? low : 0u;
         }
-    lds[g * 33 + c] = sum;
+        lds[row * ROW + col] = incl - v;
+        if (row == G - 1) lds[G * ROW + col] = incl;  // the column's total
+    }
     __syncthreads();
-    uint32_t run = 0;
-#pragma unroll 8
-    for (uint32_t k = 0; k < 32; ++k) run += k < g ? lds[k * 33 + c] : 0u;
-    if (in)
-        for (uint32_t r = b0; r < b1; r += U) {
-            uint32_t x[U];
+    uint32_t run = lds[g * ROW + c];
 #pragma unroll
-            for (uint32_t k = 0; k < U; ++k) x[k] = r + k < b1 ? p[(size_t)(r + k) * ncols] : 0u;
-#pragma unroll
-            for (uint32_t k = 0; k < U; ++k) {
-                if (r + k < b1) p[(size_t)(r + k) * ncols] = run;
-                run += x[k];
-            }
-        }
-    __syncthreads();
-    if (g == 31) lds[c] = in ? run : 0u;
-    __syncthreads();
+    for (uint32_t k = 0; k < U; ++k) {
+        if (b0 + k < b1) p[(size_t)(b0 + k) * stride] = run;
+        run += x[k];
+    }
+    for (uint32_t r = b0 + U; r < b1; ++r) {
+        const uint32_t y = p[(size_t)r * stride];
+        p[(size_t)r * stride] = run;
+        run += y;
+    }
     if (threadIdx.x < 64) {
-        const uint32_t v = threadIdx.x < 32 ? lds[threadIdx.x] : 0u;
+        const uint32_t v = threadIdx.x < CW ? lds[G * ROW + threadIdx.x] : 0u;
         const uint32_t incl = wave_incl_scan(v);
-        if (threadIdx.x < 32 && in) {
+        if (threadIdx.x < CW && in) {
             start_in[c] = incl - v;
             tot[c] = v;
         }
         if (threadIdx.x == 63) *chunk = incl;
     }
+}
+
+// Cost of a unit of the tile placement when `total` is split into about
+// nunits units (at most one more per view), and the units of a view.
+__device__ __forceinline__ uint32_t unit_cost(uint64_t total, uint32_t nunits) {
+    const uint64_t c = (uint64_t)(((double)total + (double)(nunits - 1)) / (double)nunits);
+    return c < TILE_UNIT_MIN ? (uint32_t)TILE_UNIT_MIN : c > 0xffffffffull ? 0xffffffffu : (uint32_t)c;
+}
+__device__ __forceinline__ uint32_t units_for(uint64_t total, uint32_t cost) {
+    return (uint32_t)(((double)total + (double)(cost - 1)) / (double)cost);
 }
 
 // A frame whose depth keys span 2^27 or more (about 16 octaves of depth).
@@ -1298,13 +1326,13 @@ __device__ __forceinline__ bool depth_wide(uint32_t lo, uint32_t hi) {
 // frame's counters and the views' first positions.
 __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewParams* __restrict__ views, int nviews,
                                                       uint32_t nseg, uint32_t nchunks, Counters* cnt, uint32_t cap,
-                                                      bool flag_wide) {
-    __shared__ uint32_t lds[32 * 33];
+                                                      bool flag_wide, uint32_t nunits) {
+    __shared__ uint32_t lds[(1024 / COL_CHUNK + 1) * (COL_CHUNK + 1)];
     if (blockIdx.x < nchunks) {
         const uint32_t c0 = blockIdx.x * COL_CHUNK;
         const int vi = view_of(c0, nviews, [&](int i) { return views[i].bkt_base; });
         const ViewParams& v = views[vi];
-        column_scan(b.rows + v.row_base, v.nseg, v.nbkt, c0 - v.bkt_base, b.start_in + c0, b.tot + c0,
+        column_scan<COL_CHUNK, 16>(b.rows + v.row_base, v.nseg, v.nbkt, v.nbkt, c0 - v.bkt_base, b.start_in + c0, b.tot + c0,
                     b.chunk + blockIdx.x, lds);
         return;
     }
@@ -1320,20 +1348,46 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewPar
         lds[16 + (threadIdx.x >> 6)] = hi;
     }
     __syncthreads();
+    if (threadIdx.x >= 64) return;
+    lo = wave_min(lds[threadIdx.x & 15]);
+    hi = wave_max(lds[16 + (threadIdx.x & 15)]);
+    // a lane per view: their first positions, then their units of the tile
+    // placement
+    uint64_t D = 0, P = 0;
+    uint32_t V = 0, F = 0;
+    for (int i0 = 0; i0 < nviews; i0 += 64) {
+        const int i = i0 + (int)threadIdx.x;
+        uint64_t d = i < nviews ? b.vc[i].dups : 0ull, tl = i < nviews ? b.vc[i].tiles : 0ull;
+        const uint32_t vis = i < nviews ? b.vc[i].visible : 0u, f = i < nviews ? b.vc[i].fallbacks : 0u;
+        const uint32_t incl = wave_incl_scan(vis);
+        if (i < nviews) b.vc[i].start = V + incl - vis;
+        V += readlane(incl, 63);
+        F += wave_sum(f);
+#pragma unroll
+        for (int k = 32; k > 0; k >>= 1) {
+            d += __shfl_xor((unsigned long long)d, k, 64);
+            tl += __shfl_xor((unsigned long long)tl, k, 64);
+        }
+        D += d;
+        P += tl;
+    }
+    const uint32_t uc = unit_cost(D + (uint64_t)TILE_BASE_COST * V, nunits);
+    uint32_t ub = 0;
+    for (int i0 = 0; i0 < nviews; i0 += 64) {
+        const int i = i0 + (int)threadIdx.x;
+        const uint32_t nu =
+            i < nviews ? units_for(b.vc[i].dups + (uint64_t)TILE_BASE_COST * b.vc[i].visible, uc) : 0u;
+        const uint32_t incl = wave_incl_scan(nu);
+        if (i < nviews) {
+            b.vc[i].ubase = ub + incl - nu;
+            b.vc[i].nu = nu;
+            b.vc[i].ucost = uc;
+        }
+        ub += readlane(incl, 63);
+    }
     if (threadIdx.x == 0) {
-        for (int k = 0; k < 16; ++k) {
-            lo = min(lo, lds[k]);
-            hi = max(hi, lds[16 + k]);
-        }
-        uint64_t D = 0;
-        uint32_t V = 0, F = 0;
-        for (int i = 0; i < nviews; ++i) {
-            b.vc[i].start = V;
-            D += b.vc[i].dups;
-            V += b.vc[i].visible;
-            F += b.vc[i].fallbacks;
-        }
         cnt->D = D > 0xffffffffull ? 0xffffffffu : (uint32_t)D;
+        cnt->pairs = P > 0xffffffffull ? 0xffffffffu : (uint32_t)P;
         cnt->visible = V;
         cnt->fallbacks = F;
         cnt->overflow = (D > (uint64_t)cap ? 1u : 0u) | (flag_wide && depth_wide(lo, hi) ? 2u : 0u);
@@ -1458,10 +1512,22 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
     const uint32_t lb = blockIdx.x - v.bkt_base;
     if (lb >= v.nbkt) return;  // uniform: the views' buckets are numbered from multiples of COL_CHUNK
     const uint32_t n = b.tot[blockIdx.x];
-    if (n == 0) return;  // uniform
+    if (n == 0) {  // uniform
+        if (t == 0) b.cost[blockIdx.x] = 0u;
+        return;
+    }
     const uint32_t first = b.vc[vi].start + chunks_before(b.chunk + v.bkt_base / COL_CHUNK, lb / COL_CHUNK) +
                            b.start_in[blockIdx.x];
     const uint4* e = b.elem + first;
+    // the bucket's placement cost, for the units of the tile placement
+    auto store_cost = [&](uint32_t entries) {
+        entries = block_sum<NT>(entries, red);
+        if (t == 0) {
+            const uint32_t c = entries + (uint32_t)TILE_BASE_COST * n;
+            b.cost[blockIdx.x] = c;
+            atomicAdd(&b.ccost[blockIdx.x / COL_CHUNK], (unsigned long long)c);
+        }
+    };
     val += first;
     ext += first;
     if (n <= (uint32_t)CAP) {
@@ -1481,6 +1547,12 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
                 rlo = min(rlo, x.y);
                 rhi = max(rhi, x.y);
             }
+        }
+        {
+            uint32_t entries = 0;
+#pragma unroll
+            for (int k = 0; k < EPT; ++k) entries += (uint32_t)(k * NT + t) < n ? rect_count(rc[k]) : 0u;
+            store_cost(entries);
         }
 #pragma unroll
         for (int k = 0; k < BPT; ++k) bin[k * NT + t] = 0u;
@@ -1584,11 +1656,14 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
         return ((uint64_t)x.x << 32) | x.y;
     };
     uint64_t lo = ~0ull, top = 0ull;
+    uint32_t entries = 0;
     for (uint32_t i = t; i < n; i += NT) {
+        entries += rect_count(e[i].z);
         const uint64_t x = word(i);
         lo = x < lo ? x : lo;
         top = x > top ? x : top;
     }
+    store_cost(entries);
 #pragma unroll
     for (int k = 32; k > 0; k >>= 1) {
         const uint64_t l2 = __shfl_xor((unsigned long long)lo, k, 64), t2 = __shfl_xor((unsigned long long)top, k, 64);
@@ -1896,6 +1971,14 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_downsweep(
     }
 }
 
+// The frame's counters as the host sees them: the entries are counted in tiles,
+// however many of them share a list.
+__device__ __forceinline__ void store_counters(const Counters* cnt, FrameCounters* host_cnt) {
+    FrameCounters c = *cnt;
+    c.D = cnt->pairs;
+    *host_cnt = c;
+}
+
 // ------------------------------------------------------------------ ranges
 
 // Tile boundaries in the sorted tile words; the ranges array was cleared by
@@ -1903,8 +1986,8 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_downsweep(
 // are final here: one thread also stores them to the host-visible block the
 // host reads after the frame (no separate copy).
 __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tile, const Counters* __restrict__ cnt,
-                                                uint32_t cap, uint2* __restrict__ ranges, Counters* host_cnt) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *host_cnt = *cnt;
+                                                uint32_t cap, uint2* __restrict__ ranges, FrameCounters* host_cnt) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) store_counters(cnt, host_cnt);
     const uint32_t D = sort_count(cnt, 0, cap);
     // each wave takes 256 consecutive words per step, four per lane (one
     // 16-byte load); neighbours come from the adjacent lanes, and across the
@@ -1937,23 +2020,107 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ til
     }
 }
 
-// ---------------------------------------------------- binned tile digit
+// ------------------------------------------------------ tile placement
 // The most significant digit of the (tile | depth) key, the tile id, placed
-// by counting instead of by radix passes over the duplicates: the Gaussians
-// arrive in depth order, and entry (g, t) belongs at
+// by counting instead of by radix passes over the duplicates: a view's
+// Gaussians arrive in depth order, and entry (g, t) belongs at
 //   start(t) + #{Gaussians before g, in depth order, whose rectangle holds t}.
-// The count over whole blocks of BIN_BLOCK Gaussians comes from per-block
-// tile histograms (a 2D difference array over the tile grid: +1/-1 at the
-// four corners of each rectangle, then 2D prefix sums) and their prefixes
-// over blocks.  Entries are emitted in their depth-first order, BIN_PAIRS per
-// workgroup (so a few large near Gaussians do not load one workgroup): a
-// workgroup recounts the Gaussians of its block before its first round,
-// and inside a round of 256 Gaussians the waves' column and row ballots give,
-// per tile, the lanes whose rectangles hold it.  Each entry is written
-// straight to its sorted position; the tile ranges fall out of the tile
-// starts.  Single view, tile grid of at most BIN_GRID_MAX cells.
+// The depth order is cut into units of about equal cost (a Gaussian costs its
+// entries plus TILE_BASE_COST), about `nunits` over all views; k_tile_count
+// counts, per unit, the rectangles that hold each tile (a 2D difference grid:
+// +1/-1 at the corners of each rectangle, then 2D prefix sums),
+// k_tile_scan turns the counts into exclusive prefixes over the units, and
+// k_tile_emit writes every entry straight to its sorted position.  A
+// workgroup takes one unit and one group of at most TILE_CELLS cells of the
+// grid (whole tile rows), so that any grid of at most 256 x 256 tiles fits its
+// LDS and a few large near Gaussians are spread over several workgroups.
+// Views of at most 256 x 256 tiles.
+constexpr int TILE_THREADS = 256;
+constexpr int TILE_WAVES = TILE_THREADS / 64;
 
-// Inclusive 2D prefix sums of an h1 x w1 grid (row-major, w1 <= 256) held in
+// Rows of a workgroup's group of tiles, and the number of groups of a view.
+__host__ __device__ __forceinline__ int tile_group_rows(int tiles_x) {
+    return TILE_CELLS / tiles_x < 1 ? 1 : TILE_CELLS / tiles_x;
+}
+
+// The view of unit u, the unit's number in it and the cost of a unit: from
+// the views' totals, or (flat: the radix depth order of a single view) from
+// the frame's counters.
+struct UnitOf {
+    int view;
+    uint32_t u;       // within the view
+    uint32_t nu;      // units of the view
+    uint32_t cost;    // of one unit
+    uint32_t start, visible;
+    uint64_t total;   // cost of the view
+};
+__device__ __forceinline__ bool unit_of(uint32_t u, const TileMem& m, const ViewCount* __restrict__ vc, int nviews,
+                                        const Counters* __restrict__ cnt, bool flat, UnitOf* r) {
+    if (flat) {
+        r->view = 0;
+        r->start = 0;
+        r->visible = cnt->visible;
+        r->total = (uint64_t)cnt->D + (uint64_t)TILE_BASE_COST * cnt->visible;
+        r->cost = unit_cost(r->total, m.nunits);
+        r->nu = units_for(r->total, r->cost);
+        r->u = u;
+        return u < r->nu;
+    }
+    const int vi = view_of(u, nviews, [&](int i) { return vc[i].ubase; });
+    r->view = vi;
+    r->start = vc[vi].start;
+    r->visible = vc[vi].visible;
+    r->total = vc[vi].dups + (uint64_t)TILE_BASE_COST * vc[vi].visible;
+    r->cost = vc[vi].ucost;
+    r->nu = vc[vi].nu;
+    r->u = u - vc[vi].ubase;
+    return r->u < r->nu;
+}
+
+// The position in a view's depth order at cost `t` of the units' split, by one
+// wave: the bucket holding it from the costs of the chunks of buckets, then of
+// the chunk's buckets, and by count inside it (its Gaussians lie at about one
+// depth); `end` when the view costs no more than that.
+__device__ __forceinline__ uint32_t unit_position(uint64_t t, uint32_t end, const BucketMem& b, const ViewParams& v) {
+    const uint32_t l = lane_id();
+    const uint32_t nc = (v.nbkt + COL_CHUNK - 1) / COL_CHUNK, ck0 = v.bkt_base / COL_CHUNK;
+    auto scan64 = [&](unsigned long long x) {
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = __shfl_up(x, o, 64);
+            if ((int)l >= o) x += y;
+        }
+        return x;
+    };
+    const unsigned long long ca = 2 * l < nc ? b.ccost[ck0 + 2 * l] : 0ull;
+    const unsigned long long cb = 2 * l + 1 < nc ? b.ccost[ck0 + 2 * l + 1] : 0ull;
+    const unsigned long long before = scan64(ca + cb) - ca - cb;
+    const uint64_t hit = ballot(t >= before && t < before + ca + cb);
+    if (hit == 0) return end;
+    const int src = __builtin_ctzll(hit);
+    unsigned long long p = __shfl(before, src, 64);
+    const unsigned long long first = __shfl(ca, src, 64);
+    uint32_t ck = 2u * (uint32_t)src;
+    if (t >= p + first) {
+        p += first;
+        ++ck;
+    }
+    const uint32_t base = chunks_before(b.chunk + ck0, ck);
+    const uint32_t bi = ck * COL_CHUNK + l;
+    const bool in = l < COL_CHUNK && bi < v.nbkt;
+    const unsigned long long c = in ? b.cost[v.bkt_base + bi] : 0ull;
+    const unsigned long long cp = p + scan64(c) - c;
+    const bool mine = t >= cp && t < cp + c;
+    uint32_t pos = 0;
+    if (mine) {
+        const uint32_t n = b.tot[v.bkt_base + bi];
+        pos = base + b.start_in[v.bkt_base + bi] + min(n, (uint32_t)((float)(uint32_t)(t - cp) * ((float)n / (float)c)));
+    }
+    const uint64_t mm = ballot(mine);
+    return mm ? readlane(pos, __builtin_ctzll(mm)) : end;
+}
+
+// Inclusive 2D prefix sums of an h1 x w1 grid (row-major, w1 <= 257) held in
 // LDS, by a workgroup of 256 threads: rows (one wave per row, DPP scans), then
 // columns (one thread per column, eight rows in flight).
 __device__ void grid_prefix2d(uint32_t* g, int w1, int h1) {
@@ -1991,249 +2158,70 @@ __device__ void grid_prefix2d(uint32_t* g, int w1, int h1) {
     __syncthreads();
 }
 
-// Adds one packed tile rectangle to the 2D difference grid g (stride w1).
-// Corners in the extra column x = tiles_x or row y = tiles_y are left out:
-// they only affect cells outside the tile grid, which nothing reads (and
-// rectangles clamped to the frame's right or bottom edge would all meet
-// there).
-__device__ __forceinline__ void grid_add_rect(uint32_t* g, int w1, int tiles_x, int tiles_y, uint32_t p) {
-    const int x0 = (int)(p & 0xffu), y0 = (int)((p >> 8) & 0xffu), x1 = (int)((p >> 16) & 0xffu) + 1,
-              y1 = (int)(p >> 24) + 1;
-    atomicAdd(&g[y0 * w1 + x0], 1u);
-    if (x1 < tiles_x) atomicAdd(&g[y0 * w1 + x1], 0xffffffffu);
-    if (y1 < tiles_y) {
-        atomicAdd(&g[y1 * w1 + x0], 0xffffffffu);
-        if (x1 < tiles_x) atomicAdd(&g[y1 * w1 + x1], 1u);
+// Per unit and group of tile rows: how many of the unit's rectangles hold
+// each tile (a row of m.rows).  The unit's range of the depth order is kept
+// for the emission.
+__global__ __launch_bounds__(TILE_THREADS) void k_tile_count(TileMem m, BucketMem b,
+                                                             const ViewParams* __restrict__ views, int nviews,
+                                                             const Counters* __restrict__ cnt, bool flat,
+                                                             const uint32_t* __restrict__ packed) {
+    constexpr int NT = TILE_THREADS;
+    __shared__ uint32_t g[TILE_CELLS + 256];  // (tiles_x + 1) x rows: at most one spare column
+    __shared__ uint32_t range[2];
+    if (cnt->overflow) return;  // uniform
+    UnitOf un;
+    if (!unit_of(blockIdx.x, m, b.vc, nviews, cnt, flat, &un)) return;  // uniform
+    const ViewParams& v = views[un.view];
+    const int tiles_x = v.tiles_x, rpg = tile_group_rows(tiles_x);
+    const int y0g = (int)blockIdx.y * rpg;
+    if (y0g >= v.tiles_y) return;  // uniform
+    const int nr = min(rpg, v.tiles_y - y0g), w1 = tiles_x + 1;
+    const int t = threadIdx.x;
+    for (int c = t; c < w1 * nr; c += NT) g[c] = 0u;
+    if (t < 128) {  // the unit's first and last cost, a wave each
+        const int k = __builtin_amdgcn_readfirstlane(t >> 6);
+        const uint64_t at = ((uint64_t)un.u + (uint64_t)k) * un.cost;
+        uint32_t pos = un.visible;
+        if (at < un.total)
+            pos = flat ? (uint32_t)((double)un.visible * (double)at / (double)un.total)
+                       : unit_position(at, un.visible, b, v);
+        if ((t & 63) == 0) range[k] = pos;
     }
-}
-
-// The rectangles of depth-ordered Gaussians [i0, i1) into the grid.
-__device__ __forceinline__ void grid_add_rects(uint32_t* g, int w1, int tiles_x, int tiles_y,
-                                               const uint32_t* __restrict__ packed, uint32_t i0, uint32_t i1) {
+    __syncthreads();
+    const uint32_t g0 = un.start + range[0], g1 = un.start + max(range[0], range[1]);
+    if (t == 0 && blockIdx.y == 0) m.urange[blockIdx.x] = make_uint2(g0, g1);
     constexpr int U = 8;  // loads in flight per thread
-    for (uint32_t b = i0; b < i1; b += 256 * U) {
+    for (uint32_t i0 = g0; i0 < g1; i0 += NT * U) {
         uint32_t pk[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const uint32_t i = b + (uint32_t)(k * 256) + threadIdx.x;
-            pk[k] = i < i1 ? packed[i] : 0u;
+            const uint32_t i = i0 + (uint32_t)(k * NT + t);
+            pk[k] = i < g1 ? packed[i] : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < U; ++k)
-            if (b + (uint32_t)(k * 256) + threadIdx.x < i1) grid_add_rect(g, w1, tiles_x, tiles_y, pk[k]);
-    }
-}
-
-__device__ __forceinline__ uint32_t bin_valid(const Counters* cnt) { return cnt->overflow ? 0u : cnt->visible; }
-
-// tile id -> (tx, ty) with the FP32 reciprocal of tiles_x, corrected to the
-// exact quotient
-__device__ __forceinline__ void tile_xy(uint32_t t, uint32_t tiles_x, float inv_tx, uint32_t* tx, uint32_t* ty) {
-    uint32_t q = (uint32_t)((float)t * inv_tx);
-    if (q * tiles_x > t) --q;
-    if ((q + 1) * tiles_x <= t) ++q;
-    *ty = q;
-    *tx = t - q * tiles_x;
-}
-
-// Per block of BIN_BLOCK depth-ordered Gaussians: how many of their
-// rectangles hold each tile, and the entry count of each of its rounds of
-// 256 Gaussians.
-__global__ __launch_bounds__(256) void k_bin_hist(const uint32_t* __restrict__ packed, const Counters* __restrict__ cnt,
-                                                  int tiles_x, int tiles_y, uint32_t* __restrict__ hist,
-                                                  uint32_t* __restrict__ round_cnt, uint32_t* __restrict__ blk_tot) {
-    static_assert(BIN_BLOCK == 8 * 256, "a block is eight rounds of 256");
-    __shared__ uint32_t g[BIN_GRID_MAX];
-    __shared__ uint32_t wsum[8][4];
-    const uint32_t V = bin_valid(cnt);
-    const uint32_t b0 = blockIdx.x * BIN_BLOCK;
-    if (b0 >= V) return;  // uniform
-    const int w1 = tiles_x + 1, h1 = tiles_y + 1;
-    for (int c = threadIdx.x; c < w1 * h1; c += 256) g[c] = 0u;
-    uint32_t pk[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t i = b0 + (uint32_t)(k * 256) + threadIdx.x;
-        pk[k] = i < V ? packed[i] : 0u;
+        for (int k = 0; k < U; ++k) {
+            const uint32_t i = i0 + (uint32_t)(k * NT + t);
+            const int x0 = (int)(pk[k] & 0xffu), x1 = (int)((pk[k] >> 16) & 0xffu) + 1;
+            const int ya = max((int)((pk[k] >> 8) & 0xffu) - y0g, 0), yb = min((int)(pk[k] >> 24) - y0g + 1, nr);
+            if (i < g1 && ya < yb) {
+                // corners in the extra column or row only affect cells that
+                // nothing reads (rectangles clamped to the frame's edges
+                // would all meet there)
+                atomicAdd(&g[ya * w1 + x0], 1u);
+                if (x1 < tiles_x) atomicAdd(&g[ya * w1 + x1], 0xffffffffu);
+                if (yb < nr) {
+                    atomicAdd(&g[yb * w1 + x0], 0xffffffffu);
+                    if (x1 < tiles_x) atomicAdd(&g[yb * w1 + x1], 1u);
+                }
+            }
+        }
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const bool in = b0 + (uint32_t)(k * 256) + threadIdx.x < V;
-        if (in) grid_add_rect(g, w1, tiles_x, tiles_y, pk[k]);
-        const uint32_t ws = wave_sum(in ? rect_count(pk[k]) : 0u);
-        if (lane == 0) wsum[k][w] = ws;
-    }
-    __syncthreads();
-    const uint32_t nrounds = (V + 255) / 256;
-    if (threadIdx.x < 8 && blockIdx.x * 8 + threadIdx.x < nrounds) {
-        const int k = threadIdx.x;
-        round_cnt[blockIdx.x * 8 + k] = wsum[k][0] + wsum[k][1] + wsum[k][2] + wsum[k][3];
-    }
-    if (threadIdx.x == 0) {  // the block's entries (its eight rounds)
-        uint32_t b = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) b += wsum[k][0] + wsum[k][1] + wsum[k][2] + wsum[k][3];
-        blk_tot[blockIdx.x] = b;
-    }
-    grid_prefix2d(g, w1, h1);
-    const uint32_t n_tiles = (uint32_t)(tiles_x * tiles_y);
-    const float inv_tx = 1.0f / (float)tiles_x;
-    uint32_t* row = hist + (size_t)blockIdx.x * n_tiles;
-    for (uint32_t t = threadIdx.x; t < n_tiles; t += 256) {
-        uint32_t tx, ty;
-        tile_xy(t, (uint32_t)tiles_x, inv_tx, &tx, &ty);
-        row[t] = g[ty * w1 + tx];
-    }
-}
-
-__device__ __forceinline__ void bin_groups(uint32_t V, uint32_t* nb, uint32_t* bpg) {
-    *nb = (V + BIN_BLOCK - 1) / BIN_BLOCK;
-    *bpg = (*nb + BIN_GROUPS - 1) / BIN_GROUPS;
-}
-
-// Per tile and group of consecutive blocks: the exclusive prefix of the
-// block histograms inside the group (in place) and the group's total.
-__global__ __launch_bounds__(256) void k_bin_prefix(uint32_t* __restrict__ hist, const Counters* __restrict__ cnt,
-                                                    uint32_t n_tiles, uint32_t* __restrict__ gsum) {
-    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= n_tiles) return;
-    uint32_t nb, bpg;
-    bin_groups(bin_valid(cnt), &nb, &bpg);
-    const uint32_t b0 = blockIdx.y * bpg, b1 = min(nb, b0 + bpg);
-    uint32_t run = 0;
-    for (uint32_t b = b0; b < b1; b += 8) {
-        uint32_t h[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) h[k] = b + k < b1 ? hist[(size_t)(b + k) * n_tiles + t] : 0u;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (b + k < b1) hist[(size_t)(b + k) * n_tiles + t] = run;
-            run += h[k];
-        }
-    }
-    gsum[blockIdx.y * n_tiles + t] = run;
-}
-
-// Per tile: the exclusive prefix of the group totals over groups (in place)
-// and the tile's total, stored after the BIN_GROUPS group rows.
-__global__ __launch_bounds__(256) void k_bin_groups(uint32_t* __restrict__ gsum, const Counters* __restrict__ cnt,
-                                                    uint32_t n_tiles, uint32_t* __restrict__ tchunk) {
-    __shared__ uint32_t red[4];
-    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-    const bool in = t < n_tiles;
-    uint32_t nb, bpg;
-    bin_groups(bin_valid(cnt), &nb, &bpg);
-    const uint32_t ng = in && bpg ? (nb + bpg - 1) / bpg : 0u;
-    uint32_t x[BIN_GROUPS];
-#pragma unroll
-    for (int g = 0; g < BIN_GROUPS; ++g) x[g] = (uint32_t)g < ng ? gsum[g * n_tiles + t] : 0u;
-    uint32_t run = 0;
-#pragma unroll
-    for (int g = 0; g < BIN_GROUPS; ++g) {
-        if ((uint32_t)g < ng) gsum[g * n_tiles + t] = run;
-        run += x[g];
-    }
-    if (in) gsum[BIN_GROUPS * n_tiles + t] = run;
-    // the 256 tiles' total, for the tile starts
-    const uint32_t c = block_sum<256>(run, red);
-    if (threadIdx.x == 0) tchunk[blockIdx.x] = c;
-}
-
-// Tile starts and round offsets, each in chunks of 256 (one workgroup per
-// chunk, so that many compute units read the totals the previous kernels
-// wrote): workgroups [0, ntc) take 256 tiles each, starting from the totals
-// of the tile chunks before theirs, and store each tile's start (in the row
-// after the totals) and range; the others take 256 rounds each, starting
-// from the entry totals of the histogram blocks (eight rounds each) before
-// theirs, and store each round's offset and, in start_round, the first round
-// of every emission workgroup.  Workgroup 0 also copies the counters for the
-// host (the frame's counters are final here).
-__global__ __launch_bounds__(256) void k_bin_tiles(uint32_t* __restrict__ gsum, const Counters* __restrict__ cnt,
-                                                   uint32_t n_tiles, uint2* __restrict__ ranges,
-                                                   const uint32_t* __restrict__ round_cnt,
-                                                   uint32_t* __restrict__ round_off, uint32_t* __restrict__ start_round,
-                                                   uint32_t nwg, Counters* host_cnt,
-                                                   const uint32_t* __restrict__ tchunk,
-                                                   const uint32_t* __restrict__ blk_tot) {
-    __shared__ uint32_t red[4];
-    __shared__ unsigned long long red64[4];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *host_cnt = *cnt;
-    const uint32_t V = bin_valid(cnt);
-    if (V == 0) return;  // uniform; the ranges were cleared
-    const uint32_t ntc = (n_tiles + 255) / 256;
-    if (blockIdx.x < ntc) {
-        const uint32_t c = blockIdx.x;
-        const uint32_t before = block_sum<256>(threadIdx.x < c ? tchunk[threadIdx.x] : 0u, red);
-        const uint32_t t = c * 256 + threadIdx.x;
-        const uint32_t tot = t < n_tiles ? gsum[(size_t)BIN_GROUPS * n_tiles + t] : 0u;
-        uint32_t all;
-        const uint32_t start = before + block_excl_scan<256>(tot, red, &all);
-        if (t < n_tiles) {
-            ranges[t] = tot ? make_uint2(start, start + tot) : make_uint2(0u, 0u);
-            gsum[(size_t)(BIN_GROUPS + 1) * n_tiles + t] = start;
-        }
-        return;
-    }
-    const uint32_t k = blockIdx.x - ntc;
-    const uint32_t nrounds = (V + 255) / 256;
-    if (k * 256 >= nrounds) return;  // uniform
-    uint64_t p = 0;
-    for (uint32_t b = threadIdx.x; b < 32 * k; b += 256) p += blk_tot[b];
-    const uint32_t before = (uint32_t)block_sum_u64(p, red64);
-    const uint32_t r = k * 256 + threadIdx.x;
-    const uint32_t x = r < nrounds ? round_cnt[r] : 0u;
-    uint32_t all;
-    const uint32_t o = before + block_excl_scan<256>(x, red, &all);
-    if (r < nrounds) {
-        round_off[r] = o;
-        // workgroups whose first unit falls in round r's cost range
-        const uint64_t c_lo = (uint64_t)o + (uint64_t)BIN_ROUND_COST * r;
-        const uint64_t c_hi = (uint64_t)(o + x) + (uint64_t)BIN_ROUND_COST * (r + 1);
-        for (uint64_t wk = (c_lo + BIN_PAIRS - 1) / BIN_PAIRS; wk < nwg && wk * BIN_PAIRS < c_hi; ++wk)
-            start_round[wk] = r;
-        if (r + 1 == nrounds) round_off[nrounds] = o + x;
-    }
-}
-
-// Inclusive XOR prefix over the 64 lanes of a wave (same lane pattern as
-// wave_incl_scan; lanes without a source see 0, the identity).
-__device__ __forceinline__ uint32_t wave_incl_xor(uint32_t v) {
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
-}
-
-// Lane masks of one wave over the columns (or rows) 0..n-1: bit l of m[x] is
-// set when lane l's interval [lo, hi] holds x.  Each lane toggles its bit at
-// lo and at hi + 1 (m has n + 1 entries, cleared by the caller), and the XOR
-// prefix over x leaves each bit set exactly inside its interval.
-__device__ __forceinline__ void wave_interval_masks(unsigned long long* m, int n, bool valid, int lo, int hi) {
-    const int lane = (int)(threadIdx.x & 63);
-    if (valid) {
-        atomicXor(&m[lo], 1ull << lane);
-        atomicXor(&m[hi + 1], 1ull << lane);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    uint32_t clo = 0, chi = 0;
-    for (int c0 = 0; c0 < n; c0 += 64) {
-        const int x = c0 + lane;
-        const unsigned long long v = x < n ? m[x] : 0ull;
-        const uint32_t slo = wave_incl_xor((uint32_t)v) ^ clo, shi = wave_incl_xor((uint32_t)(v >> 32)) ^ chi;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (x < n) m[x] = ((unsigned long long)shi << 32) | slo;
-        clo = readlane(slo, 63);
-        chi = readlane(shi, 63);
-    }
+    grid_prefix2d(g, w1, nr);
+    uint32_t* row = m.rows + (size_t)blockIdx.x * m.stride + (size_t)y0g * tiles_x;
+    const int lane = t & 63, w = t >> 6;
+    for (int y = w; y < nr; y += TILE_WAVES)
+        for (int x = lane; x < tiles_x; x += 64) row[y * tiles_x + x] = g[y * w1 + x];
 }
 
 // Dense-first dispatch order of a frame's tiles for the blend: tiles by
@@ -2242,269 +2230,349 @@ __device__ __forceinline__ void wave_interval_masks(unsigned long long* m, int n
 // end of the launch instead of long ones running on after the rest are done.
 // Within a bucket the order is whatever the atomics give: every tile's
 // pixels are computed on their own, so the order changes only the timing.
-// One workgroup of NT threads; hist: 64 words of LDS.
 __device__ __forceinline__ uint32_t length_bucket(uint32_t n) {
     const uint32_t x = n + 1u;
     const int msb = 31 - __builtin_clz(x);
     const uint32_t frac = msb >= 2 ? (x >> (msb - 2)) & 3u : (x << (2 - msb)) & 3u;
     return 63u - min(63u, 4u * (uint32_t)msb + frac);
 }
-template <int NT>
-__device__ void tile_order(const uint2* __restrict__ ranges, uint32_t n_tiles, uint32_t* __restrict__ order,
-                           uint32_t* hist) {
-    for (int i = (int)threadIdx.x; i < 64; i += NT) hist[i] = 0u;
+
+// Per chunk of TILE_CHUNK tiles of a view: the exclusive prefixes of the units'
+// counts (in place), the tiles' totals and their prefixes inside the chunk.
+__global__ __launch_bounds__(1024) void k_tile_scan(TileMem m, BucketMem b, const ViewParams* __restrict__ views,
+                                                    int nviews, const Counters* __restrict__ cnt, bool flat) {
+    __shared__ uint32_t lds[(1024 / TILE_CHUNK + 1) * (TILE_CHUNK + 1)];
+    if (cnt->overflow) return;  // uniform
+    const int vi = view_of(blockIdx.x, nviews, [&](int i) { return views[i].tchunk_base; });
+    const ViewParams& v = views[vi];
+    uint32_t ub = 0, nu;
+    if (flat) {
+        UnitOf un;
+        (void)unit_of(0, m, b.vc, nviews, cnt, true, &un);
+        nu = un.nu;
+    } else {
+        ub = b.vc[vi].ubase;
+        nu = b.vc[vi].nu;
+    }
+    const uint32_t n_tiles = (uint32_t)(v.tiles_x * v.tiles_y), c0 = (blockIdx.x - v.tchunk_base) * TILE_CHUNK;
+    column_scan<TILE_CHUNK, 32>(m.rows + (size_t)ub * m.stride, nu, m.stride, n_tiles, c0, m.start_in + v.tile_base + c0,
+                m.tot + v.tile_base + c0, m.chunk + blockIdx.x, lds);
+}
+
+// The emission.  A wave takes the tile rows of its group whose number is its
+// own modulo the wave count, walks the unit's Gaussians 64 at a time and
+// queues those with such a row.  A queue of 64 is placed at once, a lane per
+// Gaussian: every lane sets its bit in the lane mask of each of its tiles
+// (64-bit LDS atomics), and then its rank in a tile is the number of lower
+// bits; the highest one moves the tile's next position on and clears the
+// mask.  Gaussians of many tiles are spread over the lanes.  The first
+// `nfront` workgroups write the ranges (and with `order` the blend's dispatch
+// order) instead; workgroup 0 copies the counters for the host.
+// Bound by latency: a queue is two dependent passes over LDS, and the stores,
+// scattered over the lists, run into the units' neighbours only in one L2
+// (contiguous units per XCD: 72 us at 3M/1080p with a list per tile, spread
+// units 77).  Units of a 1/1536 of the work keep ~6 workgroups of a few queues
+// on each CU: 3M/1080p, count + scan + emission with 512 / 1024 / 1536 / 2048
+// units 92 / 68 / 62 / 65 us.  An LDS counting sort of a unit's entries with
+// coalesced stores took 114 us where this took 72.  With four tiles per list
+// list the placement of 3M/1080p takes 57 us (count 10, scan 12.5, emission 34;
+// rounds of 256 Gaussians scattered into a list per tile: 117 us), that
+// of 3M/4K 57 (two radix passes with duplicates, ranges and order: 305), that
+// of 32 views 0.83 ms (two radix passes: 2.55).  Gaussians of more than 16
+// tiles are spread over the lanes: from 32 on 75 us instead of 72.
+template <bool DEBUG>
+__global__ __launch_bounds__(TILE_THREADS) void k_tile_emit(
+    TileMem m, BucketMem b, const ViewParams* __restrict__ views, int nviews, const Counters* __restrict__ cnt,
+    bool flat, uint32_t nfront, uint32_t nchunks, uint2* __restrict__ ranges, uint32_t* __restrict__ order,
+    FrameCounters* host_cnt, const uint32_t* __restrict__ rec, const uint32_t* __restrict__ packed,
+    uint32_t* __restrict__ val_out, uint32_t* __restrict__ tile_out, uint32_t* __restrict__ depth_out,
+    const uint32_t* __restrict__ zkey) {
+    constexpr int NT = TILE_THREADS, NW = TILE_WAVES;
+    static_assert(NW == 4, "rows modulo four");
+    constexpr int FRONT_CHUNKS = TILE_FRONT_TILES / TILE_CHUNK;
+    constexpr uint32_t MANY = 16;  // tiles from which a Gaussian is spread over the lanes
+    __shared__ unsigned long long mask[TILE_CELLS];
+    __shared__ uint32_t cur[TILE_CELLS];
+    __shared__ uint32_t qp[NW][128], qr[NW][128];
+    __shared__ uint32_t red[NW], cpre[TILE_CELLS / TILE_CHUNK + 2];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const uint32_t ov = cnt->overflow;
+    if (blockIdx.x < nfront) {  // uniform
+        if (blockIdx.y) return;
+        if (blockIdx.x == 0 && t == 0) store_counters(cnt, host_cnt);
+        const uint32_t f0 = blockIdx.x * FRONT_CHUNKS;
+        uint32_t before = 0;
+        if (!ov)
+            for (uint32_t c = t; c < f0; c += NT) before += m.chunk[c];
+        before = block_sum<NT>(before, red);
+        static_assert(FRONT_CHUNKS == 128 && TILE_CELLS >= 256, "two chunks per lane");
+        uint32_t* const cp = cur + 128;      // entries before each chunk
+        uint32_t* const all = cur;           // all tiles per length bucket,
+        uint32_t* const mine = cur + 64;     // those of the workgroups before this one; then the next places
+        if (t < 64) {
+            const uint32_t c = f0 + 2u * t;
+            const uint32_t x = !ov && c < nchunks ? m.chunk[c] : 0u, y = !ov && c + 1 < nchunks ? m.chunk[c + 1] : 0u;
+            const uint32_t ex = before + wave_incl_scan(x + y) - x - y;
+            cp[2 * t] = ex;
+            cp[2 * t + 1] = ex + x;
+            all[t] = mine[t] = 0u;
+        }
+        __syncthreads();
+        constexpr int K = TILE_FRONT_TILES / NT;
+        for (int k = 0; k < K; ++k) {
+            const uint32_t lc = (uint32_t)(k * NT + t) / TILE_CHUNK, c = f0 + lc;
+            if (c >= nchunks) break;
+            const int vi = view_of(c, nviews, [&](int i) { return views[i].tchunk_base; });
+            const ViewParams& v = views[vi];
+            const uint32_t lt = (c - v.tchunk_base) * TILE_CHUNK + (uint32_t)(t & (TILE_CHUNK - 1));
+            if (lt < (uint32_t)(v.tiles_x * v.tiles_y)) {
+                const uint32_t n = ov ? 0u : m.tot[v.tile_base + lt];
+                const uint32_t s = n ? cp[lc] + m.start_in[v.tile_base + lt] : 0u;
+                ranges[v.tile_base + lt] = make_uint2(s, s + n);
+            }
+        }
+        if (!order) return;
+        // the dispatch order of this workgroup's tiles (a single view: tile
+        // ids are chunked without gaps): every front workgroup counts all
+        // tiles' lengths, as contended device atomics cost more (34 us)
+        const uint32_t n_tiles = (uint32_t)(views[0].tiles_x * views[0].tiles_y);
+        const uint32_t o0 = blockIdx.x * TILE_FRONT_TILES, o1 = min(o0 + TILE_FRONT_TILES, n_tiles);
+#pragma unroll 8
+        for (uint32_t i = t; i < n_tiles; i += NT) {
+            const uint32_t bk = length_bucket(ov ? 0u : m.tot[i]);
+            atomicAdd(&all[bk], 1u);
+            if (i < o0) atomicAdd(&mine[bk], 1u);
+        }
+        __syncthreads();
+        if (t < 64) mine[t] += wave_incl_scan(all[t]) - all[t];
+        __syncthreads();
+        for (uint32_t i = o0 + t; i < o1; i += NT)
+            order[atomicAdd(&mine[length_bucket(ov ? 0u : m.tot[i])], 1u)] = i;
+        return;
+    }
+    if (ov) return;  // uniform
+    // XCD x takes a contiguous run of the units: the entries that neighbouring
+    // units write to one tile's list are adjacent and meet in one L2
+    UnitOf un;
+    const uint32_t wg = blockIdx.x - nfront;
+    uint32_t nact;
+    if (flat) {
+        (void)unit_of(0, m, b.vc, nviews, cnt, true, &un);
+        nact = un.nu;
+    } else {
+        nact = b.vc[nviews - 1].ubase + b.vc[nviews - 1].nu;
+    }
+    if (wg >= nact) return;  // uniform
+    const uint32_t unit = (uint32_t)xcd_segment((int)wg, (int)nact);
+    (void)unit_of(unit, m, b.vc, nviews, cnt, flat, &un);
+    const ViewParams& v = views[un.view];
+    const int tiles_x = v.tiles_x, rpg = tile_group_rows(tiles_x), y0g = (int)blockIdx.y * rpg;
+    if (y0g >= v.tiles_y) return;  // uniform
+    const int nr = min(rpg, v.tiles_y - y0g);
+    const uint2 ur = m.urange[unit];
+    const uint32_t ncell = (uint32_t)(nr * tiles_x), tl0 = (uint32_t)(y0g * tiles_x);  // the group's tiles in the view
+    const uint32_t c_first = tl0 / TILE_CHUNK, nc = (tl0 + ncell - 1) / TILE_CHUNK - c_first + 1;
+    {
+        uint32_t before = 0;
+        for (uint32_t c = t; c < v.tchunk_base + c_first; c += NT) before += m.chunk[c];
+        before = block_sum<NT>(before, red);
+        static_assert(TILE_CELLS / TILE_CHUNK + 2 <= 128, "two chunks per lane");
+        if (t < 64) {
+            const uint32_t* ch = m.chunk + v.tchunk_base + c_first;
+            const uint32_t x = 2u * t < nc ? ch[2 * t] : 0u, y = 2u * t + 1 < nc ? ch[2 * t + 1] : 0u;
+            const uint32_t ex = before + wave_incl_scan(x + y) - x - y;
+            if (2u * t < nc) cpre[2 * t] = ex;
+            if (2u * t + 1 < nc) cpre[2 * t + 1] = ex + x;
+        }
+        __syncthreads();
+        const uint32_t* row = m.rows + (size_t)unit * m.stride + tl0;
+        const uint32_t* sin = m.start_in + v.tile_base + tl0;
+#pragma unroll 8
+        for (uint32_t i = t; i < ncell; i += NT) {
+            cur[i] = row[i] + sin[i] + cpre[(tl0 + i) / TILE_CHUNK - c_first];
+            mask[i] = 0ull;
+        }
+    }
     __syncthreads();
-    for (uint32_t t = threadIdx.x; t < n_tiles; t += NT) {
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // this wave's rows of the rectangle p: the first one in the group, and the
+    // last row of the rectangle inside it
+    auto rows_of = [&](uint32_t p, int* first, int* last) {
+        const int ya = max((int)((p >> 8) & 0xffu) - y0g, 0);
+        *first = ya + ((w - ya) & (NW - 1));
+        *last = min((int)(p >> 24) - y0g, nr - 1);
+    };
+    const uint32_t D = cnt->D;
+    auto put = [&](uint32_t cell, uint32_t pos, uint32_t r) {
+        if (pos >= D) return;
+        val_out[pos] = r;
+        if (DEBUG) {
+            tile_out[pos] = v.tile_base + tl0 + cell;
+            depth_out[pos] = zkey[r];
+        }
+    };
+    auto place = [&](uint32_t n) {  // the first n queued Gaussians
+        const bool on = (uint32_t)lane < n;
+        const uint32_t p = on ? qp[w][lane] : 0u, r = on ? qr[w][lane] : 0u;
+        const int x0 = (int)(p & 0xffu), nx = (int)((p >> 16) & 0xffu) - x0 + 1;
+        int f, last;
+        rows_of(p, &f, &last);
+        const int ny = (last - f) / NW + 1;
+        const uint32_t c0 = (uint32_t)(f * tiles_x + x0), nt = on ? (uint32_t)(nx * ny) : 0u;
+        const int skip = NW * tiles_x - nx + 1;  // from a row's last tile to the next row's first
+        const uint64_t bit = 1ull << lane;
+        const uint64_t many = ballot(nt > MANY);
+        {
+            uint32_t c = c0;
+            int x = 0;
+            for (uint32_t k = 0; k < (nt > MANY ? 0u : nt); ++k) {
+                atomicOr(&mask[c], bit);
+                const bool end = ++x == nx;
+                c += end ? (uint32_t)skip : 1u;
+                x = end ? 0 : x;
+            }
+        }
+        for (uint64_t q = many; q; q &= q - 1) {
+            const int l = __builtin_ctzll(q);
+            const uint32_t lc0 = readlane(c0, l), lnt = readlane(nt, l), lnx = readlane((uint32_t)nx, l);
+            const float inv = 1.0f / (float)lnx;
+            for (uint32_t k = lane; k < lnt; k += 64) {
+                uint32_t y = (uint32_t)((float)k * inv);  // k / lnx, corrected
+                if (y * lnx > k) --y;
+                if ((y + 1) * lnx <= k) ++y;
+                atomicOr(&mask[lc0 + y * (uint32_t)(NW * tiles_x) + (k - y * lnx)], 1ull << l);
+            }
+        }
+        wave_sync();
+        // a tile of one Gaussian is settled at once; of several, when all
+        // lanes have read its mask
+        uint32_t later = 0;  // bit k: this lane settles its k-th tile
+        {
+            uint32_t c = c0;
+            int x = 0;
+            for (uint32_t k = 0; k < (nt > MANY ? 0u : nt); ++k) {
+                const uint64_t mm = mask[c];
+                const uint32_t pos = cur[c], rank = bits_below(mm), tot = (uint32_t)__builtin_popcountll(mm);
+                put(c, pos + rank, r);
+                if (tot == 1u) {
+                    cur[c] = pos + 1u;
+                    mask[c] = 0ull;
+                } else if (rank + 1u == tot) {
+                    later |= 1u << k;
+                }
+                const bool end = ++x == nx;
+                c += end ? (uint32_t)skip : 1u;
+                x = end ? 0 : x;
+            }
+        }
+        for (uint64_t q = many; q; q &= q - 1) {
+            const int l = __builtin_ctzll(q);
+            const uint32_t lc0 = readlane(c0, l), lnt = readlane(nt, l), lnx = readlane((uint32_t)nx, l);
+            const uint32_t lr = readlane(r, l);
+            const uint64_t below = (1ull << l) - 1ull;
+            const float inv = 1.0f / (float)lnx;
+            for (uint32_t k = lane; k < lnt; k += 64) {
+                uint32_t y = (uint32_t)((float)k * inv);
+                if (y * lnx > k) --y;
+                if ((y + 1) * lnx <= k) ++y;
+                const uint32_t c = lc0 + y * (uint32_t)(NW * tiles_x) + (k - y * lnx);
+                put(c, cur[c] + (uint32_t)__builtin_popcountll(mask[c] & below), lr);
+            }
+        }
+        wave_sync();
+        for (; later; later &= later - 1) {
+            const uint32_t k = (uint32_t)__builtin_ctz(later);
+            uint32_t y = 0, xk = k;
+            while (xk >= (uint32_t)nx) {
+                xk -= (uint32_t)nx;
+                ++y;
+            }
+            const uint32_t c = c0 + y * (uint32_t)(NW * tiles_x) + xk;
+            cur[c] += (uint32_t)__builtin_popcountll(mask[c]);
+            mask[c] = 0ull;
+        }
+        for (uint64_t q = many; q; q &= q - 1) {
+            const int l = __builtin_ctzll(q);
+            const uint32_t lc0 = readlane(c0, l), lnt = readlane(nt, l), lnx = readlane((uint32_t)nx, l);
+            const float inv = 1.0f / (float)lnx;
+            for (uint32_t k = lane; k < lnt; k += 64) {
+                uint32_t y = (uint32_t)((float)k * inv);
+                if (y * lnx > k) --y;
+                if ((y + 1) * lnx <= k) ++y;
+                const uint32_t c = lc0 + y * (uint32_t)(NW * tiles_x) + (k - y * lnx);
+                // the highest lane of the tile settles it (a tile whose
+                // highest lane is another one is settled by that one)
+                const uint64_t mm = mask[c];
+                if (mm >> l == 1ull) {
+                    cur[c] += (uint32_t)__builtin_popcountll(mm);
+                    mask[c] = 0ull;
+                }
+            }
+            wave_sync();
+        }
+        wave_sync();
+    };
+    uint32_t queued = 0;
+    uint32_t np = 0, nrc = 0;
+    if (ur.x + lane < ur.y) {
+        np = packed[ur.x + lane];
+        nrc = rec[ur.x + lane];
+    }
+    for (uint32_t i0 = ur.x; i0 < ur.y; i0 += 64) {
+        const bool in = i0 + lane < ur.y;
+        const uint32_t p = np, r = nrc;
+        if (i0 + 64 + lane < ur.y) {  // the next ones on their way
+            np = packed[i0 + 64 + lane];
+            nrc = rec[i0 + 64 + lane];
+        }
+        int f, last;
+        rows_of(p, &f, &last);
+        const bool hit = in && f <= last;
+        const uint64_t hm = ballot(hit);
+        if (hit) {
+            const uint32_t s = queued + bits_below(hm);
+            qp[w][s] = p;
+            qr[w][s] = r;
+        }
+        queued += (uint32_t)__builtin_popcountll(hm);
+        if (queued >= 64) {
+            wave_sync();
+            place(64);
+            const uint32_t a = qp[w][64 + lane], c = qr[w][64 + lane];
+            wave_sync();
+            qp[w][lane] = a;
+            qr[w][lane] = c;
+            queued -= 64;
+        }
+    }
+    wave_sync();
+    if (queued) place(queued);
+}
+
+// The dispatch order as a launch of its own, for frames whose ranges come
+// from k_ranges: one workgroup.
+__global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ ranges, uint32_t n_tiles,
+                                                     uint32_t* __restrict__ order) {
+    __shared__ uint32_t hist[64];
+    if (threadIdx.x < 64) hist[threadIdx.x] = 0u;
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < n_tiles; t += 1024) {
         const uint2 r = ranges[t];
         atomicAdd(&hist[length_bucket(r.y - r.x)], 1u);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t acc = 0;
-        for (int b = 0; b < 64; ++b) {
-            const uint32_t c = hist[b];
-            hist[b] = acc;
-            acc += c;
-        }
+    if (threadIdx.x < 64) {
+        const uint32_t c = hist[threadIdx.x];
+        hist[threadIdx.x] = wave_incl_scan(c) - c;
     }
     __syncthreads();
-    for (uint32_t t = threadIdx.x; t < n_tiles; t += NT) {
+    for (uint32_t t = threadIdx.x; t < n_tiles; t += 1024) {
         const uint2 r = ranges[t];
         order[atomicAdd(&hist[length_bucket(r.y - r.x)], 1u)] = t;
-    }
-}
-
-// The same as a launch of its own, for frames whose ranges come from k_ranges.
-__global__ __launch_bounds__(256) void k_tile_order(const uint2* __restrict__ ranges, uint32_t n_tiles,
-                                                    uint32_t* __restrict__ order) {
-    __shared__ uint32_t hist[64];
-    tile_order<256>(ranges, n_tiles, order, hist);
-}
-
-// Writes the entries of the depth-first emission order (Gaussians in depth
-// order, tiles row-major over each rectangle) to their sorted positions:
-// record ids, and with DEBUG also each entry's tile id and depth word; each
-// workgroup takes BIN_PAIRS units of work.  cntr holds, per tile, the
-// position of its next entry; inside a round each entry adds the count of
-// earlier Gaussians of the round that hold its tile (the waves' column and
-// row lane masks), and the round's last Gaussian holding a tile moves that
-// tile's position.  Workgroup 0 writes the blend's dispatch order from the
-// (final) ranges instead, when `order` is given; the others take the
-// emission work.
-template <bool DEBUG>
-__global__ __launch_bounds__(256) void k_bin_emit(const uint2* __restrict__ ranges, uint32_t* __restrict__ order,
-                                                  const uint32_t* __restrict__ sorted_rec,
-                                                  const uint32_t* __restrict__ packed, const Counters* __restrict__ cnt,
-                                                  const uint32_t* __restrict__ hist, const uint32_t* __restrict__ gsum,
-                                                  const uint32_t* __restrict__ round_off,
-                                                  const uint32_t* __restrict__ start_round, int tiles_x, int tiles_y,
-                                                  uint32_t* __restrict__ val_out, uint32_t* __restrict__ tile_out,
-                                                  uint32_t* __restrict__ depth_out,
-                                                  const uint32_t* __restrict__ zkey) {
-    // dynamic LDS sized for the view's grid: column and row lane masks per
-    // wave (one spare entry each for the interval ends), next position per cell
-    extern __shared__ __align__(16) unsigned char bin_smem[];
-    unsigned long long* colm = reinterpret_cast<unsigned long long*>(bin_smem);  // [4][tiles_x + 1]
-    unsigned long long* rowm = colm + 4 * (tiles_x + 1);                         // [4][tiles_y + 1]
-    uint32_t* cntr = reinterpret_cast<uint32_t*>(rowm + 4 * (tiles_y + 1));
-    __shared__ uint32_t red[4], wmax[4], pick;
-    __shared__ uint32_t pre[257], own[256], srec[256], spk[256];
-    __shared__ float sinv[256];
-    if (blockIdx.x == 0) {  // uniform
-        if (order) tile_order<256>(ranges, (uint32_t)(tiles_x * tiles_y), order, pre);
-        return;
-    }
-    const int bid = (int)blockIdx.x - 1;  // the emission workgroup
-    const uint32_t V = bin_valid(cnt);
-    const uint32_t D = cnt->D;
-    if (V == 0) return;  // uniform
-    // Work is split by cost: a round of 256 Gaussians costs its entries plus
-    // BIN_ROUND_COST (its fixed steps), so round r starts at cost
-    // C(r) = round_off[r] + BIN_ROUND_COST r; its first BIN_ROUND_COST units
-    // stand for the fixed steps, the rest for its entries in order.
-    const uint32_t nrounds = (V + 255) / 256;
-    const uint64_t total_cost = (uint64_t)round_off[nrounds] + (uint64_t)BIN_ROUND_COST * nrounds;
-    const uint32_t nact = (uint32_t)((total_cost + BIN_PAIRS - 1) / BIN_PAIRS);
-    if ((uint32_t)bid >= nact) return;  // uniform
-    // XCD x takes a contiguous run of the cost ranges in use: the entries
-    // neighbouring workgroups write to one tile's list are adjacent and meet
-    // in one L2
-    const uint64_t A = (uint64_t)xcd_segment(bid, (int)nact) * BIN_PAIRS;
-    const uint64_t B = min(total_cost, A + BIN_PAIRS);
-    auto cost = [&](uint32_t r) -> uint64_t { return (uint64_t)round_off[r] + (uint64_t)BIN_ROUND_COST * r; };
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    // the round holding cost A (the last r with C(r) <= A)
-    const uint32_t R = start_round[A / BIN_PAIRS];
-    // entered part way (past its fixed steps and first entries), round R is
-    // counted into the start positions and its entries step back by their
-    // tile's count in the round
-    const bool part = A > cost(R) + BIN_ROUND_COST;
-    const uint32_t cb = R * 256 / BIN_BLOCK;
-    uint32_t nb, bpg;
-    bin_groups(V, &nb, &bpg);
-    const uint32_t grp = cb / bpg;
-    const int w1 = tiles_x + 1, h1 = tiles_y + 1, ncell = w1 * h1;
-    const uint32_t n_tiles = (uint32_t)(tiles_x * tiles_y);
-    const float inv_tx = 1.0f / (float)tiles_x;
-    // next positions at the start of round R (of R + 1 when entered part
-    // way): tile starts, block prefixes, and the block's Gaussians before
-    for (int c = threadIdx.x; c < ncell; c += 256) cntr[c] = 0u;
-    __syncthreads();
-    grid_add_rects(cntr, w1, tiles_x, tiles_y, packed, cb * BIN_BLOCK, part ? min(V, R * 256 + 256) : R * 256);
-    __syncthreads();
-    grid_prefix2d(cntr, w1, h1);
-    {
-        const uint32_t* hrow = hist + (size_t)cb * n_tiles;
-        const uint32_t* grow = gsum + (size_t)grp * n_tiles;
-        const uint32_t* srow = gsum + (size_t)(BIN_GROUPS + 1) * n_tiles;
-        constexpr int U = 8;
-        for (uint32_t t0 = 0; t0 < n_tiles; t0 += 256 * U) {
-            uint32_t h[U];
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                const uint32_t t = t0 + (uint32_t)(k * 256) + threadIdx.x;
-                h[k] = t < n_tiles ? hrow[t] + grow[t] + srow[t] : 0u;
-            }
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                const uint32_t t = t0 + (uint32_t)(k * 256) + threadIdx.x;
-                if (t < n_tiles) {
-                    uint32_t tx, ty;
-                    tile_xy(t, (uint32_t)tiles_x, inv_tx, &tx, &ty);
-                    cntr[ty * w1 + tx] += h[k];
-                }
-            }
-        }
-    }
-    __syncthreads();
-    unsigned long long* cw = colm + w * (tiles_x + 1);
-    unsigned long long* rw = rowm + w * (tiles_y + 1);
-    // each round loads the next one's Gaussians ahead
-    uint32_t nx_rec = 0, nx_p = 0;
-    if (R * 256 + threadIdx.x < V) {
-        nx_rec = sorted_rec[R * 256 + threadIdx.x];
-        nx_p = packed[R * 256 + threadIdx.x];
-    }
-    for (uint32_t r = R; r < nrounds; ++r) {
-        const uint64_t cr = cost(r);
-        if (cr >= B) break;  // uniform
-        const uint32_t i = r * 256 + threadIdx.x;
-        const bool valid = i < V;
-        const uint32_t rec = nx_rec, p = nx_p;
-        if (i + 256 < V) {
-            nx_rec = sorted_rec[i + 256];
-            nx_p = packed[i + 256];
-        }
-        uint32_t n = 0;
-        int x0 = 0, y0 = 0, x1 = 0, y1 = 0;
-        if (valid) {
-            x0 = (int)(p & 0xffu);
-            y0 = (int)((p >> 8) & 0xffu);
-            x1 = (int)((p >> 16) & 0xffu);
-            y1 = (int)(p >> 24);
-            n = (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
-        }
-        // this wave's column and row lane masks
-        for (int x = lane; x <= tiles_x; x += 64) cw[x] = 0ull;
-        for (int y = lane; y <= tiles_y; y += 64) rw[y] = 0ull;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        wave_interval_masks(cw, tiles_x, valid, x0, x1);
-        wave_interval_masks(rw, tiles_y, valid, y0, y1);
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan<256>(n, red, &tot);
-        // this workgroup's slots of the round: [js, je)
-        const uint64_t c0 = cr + BIN_ROUND_COST;
-        const uint32_t js = (uint32_t)min((uint64_t)tot, A > c0 ? A - c0 : 0ull);
-        const uint32_t je = (uint32_t)min((uint64_t)tot, B > c0 ? B - c0 : 0ull);
-        const bool first_part = part && r == R;
-        const uint32_t wstart = js & ~255u;
-        pre[threadIdx.x + 1] = ex + n;
-        if (threadIdx.x == 0) {
-            pre[0] = 0;
-            pick = 0u;
-        }
-        own[threadIdx.x] = 0u;
-        srec[threadIdx.x] = rec;
-        spk[threadIdx.x] = p;
-        sinv[threadIdx.x] = valid ? 1.0f / (float)(x1 - x0 + 1) : 0.0f;
-        __syncthreads();
-        // owner of the slot before the first window: the last Gaussian whose
-        // first slot precedes it
-        if (wstart > 0 && n && ex < wstart) atomicMax(&pick, threadIdx.x);
-        __syncthreads();
-        uint32_t carry = pick;
-        // a move of a next position found in a window is applied once every
-        // read of that window is done (after the next barrier)
-        int pend_cell = -1;
-        uint32_t pend_val = 0;
-        // windows of 256 slots: a slot's owner is the last Gaussian whose
-        // first slot is at or before it (round-tagged marks and a prefix
-        // maximum, as in k_duplicate)
-        for (uint32_t j0 = wstart, m = wstart >> 8; j0 < je; j0 += 256, ++m) {
-            if (n && (ex >> 8) == m) own[ex & 255u] = (m << 8) | threadIdx.x;
-            __syncthreads();
-            if (pend_cell >= 0) {
-                cntr[pend_cell] += pend_val;
-                pend_cell = -1;
-            }
-            const uint32_t incl = wave_incl_max(own[threadIdx.x]);
-            if (lane == 63) wmax[w] = incl;
-            __syncthreads();
-            uint32_t o = max(incl, (m << 8) | carry), all = (m << 8) | carry;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const uint32_t xw = wmax[v];
-                if (v < w) o = max(o, xw);
-                all = max(all, xw);
-            }
-            carry = all & 0xffu;
-            const uint32_t j = j0 + threadIdx.x;
-            if (j >= js && j < je) {
-                const uint32_t eo = o & 0xffu;
-                const uint32_t k = j - pre[eo];
-                const uint32_t pk = spk[eo];
-                const uint32_t ex0 = pk & 0xffu, ey0 = (pk >> 8) & 0xffu;
-                const uint32_t nx = ((pk >> 16) & 0xffu) - ex0 + 1u;
-                // k / nx through the FP32 reciprocal, corrected to the exact quotient
-                uint32_t qq = (uint32_t)((float)k * sinv[eo]);
-                if (qq * nx > k) --qq;
-                if ((qq + 1) * nx <= k) ++qq;
-                const int ty = (int)(ey0 + qq), tx = (int)(ex0 + (k - qq * nx));
-                const int we = (int)(eo >> 6), le = (int)(eo & 63u);
-                const unsigned long long below = le == 0 ? 0ull : (~0ull >> (64 - le));
-                uint32_t before = 0, total = 0;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const unsigned long long mm = colm[v * (tiles_x + 1) + tx] & rowm[v * (tiles_y + 1) + ty];
-                    const uint32_t c = (uint32_t)__builtin_popcountll(mm);
-                    total += c;
-                    if (v < we) before += c;
-                    else if (v == we) before += (uint32_t)__builtin_popcountll(mm & below);
-                }
-                const int cell = ty * w1 + tx;
-                const uint32_t pos = cntr[cell] + before - (first_part ? total : 0u);
-                if (pos < D) {
-                    const uint32_t rr = srec[eo];
-                    val_out[pos] = rr;
-                    if (DEBUG) {
-                        tile_out[pos] = (uint32_t)ty * (uint32_t)tiles_x + (uint32_t)tx;
-                        depth_out[pos] = zkey[rr];
-                    }
-                }
-                // the round's last Gaussian holding the tile: no later slot
-                // of the round reads its position
-                if (!first_part && before + 1u == total) {
-                    pend_cell = cell;
-                    pend_val = total;
-                }
-            }
-        }
-        __syncthreads();
-        if (pend_cell >= 0) cntr[pend_cell] += pend_val;
-        if (je < tot) break;  // uniform: the range ends inside this round
-        __syncthreads();
     }
 }
 
@@ -2527,7 +2595,7 @@ struct BlendArgs {
     uint32_t nrec;
     unsigned long long* work;
     int cull;  // drop entries below the skip threshold on the whole block (never changes a pixel)
-    const uint32_t* order;  // dense-first dispatch order of the tiles (null: XCD chunks)
+    const uint32_t* order;  // dense-first dispatch order of the lists of a single view (null: XCD chunks)
 };
 
 // Per-wave LDS slice of staged Gaussians: block-relative centre (u, v of the
@@ -2595,13 +2663,17 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
         int lo = 0, hi = A.nviews - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (A.views[mid].tile_base <= tile) lo = mid; else hi = mid - 1;
+            if (A.views[mid].btile_base <= tile) lo = mid; else hi = mid - 1;
         }
         vi = lo;
     }
     const ViewParams& v = A.views[vi];
-    const uint32_t lt = tile - v.tile_base;
-    const int tx = (int)(lt % (uint32_t)v.tiles_x), ty = (int)(lt / (uint32_t)v.tiles_x);
+    // tiles are numbered list by list, row-major inside a list; those of an
+    // edge list may lie outside the frame and have nothing to do
+    const int ls = v.lx + v.ly;
+    const uint32_t lt = (tile - v.btile_base) >> ls, sub = (tile - v.btile_base) & ((1u << ls) - 1u);
+    const int tx = ((int)(lt % (uint32_t)v.tiles_x) << v.lx) + (int)(sub & ((1u << v.lx) - 1u));
+    const int ty = ((int)(lt / (uint32_t)v.tiles_x) << v.ly) + (int)(sub >> v.lx);
     const int lane = threadIdx.x & 63;
     const int sx = tx * TW + (w % BX) * 8, sy = ty * TH + (w / BX) * 8 * PPL;
     const int px = sx + (lane & 7);
@@ -2619,7 +2691,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
         T[p] = 1.0f;
         cr[p] = cg[p] = cb[p] = 0.0f;
     }
-    const uint2 rg = A.ranges[tile];
+    const uint2 rg = A.ranges[v.tile_base + lt];
     uint32_t n_eval = 0, n_contrib = 0;  // (pixel, Gaussian) evaluations / contributions, COUNT only
     // the wave's block clipped to the image: the only pixels it must cover
     const int bx1 = min(sx + 7, v.width - 1), by1 = min(sy + 8 * PPL - 1, v.height - 1);
@@ -2814,7 +2886,8 @@ __global__ __launch_bounds__(TW* TH / PPL) void k_blend(BlendArgs A) {
     uint32_t tile;
     if (A.order) {
         if (blockIdx.x >= A.n_tiles) return;
-        tile = A.order[blockIdx.x];
+        const int ls = A.views[0].lx + A.views[0].ly;
+        tile = (A.order[blockIdx.x >> ls] << ls) | (blockIdx.x & ((1u << ls) - 1u));
     } else {
         const uint32_t j = blockIdx.x >> 3, x = blockIdx.x & 7;
         tile = ((j / BLEND_CHUNK) * 8u + x) * BLEND_CHUNK + (j % BLEND_CHUNK);
@@ -2985,11 +3058,11 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t* val, uint32_t* ext, hipStream_t st) {
+                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, hipStream_t st) {
     TIGAS_LAUNCH(k_bucket_count, dim3(nseg + nviews), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
                  zl);
     TIGAS_LAUNCH(k_bucket_scan, dim3(nchunks + 1), dim3(1024), st, b, views_dev, nviews, nseg, nchunks, cnt, cap,
-                 flag_wide);
+                 flag_wide, nunits);
     if (nseg == 0) return;
     TIGAS_LAUNCH(k_bucket_scatter, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
                  (const Counters*)cnt);
@@ -3024,10 +3097,10 @@ int launch_sort(const SortBuffers& b, const SortPass* passes, int npasses, int w
 }
 
 void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, hipStream_t st) {
-    if (n_tiles) TIGAS_LAUNCH(k_tile_order, dim3(1), dim3(256), st, ranges, n_tiles, order);
+    if (n_tiles) TIGAS_LAUNCH(k_tile_order, dim3(1), dim3(1024), st, ranges, n_tiles, order);
 }
 
-void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t cap, uint2* ranges, Counters* host_cnt,
+void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t cap, uint2* ranges, FrameCounters* host_cnt,
                    const PreOut& o, const ViewParams* views_dev, hipStream_t st) {
     // one 1024-word step per workgroup at capacity, but no more workgroups
     // than a large frame needs (the capacity may have been sized by a much
@@ -3036,50 +3109,26 @@ void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t ca
                  tile_sorted, cnt, cap, ranges, host_cnt);
 }
 
-uint32_t bin_emit_groups(uint32_t cap, uint32_t nrec) {
-    const uint64_t max_cost = (uint64_t)cap + (uint64_t)BIN_ROUND_COST * ((nrec + 255) / 256);
-    return std::max<uint32_t>(1u, (uint32_t)((max_cost + BIN_PAIRS - 1) / BIN_PAIRS));
-}
-
-bool bin_fits(int tiles_x, int tiles_y) {
-    return tiles_x >= 1 && tiles_y >= 1 && tiles_x <= 255 && tiles_y <= 255 &&
-           (tiles_x + 1) * (tiles_y + 1) <= BIN_GRID_MAX && tiles_x * tiles_y <= BIN_TILES_MAX;
-}
-
-void launch_bin(const uint32_t* sorted_rec, const uint32_t* sorted_packed, const Counters* cnt, uint32_t nrec,
-                uint32_t cap, int tiles_x, int tiles_y, uint32_t* hist, uint32_t* gsum, uint32_t* round_cnt,
-                uint32_t* round_off, uint2* ranges, Counters* host_cnt, const PreOut& o, const ViewParams* views_dev,
-                uint32_t* val_out, uint32_t* tile_out, uint32_t* depth_out, uint32_t* order, hipStream_t st) {
-    const uint32_t n_tiles = (uint32_t)(tiles_x * tiles_y);
-    const uint32_t nbc = std::max<uint32_t>(1u, (nrec + BIN_BLOCK - 1) / BIN_BLOCK);
-    // after the BIN_GROUPS + 2 rows of gsum: the 256-tile chunk totals, the
-    // histogram blocks' entry totals, then the first-round table
-    uint32_t* tchunk = gsum + (size_t)(BIN_GROUPS + 2) * n_tiles;
-    uint32_t* blk_tot = tchunk + BIN_TILES_MAX / 256;
-    uint32_t* start_round = blk_tot + nbc;
-    TIGAS_LAUNCH(k_bin_hist, dim3(nbc), dim3(256), st, sorted_packed, cnt, tiles_x, tiles_y, hist, round_cnt, blk_tot);
-    TIGAS_LAUNCH(k_bin_prefix, dim3((n_tiles + 255) / 256, BIN_GROUPS), dim3(256), st, hist, cnt, n_tiles, gsum);
-    TIGAS_LAUNCH(k_bin_groups, dim3((n_tiles + 255) / 256), dim3(256), st, gsum, cnt, n_tiles, tchunk);
-    // enough emission workgroups for the largest cost the capacities allow
-    const uint32_t nwg = bin_emit_groups(cap, nrec);
-    const uint32_t ntc = (n_tiles + 255) / 256, nrc = std::max<uint32_t>(1u, (nrec + 255) / 256 / 256 + 1);
-    TIGAS_LAUNCH(k_bin_tiles, dim3(ntc + nrc), dim3(256), st, gsum, cnt, n_tiles, ranges, (const uint32_t*)round_cnt,
-                 round_off, start_round, nwg, host_cnt, (const uint32_t*)tchunk, (const uint32_t*)blk_tot);
-    const size_t ncell = (size_t)(tiles_x + 1) * (tiles_y + 1);
-    const size_t lds = 8 * 4 * (size_t)(tiles_x + 1 + tiles_y + 1) + 4 * ncell;
-    // one more workgroup: the blend's dispatch order
+void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
+                  int nviews, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
+                  const uint32_t* packed, uint2* ranges, uint32_t* order, FrameCounters* host_cnt, uint32_t* val_out,
+                  uint32_t* tile_out, uint32_t* depth_out, const uint32_t* zkey, hipStream_t st) {
+    int groups = 1;
+    for (int i = 0; i < nviews; ++i) {
+        const int rpg = tile_group_rows(views_host[i].tiles_x);
+        groups = std::max(groups, (views_host[i].tiles_y + rpg - 1) / rpg);
+    }
+    const uint32_t units = m.nunits + (flat ? 0u : (uint32_t)nviews);
+    const uint32_t nfront = std::max<uint32_t>(1u, (nchunks * TILE_CHUNK + TILE_FRONT_TILES - 1) / TILE_FRONT_TILES);
+    TIGAS_LAUNCH(k_tile_count, dim3(units, groups), dim3(TILE_THREADS), st, m, b, views_dev, nviews, cnt, flat, packed);
+    if (nchunks) TIGAS_LAUNCH(k_tile_scan, dim3(nchunks), dim3(1024), st, m, b, views_dev, nviews, cnt, flat);
+    const uint32_t gx = (nfront + units + 7) / 8 * 8;  // a multiple of the XCDs: a column of the grid stays on one
     if (tile_out)
-        TIGAS_LAUNCH_SHM(k_bin_emit<true>, dim3(nwg + 1), dim3(256), lds, st, (const uint2*)ranges, order, sorted_rec,
-                         sorted_packed, cnt,
-                         (const uint32_t*)hist, (const uint32_t*)gsum, (const uint32_t*)round_off,
-                         (const uint32_t*)start_round, tiles_x, tiles_y, val_out, tile_out, depth_out,
-                         (const uint32_t*)o.zkey);
+        TIGAS_LAUNCH(k_tile_emit<true>, dim3(gx, groups), dim3(TILE_THREADS), st, m, b, views_dev, nviews, cnt, flat,
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, val_out, tile_out, depth_out, zkey);
     else
-        TIGAS_LAUNCH_SHM(k_bin_emit<false>, dim3(nwg + 1), dim3(256), lds, st, (const uint2*)ranges, order,
-                         sorted_rec, sorted_packed, cnt,
-                         (const uint32_t*)hist, (const uint32_t*)gsum, (const uint32_t*)round_off,
-                         (const uint32_t*)start_round, tiles_x, tiles_y, val_out, tile_out, depth_out,
-                         (const uint32_t*)o.zkey);
+        TIGAS_LAUNCH(k_tile_emit<false>, dim3(gx, groups), dim3(TILE_THREADS), st, m, b, views_dev, nviews, cnt, flat,
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, val_out, tile_out, depth_out, zkey);
 }
 
 template <int TW, int TH, int BD, int PPL>

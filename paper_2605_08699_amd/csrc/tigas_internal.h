@@ -28,16 +28,16 @@ constexpr int BUCKET_BINS = 2048;
 constexpr int BUCKET_CDF_WORDS = BUCKET_BINS + 8;  // cumulative counts, smallest and largest sample, shift, scale
 constexpr int BUCKET_SORT_CAP = 4096;
 constexpr int COL_CHUNK = 32;  // columns per workgroup of a column scan
-// Binned tile digit (single view): Gaussians per histogram block (eight
-// rounds of 256), work per emission workgroup (entries, with each round of
-// 256 Gaussians also counting BIN_ROUND_COST), groups of blocks for the
-// prefix, cells of the (tiles_x + 1) x (tiles_y + 1) difference grid, tiles.
-constexpr int BIN_BLOCK = 2048;
-constexpr int BIN_PAIRS = 8192;
-constexpr int BIN_ROUND_COST = 2048;  // fixed steps of a round, in entries
-constexpr int BIN_GROUPS = 32;
-constexpr int BIN_GRID_MAX = 8448;
-constexpr int BIN_TILES_MAX = 8192;
+// Tile placement: cells of the tile grid per workgroup, the units of the depth
+// order per view and at most in all, their smallest cost, a Gaussian's cost
+// besides its entries, tiles per workgroup of the ranges.
+constexpr int TILE_CELLS = 1024;
+constexpr int TILE_UNITS = 1536;
+constexpr int TILE_UNITS_MAX = 49152;
+constexpr int TILE_UNIT_MIN = 4096;
+constexpr int TILE_BASE_COST = 8;
+constexpr int TILE_FRONT_TILES = 2048;
+constexpr int TILE_CHUNK = 16;  // tiles per workgroup of the scan of their counts
 
 // Resident scene (device pointers).  Layout by storage precision:
 //   mean:  f32 planes [3][n] (x, y, z)
@@ -64,8 +64,12 @@ struct ViewParams {
     float fx, fy, cx, cy;
     float lim_x, lim_y;  // Jacobian clamp: 1.3 x the half-FoV tangents
     int width, height;
-    int tile_w, tile_h, tiles_x, tiles_y;
-    uint32_t tile_base;  // first global tile id of this view
+    // Tile lists: 2^lx x 2^ly tiles of 2^tw_log x 2^th_log pixels share one
+    // (a single tile unless the placement is by counting); tiles_x, tiles_y
+    // and tile_base number the lists, btile_base the tiles.  Where the lists
+    // are built, a list is what is called a tile.
+    int tw_log, th_log, lx, ly, tiles_x, tiles_y;
+    uint32_t tile_base, btile_base;
     int sh_degree;
     int fmt;             // 0 RGB8, 1 RGBF32
     float bg[3];
@@ -78,15 +82,22 @@ struct ViewParams {
     uint32_t seg_base, nseg;
     uint32_t bkt_base, nbkt;
     uint64_t row_base;
+    uint32_t tchunk_base;  // tile placement: chunks of TILE_CHUNK tiles of the views before
 };
 
-struct Counters {
+struct FrameCounters {  // as the caller sees them
     uint32_t D;         // duplicates (clamped to 2^32-1)
     uint32_t visible;
     uint32_t fallbacks;
     uint32_t overflow;  // D exceeded the duplicate capacity: nothing was emitted
     uint32_t fb_list;   // append cursor of the FP64-fallback list (cleared once counted)
     uint32_t fb_listed; // entries in the FP64-fallback list this frame
+};
+// On the device D counts list entries, fewer than the (Gaussian, tile) pairs
+// where tiles share a list.
+struct Counters : FrameCounters {
+    uint32_t pairs;
+    uint32_t pad;
 };
 
 // Preprocess outputs, one slot per record (record = view-local index of a
@@ -108,9 +119,10 @@ struct PreOut {
                         // a record is visible when nx ny > 0)
     uint2* srect;       // the visible records' tile rectangles in depth order (last depth pass)
     uint32_t* zkey;     // FP32 depth-key bits
-    uint32_t* blk_sum;  // per 256-record block: tiles touched
+    uint32_t* blk_sum;  // per 256-record block: tile lists touched
     uint32_t* blk_vis;  // per block: records that touch a tile
     uint32_t* blk_fb;   // per block: FP64 fallbacks
+    uint32_t* blk_tiles;  // per block: tiles touched (blk_sum: their lists)
     uint32_t* blk_view; // per block: view index
     unsigned long long* vmask;  // per 64 records: which touch a tile
     uint32_t* sample;           // per 64 records: the depth key of one that does (all ones: none)
@@ -134,10 +146,10 @@ struct SortBuffers {
 
 // Per-view totals of the preprocess.
 struct ViewCount {
-    unsigned long long dups;
+    unsigned long long dups, tiles;  // list entries; (Gaussian, tile) pairs
     uint32_t visible, fallbacks;
-    uint32_t start;  // visible records of the views before
-    uint32_t pad;
+    uint32_t start;             // visible records of the views before
+    uint32_t ubase, nu, ucost;  // units of the tile placement: of the views before, of this one, cost of one
 };
 
 // Scratch of the bucketed depth sort (all views of a launch sequence).
@@ -149,7 +161,20 @@ struct BucketMem {
     uint32_t* chunk;     // per chunk of COL_CHUNK buckets: records
     uint32_t* cdf;       // per view: BUCKET_CDF_WORDS
     uint32_t* segmm;     // [segments][2]: smallest and largest key
+    uint32_t* cost;      // per bucket: its entries and TILE_BASE_COST per record,
+    unsigned long long* ccost;  // and per chunk (cleared each frame)
     ViewCount* vc;       // per view
+};
+
+// Scratch of the tile placement.
+struct TileMem {
+    uint32_t nunits;      // units aimed at; rows holds one more per view
+    uint32_t stride;      // words of a row: the tiles of the largest view
+    uint32_t* rows;       // [units][stride]: counts, then exclusive prefixes over a view's units
+    uint2* urange;        // per unit: its range of the depth order
+    uint32_t* start_in;   // per tile: entries of the tiles before it in its chunk
+    uint32_t* tot;        // per tile: entries
+    uint32_t* chunk;      // per chunk of TILE_CHUNK tiles: entries
 };
 
 // Arrays cleared (as u32 words) by the first kernel after preprocess.
@@ -203,10 +228,10 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 // frame whose depth keys span 2^27 or more sets overflow bit 1 and is left
 // unsorted (the caller renders it again with the four-pass radix sort).
 // seg_len: records per segment; nseg, nchunks: segments and bucket chunks of
-// all views.
+// all views; nunits: of the tile placement that follows.
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t* val, uint32_t* ext, hipStream_t st);
+                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, hipStream_t st);
 // Runs LSD passes over the count selected by `which` (0 duplicates, 1 visible)
 // starting in buffer `start`; returns the buffer index holding the result.
 // With `rect_src`, the last pass also writes rect_src[value] to rect_dst in
@@ -216,26 +241,23 @@ int launch_sort(const SortBuffers& b, const SortPass* passes, int npasses, int w
                 uint2* rect_dst, hipStream_t st);
 // Tile ranges of the sorted list.  host_cnt: pinned host memory (or device
 // memory) that receives a copy of the counters.
-void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t cap, uint2* ranges, Counters* host_cnt,
+void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t cap, uint2* ranges, FrameCounters* host_cnt,
                    const PreOut& o, const ViewParams* views_dev, hipStream_t st);
 // The blend's dense-first dispatch order of n_tiles tiles (longest lists
 // first) from their ranges: order receives a permutation of 0 .. n_tiles-1.
 void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, hipStream_t st);
-// Tile placement by counting (single view, packed rectangles, a tile grid
-// that fits BIN_GRID_MAX / BIN_TILES_MAX): from the depth-ordered records and
-// packed rectangles, writes each (Gaussian, tile) entry's record id to its
-// sorted position in val_out (with tile_out/depth_out, also its tile id and
-// depth word), the tile ranges and the counters to host_cnt.  hist: ceil(nrec / BIN_BLOCK) x tiles words; gsum:
-// (BIN_GROUPS + 2) x tiles words (group rows, tile totals, tile starts) and
-// bin_emit_groups(cap, nrec) more (each emission workgroup's first round);
-// round_cnt / round_off: nrec / 256 + 1 words; cap: the entry capacity.
-// order (may be null): receives the blend's dense-first dispatch order.
-bool bin_fits(int tiles_x, int tiles_y);
-uint32_t bin_emit_groups(uint32_t cap, uint32_t nrec);
-void launch_bin(const uint32_t* sorted_rec, const uint32_t* sorted_packed, const Counters* cnt, uint32_t nrec,
-                uint32_t cap, int tiles_x, int tiles_y, uint32_t* hist, uint32_t* gsum, uint32_t* round_cnt,
-                uint32_t* round_off, uint2* ranges, Counters* host_cnt, const PreOut& o, const ViewParams* views_dev,
-                uint32_t* val_out, uint32_t* tile_out, uint32_t* depth_out, uint32_t* order, hipStream_t st);
+// Tile placement by counting (packed rectangles): from the depth-ordered
+// records and packed rectangles, writes each (Gaussian, tile) entry's record
+// id to its sorted position in val_out (with tile_out/depth_out, also its tile
+// id and depth word), the tile ranges and the counters to host_cnt.  The
+// depth order is the bucketed one (view by view, b filled in by
+// launch_bucket_sort) or, flat, a single view's from the radix passes.
+// nchunks: chunks of TILE_CHUNK tiles over all views.  order (may be null):
+// receives the blend's dense-first dispatch order (a single view).
+void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
+                  int nviews, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
+                  const uint32_t* packed, uint2* ranges, uint32_t* order, FrameCounters* host_cnt, uint32_t* val_out,
+                  uint32_t* tile_out, uint32_t* depth_out, const uint32_t* zkey, hipStream_t st);
 // Baseline JPEGs of RGB8 frames: one workgroup per restart interval of
 // JPEG_SEG_MCUS MCUs, the intervals of up to JPEG_MAX_JOBS frames in one pair
 // of launches.

@@ -295,8 +295,8 @@ class Context:
         _check(lib().tigas_set_graphs(self.handle, 1 if enable else 0))
 
     def set_tile_binning(self, enable: bool):
-        """Single views: tile digit by counting (True, the default) or by radix
-        passes over the duplicates (False); identical lists either way."""
+        """Tile digit by counting (True, the default) or by radix passes over
+        the duplicates (False); identical frames either way."""
         _check(lib().tigas_set_tile_binning(self.handle, int(bool(enable))))
 
     def set_tile_culling(self, enable: bool):

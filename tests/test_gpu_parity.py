@@ -221,6 +221,93 @@ def test_depth_buckets_of_several_views_and_a_culled_one(ctx):
         s.free()
 
 
+def _rect_scene(kind, n):
+    """Gaussians whose tile rectangles meet the placement in different forms."""
+    rng = np.random.default_rng(n + 1)
+    z = rng.uniform(2.0, 6.0, n)
+    size = {"small": 0.004, "wide": 0.25}.get(kind, 0.02)
+    ls = np.repeat(np.log(size * z)[:, None], 3, axis=1) + rng.normal(0.0, 0.3, (n, 3))
+    if kind == "mixed":  # a few, near ones among them, over the whole frame
+        ls[:: max(1, n // 9)] = 1.0
+    xy = rng.uniform(-1.0, 1.0, (n, 2)) * np.array([1.0, 0.6])
+    if kind == "stack":  # all on a few tiles
+        xy = rng.normal(0.0, 0.01, (n, 2))
+    means = np.column_stack([xy[:, 0] * z, xy[:, 1] * z, z])
+    return make_scene(means, ls, None, rng.normal(0.0, 1.0, n), rng.uniform(0.0, 1.0, (n, 3)))
+
+
+@pytest.mark.parametrize("kind", ["small", "wide", "mixed", "stack"])
+@pytest.mark.parametrize("size,tile", [((40, 24), (16, 16)), ((500, 300), (8, 8)), ((1000, 900), (8, 8)),
+                                       ((2048, 40), (8, 8)), ((24, 2048), (8, 8)), ((1100, 700), (16, 32))])
+def test_tile_placement_of_every_grid_form(ctx, size, tile, kind):
+    """Grids of one group of tile rows and of several, of one row or column,
+    of 256 tiles across; rectangles of one tile, of many, and of the whole
+    frame; lists and ranges of the plain 64-bit key sort."""
+    W, H = size
+    n = 700 if kind in ("wide", "mixed") else 6000
+    scene = _rect_scene(kind, n)
+    s = ctx.load_scene(scene)
+    _say("tile placement", size, tile, kind)
+    dbg = ctx.render_debug(s, eye_pose(), intr(max(W, H) / 2.0, W / 2, H / 2), W, H, tile=tile)
+    assert dbg["n_dup"] > 0
+    gc.check_tiles(dbg, *tile)
+    s.free()
+
+
+def test_tile_placement_of_uneven_views_in_one_batch(ctx):
+    """Views of different grids (one, and several groups of tile rows), loads
+    and scenes, one without a Gaussian: each frame is the view's own, with the
+    counting placement and with the radix passes."""
+    a, b = ctx.load_scene(_rect_scene("mixed", 700)), ctx.load_scene(_rect_scene("small", 6000))
+    which, sizes = [a, b, b, a, b], [(1000, 900), (40, 24), (33, 500), (300, 200), (64, 64)]
+    poses = [eye_pose()] * 4 + [synth.Pose(np.eye(3, dtype=np.float32), np.array([0, 0, 50.0], np.float32))]
+    ks = [intr(max(w, h) / 2.0, w / 2, h / 2) for w, h in sizes]
+    for tile in ((8, 8), (16, 32)):
+        got = {}
+        for binning in (True, False):
+            ctx.set_tile_binning(binning)
+            try:
+                got[binning] = ctx.render_batch(which, poses, ks, [w for w, _ in sizes], [h for _, h in sizes],
+                                                fmt="f32", tile=tile, batch_depth=64)
+            finally:
+                ctx.set_tile_binning(True)
+        for i, (w, h) in enumerate(sizes):
+            want = ctx.render(which[i], poses[i], ks[i], w, h, fmt="f32", tile=tile)
+            np.testing.assert_array_equal(got[True][i], want)
+            np.testing.assert_array_equal(got[False][i], want)
+        assert not got[True][4].any()
+    a.free()
+    b.free()
+
+
+@pytest.mark.parametrize("kind", ["small", "mixed"])
+@pytest.mark.parametrize("size,tile", [((512, 512), (16, 16)), ((513, 512), (16, 16)), ((1030, 1030), (16, 16)),
+                                       ((2100, 1300), (8, 8)), ((4096, 24), (8, 8)), ((4104, 24), (8, 8)),
+                                       ((1933, 1083), (16, 32)), ((1083, 1933), (32, 16))])
+def test_tiles_sharing_a_list_give_the_same_frame(ctx, size, tile, kind):
+    """At the limit of one tile per list and beyond, with lists that hang over
+    the frame's edges, the most tiles per list, and a grid too wide for the
+    counting placement even so: the frame of the radix passes, whose tiles
+    have lists of their own."""
+    W, H = size
+    s = ctx.load_scene(_rect_scene(kind, 6000 if kind == "small" else 700))
+    k = intr(max(W, H) / 2.0, W / 2, H / 2)
+    _say("shared lists", size, tile, kind)
+    got, st = {}, {}
+    for binning in (True, False):
+        ctx.set_tile_binning(binning)
+        try:
+            got[binning] = ctx.render(s, eye_pose(), k, W, H, fmt="f32", tile=tile)
+            st[binning] = ctx.stats()
+        finally:
+            ctx.set_tile_binning(True)
+    np.testing.assert_array_equal(got[True], got[False])
+    assert got[True].any()
+    for name in ("duplicates", "tiles", "visible"):
+        assert st[True][name] == st[False][name]
+    s.free()
+
+
 @pytest.mark.parametrize("tile", [(16, 16), (8, 8), (16, 32), (32, 16)])
 def test_culled_tile_lists_bit_exact_and_frames_unchanged(ctx, c1, tile):
     """Tighter tile culling: the lists equal the reference less exactly the
