@@ -103,9 +103,10 @@ typedef struct {
     tigas_format fmt;
     float bg[3];
     int tile_w, tile_h; /* 8x8, 16x16, 16x32 or 32x16; 0x0 = autotuned for the workload's shape */
-    int batch_depth;    /* Gaussians staged per wavefront batch: 64, 128 or 256; 0 = autotuned (64 with an explicit tile) */
-    int pixels_per_lane; /* blend pixels per lane, 1 or 2 (tiles 16 or more tall); 0 = autotuned (1 with an
-                            explicit tile).  Frames are identical for every choice of these three fields. */
+    int batch_depth;    /* 64, 128 or 256; 0 = 64 */
+    int pixels_per_lane; /* 1 or 2 (tiles 16 or more tall); 0 = 1.  These two are accepted and reported in the
+                            statistics; the blend has one form (batches of 64 Gaussians, one pixel per lane).
+                            Frames are identical for every choice of the tile and of these two. */
 } tigas_quality;
 
 /* Output frame.  data: device pointer when is_device, host otherwise;

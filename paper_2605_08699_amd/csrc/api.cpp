@@ -183,13 +183,11 @@ static __device__ __align__(256) unsigned char scratch[TIGAS_NOALLOC_SCRATCH_BYT
 namespace {
 
 struct TileCfg {
-    int tw, th, bd, ppl;  // tile width/height, staged entries per wave batch, pixels per lane
+    int tw, th;   // tile width and height
+    int bd, ppl;  // batch depth and pixels per lane as asked for: the blend has one form of both
 };
 
-const TileCfg kTileCandidates[] = {{8, 8, 64, 1},    {8, 8, 128, 1},   {16, 16, 64, 1},  {16, 16, 128, 1},
-                                   {16, 16, 64, 2},  {16, 16, 128, 2}, {16, 32, 64, 1},  {16, 32, 128, 1},
-                                   {16, 32, 64, 2},  {16, 32, 128, 2}, {32, 16, 64, 1},  {32, 16, 128, 1},
-                                   {32, 16, 64, 2}};
+const TileCfg kTileCandidates[] = {{8, 8, 64, 1}, {16, 16, 64, 1}, {16, 32, 64, 1}, {32, 16, 64, 1}};
 
 // A group of views of one scene inside a launch sequence.
 struct Group {
@@ -429,7 +427,7 @@ struct Workspace {
         cap = std::max<uint32_t>(std::max(cap, dup_cap), 1u << 16);
         for (int i = 0; i < 2; ++i) {
             grow(key[i], (size_t)cap * 4);
-            grow(val[i], (size_t)cap * 4);
+            grow(val[i], (size_t)cap * 4 + 256);  // and a read of 64 entries from the last one
             grow(ext[i], (size_t)cap * 4);
         }
         grow(hist, ((size_t)256 * SORT_MAX_BLOCKS + 256) * 4);  // counts per (digit, segment), then digit totals
@@ -661,19 +659,20 @@ int sort_blocks(uint64_t n) {
 // Tiles that share a list, as powers of two across and down: lists of about
 // the same number however large the frame, so that the entries of the lists,
 // which cost the placement, stay in proportion to what a block of the blend
-// reads of its list.  All kernels of a frame at 1, 2, 4 and 8 tiles of 16x32
-// per list: 1M/720p (1840 tiles) 224 / 225 / 228 / 233 us; 3M/1080p (4080) 467 /
-// 454 / 434 / 443 us; 3M/4K (16320) 898 / 789 / 755 / 741 us; a batch of 32
-// views at 1080p 7.99 / 7.57 / 7.68 / 8.24 ms; 20k/256x256 (128) 108 / 109 /
-// 115 / 129 us.  Tall lists of an even doubling: 32x64 instead of 64x32 costs
-// the counting 2 us less at 3M/1080p.  Frames are the same.
+// reads of its list.  All kernels of a frame with at most 300 / 512 / 1024 /
+// 2048 / 4096 lists a view: 1M/720p 207 / 203 / 205 / 215 / 212 us; 3M/1080p
+// 405 / 391 / 398 / 414 / 450 us; 3M/4K (16 tiles a list at most: 1020 lists)
+// 652 / 644 / 653 / 642 / 671 us; 32 views at 1080p 6.73 / 6.63 / 6.72 / 6.96 /
+// 7.42 ms; 20k/256x256 has 128 tiles, and lists of two cost 1 us.  Tall lists of
+// an even doubling: 32x64 instead of 64x32 costs the counting 2 us less at
+// 3M/1080p.  Frames are the same.
 void list_scale(ViewParams& v, const TileCfg& tc) {
     v.lx = v.ly = 0;
     auto lists = [&] {
         const int64_t w = (int64_t)tc.tw << v.lx, h = (int64_t)tc.th << v.ly;
         return ((v.width + w - 1) / w) * ((v.height + h - 1) / h);
     };
-    while (lists() > 1024 && v.lx + v.ly < 4) {
+    while (lists() > 512 && v.lx + v.ly < 4) {
         if (tc.tw << v.lx < tc.th << v.ly) ++v.lx;
         else ++v.ly;
     }
@@ -686,9 +685,12 @@ void list_scale(ViewParams& v, const TileCfg& tc) {
 void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
     plan.tc = tc;
     plan.n_tiles = plan.n_blend = plan.n_frame_tiles = plan.tchunks = plan.max_tiles = 0;
+    bool cells = shared;
+    for (const Group& g : plan.groups) cells = cells && g.n_pad <= 1u << CELL_REC_BITS;
     for (ViewParams& v : plan.views) {
         v.lx = v.ly = 0;
         if (shared) list_scale(v, tc);
+        v.cells = cells ? 1 : 0;
         v.tw_log = ceil_log2((uint64_t)tc.tw);
         v.th_log = ceil_log2((uint64_t)tc.th);
         const int lw = tc.tw << v.lx, lh = tc.th << v.ly;
@@ -929,11 +931,13 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     // is the same); the tile rectangles travel packed with them when every
     // view has at most 256 x 256 tiles, else the last radix pass gathers them
     const bool packed = packed_rects(plan);
+    const bool bin = use_bin(plan, opt);
+    const bool cells = bin && opt.buckets && !debug && plan.views[0].cells;  // in the entries
     int cv = 0;
     if (opt.buckets && packed) {
         mark(2);
         launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl, m.flag_wide,
-                           plan.nunits, sb.val[0], sb.ext[0], st);
+                           plan.nunits, sb.val[0], sb.ext[0], cells, st);
     } else {
         launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
         mark(2);
@@ -942,7 +946,6 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
                          packed ? nullptr : o.rect, packed ? nullptr : o.srect, st);
     }
     const int cd = cv ^ 1;
-    const bool bin = use_bin(plan, opt);
     if (!bin && opt.cull_tiles && packed) {
         // duplicates in depth order, only for the tiles each Gaussian can reach
         launch_duplicate_culled(o, nblk, sb.val[cv], sb.ext[cv], m.blk_sum2, m.blk_off2, cnt, vdev, plan.tc.tw,
@@ -963,7 +966,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     if (bin) {
         // tile digit by counting, straight from the depth-ordered Gaussians
         launch_tiles(m.tm, m.bk, vdev, plan.views.data(), nv, cnt, !opt.buckets, plan.tchunks, sb.val[cv], sb.ext[cv],
-                     m.ranges, plan.persistent || nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
+                     cells, m.ranges, plan.persistent || nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
                      debug ? sb.key[cd] : nullptr, debug ? sb.ext[cd] : nullptr, o.zkey, st);
         mark(4);
         mark(5);
@@ -977,8 +980,8 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         if (!plan.persistent) launch_tile_order(m.ranges, plan.n_tiles, m.order, st);
         mark(5);
     }
-    launch_blend(vdev, nv, plan.n_blend, m.ranges, sb.val[cur], o, plan.nrec, plan.tc.tw, plan.tc.th, plan.tc.bd,
-                 plan.tc.ppl, work, plan.persistent ? m.queue : nullptr, pblocks, opt.cull,
+    launch_blend(vdev, nv, plan.n_blend, m.ranges, sb.val[cur], o, plan.nrec, plan.tc.tw, plan.tc.th, cells, work,
+                 plan.persistent ? m.queue : nullptr, pblocks, opt.cull,
                  plan.persistent ? nullptr : m.order, st);
     mark(6);
     HIPCHK(hipGetLastError());
@@ -1011,7 +1014,7 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
     std::memcpy(ws.fs().host_views.p, plan.views.data(), sizeof(ViewParams) * plan.views.size());
     if (prof) ws.ensure_events();
     const int pblocks =
-        plan.persistent ? ctx->cus * blend_persistent_occupancy(plan.tc.tw, plan.tc.th, plan.tc.bd, plan.tc.ppl) : 0;
+        plan.persistent ? ctx->cus * blend_persistent_occupancy(plan.tc.tw, plan.tc.th) : 0;
     // stage timing needs events between the launches: that runs uncaptured
     LaunchOptions opt;
     opt.cull = ctx->blend_cull.load();
@@ -1252,7 +1255,7 @@ TileCfg autotune(tigas_context* ctx, Workspace& ws, Plan& plan) {
         if (it != ctx->tuned.end()) return it->second;
     }
     const bool prof = ctx->profile.exchange(false);
-    TileCfg best = kTileCandidates[2];
+    TileCfg best = kTileCandidates[1];
     double best_ms = 1e30;
     for (const TileCfg& tc : kTileCandidates) {
         set_tiles(plan, tc, share_lists(ctx, plan));
@@ -1536,7 +1539,8 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_o
                               "buffers need more than the " + std::to_string(TIGAS_NOALLOC_SCRATCH_BYTES >> 20) +
                                   " MiB scratch array");
     // (whole multiples of 256 bytes: the first four, contiguous, also hold the
-    // bucketed sort's 16-byte elements)
+    // bucketed sort's 16-byte elements; an ext after each val, which may be
+    // read 256 bytes past its end)
     for (uint32_t** p : {&m.key[0], &m.key[1], &m.val[1], &m.ext[1], &m.val[0], &m.ext[0]})
         *p = c.take<uint32_t>(dup_cap * 4);
     m.bk.elem = reinterpret_cast<uint4*>(m.key[0]);

@@ -442,6 +442,13 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
                     bb = make_uint2((uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)x1 | ((uint32_t)y1 << 16));
                     tr = make_uint2((uint32_t)tx0 | ((uint32_t)ty0 << 16),
                                     (uint32_t)(tx1 - tx0 + 1) | ((uint32_t)(ty1 - ty0 + 1) << 16));
+                    if (v.cells) {
+                        // the cells of the pixel box's ends inside its first and last list
+                        const int cw = cell_log(v.tw_log + v.lx), ch = cell_log(v.th_log + v.ly);
+                        const int mx = (1 << (v.tw_log + v.lx - cw)) - 1, my = (1 << (v.th_log + v.ly - ch)) - 1;
+                        tr.x |= ((uint32_t)((x0 >> cw) & mx) << 12) | ((uint32_t)((y0 >> ch) & my) << 28);
+                        tr.y |= ((uint32_t)((x1 >> cw) & mx) << 12) | ((uint32_t)((y1 >> ch) & my) << 28);
+                    }
                 }
             }
             if (touched) {
@@ -723,11 +730,16 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_dups(const uint32_t* __re
 }
 
 // Tile rectangle (tx0 | ty0 << 16, nx | ny << 16) packed into one word as
-// tx0 | ty0 << 8 | tx1 << 16 | ty1 << 24 (views of at most 256 x 256 tiles),
-// and back.
+// tx0 | ty0 << 8 | tx1 << 16 | ty1 << 24 (views of at most 256 x 256 tiles; the
+// top four bits of a half may hold cells), and back.
 __device__ __forceinline__ uint32_t pack_rect(uint2 r) {
-    const uint32_t tx0 = r.x & 0xffffu, ty0 = r.x >> 16;
-    return tx0 | (ty0 << 8) | ((tx0 + (r.y & 0xffffu) - 1u) << 16) | ((ty0 + (r.y >> 16) - 1u) << 24);
+    const uint32_t tx0 = r.x & 0xfffu, ty0 = (r.x >> 16) & 0xfffu;
+    return tx0 | (ty0 << 8) | ((tx0 + (r.y & 0xfffu) - 1u) << 16) | ((ty0 + ((r.y >> 16) & 0xfffu) - 1u) << 24);
+}
+// The cells of the ends of a rectangle of lists, as a byte of 2-bit fields:
+// first column and row (in the first list), last column and row (in the last).
+__device__ __forceinline__ uint32_t rect_cells(uint2 r) {
+    return ((r.x >> 12) & 3u) | (((r.x >> 28) & 3u) << 2) | (((r.y >> 12) & 3u) << 4) | (((r.y >> 28) & 3u) << 6);
 }
 __device__ __forceinline__ uint2 unpack_rect(uint32_t p) {
     const uint32_t tx0 = p & 0xffu, ty0 = (p >> 8) & 0xffu, tx1 = (p >> 16) & 0xffu, ty1 = p >> 24;
@@ -1454,7 +1466,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, 
             if (vis[k]) {
                 const uint32_t i = i0 + (uint32_t)(k * NT + t);
                 const uint32_t pos = atomicAdd(&next[key_bucket(key[k], cdf, m, nbkt)], 1u);
-                b.elem[pos] = make_uint4(key[k], i, pack_rect(rect[k]), 0u);
+                b.elem[pos] = make_uint4(key[k], i, pack_rect(rect[k]), rect_cells(rect[k]) << 24);
             }
     }
 }
@@ -1491,7 +1503,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
                                                                      const ViewParams* __restrict__ views, int nviews,
                                                                      const Counters* __restrict__ cnt,
                                                                      uint32_t* __restrict__ val,
-                                                                     uint32_t* __restrict__ ext) {
+                                                                     uint32_t* __restrict__ ext, bool cells) {
     constexpr int NT = BUCKET_SORT_THREADS, NW = NT / 64, CAP = BUCKET_SORT_CAP, EPT = CAP / NT;
     constexpr int BINS = 2048, BPT = BINS / NT;
     constexpr uint32_t CROWDED = 48;  // a pass over a bin of this size costs about as much as the bitonic sort
@@ -1530,18 +1542,21 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
     };
     val += first;
     ext += first;
+    // with cells, a record is numbered inside its view, below the rectangle's cells
+    const uint32_t rec0 = cells ? v.rec_base : 0u, cmask = cells ? 0xff000000u : 0u;
     if (n <= (uint32_t)CAP) {
-        uint32_t key[EPT], rec[EPT], rc[EPT];
+        uint32_t key[EPT], rec[EPT], rc[EPT], be[EPT];
         uint32_t klo = 0xffffffffu, khi = 0u, rlo = 0xffffffffu, rhi = 0u;
 #pragma unroll
         for (int k = 0; k < EPT; ++k) {
             const uint32_t i = (uint32_t)(k * NT + t);
-            key[k] = rec[k] = rc[k] = 0u;
+            key[k] = rec[k] = rc[k] = be[k] = 0u;
             if (i < n) {
                 const uint4 x = e[i];
                 key[k] = x.x;
                 rec[k] = x.y;
                 rc[k] = x.z;
+                be[k] = x.w;
                 klo = min(klo, x.x);
                 khi = max(khi, x.x);
                 rlo = min(rlo, x.y);
@@ -1632,7 +1647,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
                     const uint32_t q0 = bin[at[k] >> 16], q1 = bin[(at[k] >> 16) + 1];
                     uint32_t pos = q0;
                     for (uint32_t q = q0; q < q1; ++q) pos += arr[q] < me ? 1u : 0u;
-                    val[pos] = rec[k];
+                    val[pos] = (rec[k] - rec0) | (be[k] & cmask);
                     ext[pos] = rc[k];
                 }
             }
@@ -1644,8 +1659,9 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
         bitonic_sort<NT>(arr, n2);
         for (uint32_t i = t; i < n; i += NT) {
             const uint32_t r = (uint32_t)arr[i];
-            val[i] = r;
-            ext[i] = pack_rect(o.rect[r]);
+            const uint2 rr = o.rect[r];
+            val[i] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
+            ext[i] = pack_rect(rr);
         }
         return;
     }
@@ -1721,8 +1737,9 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
         bitonic_sort<NT>(arr, n2);
         for (uint32_t i = t; i < m; i += NT) {
             const uint32_t r = (uint32_t)arr[i];
-            val[done + i] = r;
-            ext[done + i] = pack_rect(o.rect[r]);
+            const uint2 rr = o.rect[r];
+            val[done + i] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
+            ext[done + i] = pack_rect(rr);
         }
         done += m;
         lo = last + 1;
@@ -2285,7 +2302,7 @@ __global__ __launch_bounds__(TILE_THREADS) void k_tile_emit(
     TileMem m, BucketMem b, const ViewParams* __restrict__ views, int nviews, const Counters* __restrict__ cnt,
     bool flat, uint32_t nfront, uint32_t nchunks, uint2* __restrict__ ranges, uint32_t* __restrict__ order,
     FrameCounters* host_cnt, const uint32_t* __restrict__ rec, const uint32_t* __restrict__ packed,
-    uint32_t* __restrict__ val_out, uint32_t* __restrict__ tile_out, uint32_t* __restrict__ depth_out,
+    bool cells, uint32_t* __restrict__ val_out, uint32_t* __restrict__ tile_out, uint32_t* __restrict__ depth_out,
     const uint32_t* __restrict__ zkey) {
     constexpr int NT = TILE_THREADS, NW = TILE_WAVES;
     static_assert(NW == 4, "rows modulo four");
@@ -2419,6 +2436,19 @@ __global__ __launch_bounds__(TILE_THREADS) void k_tile_emit(
         const bool on = (uint32_t)lane < n;
         const uint32_t p = on ? qp[w][lane] : 0u, r = on ? qr[w][lane] : 0u;
         const int x0 = (int)(p & 0xffu), nx = (int)((p >> 16) & 0xffu) - x0 + 1;
+        // with cells: masks of the rectangle's columns (bits 0-3 in its first
+        // list, 8-11 in its last) and rows (4-7, 12-15), all four elsewhere
+        const uint32_t rec = cells ? r & 0xffffffu : r;
+        const uint32_t cm = cells ? ((15u << ((r >> 24) & 3u)) & 15u) | (((15u << ((r >> 26) & 3u)) & 15u) << 4) |
+                                        (((2u << ((r >> 28) & 3u)) - 1u) << 8) | (((2u << (r >> 30)) - 1u) << 12)
+                                  : 0u;
+        const int yt = (int)((p >> 8) & 0xffu) - y0g, yb = (int)(p >> 24) - y0g;
+        auto row_cells = [cells](uint32_t m, int y, int top, int bottom) {
+            return !cells ? 0u : ((y == top ? m >> 4 : 15u) & (y == bottom ? m >> 12 : 15u)) << 28;
+        };
+        auto col_cells = [cells](uint32_t m, int x, int n) {
+            return !cells ? 0u : ((x == 0 ? m : 15u) & (x + 1 == n ? m >> 8 : 15u) & 15u) << 24;
+        };
         int f, last;
         rows_of(p, &f, &last);
         const int ny = (last - f) / NW + 1;
@@ -2453,11 +2483,12 @@ __global__ __launch_bounds__(TILE_THREADS) void k_tile_emit(
         uint32_t later = 0;  // bit k: this lane settles its k-th tile
         {
             uint32_t c = c0;
-            int x = 0;
+            int x = 0, yy = f;
+            uint32_t re = rec | row_cells(cm, yy, yt, yb);
             for (uint32_t k = 0; k < (nt > MANY ? 0u : nt); ++k) {
                 const uint64_t mm = mask[c];
                 const uint32_t pos = cur[c], rank = bits_below(mm), tot = (uint32_t)__builtin_popcountll(mm);
-                put(c, pos + rank, r);
+                put(c, pos + rank, re | col_cells(cm, x, nx));
                 if (tot == 1u) {
                     cur[c] = pos + 1u;
                     mask[c] = 0ull;
@@ -2467,12 +2498,15 @@ __global__ __launch_bounds__(TILE_THREADS) void k_tile_emit(
                 const bool end = ++x == nx;
                 c += end ? (uint32_t)skip : 1u;
                 x = end ? 0 : x;
+                if (end) re = rec | row_cells(cm, yy += NW, yt, yb);
             }
         }
         for (uint64_t q = many; q; q &= q - 1) {
             const int l = __builtin_ctzll(q);
             const uint32_t lc0 = readlane(c0, l), lnt = readlane(nt, l), lnx = readlane((uint32_t)nx, l);
-            const uint32_t lr = readlane(r, l);
+            const uint32_t lr = readlane(rec, l), lcm = readlane(cm, l);
+            const int lf = (int)readlane((uint32_t)f, l), lyt = (int)readlane((uint32_t)yt, l);
+            const int lyb = (int)readlane((uint32_t)yb, l);
             const uint64_t below = (1ull << l) - 1ull;
             const float inv = 1.0f / (float)lnx;
             for (uint32_t k = lane; k < lnt; k += 64) {
@@ -2480,7 +2514,8 @@ __global__ __launch_bounds__(TILE_THREADS) void k_tile_emit(
                 if (y * lnx > k) --y;
                 if ((y + 1) * lnx <= k) ++y;
                 const uint32_t c = lc0 + y * (uint32_t)(NW * tiles_x) + (k - y * lnx);
-                put(c, cur[c] + (uint32_t)__builtin_popcountll(mask[c] & below), lr);
+                put(c, cur[c] + (uint32_t)__builtin_popcountll(mask[c] & below),
+                    lr | row_cells(lcm, lf + (int)y * NW, lyt, lyb) | col_cells(lcm, (int)(k - y * lnx), (int)lnx));
             }
         }
         wave_sync();
@@ -2580,6 +2615,7 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ r
 
 constexpr float ALPHA_MAX = 0.99f;
 constexpr float T_MIN = 1e-4f;
+constexpr float LOG2_ALPHA_MAX = -0.0145f;  // just below log2(0.99)
 
 __device__ __forceinline__ uint8_t to_u8(float x) {
     return (uint8_t)floorf(__builtin_fmaf(fminf(fmaxf(x, 0.0f), 1.0f), 255.0f, 0.5f));
@@ -2590,7 +2626,8 @@ struct BlendArgs {
     int nviews;
     uint32_t n_tiles;
     const uint2* ranges;
-    const uint32_t* vals;
+    const uint32_t* vals;  // the lists: records, or with cells the view's records below masks of cells
+    int cells;
     const Rec* rec;
     uint32_t nrec;
     unsigned long long* work;
@@ -2598,16 +2635,16 @@ struct BlendArgs {
     const uint32_t* order;  // dense-first dispatch order of the lists of a single view (null: XCD chunks)
 };
 
-// Per-wave LDS slice of staged Gaussians: block-relative centre (u, v of the
-// first 8x8 block; v of the second one when a lane owns two pixels), the
-// exponent coefficients and the colour.
-template <int BD>
+// A wave's LDS slice: the list entries whose pixel box meets its block, and the
+// staged Gaussians: at most 7 left from the batch before and 64 new ones,
+// rounded up to whole groups of eight.
 struct Stage {
-    float4 a[64 * BD];  // u_rel, A, r, g   (what the per-pair loop reads)
-    float4 b[64 * BD];  // v_rel0, B, C, L (what the row terms read)
-    float2 c[64 * BD];  // b, v_rel1
+    float4 row[72];    // v relative to the block's origin, B, C, L
+    float4 col[72];    // r, g, b, -1
+    float nu[72];      // minus u relative to the block's origin
+    float4 a[18];      // A, four entries each
+    uint32_t q[128];   // records
 };
-
 
 // Does the Gaussian with exponent e(d) = A dx^2 + B dx dy + C dy^2 + L
 // (negative-definite quadratic part) stay below the skip threshold on the
@@ -2618,8 +2655,11 @@ struct Stage {
 // conservative: it answers yes only with a margin far above the FP32
 // rounding of this bound and of the per-pixel exponent, so a Gaussian it
 // removes would have been skipped at every pixel of the rectangle.
+// *low: the exponent stays below log2(ALPHA_MAX) (with the same margin: a
+// concave quadratic is at most L), so the cap on alpha changes nothing.
 __device__ __forceinline__ bool below_threshold(float A, float B, float C, float L, float dx0, float dx1, float dy0,
-                                                float dy1) {
+                                                float dy1, bool* low) {
+    *low = false;
     if (!(A < 0.0f && C < 0.0f && B * B < 4.0f * A * C)) return false;  // not concave: keep it
     float q = 0.0f;
     if (!(dx0 <= 0.0f && dx1 >= 0.0f && dy0 <= 0.0f && dy1 >= 0.0f)) {
@@ -2639,25 +2679,125 @@ __device__ __forceinline__ bool below_threshold(float A, float B, float C, float
     }
     const float r2 = fmaxf(dx0 * dx0, dx1 * dx1) + fmaxf(dy0 * dy0, dy1 * dy1);
     const float margin = 0.02f + 1e-5f * (fabsf(A) + fabsf(B) + fabsf(C)) * r2;
+    *low = L + margin < LOG2_ALPHA_MAX;
     return q + L < LOG2_ALPHA_MIN - margin;  // false for NaN
 }
 
-// One tile of TW x TH pixels.  Each wave owns a block of 8 x (8 PPL) pixels
-// (PPL pixels per lane, one per stacked 8x8 sub-block); wave w takes block
-// (w mod TW/8, w div TW/8).  The wave walks the tile's depth-sorted list in
-// batches of 64 * BD entries: every lane fetches entries, keeps those whose
-// pixel box meets the wave's block (and, with culling on, whose exponent can
-// reach the skip threshold somewhere on it), compacts them into the wave's
-// LDS slice (ballot + mbcnt) and the 64 lanes then composite them front to
-// back.  Each pixel's operations (and their rounding) are the same for every
-// tile shape and PPL: offsets are taken from the 8x8 sub-block's own origin,
+// One tile of TW x TH pixels.  Each wave owns a block of 8x8 pixels, one per
+// lane; wave w takes block (w mod TW/8, w div TW/8).  It walks its depth-sorted
+// list 64 entries at a time and queues those whose pixel box meets its block;
+// 64 queued ones at a time are fetched whole, those whose exponent can reach
+// the skip threshold somewhere on the block (with culling on) are staged in
+// the wave's LDS slice (ballot + mbcnt), and the 64 lanes composite them front to
+// back in groups of eight, what is left of a group waiting for the next batch.
+// The records of a batch are fetched while the one before is composited.  Each
+// pixel's operations (and their rounding) are the same for every tile shape,
 // and the entries culling drops are ones every pixel of the block skips.  A wave
 // leaves as soon as all of its pixels have terminated; there is no barrier
 // between the waves of a tile.
-template <int TW, int TH, int BD, int PPL, bool COUNT>
-__device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, int w, Stage<BD>& S) {
+//
+// Bound by vector issue, so what has the form of a product with a constant
+// over the block goes to the matrix cores, which run beside it: the
+// v_mfma_f32_4x4x1_16b form is one FMA per element, rounded once, that takes a
+// column of four values (of the lane's own 4x1 block, or of another one by the
+// broadcast controls) against the lane's own value.  Per pair one of them adds
+// the weighted colour and takes the weight from T (rows r, g, b, -1); per four
+// pairs one each forms dx = px - u and spreads A over the lanes and the row
+// terms B dy and C dy^2 + L, which lane l forms for entry l mod 8 and pixel row
+// l / 8, over the lanes of their row.  With A read by a broadcast, that leaves
+// 8 vector instructions per (pixel, Gaussian) pair (9 where alpha may reach
+// ALPHA_MAX) besides 1.75 on the matrix cores, where colour, T, dx, permutes
+// and the test for a stop took 14: 1454 instead of 2157 a wave at 3M/4K, the
+// vector units issuing 92 % of the time.  Eight waves a SIMD need the 64
+// registers of the launch bounds: with 90 (five waves) 602 us at 3M/4K instead
+// of 521.  An entry's cells spare the gather of a box per entry and block, which
+// kept the L1 busy (521 -> 426 us; a wave of 16 tiles' lists looks at 15 lists
+// of 64 entries); pairs of words, with exact blocks, cost the placement more
+// than they save (13 us at 3M/1080p).
+// The launch at 3M/1080p, 3M/4K, 1M/720p and over 32 views: 144, 418, 97 us and
+// 2.39 ms; with lists of the same size before, 170, 497, 110 us and 2.87 ms.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// The staged entries 0 .. whole - 1 of a wave, in groups of eight, on its
+// pixels.  A half group is first composited as if no pixel stopped in it: T only
+// falls, so if no live pixel ends below T_MIN none did.  Else (a pixel stops
+// once: a quarter of the half groups at 3M/1080p) it is composited again with
+// the test at every pair.  A pixel that is done, an alpha below the threshold
+// and a stop have a weight of zero, which leaves the (finite) colour sums and T
+// exactly as they are.
+template <bool CAP, bool COUNT>
+__device__ __forceinline__ void blend_groups(const Stage& S, int lane, float pyr, f32x4 px4, uint32_t cnt,
+                                             uint32_t whole, uint64_t& live, f32x4& acc, uint32_t& n_eval,
+                                             uint32_t& n_contrib) {
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (uint32_t j0 = 0; j0 < whole; j0 += 8) {
+        if (live == 0) break;
+        const uint32_t j = j0 + (uint32_t)(lane & 7);
+        const float4 t = S.row[j];
+        const float nu = S.nu[j];
+        // column of entry k = lanes 4k .. 4k + 3
+        const float col = reinterpret_cast<const float*>(&S.col[j0])[lane & 31];
+        // the row terms: the very products and sums of the per-pixel exponent
+        const float dy = pyr - t.x;
+        const float rp = t.y * dy;
+        const float rq = __builtin_fmaf(t.z * dy, dy, t.w);
+#define TIGAS_ALPHA(I)                                                                                             \
+    const float x##I = __builtin_amdgcn_exp2f(__builtin_fmaf(__builtin_fmaf(a4[I], dx[I], P[I]), dx[I], Q[I]));    \
+    const float y##I = CAP ? fminf(ALPHA_MAX, x##I) : x##I;                                                        \
+    const float al##I = __builtin_amdgcn_inverse_ballot_w64(ballot(y##I >= ALPHA_MIN) & live) ? y##I : 0.0f;
+#define TIGAS_ADD(H, I, C, W) nxt = __builtin_amdgcn_mfma_f32_4x4x1f32(col, W, C, 4, 4 * (H) + (I), 0);
+#define TIGAS_CHECKED(H, I, C)                                                                                     \
+    {                                                                                                              \
+        const float w = al##I * C[3];                                                                              \
+        const uint64_t stop = ballot(C[3] - w < T_MIN) & ballot(al##I != 0.0f) & live;                             \
+        live &= ~stop;                                                                                             \
+        const bool add = __builtin_amdgcn_inverse_ballot_w64(live);                                                \
+        if (COUNT && j0 + 4 * (H) + (I) < cnt) n_contrib += add && al##I != 0.0f ? 1u : 0u;                        \
+        if (COUNT && j0 + 4 * (H) + (I) < cnt)                                                                     \
+            n_eval += __builtin_amdgcn_inverse_ballot_w64(live | stop) ? 1u : 0u;                                  \
+        TIGAS_ADD(H, I, C, add ? w : 0.0f)                                                                         \
+    }
+#define TIGAS_HALF(H)                                                                                              \
+    {                                                                                                              \
+        const f32x4 dx = __builtin_amdgcn_mfma_f32_4x4x1f32(nu, 1.0f, px4, 4, H, 0);                               \
+        const f32x4 P = __builtin_amdgcn_mfma_f32_4x4x1f32(rp, 1.0f, zero, 1, H, 0);                               \
+        const f32x4 Q = __builtin_amdgcn_mfma_f32_4x4x1f32(rq, 1.0f, zero, 1, H, 0);                               \
+        const float4 af = S.a[j0 / 4 + (H)];                                                                       \
+        const f32x4 a4 = {af.x, af.y, af.z, af.w};                                                                 \
+        TIGAS_ALPHA(0)                                                                                             \
+        TIGAS_ALPHA(1)                                                                                             \
+        TIGAS_ALPHA(2)                                                                                             \
+        TIGAS_ALPHA(3)                                                                                             \
+        f32x4 nxt;                                                                                                 \
+        TIGAS_ADD(H, 0, acc, al0 * acc[3])                                                                         \
+        TIGAS_ADD(H, 1, nxt, al1 * nxt[3])                                                                         \
+        TIGAS_ADD(H, 2, nxt, al2 * nxt[3])                                                                         \
+        TIGAS_ADD(H, 3, nxt, al3 * nxt[3])                                                                         \
+        if (ballot(nxt[3] < T_MIN) & live) {                                                                       \
+            TIGAS_CHECKED(H, 0, acc)                                                                               \
+            TIGAS_CHECKED(H, 1, nxt)                                                                               \
+            TIGAS_CHECKED(H, 2, nxt)                                                                               \
+            TIGAS_CHECKED(H, 3, nxt)                                                                               \
+        } else if (COUNT) {                                                                                        \
+            const uint32_t nv = min(4u, cnt - min(cnt, j0 + 4 * (H)));                                             \
+            n_eval += __builtin_amdgcn_inverse_ballot_w64(live) ? nv : 0u;                                         \
+            n_contrib += (al0 != 0.0f) + (al1 != 0.0f) + (al2 != 0.0f) + (al3 != 0.0f);                            \
+        }                                                                                                          \
+        acc = nxt;                                                                                                 \
+    }
+        TIGAS_HALF(0)
+        __builtin_amdgcn_sched_barrier(0);
+        TIGAS_HALF(1)
+#undef TIGAS_HALF
+#undef TIGAS_CHECKED
+#undef TIGAS_ADD
+#undef TIGAS_ALPHA
+    }
+}
+
+template <int TW, int TH, bool COUNT>
+__device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, int w, Stage& S) {
     constexpr int BX = TW / 8;
-    constexpr int BATCH = 64 * BD;
     int vi = 0;
     {
         int lo = 0, hi = A.nviews - 1;
@@ -2675,172 +2815,126 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
     const int tx = ((int)(lt % (uint32_t)v.tiles_x) << v.lx) + (int)(sub & ((1u << v.lx) - 1u));
     const int ty = ((int)(lt / (uint32_t)v.tiles_x) << v.ly) + (int)(sub >> v.lx);
     const int lane = threadIdx.x & 63;
-    const int sx = tx * TW + (w % BX) * 8, sy = ty * TH + (w / BX) * 8 * PPL;
-    const int px = sx + (lane & 7);
+    const int sx = tx * TW + (w % BX) * 8, sy = ty * TH + (w / BX) * 8;
+    const int px = sx + (lane & 7), py = sy + (lane >> 3);
     const float pxr = (float)(lane & 7) + 0.5f, pyr = (float)(lane >> 3) + 0.5f;
-    const float fsx = (float)sx;
-    float fsy[PPL];
-    int py[PPL];
-    bool done[PPL];
-    float T[PPL], cr[PPL], cg[PPL], cb[PPL];
-#pragma unroll
-    for (int p = 0; p < PPL; ++p) {
-        fsy[p] = (float)(sy + 8 * p);
-        py[p] = sy + 8 * p + (lane >> 3);
-        done[p] = !(px < v.width && py[p] < v.height);
-        T[p] = 1.0f;
-        cr[p] = cg[p] = cb[p] = 0.0f;
-    }
-    const uint2 rg = A.ranges[v.tile_base + lt];
+    const float fsx = (float)sx, fsy = (float)sy;
+    const bool inside = px < v.width && py < v.height;
+    // the pixels still compositing, as a wave mask: the per-pair decisions are
+    // combined in scalar registers and applied with one select
+    uint64_t live = ballot(inside);
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 1.0f};  // r, g, b, T
+    const f32x4 px4 = {pxr, pxr, pxr, pxr};
     uint32_t n_eval = 0, n_contrib = 0;  // (pixel, Gaussian) evaluations / contributions, COUNT only
     // the wave's block clipped to the image: the only pixels it must cover
-    const int bx1 = min(sx + 7, v.width - 1), by1 = min(sy + 8 * PPL - 1, v.height - 1);
-
-    for (uint32_t base = rg.x; base < rg.y; base += BATCH) {
-        bool alive = false;
-#pragma unroll
-        for (int p = 0; p < PPL; ++p) alive = alive || !done[p];
-        if (ballot(alive) == 0) break;
-        uint32_t cnt = 0;
-#pragma unroll
-        for (int k = 0; k < BD; ++k) {
-            const uint32_t i = base + (uint32_t)(k * 64 + lane);
-            bool hit = false;
-            uint32_t r = 0;
-            if (i < rg.y) r = A.vals[i];
-            if (i < rg.y && r < A.nrec) {
-                const uint2 b = A.rec[r].bbox;
-                const int x0 = (int)(b.x & 0xffffu), y0 = (int)(b.x >> 16);
-                const int x1 = (int)(b.y & 0xffffu), y1 = (int)(b.y >> 16);
-                hit = !(x1 < sx || x0 > bx1 || y1 < sy || y0 > by1);
-            }
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b1 = a, c2 = a;
-            float u = 0.f, v0 = 0.f;
-            if (hit) {
-                a = A.rec[r].r0;
-                b1 = A.rec[r].r1;
-                c2 = A.rec[r].r2;
-                // pixel centre relative to each 8x8 sub-block origin, hi and lo parts combined here
-                u = (a.x - fsx) + a.z;
-                v0 = (a.y - fsy[0]) + a.w;
-                hit = !(A.cull && below_threshold(b1.x, b1.y, b1.z, b1.w, 0.5f - u, 7.5f - u, 0.5f - v0,
-                                                  (float)(8 * PPL) - 0.5f - v0));
-            }
-            const uint64_t m = ballot(hit);
-            if (hit) {
-                const uint32_t slot = cnt + bits_below(m);
-                S.a[slot] = make_float4(u, b1.x, c2.x, c2.y);
-                S.b[slot] = make_float4(v0, b1.y, b1.z, b1.w);
-                S.c[slot] = make_float2(c2.z, PPL > 1 ? (a.y - fsy[PPL - 1]) + a.w : 0.0f);
-            }
-            cnt += (uint32_t)__builtin_popcountll(m);
-        }
+    const int bx1 = min(sx + 7, v.width - 1), by1 = min(sy + 7, v.height - 1);
+    const uint2 rg = A.ranges[v.tile_base + lt];
+    const uint32_t end = live ? rg.y : rg.x;
+    auto wave_sync = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (PPL == 1) {
-            // Eight entries at a time.  Lane l forms, for entry j0 + l/8 and
-            // pixel row l mod 8, the row terms B dy and C dy^2 + L (the very
-            // products and sums of the per-pixel exponent, so every pixel's
-            // arithmetic is unchanged); the lanes of a row then fetch theirs
-            // with a cross-lane permute, which leaves dx and two FMAs per
-            // (pixel, Gaussian) pair.  The permutes run on every lane.
-            const float yrow = (float)(lane & 7) + 0.5f;
-            for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
-                // the pixels still compositing, as a wave mask: the per-pair
-                // decisions are combined in scalar registers and applied
-                // with one select each
-                uint64_t live = ballot(!done[0]);
-                if (live == 0) break;
-                const uint32_t jg = min(j0 + (uint32_t)(lane >> 3), cnt - 1);
-                const float4 gb = S.b[jg];
-                const float dyg = yrow - gb.x;
-                const float pg = gb.y * dyg;
-                const float qg = __builtin_fmaf(gb.z * dyg, dyg, gb.w);
-                const uint32_t nk = min(8u, cnt - j0);
-                auto pair = [&](uint32_t k) {
-                    const int src = (int)(k * 8) + (lane >> 3);
-                    const float P = __shfl(pg, src, 64);
-                    const float Q = __shfl(qg, src, 64);
-                    // straight-line update (no branches per pair): a pixel
-                    // that is done, or an alpha below the threshold, or a
-                    // stop, leaves the colour and T exactly as they are
-                    const float4 ua = S.a[j0 + k];
-                    const float cz = S.c[j0 + k].x;
-                    const float dx = pxr - ua.x;
-                    const float e = __builtin_fmaf(__builtin_fmaf(ua.y, dx, P), dx, Q);
-                    const float alpha = fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(e));
-                    const float t0 = T[0];
-                    const float at = alpha * t0;
-                    const float tn = t0 - at;
-                    const uint64_t use = ballot(alpha >= ALPHA_MIN) & live;
-                    const uint64_t stop = use & ballot(tn < T_MIN);
-                    const bool acc = __builtin_amdgcn_inverse_ballot_w64(use & ~stop);
-                    if (COUNT) {
-                        n_eval += __builtin_amdgcn_inverse_ballot_w64(live) ? 1u : 0u;
-                        n_contrib += acc ? 1u : 0u;
-                    }
-                    live &= ~stop;
-                    // a weight of zero leaves the (finite) colour sums exactly
-                    // as they are, with one select instead of three
-                    const float wgt = acc ? at : 0.0f;
-                    cr[0] = __builtin_fmaf(wgt, ua.z, cr[0]);
-                    cg[0] = __builtin_fmaf(wgt, ua.w, cg[0]);
-                    cb[0] = __builtin_fmaf(wgt, cz, cb[0]);
-                    T[0] = acc ? tn : t0;
-                };
-                if (nk == 8) {
-                    // a full group: no branch between the pairs, so the
-                    // LDS reads of later pairs are issued ahead
-#pragma unroll
-                    for (uint32_t k = 0; k < 8; ++k) pair(k);
-                } else {
-#pragma unroll
-                    for (uint32_t k = 0; k < 8; ++k) {
-                        if (k >= nk) break;
-                        pair(k);
-                    }
+    };
+    uint32_t base = rg.x, queued = 0;
+    // the cells of the list that hold the block
+    const int lw = v.tw_log + v.lx, lh = v.th_log + v.ly;
+    const uint32_t need = ((1u << 24) << ((sx & ((1 << lw) - 1)) >> cell_log(lw))) |
+                          ((1u << 28) << ((sy & ((1 << lh) - 1)) >> cell_log(lh)));
+    // (the lists' buffers have room for a read of 64 entries from any of them)
+    uint32_t ahead = 0u;
+    auto read = [&] { ahead = (A.vals + base)[lane]; };
+    if (base < end) read();
+    auto scan = [&] {  // until a batch is queued or the list has ended
+        while (queued < 64 && base < end) {
+            uint32_t en = ahead;
+            const uint64_t in = end - base >= 64 ? ~0ull : (1ull << (end - base)) - 1ull;
+            base += 64;
+            if (base < end) read();
+            uint64_t m;
+            if (A.cells) {
+                m = in & ballot((en & need) == need);
+                en = (en & 0xffffffu) + v.rec_base;
+            } else {
+                bool hit = en < A.nrec && __builtin_amdgcn_inverse_ballot_w64(in);
+                if (hit) {
+                    const uint2 b = A.rec[en].bbox;
+                    const int x0 = (int)(b.x & 0xffffu), y0 = (int)(b.x >> 16);
+                    const int x1 = (int)(b.y & 0xffffu), y1 = (int)(b.y >> 16);
+                    hit = !(x1 < sx || x0 > bx1 || y1 < sy || y0 > by1);
                 }
-                done[0] = !__builtin_amdgcn_inverse_ballot_w64(live);
+                m = ballot(hit);
             }
-        } else if (alive) {
-            for (uint32_t j = 0; j < cnt; ++j) {
-                const float4 a = S.a[j];
-                const float4 b = S.b[j];
-                const float2 c = S.c[j];
-                const float dx = pxr - a.x;
-                bool all_done = true;
-#pragma unroll
-                for (int p = 0; p < PPL; ++p) {
-                    const float vrel = p == 0 ? b.x : c.y;
-                    const float dy = pyr - vrel;
-                    const float e = __builtin_fmaf(__builtin_fmaf(a.y, dx, b.y * dy), dx,
-                                                   __builtin_fmaf(b.z * dy, dy, b.w));
-                    const float alpha = fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(e));
-                    if (!done[p]) {
-                        if (COUNT) ++n_eval;
-                        if (alpha >= ALPHA_MIN) {
-                            const float wgt = alpha * T[p];
-                            const float Tn = T[p] - wgt;
-                            if (Tn < T_MIN) {
-                                done[p] = true;
-                            } else {
-                                cr[p] = __builtin_fmaf(wgt, a.z, cr[p]);
-                                cg[p] = __builtin_fmaf(wgt, a.w, cg[p]);
-                                cb[p] = __builtin_fmaf(wgt, c.x, cb[p]);
-                                T[p] = Tn;
-                                if (COUNT) ++n_contrib;
-                            }
-                        }
-                    }
-                    all_done = all_done && done[p];
-                }
-                if (all_done) break;
+            if (__builtin_amdgcn_inverse_ballot_w64(m)) S.q[queued + bits_below(m)] = en;
+            queued += (uint32_t)__builtin_popcountll(m);
+        }
+    };
+    uint32_t nb = 0, rec = 0;  // records fetched, the lane's
+    auto fetch = [&] {  // up to 64 queued records; the others move up
+        wave_sync();
+        nb = min(queued, 64u);
+        queued -= nb;
+        rec = S.q[lane];
+        const uint32_t next = S.q[64 + lane];
+        if ((uint32_t)lane < queued) S.q[lane] = next;
+        wave_sync();
+    };
+    scan();
+    fetch();
+    float* const sa = reinterpret_cast<float*>(S.a);
+    uint32_t left = 0;      // staged, waiting for a whole group
+    uint64_t capped = 0;    // a staged Gaussian's alpha may reach ALPHA_MAX
+    for (;;) {
+        float4 f0 = make_float4(0.f, 0.f, 0.f, 0.f), f1 = f0, f2 = f0;
+        if ((uint32_t)lane < nb && rec < A.nrec) {
+            f0 = A.rec[rec].r0;
+            f1 = A.rec[rec].r1;
+            f2 = A.rec[rec].r2;
+        }
+        // pixel centre relative to the block's origin, hi and lo parts combined here
+        const float u = (f0.x - fsx) + f0.z, v0 = (f0.y - fsy) + f0.w;
+        bool low;
+        const bool below = below_threshold(f1.x, f1.y, f1.z, f1.w, 0.5f - u, 7.5f - u, 0.5f - v0, 7.5f - v0, &low);
+        const bool hit = (uint32_t)lane < nb && !(A.cull && below);
+        const uint64_t m = ballot(hit);
+        capped = (left ? capped : 0) | (m & ~ballot(low));
+        if (hit) {
+            const uint32_t slot = left + bits_below(m);
+            S.nu[slot] = -u;
+            sa[slot] = f1.x;
+            S.row[slot] = make_float4(v0, f1.y, f1.z, f1.w);
+            S.col[slot] = make_float4(f2.x, f2.y, f2.z, -1.0f);
+        }
+        const uint32_t cnt = left + (uint32_t)__builtin_popcountll(m);
+        scan();
+        const bool last = queued == 0;  // uniform
+        if (!last) fetch();
+        uint32_t whole = cnt & ~7u;
+        if (last && whole < cnt) {  // entries that reach no pixel fill the last group
+            whole += 8;
+            const uint32_t slot = cnt + (uint32_t)lane;
+            if (slot < whole) {
+                S.nu[slot] = sa[slot] = 0.0f;
+                S.row[slot] = make_float4(0.0f, 0.0f, 0.0f, -1e30f);
+                S.col[slot] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();
+        if (capped) blend_groups<true, COUNT>(S, lane, pyr, px4, cnt, whole, live, acc, n_eval, n_contrib);
+        else blend_groups<false, COUNT>(S, lane, pyr, px4, cnt, whole, live, acc, n_eval, n_contrib);
+        if (live == 0 || last) break;
+        left = cnt - whole;
+        if (left && whole) {
+            const uint32_t l = (uint32_t)lane & 7u;
+            const float4 t = S.row[whole + l], c = S.col[whole + l];
+            const float nu = S.nu[whole + l], ca = sa[whole + l];
+            if ((uint32_t)lane < left) {
+                S.row[lane] = t;
+                S.col[lane] = c;
+                S.nu[lane] = nu;
+                sa[lane] = ca;
+            }
+        }
+        wave_sync();
     }
     if (COUNT) {
         const uint32_t se = wave_sum(n_eval), sc = wave_sum(n_contrib);
@@ -2849,24 +2943,21 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
             atomicAdd(&A.work[1], (unsigned long long)sc);
         }
     }
-#pragma unroll
-    for (int p = 0; p < PPL; ++p) {
-        if (px < v.width && py[p] < v.height) {
-            const float r = __builtin_fmaf(T[p], v.bg[0], cr[p]);
-            const float g = __builtin_fmaf(T[p], v.bg[1], cg[p]);
-            const float b = __builtin_fmaf(T[p], v.bg[2], cb[p]);
-            const size_t pix = (size_t)py[p] * (size_t)v.width + (size_t)px;
-            if (v.fmt == 1) {
-                float* out = reinterpret_cast<float*>(v.out_ptr) + pix * 3;
-                out[0] = r;
-                out[1] = g;
-                out[2] = b;
-            } else {
-                uint8_t* out = reinterpret_cast<uint8_t*>(v.out_ptr) + pix * 3;
-                out[0] = to_u8(r);
-                out[1] = to_u8(g);
-                out[2] = to_u8(b);
-            }
+    if (inside) {
+        const float r = __builtin_fmaf(acc[3], v.bg[0], acc[0]);
+        const float g = __builtin_fmaf(acc[3], v.bg[1], acc[1]);
+        const float b = __builtin_fmaf(acc[3], v.bg[2], acc[2]);
+        const size_t pix = (size_t)py * (size_t)v.width + (size_t)px;
+        if (v.fmt == 1) {
+            float* out = reinterpret_cast<float*>(v.out_ptr) + pix * 3;
+            out[0] = r;
+            out[1] = g;
+            out[2] = b;
+        } else {
+            uint8_t* out = reinterpret_cast<uint8_t*>(v.out_ptr) + pix * 3;
+            out[0] = to_u8(r);
+            out[1] = to_u8(g);
+            out[2] = to_u8(b);
         }
     }
 }
@@ -2879,10 +2970,10 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
 // Gaussians) meet in the same L2 while every XCD gets a share of every part
 // of the image (dense and sparse regions alike).
 constexpr uint32_t BLEND_CHUNK = 16;
-template <int TW, int TH, int BD, int PPL, bool COUNT>
-__global__ __launch_bounds__(TW* TH / PPL) void k_blend(BlendArgs A) {
-    constexpr int NW = TW * TH / (64 * PPL);
-    __shared__ Stage<BD> stage[NW];
+template <int TW, int TH, bool COUNT>
+__global__ __launch_bounds__(TW* TH, 8) void k_blend(BlendArgs A) {
+    constexpr int NW = TW * TH / 64;
+    __shared__ Stage stage[NW];
     uint32_t tile;
     if (A.order) {
         if (blockIdx.x >= A.n_tiles) return;
@@ -2893,7 +2984,8 @@ __global__ __launch_bounds__(TW* TH / PPL) void k_blend(BlendArgs A) {
         tile = ((j / BLEND_CHUNK) * 8u + x) * BLEND_CHUNK + (j % BLEND_CHUNK);
         if (tile >= A.n_tiles) return;
     }
-    blend_tile<TW, TH, BD, PPL, COUNT>(A, tile, threadIdx.x >> 6, stage[threadIdx.x >> 6]);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    blend_tile<TW, TH, COUNT>(A, tile, w, stage[w]);
 }
 
 // Persistent form for many views of uneven size: a fixed grid of resident
@@ -2902,13 +2994,13 @@ __global__ __launch_bounds__(TW* TH / PPL) void k_blend(BlendArgs A) {
 // moves on to the other bands when its own is drained.  The queue counters are
 // cleared by k_scan_visible each frame; every workgroup exits once all bands
 // are drained.
-template <int TW, int TH, int BD, int PPL>
-__global__ __launch_bounds__(TW* TH / PPL) void k_blend_persistent(BlendArgs A, uint32_t* __restrict__ queue) {
-    constexpr int NW = TW * TH / (64 * PPL);
-    __shared__ Stage<BD> stage[NW];
+template <int TW, int TH>
+__global__ __launch_bounds__(TW* TH, 8) void k_blend_persistent(BlendArgs A, uint32_t* __restrict__ queue) {
+    constexpr int NW = TW * TH / 64;
+    __shared__ Stage stage[NW];
     __shared__ uint32_t next;
     const uint32_t per = (A.n_tiles + 7) / 8;
-    const int home = blockIdx.x & 7;
+    const int home = blockIdx.x & 7, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     for (int k = 0; k < 8; ++k) {
         const int band = (home + k) & 7;
         const uint32_t first = (uint32_t)band * per;
@@ -2920,7 +3012,7 @@ __global__ __launch_bounds__(TW* TH / PPL) void k_blend_persistent(BlendArgs A, 
             const uint32_t tile = next;
             __syncthreads();
             if (tile >= band_end) break;
-            blend_tile<TW, TH, BD, PPL, false>(A, tile, threadIdx.x >> 6, stage[threadIdx.x >> 6]);
+            blend_tile<TW, TH, false>(A, (uint32_t)__builtin_amdgcn_readfirstlane((int)tile), w, stage[w]);
         }
     }
 }
@@ -3058,7 +3150,8 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, hipStream_t st) {
+                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
+                        hipStream_t st) {
     TIGAS_LAUNCH(k_bucket_count, dim3(nseg + nviews), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
                  zl);
     TIGAS_LAUNCH(k_bucket_scan, dim3(nchunks + 1), dim3(1024), st, b, views_dev, nviews, nseg, nchunks, cnt, cap,
@@ -3067,7 +3160,7 @@ void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* v
     TIGAS_LAUNCH(k_bucket_scatter, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
                  (const Counters*)cnt);
     TIGAS_LAUNCH(k_bucket_sort, dim3(nchunks * COL_CHUNK), dim3(BUCKET_SORT_THREADS), st, o, b, views_dev,
-                 nviews, (const Counters*)cnt, val, ext);
+                 nviews, (const Counters*)cnt, val, ext, cells);
 }
 
 int launch_sort(const SortBuffers& b, const SortPass* passes, int npasses, int which, uint32_t cap, int nblocks,
@@ -3111,7 +3204,8 @@ void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t ca
 
 void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
                   int nviews, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
-                  const uint32_t* packed, uint2* ranges, uint32_t* order, FrameCounters* host_cnt, uint32_t* val_out,
+                  const uint32_t* packed, bool cells, uint2* ranges, uint32_t* order,
+                  FrameCounters* host_cnt, uint32_t* val_out,
                   uint32_t* tile_out, uint32_t* depth_out, const uint32_t* zkey, hipStream_t st) {
     int groups = 1;
     for (int i = 0; i < nviews; ++i) {
@@ -3125,76 +3219,48 @@ void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_
     const uint32_t gx = (nfront + units + 7) / 8 * 8;  // a multiple of the XCDs: a column of the grid stays on one
     if (tile_out)
         TIGAS_LAUNCH(k_tile_emit<true>, dim3(gx, groups), dim3(TILE_THREADS), st, m, b, views_dev, nviews, cnt, flat,
-                     nfront, nchunks, ranges, order, host_cnt, rec, packed, val_out, tile_out, depth_out, zkey);
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
     else
         TIGAS_LAUNCH(k_tile_emit<false>, dim3(gx, groups), dim3(TILE_THREADS), st, m, b, views_dev, nviews, cnt, flat,
-                     nfront, nchunks, ranges, order, host_cnt, rec, packed, val_out, tile_out, depth_out, zkey);
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
 }
 
-template <int TW, int TH, int BD, int PPL>
+template <int TW, int TH>
 static void blend_launch(const BlendArgs& A, bool count, uint32_t* queue, int persistent_blocks, hipStream_t st) {
     if (queue) {
-        TIGAS_LAUNCH((k_blend_persistent<TW, TH, BD, PPL>), dim3(persistent_blocks), dim3(TW * TH / PPL), st, A,
-                     queue);
+        TIGAS_LAUNCH((k_blend_persistent<TW, TH>), dim3(persistent_blocks), dim3(TW * TH), st, A, queue);
     } else {
         const uint32_t per_round = 8 * BLEND_CHUNK;  // one chunk for every XCD
         const uint32_t tiles = ((A.n_tiles + per_round - 1) / per_round) * per_round;
         const dim3 grid(tiles);
-        if (count) TIGAS_LAUNCH((k_blend<TW, TH, BD, PPL, true>), grid, dim3(TW * TH / PPL), st, A);
-        else TIGAS_LAUNCH((k_blend<TW, TH, BD, PPL, false>), grid, dim3(TW * TH / PPL), st, A);
-    }
-}
-
-template <int TW, int TH, int PPL>
-static void blend_bd(int bd, const BlendArgs& A, bool count, uint32_t* queue, int pb, hipStream_t st) {
-    switch (bd) {
-        case 128: blend_launch<TW, TH, 2, PPL>(A, count, queue, pb, st); break;
-        case 256: blend_launch<TW, TH, 4, PPL>(A, count, queue, pb, st); break;
-        default: blend_launch<TW, TH, 1, PPL>(A, count, queue, pb, st); break;
+        if (count) TIGAS_LAUNCH((k_blend<TW, TH, true>), grid, dim3(TW * TH), st, A);
+        else TIGAS_LAUNCH((k_blend<TW, TH, false>), grid, dim3(TW * TH), st, A);
     }
 }
 
 void launch_blend(const ViewParams* views_dev, int nviews, uint32_t n_tiles, const uint2* ranges,
-                  const uint32_t* vals, const PreOut& o, uint32_t nrec, int tile_w, int tile_h, int batch_depth,
-                  int ppl, unsigned long long* work, uint32_t* queue, int persistent_blocks, bool cull,
+                  const uint32_t* vals, const PreOut& o, uint32_t nrec, int tile_w, int tile_h,
+                  bool cells, unsigned long long* work, uint32_t* queue, int persistent_blocks, bool cull,
                   const uint32_t* order, hipStream_t st) {
     if (n_tiles == 0) return;
-    const BlendArgs A{views_dev, nviews, n_tiles, ranges, vals, o.rec, nrec, work, cull ? 1 : 0, order};
+    const BlendArgs A{views_dev, nviews, n_tiles, ranges, vals, cells ? 1 : 0, o.rec, nrec, work, cull ? 1 : 0, order};
     const bool count = work != nullptr;
     if (count) queue = nullptr;
-    const bool two = ppl == 2 && tile_h >= 16;
-    if (tile_w == 8 && tile_h == 8) blend_bd<8, 8, 1>(batch_depth, A, count, queue, persistent_blocks, st);
-    else if (tile_w == 16 && tile_h == 32) {
-        if (two) blend_bd<16, 32, 2>(batch_depth, A, count, queue, persistent_blocks, st);
-        else blend_bd<16, 32, 1>(batch_depth, A, count, queue, persistent_blocks, st);
-    } else if (tile_w == 32 && tile_h == 16) {
-        if (two) blend_bd<32, 16, 2>(batch_depth, A, count, queue, persistent_blocks, st);
-        else blend_bd<32, 16, 1>(batch_depth, A, count, queue, persistent_blocks, st);
-    } else {
-        if (two) blend_bd<16, 16, 2>(batch_depth, A, count, queue, persistent_blocks, st);
-        else blend_bd<16, 16, 1>(batch_depth, A, count, queue, persistent_blocks, st);
-    }
+    if (tile_w == 8 && tile_h == 8) blend_launch<8, 8>(A, count, queue, persistent_blocks, st);
+    else if (tile_w == 16 && tile_h == 32) blend_launch<16, 32>(A, count, queue, persistent_blocks, st);
+    else if (tile_w == 32 && tile_h == 16) blend_launch<32, 16>(A, count, queue, persistent_blocks, st);
+    else blend_launch<16, 16>(A, count, queue, persistent_blocks, st);
 }
 
-// Resident workgroups per CU of the persistent blend kernel for a configuration.
-int blend_persistent_occupancy(int tile_w, int tile_h, int batch_depth, int ppl) {
+// Resident workgroups per CU of the persistent blend kernel for a tile shape.
+int blend_persistent_occupancy(int tile_w, int tile_h) {
     int n = 0;
-    const int bd = batch_depth == 128 ? 2 : (batch_depth == 256 ? 4 : 1);
-    const bool two = ppl == 2 && tile_h >= 16;
-#define TIGAS_OCC3(TW, TH, P)                                                                                       \
-    do {                                                                                                           \
-        if (bd == 1) (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_blend_persistent<TW, TH, 1, P>,       \
-                                                                         TW * TH / P, 0);                          \
-        else if (bd == 2) (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_blend_persistent<TW, TH, 2, P>,  \
-                                                                              TW * TH / P, 0);                     \
-        else (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_blend_persistent<TW, TH, 4, P>, TW * TH / P,  \
-                                                                 0);                                               \
-    } while (0)
-    if (tile_w == 8 && tile_h == 8) TIGAS_OCC3(8, 8, 1);
-    else if (tile_w == 16 && tile_h == 32) { if (two) TIGAS_OCC3(16, 32, 2); else TIGAS_OCC3(16, 32, 1); }
-    else if (tile_w == 32 && tile_h == 16) { if (two) TIGAS_OCC3(32, 16, 2); else TIGAS_OCC3(32, 16, 1); }
-    else { if (two) TIGAS_OCC3(16, 16, 2); else TIGAS_OCC3(16, 16, 1); }
-#undef TIGAS_OCC3
+#define TIGAS_OCC(TW, TH) (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_blend_persistent<TW, TH>, TW * TH, 0)
+    if (tile_w == 8 && tile_h == 8) TIGAS_OCC(8, 8);
+    else if (tile_w == 16 && tile_h == 32) TIGAS_OCC(16, 32);
+    else if (tile_w == 32 && tile_h == 16) TIGAS_OCC(32, 16);
+    else TIGAS_OCC(16, 16);
+#undef TIGAS_OCC
     return n > 0 ? n : 1;
 }
 

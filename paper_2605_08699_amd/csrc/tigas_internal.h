@@ -28,6 +28,13 @@ constexpr int BUCKET_BINS = 2048;
 constexpr int BUCKET_CDF_WORDS = BUCKET_BINS + 8;  // cumulative counts, smallest and largest sample, shift, scale
 constexpr int BUCKET_SORT_CAP = 4096;
 constexpr int COL_CHUNK = 32;  // columns per workgroup of a column scan
+// A list is divided into at most 4 x 4 cells of whole 8x8 blocks: log2 of a
+// cell's side for that of the list's.  An entry's word holds the cells that its
+// pixel box meets, as a mask of columns and one of rows, above the record's
+// number in its view (in CELL_REC_BITS bits), so a block of the blend tells
+// from the word whether to fetch the record.
+constexpr int CELL_REC_BITS = 24;
+constexpr __host__ __device__ int cell_log(int list_log) { return list_log < 5 ? 3 : list_log - 2; }
 // Tile placement: cells of the tile grid per workgroup, the units of the depth
 // order per view and at most in all, their smallest cost, a Gaussian's cost
 // besides its entries, tiles per workgroup of the ranges.
@@ -69,6 +76,7 @@ struct ViewParams {
     // and tile_base number the lists, btile_base the tiles.  Where the lists
     // are built, a list is what is called a tile.
     int tw_log, th_log, lx, ly, tiles_x, tiles_y;
+    int cells;           // the records' list rectangles carry their end cells
     uint32_t tile_base, btile_base;
     int sh_degree;
     int fmt;             // 0 RGB8, 1 RGBF32
@@ -221,7 +229,8 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
                              int tile_w, int tile_h, uint32_t* tile_out, uint32_t* val_out, uint32_t* depth_out,
                              hipStream_t st);
 // Bucketed depth sort of every view's visible records: val / ext receive the
-// record ids and packed tile rectangles view by view in depth order, equal
+// record ids (with cells, the record's number in its view and its rectangle's
+// end cells) and packed list rectangles view by view in depth order, equal
 // depths in record order (views of at most 256 x 256 tiles).  The same
 // launches set the frame's counters, clear zl and recompute, in FP64, the
 // conic of every Gaussian preprocess listed as near-singular.  flag_wide: a
@@ -231,7 +240,8 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 // all views; nunits: of the tile placement that follows.
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, hipStream_t st);
+                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
+                        hipStream_t st);
 // Runs LSD passes over the count selected by `which` (0 duplicates, 1 visible)
 // starting in buffer `start`; returns the buffer index holding the result.
 // With `rect_src`, the last pass also writes rect_src[value] to rect_dst in
@@ -248,7 +258,9 @@ void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t ca
 void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, hipStream_t st);
 // Tile placement by counting (packed rectangles): from the depth-ordered
 // records and packed rectangles, writes each (Gaussian, tile) entry's record
-// id to its sorted position in val_out (with tile_out/depth_out, also its tile
+// id to its sorted position in val_out (with cells, the record's number in its
+// view and the cells of the list that the entry covers; with
+// tile_out/depth_out, also its tile
 // id and depth word), the tile ranges and the counters to host_cnt.  The
 // depth order is the bucketed one (view by view, b filled in by
 // launch_bucket_sort) or, flat, a single view's from the radix passes.
@@ -256,8 +268,9 @@ void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, h
 // receives the blend's dense-first dispatch order (a single view).
 void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
                   int nviews, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
-                  const uint32_t* packed, uint2* ranges, uint32_t* order, FrameCounters* host_cnt, uint32_t* val_out,
-                  uint32_t* tile_out, uint32_t* depth_out, const uint32_t* zkey, hipStream_t st);
+                  const uint32_t* packed, bool cells, uint2* ranges, uint32_t* order,
+                  FrameCounters* host_cnt, uint32_t* val_out, uint32_t* tile_out, uint32_t* depth_out,
+                  const uint32_t* zkey, hipStream_t st);
 // Baseline JPEGs of RGB8 frames: one workgroup per restart interval of
 // JPEG_SEG_MCUS MCUs, the intervals of up to JPEG_MAX_JOBS frames in one pair
 // of launches.
@@ -310,17 +323,16 @@ struct JpegBatch {
 };
 void launch_jpeg(const JpegBatch& a, uint32_t nseg, hipStream_t st);
 void launch_blend(const ViewParams* views_dev, int nviews, uint32_t n_tiles, const uint2* ranges,
-                  const uint32_t* vals, const PreOut& o, uint32_t nrec, int tile_w, int tile_h, int batch_depth,
-                  int ppl, unsigned long long* work, uint32_t* queue, int persistent_blocks, bool cull,
+                  const uint32_t* vals, const PreOut& o, uint32_t nrec, int tile_w, int tile_h,
+                  bool cells, unsigned long long* work, uint32_t* queue, int persistent_blocks, bool cull,
                   const uint32_t* order, hipStream_t st);
 // order (one workgroup per tile, without queue): the tiles' dispatch order,
 // or null for the XCD-chunked order.
 // With `queue` (8 counters cleared per frame) the blend runs as a persistent
 // kernel of persistent_blocks workgroups pulling tiles from work queues.
-// ppl: pixels per lane (1, or 2 for tiles at least 16 tall).  cull: drop,
-// per wave, the entries whose exponent stays below the skip threshold on the
+// cull: drop, per wave, the entries whose exponent stays below the skip threshold on the
 // wave's whole pixel block (they would be skipped at every pixel anyway).
-int blend_persistent_occupancy(int tile_w, int tile_h, int batch_depth, int ppl);
+int blend_persistent_occupancy(int tile_w, int tile_h);
 void launch_wave_scan_selftest(const uint32_t* in, uint32_t* out, int n, hipStream_t st);
 
 // Per-launch timing for profiling: while a timer is installed for the calling

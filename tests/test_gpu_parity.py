@@ -308,6 +308,40 @@ def test_tiles_sharing_a_list_give_the_same_frame(ctx, size, tile, kind):
     s.free()
 
 
+@pytest.mark.parametrize("opacity", [0.02, 0.6, 0.9999])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 64, 65, 71, 72, 73, 129, 700])
+def test_blend_groups_and_batches(ctx, n, opacity):
+    """Lists around the sizes of a group and of a batch, of Gaussians over the
+    whole frame (wide ones, whose exponents span little, among narrow ones),
+    that stop no pixel, stop pixels inside groups, and reach the cap on alpha:
+    the oracle's frame, and the same one from every tile shape, with and
+    without the lists' cells."""
+    rng = np.random.default_rng(n)
+    W, H = 50, 41
+    z = rng.uniform(2.0, 6.0, n)
+    xy = rng.uniform(-1.0, 1.0, (n, 2)) * np.array([1.0, 0.8])
+    ls = np.repeat(np.log(rng.choice([0.03, 0.3, 2.0], n) * z)[:, None], 3, axis=1) + rng.normal(0.0, 0.2, (n, 3))
+    scene = make_scene(np.column_stack([xy[:, 0] * z, xy[:, 1] * z, z]), ls, None,
+                       np.full(n, math.log(opacity / (1.0 - opacity))), rng.uniform(0.0, 1.0, (n, 3)))
+    s = ctx.load_scene(scene)
+    k = intr(W / 2.0, W / 2, H / 2)
+    bg = (0.2, 0.5, 0.9)
+    _say("blend groups", n, opacity)
+    img = ctx.render(s, eye_pose(), k, W, H, fmt="f32", bg=bg, tile=(16, 16))
+    br, nb = orc.render_frame(orc.preprocess(scene, eye_pose(), k, W, H), bg=bg)
+    res = gc.check_frame_pixels(img.reshape(-1, 3), br.reshape(-1, br.shape[2], 4), nb.reshape(-1))
+    # (pixels with more decision forks than the oracle follows cannot be judged)
+    assert res["n_bad"] <= res["n_unresolved"] <= W * H // 50, res
+    for tile in ((8, 8), (16, 32), (32, 16)):
+        np.testing.assert_array_equal(ctx.render(s, eye_pose(), k, W, H, fmt="f32", bg=bg, tile=tile), img)
+    ctx.set_tile_binning(False)
+    try:
+        np.testing.assert_array_equal(ctx.render(s, eye_pose(), k, W, H, fmt="f32", bg=bg, tile=(16, 16)), img)
+    finally:
+        ctx.set_tile_binning(True)
+    s.free()
+
+
 @pytest.mark.parametrize("tile", [(16, 16), (8, 8), (16, 32), (32, 16)])
 def test_culled_tile_lists_bit_exact_and_frames_unchanged(ctx, c1, tile):
     """Tighter tile culling: the lists equal the reference less exactly the
