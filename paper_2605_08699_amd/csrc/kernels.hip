@@ -2716,6 +2716,13 @@ __device__ __forceinline__ bool below_threshold(float A, float B, float C, float
 // than they save (13 us at 3M/1080p).
 // The launch at 3M/1080p, 3M/4K, 1M/720p and over 32 views: 144, 418, 97 us and
 // 2.39 ms; with lists of the same size before, 170, 497, 110 us and 2.87 ms.
+// x, from which nothing is formed ahead of this point: addresses and constants
+// that the compiler keeps over a loop for a rare step in it take registers.
+__device__ __forceinline__ uint32_t fresh(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // The staged entries 0 .. whole - 1 of a wave, in groups of eight, on its
@@ -2730,6 +2737,7 @@ __device__ __forceinline__ void blend_groups(const Stage& S, int lane, float pyr
                                              uint32_t whole, uint64_t& live, f32x4& acc, uint32_t& n_eval,
                                              uint32_t& n_contrib) {
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    lane = (int)fresh((uint32_t)lane);
     for (uint32_t j0 = 0; j0 < whole; j0 += 8) {
         if (live == 0) break;
         const uint32_t j = j0 + (uint32_t)(lane & 7);
@@ -2814,15 +2822,13 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
     const uint32_t lt = (tile - v.btile_base) >> ls, sub = (tile - v.btile_base) & ((1u << ls) - 1u);
     const int tx = ((int)(lt % (uint32_t)v.tiles_x) << v.lx) + (int)(sub & ((1u << v.lx) - 1u));
     const int ty = ((int)(lt / (uint32_t)v.tiles_x) << v.ly) + (int)(sub >> v.lx);
-    const int lane = threadIdx.x & 63;
+    const int lane = (int)fresh(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(fresh(~0u), 0u)));
     const int sx = tx * TW + (w % BX) * 8, sy = ty * TH + (w / BX) * 8;
-    const int px = sx + (lane & 7), py = sy + (lane >> 3);
     const float pxr = (float)(lane & 7) + 0.5f, pyr = (float)(lane >> 3) + 0.5f;
     const float fsx = (float)sx, fsy = (float)sy;
-    const bool inside = px < v.width && py < v.height;
     // the pixels still compositing, as a wave mask: the per-pair decisions are
     // combined in scalar registers and applied with one select
-    uint64_t live = ballot(inside);
+    uint64_t live = ballot(sx + (lane & 7) < v.width && sy + (lane >> 3) < v.height);
     f32x4 acc = {0.0f, 0.0f, 0.0f, 1.0f};  // r, g, b, T
     const f32x4 px4 = {pxr, pxr, pxr, pxr};
     uint32_t n_eval = 0, n_contrib = 0;  // (pixel, Gaussian) evaluations / contributions, COUNT only
@@ -2842,7 +2848,9 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
                           ((1u << 28) << ((sy & ((1 << lh) - 1)) >> cell_log(lh)));
     // (the lists' buffers have room for a read of 64 entries from any of them)
     uint32_t ahead = 0u;
-    auto read = [&] { ahead = (A.vals + base)[lane]; };
+    auto read = [&] {  // scalar base, 32-bit lane offset
+        ahead = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(A.vals + base) + ((uint32_t)lane << 2));
+    };
     if (base < end) read();
     auto scan = [&] {  // until a batch is queued or the list has ended
         while (queued < 64 && base < end) {
@@ -2858,9 +2866,9 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
                 bool hit = en < A.nrec && __builtin_amdgcn_inverse_ballot_w64(in);
                 if (hit) {
                     const uint2 b = A.rec[en].bbox;
-                    const int x0 = (int)(b.x & 0xffffu), y0 = (int)(b.x >> 16);
-                    const int x1 = (int)(b.y & 0xffffu), y1 = (int)(b.y >> 16);
-                    hit = !(x1 < sx || x0 > bx1 || y1 < sy || y0 > by1);
+                    // x in the low halves, y in the high ones: compared where they are
+                    hit = !(b.y << 16 < (uint32_t)sx << 16 || b.x << 16 > (uint32_t)bx1 << 16 ||
+                            b.y < (uint32_t)sy << 16 || b.x >= (uint32_t)(by1 + 1) << 16);
                 }
                 m = ballot(hit);
             }
@@ -2884,7 +2892,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
     uint32_t left = 0;      // staged, waiting for a whole group
     uint64_t capped = 0;    // a staged Gaussian's alpha may reach ALPHA_MAX
     for (;;) {
-        float4 f0 = make_float4(0.f, 0.f, 0.f, 0.f), f1 = f0, f2 = f0;
+        float4 f0, f1, f2;  // of the first nb lanes
         if ((uint32_t)lane < nb && rec < A.nrec) {
             f0 = A.rec[rec].r0;
             f1 = A.rec[rec].r1;
@@ -2902,7 +2910,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
             S.nu[slot] = -u;
             sa[slot] = f1.x;
             S.row[slot] = make_float4(v0, f1.y, f1.z, f1.w);
-            S.col[slot] = make_float4(f2.x, f2.y, f2.z, -1.0f);
+            S.col[slot] = make_float4(f2.x, f2.y, f2.z, __uint_as_float(fresh(__float_as_uint(-1.0f))));
         }
         const uint32_t cnt = left + (uint32_t)__builtin_popcountll(m);
         scan();
@@ -2911,11 +2919,12 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
         uint32_t whole = cnt & ~7u;
         if (last && whole < cnt) {  // entries that reach no pixel fill the last group
             whole += 8;
-            const uint32_t slot = cnt + (uint32_t)lane;
+            const uint32_t slot = cnt + fresh(lane);
             if (slot < whole) {
-                S.nu[slot] = sa[slot] = 0.0f;
-                S.row[slot] = make_float4(0.0f, 0.0f, 0.0f, -1e30f);
-                S.col[slot] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+                const float z = __uint_as_float(fresh(0u));
+                S.nu[slot] = sa[slot] = z;
+                S.row[slot] = make_float4(z, z, z, __uint_as_float(fresh(__float_as_uint(-1e30f))));
+                S.col[slot] = make_float4(z, z, z, z);
             }
         }
         wave_sync();
@@ -2924,14 +2933,14 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
         if (live == 0 || last) break;
         left = cnt - whole;
         if (left && whole) {
-            const uint32_t l = (uint32_t)lane & 7u;
+            const uint32_t ln = fresh(lane), l = ln & 7u;
             const float4 t = S.row[whole + l], c = S.col[whole + l];
             const float nu = S.nu[whole + l], ca = sa[whole + l];
-            if ((uint32_t)lane < left) {
-                S.row[lane] = t;
-                S.col[lane] = c;
-                S.nu[lane] = nu;
-                sa[lane] = ca;
+            if (ln < left) {
+                S.row[ln] = t;
+                S.col[ln] = c;
+                S.nu[ln] = nu;
+                sa[ln] = ca;
             }
         }
         wave_sync();
@@ -2943,7 +2952,8 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
             atomicAdd(&A.work[1], (unsigned long long)sc);
         }
     }
-    if (inside) {
+    const int ln = (int)fresh(lane), px = sx + (ln & 7), py = sy + (ln >> 3);
+    if (px < v.width && py < v.height) {
         const float r = __builtin_fmaf(acc[3], v.bg[0], acc[0]);
         const float g = __builtin_fmaf(acc[3], v.bg[1], acc[1]);
         const float b = __builtin_fmaf(acc[3], v.bg[2], acc[2]);
@@ -2971,7 +2981,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
 // of the image (dense and sparse regions alike).
 constexpr uint32_t BLEND_CHUNK = 16;
 template <int TW, int TH, bool COUNT>
-__global__ __launch_bounds__(TW* TH, 8) void k_blend(BlendArgs A) {
+__global__ __launch_bounds__(TW* TH, COUNT ? 1 : 8) void k_blend(BlendArgs A) {
     constexpr int NW = TW * TH / 64;
     __shared__ Stage stage[NW];
     uint32_t tile;
@@ -2995,7 +3005,7 @@ __global__ __launch_bounds__(TW* TH, 8) void k_blend(BlendArgs A) {
 // cleared by k_scan_visible each frame; every workgroup exits once all bands
 // are drained.
 template <int TW, int TH>
-__global__ __launch_bounds__(TW* TH, 8) void k_blend_persistent(BlendArgs A, uint32_t* __restrict__ queue) {
+__global__ __launch_bounds__(TW* TH, TW* TH == 64 ? 7 : 8) void k_blend_persistent(BlendArgs A, uint32_t* __restrict__ queue) {
     constexpr int NW = TW * TH / 64;
     __shared__ Stage stage[NW];
     __shared__ uint32_t next;
@@ -3007,7 +3017,7 @@ __global__ __launch_bounds__(TW* TH, 8) void k_blend_persistent(BlendArgs A, uin
         const uint32_t band_end = min(A.n_tiles, first + per);
         if (first >= band_end) continue;
         for (;;) {
-            if (threadIdx.x == 0) next = first + atomicAdd(&queue[band], 1u);
+            if (w == 0 && lane_id() == 0) next = first + atomicAdd(&queue[band], 1u);
             __syncthreads();
             const uint32_t tile = next;
             __syncthreads();
