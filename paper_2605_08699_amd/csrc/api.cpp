@@ -722,7 +722,7 @@ void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
 // of the view's buckets however few records it has), and a power of two of
 // buckets, about BUCKET_RECORDS records each.
 void set_buckets(Plan& plan) {
-    plan.seg_len = std::min<uint32_t>(65536, std::max<uint32_t>(4096, round_up((uint64_t)plan.nrec / 500 + 1, 1024)));
+    plan.seg_len = std::min<uint32_t>(SEG_MAX, std::max<uint32_t>(4096, round_up((uint64_t)plan.nrec / 500 + 1, 1024)));
     plan.nseg = plan.nchunks = 0;
     plan.row_words = 0;
     for (const Group& g : plan.groups)
@@ -762,7 +762,7 @@ BucketMem carve_buckets(const Plan& plan, void* rows, void* small, size_t* rows_
     b.ccost = reinterpret_cast<unsigned long long*>(take((size_t)plan.nchunks * 8));
     b.chunk = reinterpret_cast<uint32_t*>(take((size_t)plan.nchunks * 4));
     b.cdf = reinterpret_cast<uint32_t*>(take(plan.views.size() * BUCKET_CDF_WORDS * 4));
-    b.segmm = reinterpret_cast<uint32_t*>(take((size_t)plan.nseg * 8));
+    b.seg = reinterpret_cast<SegTotals*>(take((size_t)plan.nseg * sizeof(SegTotals)));
     *small_bytes = std::max<size_t>(off, 256);
     return b;
 }

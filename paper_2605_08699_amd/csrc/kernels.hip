@@ -192,16 +192,28 @@ __device__ __forceinline__ void sh_colour(const float* k, float x, float y, floa
             Y[15] = -SH_C3A * (x * (xx - 3.0f * yy));
         }
     }
-    const int nc = (DEG + 1) * (DEG + 1);
-    const int nuse = (deg + 1) * (deg + 1);
+    float s[3] = {0.5f, 0.5f, 0.5f};
+    auto add = [&](int i) {
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        float s = 0.5f;
+        for (int ch = 0; ch < 3; ++ch) s[ch] = __builtin_fmaf(Y[i], k[i * 3 + ch], s[ch]);
+    };
+    // a uniform branch per degree: a select per coefficient takes 48 more
+    // instructions a view (32 views of 3M records 1.95 ms, with the branches 1.90)
+    add(0);
+    if (DEG >= 1 && deg >= 1) {
 #pragma unroll
-        for (int i = 0; i < nc; ++i)
-            if (i < nuse) s = __builtin_fmaf(Y[i], k[i * 3 + ch], s);
-        rgb[ch] = fmaxf(s, 0.0f);
+        for (int i = 1; i < 4; ++i) add(i);
+        if (DEG >= 2 && deg >= 2) {
+#pragma unroll
+            for (int i = 4; i < 9; ++i) add(i);
+            if (DEG >= 3 && deg >= 3) {
+#pragma unroll
+                for (int i = 9; i < 16; ++i) add(i);
+            }
+        }
     }
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) rgb[ch] = fmaxf(s[ch], 0.0f);
 }
 
 // ------------------------------------------------------------- preprocess
@@ -357,8 +369,8 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
         const float z32 = __builtin_fmaf(v.V[6], mx, __builtin_fmaf(v.V[7], my, __builtin_fmaf(v.V[8], mz, v.tz_key)));
         bool vis = ok && z32 > NEAR_Z;
         uint32_t touched = 0, tiles = 0, fb = 0;  // lists and tiles met, FP64 fallback
-        float4 r0 = {0, 0, 0, 0}, r1 = {0, 0, 0, 0}, r2 = {0, 0, 0, 0};
-        uint2 bb = {0u, 0u}, tr = {0u, 0u};
+        float4 r0, r1, r2;  // of touched records only
+        uint2 bb, tr = {0u, 0u};
         if (vis) {
             // camera-space centre, double-float: d = mu - t exactly, p = V d
             const df dX = two_sum(mx, -v.cam[0]), dY = two_sum(my, -v.cam[1]), dZ = two_sum(mz, -v.cam[2]);
@@ -590,6 +602,11 @@ __device__ void conic_fp64(const uint2 e, const ViewParams* __restrict__ views, 
 constexpr int SCAN_STAGE = SCAN_CHUNK + SCAN_CHUNK / 32;
 __device__ __forceinline__ int spad(int i) { return i + (i >> 5); }
 
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor((unsigned long long)v, o, 64);
+    return v;
+}
 __device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, unsigned long long* lds) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -1119,42 +1136,25 @@ __device__ __forceinline__ uint32_t key_bucket(uint32_t key, const uint32_t* cdf
 // smallest and largest visible key.  Every workgroup forms the view's sample
 // distribution itself (the first one of the view also stores it for the
 // scatter): the samples are 1/64 of the keys, and a launch of its own would
-// cost more.  Further workgroups, one per view, sum the preprocess blocks'
-// counts; all share the clearing of zl.  64 VGPRs: two workgroups per CU.
+// cost more.  All share the clearing of zl.  64 VGPRs: two workgroups per CU.
+// Bound by latency (3M records: 512 workgroups of six rounds, 8192 samples
+// each); the preprocess blocks' totals are summed segment by segment: one
+// workgroup for all 11720 blocks of 3M records was the last to end.
+// 3M records: 25 us with that workgroup, 18 without.
 __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, BucketMem b,
                                                                     const ViewParams* __restrict__ views, int nviews,
                                                                     uint32_t nseg, uint32_t seg_len, ZeroList zl) {
     constexpr int NT = BUCKET_THREADS, NW = NT / 64, SPT = BUCKET_SAMPLES / NT, RPT = 6;
     static_assert(BUCKET_BINS == 2 * NT, "two bins per thread");
     __shared__ uint32_t cdf[BUCKET_BINS + 1], hist[BUCKET_MAX];
-    __shared__ uint32_t red[NW], red2[NW];
-    __shared__ unsigned long long red64[NW];
+    __shared__ uint32_t red[NW], red2[NW], tot32[2];
+    __shared__ unsigned long long tot64[2];
+    static_assert(NT / 4 >= SEG_MAX / K1_THREADS, "a thread of the first waves per preprocess block");
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
 #pragma unroll
     for (int k = 0; k < ZeroList::N; ++k)
         for (uint32_t i = blockIdx.x * NT + t; i < zl.n[k]; i += gridDim.x * NT) zl.p[k][i] = 0u;
-    if (blockIdx.x >= nseg) {  // a view's totals
-        const int vi = (int)(blockIdx.x - nseg);
-        const uint32_t k0 = views[vi].rec_base / K1_THREADS, n = views[vi].n_pad / K1_THREADS;
-        uint64_t d = 0, vis = 0, fb = 0, tl = 0;
-        for (uint32_t i = t; i < n; i += NT) {
-            tl += o.blk_tiles[k0 + i];
-            d += o.blk_sum[k0 + i];
-            vis += o.blk_vis[k0 + i];
-            fb += o.blk_fb[k0 + i];
-        }
-        d = block_sum_u64(d, red64);
-        vis = block_sum_u64(vis, red64);
-        fb = block_sum_u64(fb, red64);
-        tl = block_sum_u64(tl, red64);
-        if (t == 0) {
-            b.vc[vi].tiles = tl;
-            b.vc[vi].dups = d;
-            b.vc[vi].visible = (uint32_t)vis;
-            b.vc[vi].fallbacks = (uint32_t)fb;
-        }
-        return;
-    }
+    if (blockIdx.x >= nseg) return;  // no records at all: the clearing only
     const int vi = view_of(blockIdx.x, nviews, [&](int i) { return views[i].seg_base; });
     const ViewParams& v = views[vi];
     const uint32_t seg = blockIdx.x - v.seg_base, nbkt = v.nbkt;
@@ -1172,6 +1172,10 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
         }
     };
     load(r0);
+    if (t < 2) {
+        tot64[t] = 0ull;
+        tot32[t] = 0u;
+    }
     // the samples' distribution
     // (four samples per bucket: a bucket of twice the mean size is rare, and
     // one of more than BUCKET_SORT_CAP only costs time)
@@ -1211,6 +1215,14 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
 #pragma unroll
     for (int k = 0; k < SPT; ++k)
         if (sk[k] != 0xffffffffu) atomicAdd(&cdf[(sk[k] - m.lo) >> m.shift], 1u);
+    uint32_t bd = 0, bt = 0, bn = 0, bf = 0;  // a preprocess block's counts
+    if ((uint32_t)t < (r1 - r0) / K1_THREADS) {
+        const uint32_t i = r0 / K1_THREADS + (uint32_t)t;
+        bd = o.blk_sum[i];
+        bt = o.blk_tiles[i];
+        bn = o.blk_vis[i];
+        bf = o.blk_fb[i];
+    }
     __syncthreads();
     const uint32_t c0 = cdf[2 * t], c1 = cdf[2 * t + 1];
     uint32_t total;
@@ -1219,6 +1231,16 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
     cdf[2 * t + 1] = ex + c0;
     if (t == 0) cdf[BUCKET_BINS] = total;
     m.scale = total ? (nbkt << 16) / total : 0u;
+    if (w < NW / 4) {  // the totals of the segment's preprocess blocks
+        const uint64_t d = wave_sum_u64(bd), tl = wave_sum_u64(bt);
+        const uint32_t n = wave_sum(bn), f = wave_sum(bf);
+        if (lane == 0) {
+            atomicAdd(&tot64[0], (unsigned long long)d);
+            atomicAdd(&tot64[1], (unsigned long long)tl);
+            atomicAdd(&tot32[0], n);
+            atomicAdd(&tot32[1], f);
+        }
+    }
     __syncthreads();
     if (seg == 0) {
         uint32_t* out = b.cdf + (size_t)vi * BUCKET_CDF_WORDS;
@@ -1252,8 +1274,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
             lo = min(lo, red[k]);
             hi = max(hi, red2[k]);
         }
-        b.segmm[2 * blockIdx.x] = lo;
-        b.segmm[2 * blockIdx.x + 1] = hi;
+        b.seg[blockIdx.x] = SegTotals{tot64[0], tot64[1], tot32[0], tot32[1], lo, hi};
     }
     uint32_t* row = b.rows + v.row_base + (size_t)seg * nbkt;
     for (uint32_t i = t; i < nbkt; i += NT) row[i] = hist[i];
@@ -1350,8 +1371,30 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewPar
     }
     uint32_t lo = 0xffffffffu, hi = 0u;
     for (uint32_t i = threadIdx.x; i < nseg; i += 1024) {
-        lo = min(lo, b.segmm[2 * i]);
-        hi = max(hi, b.segmm[2 * i + 1]);
+        lo = min(lo, b.seg[i].lo);
+        hi = max(hi, b.seg[i].hi);
+    }
+    // a wave per view: its totals
+    for (int i = (int)(threadIdx.x >> 6); i < nviews; i += 16) {
+        uint64_t d = 0, tl = 0;
+        uint32_t n = 0, f = 0;
+        for (uint32_t k = threadIdx.x & 63u; k < views[i].nseg; k += 64) {
+            const SegTotals sg = b.seg[views[i].seg_base + k];
+            d += sg.dups;
+            tl += sg.tiles;
+            n += sg.visible;
+            f += sg.fallbacks;
+        }
+        d = wave_sum_u64(d);
+        tl = wave_sum_u64(tl);
+        n = wave_sum(n);
+        f = wave_sum(f);
+        if ((threadIdx.x & 63) == 0) {
+            b.vc[i].dups = d;
+            b.vc[i].tiles = tl;
+            b.vc[i].visible = n;
+            b.vc[i].fallbacks = f;
+        }
     }
     lo = wave_min(lo);
     hi = wave_max(hi);
@@ -3162,8 +3205,8 @@ void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* v
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
                         bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
                         hipStream_t st) {
-    TIGAS_LAUNCH(k_bucket_count, dim3(nseg + nviews), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
-                 zl);
+    TIGAS_LAUNCH(k_bucket_count, dim3(std::max(nseg, 1u)), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,
+                 seg_len, zl);
     TIGAS_LAUNCH(k_bucket_scan, dim3(nchunks + 1), dim3(1024), st, b, views_dev, nviews, nseg, nchunks, cnt, cap,
                  flag_wide, nunits);
     if (nseg == 0) return;

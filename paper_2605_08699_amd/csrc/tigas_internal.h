@@ -23,6 +23,7 @@ constexpr int MAX_SORT_PASSES = 8;
 // samples' distribution, and the elements a workgroup sorts at once.
 constexpr int BUCKET_RECORDS = 1024;
 constexpr int BUCKET_MAX = 4096;
+constexpr int SEG_MAX = 65536;  // records per segment at most
 constexpr int BUCKET_SAMPLES = 16384;
 constexpr int BUCKET_BINS = 2048;
 constexpr int BUCKET_CDF_WORDS = BUCKET_BINS + 8;  // cumulative counts, smallest and largest sample, shift, scale
@@ -160,6 +161,13 @@ struct ViewCount {
     uint32_t ubase, nu, ucost;  // units of the tile placement: of the views before, of this one, cost of one
 };
 
+// A segment of a view's records: list entries, (Gaussian, tile) pairs, visible
+// records, FP64 fallbacks, smallest and largest visible depth key.
+struct SegTotals {
+    unsigned long long dups, tiles;
+    uint32_t visible, fallbacks, lo, hi;
+};
+
 // Scratch of the bucketed depth sort (all views of a launch sequence).
 struct BucketMem {
     uint4* elem;         // [visible] (depth key, record, packed rectangle, -) in bucket order
@@ -168,7 +176,7 @@ struct BucketMem {
     uint32_t* tot;       // per bucket: records
     uint32_t* chunk;     // per chunk of COL_CHUNK buckets: records
     uint32_t* cdf;       // per view: BUCKET_CDF_WORDS
-    uint32_t* segmm;     // [segments][2]: smallest and largest key
+    SegTotals* seg;      // [segments]
     uint32_t* cost;      // per bucket: its entries and TILE_BASE_COST per record,
     unsigned long long* ccost;  // and per chunk (cleared each frame)
     ViewCount* vc;       // per view
