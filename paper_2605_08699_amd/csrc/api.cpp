@@ -898,7 +898,8 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         HIPCHK(hipMemcpyAsync(m.views, m.views_src, sizeof(ViewParams) * nv, hipMemcpyHostToDevice, st));
     } else {
         if (nv != 1) fail(TIGAS_E_INVALID, "kernel-argument view upload takes one view");
-        launch_store_view(plan.views[0], m.views, st);
+        // the previous call's counters stay in the fixed array: start this frame from zero
+        launch_store_view(plan.views[0], m.views, reinterpret_cast<uint32_t*>(m.cnt), sizeof(Counters) / 4, st);
     }
     const PreOut& o = m.pre;
     const ViewParams* vdev = m.views;
@@ -1575,8 +1576,6 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     const hipStream_t st = pick_stream(ctx, hip_stream);
     const FrameMem m =
         carve_scratch(scratch_dev, plan, reinterpret_cast<FrameCounters*>(counters), st);
-    // the previous call's counters stay in the array: start this frame from zero
-    launch_fill_u32(reinterpret_cast<uint32_t*>(m.cnt), sizeof(Counters) / 4, 0u, st);
     LaunchOptions opt;
     opt.cull = ctx->blend_cull.load();
     opt.bin = ctx->tile_bin.load();

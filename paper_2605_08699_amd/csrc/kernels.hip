@@ -3071,18 +3071,16 @@ __global__ __launch_bounds__(TW* TH, TW* TH == 64 ? 7 : 8) void k_blend_persiste
 }
 
 // One view's parameters, passed by value as a kernel argument, stored to
-// device memory (the allocation-free entry point has no pinned host copy).
-__global__ void k_store_view(ViewParams v, ViewParams* __restrict__ dst) {
+// device memory (the allocation-free entry point has no pinned host copy), and
+// the clearing of the counters it keeps in its fixed scratch array: one launch
+// instead of two (100k records at 960x540 82.8 -> 80.4 us).
+__global__ void k_store_view(ViewParams v, ViewParams* __restrict__ dst, uint32_t* __restrict__ clear,
+                             uint32_t nclear) {
     constexpr int W = (int)(sizeof(ViewParams) / 4);
     static_assert(sizeof(ViewParams) % 4 == 0, "view parameters are whole words");
     const uint32_t* src = reinterpret_cast<const uint32_t*>(&v);
     for (int i = threadIdx.x; i < W; i += blockDim.x) reinterpret_cast<uint32_t*>(dst)[i] = src[i];
-}
-
-// Fill of n words (clears the counter block the allocation-free entry point
-// keeps in its fixed scratch array).
-__global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t n, uint32_t value) {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = value;
+    for (uint32_t i = threadIdx.x; i < nclear; i += blockDim.x) clear[i] = 0u;
 }
 
 __global__ void k_wave_scan_selftest(const uint32_t* in, uint32_t* out, int n) {
@@ -3126,13 +3124,8 @@ void launch_preprocess(const SceneView& s, const ViewParams* views_dev, const Vi
 }
 
 
-void launch_store_view(const ViewParams& v, ViewParams* dst, hipStream_t st) {
-    TIGAS_LAUNCH(k_store_view, dim3(1), dim3(64), st, v, dst);
-}
-
-void launch_fill_u32(uint32_t* p, uint32_t n, uint32_t value, hipStream_t st) {
-    if (n == 0) return;
-    TIGAS_LAUNCH(k_fill_u32, dim3(std::min<uint32_t>(1024u, (n + 255) / 256)), dim3(256), st, p, n, value);
+void launch_store_view(const ViewParams& v, ViewParams* dst, uint32_t* clear, uint32_t nclear, hipStream_t st) {
+    TIGAS_LAUNCH(k_store_view, dim3(1), dim3(64), st, v, dst, clear, nclear);
 }
 
 void launch_scan_visible(const PreOut& o, int nblk, uint32_t* blk_off, Counters* cnt, uint32_t cap,
