@@ -200,13 +200,12 @@ struct Plan {
     std::vector<ViewParams> views;
     std::vector<Group> groups;
     uint32_t nrec = 0;
-    uint32_t n_tiles = 0;   // tile lists; the tiles the blend is launched over, and those of the frames
-    uint32_t n_blend = 0, n_frame_tiles = 0;
+    uint32_t n_tiles = 0, n_frame_tiles = 0;  // tile lists; the tiles of the frames
     uint32_t seg_len = 0, nseg = 0, nchunks = 0;  // bucketed depth sort (set_buckets)
     uint64_t row_words = 0;
     uint32_t nunits = 0, tchunks = 0, max_tiles = 0;  // tile placement (set_tiles)
     TileCfg tc{16, 16, 64, 1};
-    bool persistent = false;  // blend as a persistent kernel over a tile work queue
+    bool batch = false;  // a batch's plan: tuned apart from single frames
     bool allow_graph = true;  // capture/replay (off for one-off shapes such as serving batches)
 };
 
@@ -301,7 +300,6 @@ struct FrameMem {
     uint32_t* hist_tot = nullptr;  // per-digit totals
     BucketMem bk{};                // bucketed depth sort
     bool flag_wide = true;         // flag frames too deep for it (the caller renders them again)
-    uint32_t* queue = nullptr;
     uint2* ranges = nullptr;
     uint32_t* order = nullptr;     // the blend's dispatch order of the tiles
     TileMem tm{};                  // tile placement by counting
@@ -326,7 +324,7 @@ struct Workspace {
     DevBuf counters;
     // per duplicate (also holds the visible Gaussians during the depth passes)
     DevBuf key[2], val[2], ext[2];
-    DevBuf hist, queue;
+    DevBuf hist;
     DevBuf vmask, sample;        // per 64 records
     DevBuf bkt_rows, bkt_small;  // bucketed depth sort: counts, everything else
     // emission-order copies for the inspection entry point
@@ -367,7 +365,6 @@ struct Workspace {
         }
         m.hist = hist.as<uint32_t>();
         m.hist_tot = m.hist + (size_t)256 * SORT_MAX_BLOCKS;
-        m.queue = queue.as<uint32_t>();
         m.ranges = ranges.as<uint2>();
         m.order = reinterpret_cast<uint32_t*>(m.ranges + tile_cap);  // after the ranges, in the same buffer
         m.blk_off = blk_off.as<uint32_t>();
@@ -431,7 +428,6 @@ struct Workspace {
             grow(ext[i], (size_t)cap * 4);
         }
         grow(hist, ((size_t)256 * SORT_MAX_BLOCKS + 256) * 4);  // counts per (digit, segment), then digit totals
-        grow(queue, 8 * 4);                                  // blend band queues
         dup_cap = cap;
     }
     void ensure_tiles(uint32_t n) {
@@ -471,7 +467,6 @@ struct Workspace {
 
 struct tigas_context {
     int device = 0;
-    int cus = 256;
     hipStream_t stream = nullptr;
     std::mutex mu;
     std::map<hipStream_t, std::unique_ptr<Workspace>> ws;
@@ -684,7 +679,7 @@ void list_scale(ViewParams& v, const TileCfg& tc) {
 // tiles' own lists).
 void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
     plan.tc = tc;
-    plan.n_tiles = plan.n_blend = plan.n_frame_tiles = plan.tchunks = plan.max_tiles = 0;
+    plan.n_tiles = plan.n_frame_tiles = plan.tchunks = plan.max_tiles = 0;
     bool cells = shared;
     for (const Group& g : plan.groups) cells = cells && g.n_pad <= 1u << CELL_REC_BITS;
     for (ViewParams& v : plan.views) {
@@ -697,11 +692,9 @@ void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
         v.tiles_x = (v.width + lw - 1) / lw;
         v.tiles_y = (v.height + lh - 1) / lh;
         v.tile_base = plan.n_tiles;
-        v.btile_base = plan.n_blend;
         v.tchunk_base = plan.tchunks;
         const uint32_t n = (uint32_t)(v.tiles_x * v.tiles_y);
         plan.n_tiles += n;
-        plan.n_blend += n << (v.lx + v.ly);
         plan.n_frame_tiles += (uint32_t)(((v.width + tc.tw - 1) / tc.tw) * ((v.height + tc.th - 1) / tc.th));
         plan.tchunks += (n + TILE_CHUNK - 1) / TILE_CHUNK;
         plan.max_tiles = std::max(plan.max_tiles, n);
@@ -788,7 +781,7 @@ std::string shape_key(const Plan& plan, bool with_tiles) {
     }
     if (with_tiles) {
         std::snprintf(buf, sizeof buf, "t%dx%d:%d:%d:%d", plan.tc.tw, plan.tc.th, plan.tc.bd, plan.tc.ppl,
-                      (int)plan.persistent);
+                      (int)plan.batch);
         k += buf;
     }
     return k;
@@ -887,7 +880,7 @@ bool use_bin(const Plan& plan, const LaunchOptions& opt) {
     return opt.bin && !opt.cull_tiles && packed_rects(plan) && (opt.buckets || plan.views.size() == 1);
 }
 
-int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned long long* work, int pblocks,
+int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned long long* work,
             const LaunchOptions& opt) {
     hipStream_t st = m.stream;
     auto mark = [&](int i) {
@@ -913,12 +906,10 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     const int nblk = (int)(plan.nrec / K1_THREADS);
     Counters* cnt = m.cnt;
     ZeroList zl{};
-    zl.p[0] = m.queue;
-    zl.n[0] = 8;
-    zl.p[1] = reinterpret_cast<uint32_t*>(m.ranges);
-    zl.n[1] = 2 * plan.n_tiles;
-    zl.p[2] = reinterpret_cast<uint32_t*>(m.bk.ccost);
-    zl.n[2] = 2 * plan.nchunks;
+    zl.p[0] = reinterpret_cast<uint32_t*>(m.ranges);
+    zl.n[0] = 2 * plan.n_tiles;
+    zl.p[1] = reinterpret_cast<uint32_t*>(m.bk.ccost);
+    zl.n[1] = 2 * plan.nchunks;
     SortBuffers sb;
     for (int i = 0; i < 2; ++i) {
         sb.key[i] = m.key[i];
@@ -967,7 +958,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     if (bin) {
         // tile digit by counting, straight from the depth-ordered Gaussians
         launch_tiles(m.tm, m.bk, vdev, plan.views.data(), nv, cnt, !opt.buckets, plan.tchunks, sb.val[cv], sb.ext[cv],
-                     cells, m.ranges, plan.persistent || nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
+                     cells, m.ranges, nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
                      debug ? sb.key[cd] : nullptr, debug ? sb.ext[cd] : nullptr, o.zkey, st);
         mark(4);
         mark(5);
@@ -978,12 +969,11 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
                           cnt, nullptr, nullptr, st);
         mark(4);
         launch_ranges(sb.key[cur], cnt, m.dup_cap, m.ranges, m.cnt_out, o, vdev, st);
-        if (!plan.persistent) launch_tile_order(m.ranges, plan.n_tiles, m.order, st);
+        if (nv == 1) launch_tile_order(m.ranges, plan.n_tiles, m.order, st);
         mark(5);
     }
-    launch_blend(vdev, nv, plan.n_blend, m.ranges, sb.val[cur], o, plan.nrec, plan.tc.tw, plan.tc.th, cells, work,
-                 plan.persistent ? m.queue : nullptr, pblocks, opt.cull,
-                 plan.persistent ? nullptr : m.order, st);
+    launch_blend(vdev, plan.views.data(), nv, plan.n_tiles, m.ranges, sb.val[cur], o, plan.nrec, cells, work, opt.cull,
+                 nv > 1 ? nullptr : m.order, st);
     mark(6);
     HIPCHK(hipGetLastError());
     return cur;
@@ -1014,8 +1004,6 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
                 unsigned long long* work) {
     std::memcpy(ws.fs().host_views.p, plan.views.data(), sizeof(ViewParams) * plan.views.size());
     if (prof) ws.ensure_events();
-    const int pblocks =
-        plan.persistent ? ctx->cus * blend_persistent_occupancy(plan.tc.tw, plan.tc.th) : 0;
     // stage timing needs events between the launches: that runs uncaptured
     LaunchOptions opt;
     opt.cull = ctx->blend_cull.load();
@@ -1027,9 +1015,9 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
     if (kprof) {
         ws.ktimer.reset();
         TimerScope ts(&ws.ktimer);
-        return enqueue(frame_mem(ws, plan), plan, debug, prof, work, pblocks, opt);
+        return enqueue(frame_mem(ws, plan), plan, debug, prof, work, opt);
     }
-    if (!graph) return enqueue(frame_mem(ws, plan), plan, debug, prof, work, pblocks, opt);
+    if (!graph) return enqueue(frame_mem(ws, plan), plan, debug, prof, work, opt);
     const std::string key = shape_key(plan, true) + (opt.cull ? "c1" : "c0") + (opt.bin ? "b1" : "b0") + (opt.cull_tiles ? "t1" : "t0") +
                             (opt.buckets ? "d3" : "d4") + (ws.active ? "f1" : "f0");
     GraphEntry& g = ws.graphs[key];
@@ -1044,7 +1032,7 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
         HIPCHK(hipStreamBeginCapture(ws.stream, hipStreamCaptureModeThreadLocal));
         int cur = 0;
         try {
-            cur = enqueue(frame_mem(ws, plan), plan, debug, prof, work, pblocks, opt);
+            cur = enqueue(frame_mem(ws, plan), plan, debug, prof, work, opt);
         } catch (...) {
             (void)hipStreamEndCapture(ws.stream, &graph_t);
             if (graph_t) (void)hipGraphDestroy(graph_t);
@@ -1249,7 +1237,7 @@ void save_tune_file(tigas_context* ctx) {
 // replays; the fastest is cached per shape (and in the file named by TIGAS_TUNE_CACHE).
 // Frames are identical for every candidate, so tuning changes only speed.
 TileCfg autotune(tigas_context* ctx, Workspace& ws, Plan& plan) {
-    const std::string key = shape_key(plan, false) + (plan.persistent ? "|P" : "|G");
+    const std::string key = shape_key(plan, false) + (plan.batch ? "|P" : "|G");
     {
         std::lock_guard<std::mutex> lk(ctx->tune_mu);
         auto it = ctx->tuned.find(key);
@@ -1487,7 +1475,6 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_o
     m.views_src = nullptr;  // the view is stored by a kernel
     m.cnt = c.take<Counters>(sizeof(Counters));
     m.cnt_out = cnt_out ? cnt_out : c.take<FrameCounters>(sizeof(FrameCounters));
-    m.queue = c.take<uint32_t>(8 * 4);
     PreOut& o = m.pre;
     o.rec = c.take<Rec>((size_t)nrec * sizeof(Rec));
     o.rect = c.take<uint2>((size_t)nrec * 8);
@@ -1580,7 +1567,7 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     opt.cull = ctx->blend_cull.load();
     opt.bin = ctx->tile_bin.load();
     opt.cull_tiles = ctx->tile_cull.load();
-    (void)enqueue(m, plan, false, false, nullptr, 0, opt);
+    (void)enqueue(m, plan, false, false, nullptr, opt);
 }
 
 void debug_copy(Workspace& ws, const Plan& plan, int cur, int64_t n, uint32_t n_pad, tigas_debug_out* dbg) {
@@ -1746,7 +1733,7 @@ void server_render(tigas_server* sv, tigas_server::Slot& slot) {
     });
     tigas_context* ctx = sv->ctx;
     Plan plan;
-    plan.persistent = true;
+    plan.batch = true;
     plan.allow_graph = false;
     std::vector<tigas_frame> outs;
     std::vector<std::unique_ptr<SceneRef>> refs;
@@ -2240,7 +2227,6 @@ tigas_status tigas_context_create(int device, tigas_context** out) {
         c->device = device;
         hipDeviceProp_t prop;
         HIPCHK(hipGetDeviceProperties(&prop, device));
-        c->cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
         if (device < kScratchDevices) {  // device address of this device's scratch array, once per device
             std::lock_guard<std::mutex> lk(g_scratch_mu);
             if (!g_scratch_ptr[device]) {
@@ -2407,7 +2393,7 @@ tigas_status tigas_render_batch(tigas_scene* const* scenes, const tigas_pose* po
         if (!ctx) fail(TIGAS_E_INVALID, "null scene");
         HIPCHK(hipSetDevice(ctx->device));
         Plan plan;
-        plan.persistent = true;
+        plan.batch = true;
         std::vector<std::unique_ptr<SceneRef>> refs;
         for (int i = 0; i < n_views; ++i) {
             if (!scenes[i] || scenes[i]->ctx != ctx) fail(TIGAS_E_INVALID, "scenes must share one context");

@@ -687,7 +687,7 @@ __device__ void scan_chunk(const uint32_t* __restrict__ in, int n, const uint32_
 // After preprocess (second kernel of the chunked scan): compaction offsets of
 // the visible records; workgroup 0 also sets the totals V, D and FP64-fallback
 // count and the overflow flag; every workgroup clears part of the per-frame
-// accumulators of later kernels (digit totals, work queues, tile ranges).
+// accumulators of later kernels (digit totals, tile ranges).
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_visible(const uint32_t* __restrict__ blk_vis, int nblk,
                                                                const uint32_t* __restrict__ tot_vis,
                                                                const unsigned long long* __restrict__ tot_dup,
@@ -2667,7 +2667,8 @@ __device__ __forceinline__ uint8_t to_u8(float x) {
 struct BlendArgs {
     const ViewParams* views;
     int nviews;
-    uint32_t n_tiles;
+    uint32_t n_lists;
+    int block_log;
     const uint2* ranges;
     const uint32_t* vals;  // the lists: records, or with cells the view's records below masks of cells
     int cells;
@@ -2726,18 +2727,15 @@ __device__ __forceinline__ bool below_threshold(float A, float B, float C, float
     return q + L < LOG2_ALPHA_MIN - margin;  // false for NaN
 }
 
-// One tile of TW x TH pixels.  Each wave owns a block of 8x8 pixels, one per
-// lane; wave w takes block (w mod TW/8, w div TW/8).  It walks its depth-sorted
-// list 64 entries at a time and queues those whose pixel box meets its block;
+// One block of 8x8 pixels of a list's, by one wave, a pixel per lane.  It walks
+// the depth-sorted list 64 entries at a time and queues those whose pixel box meets the block;
 // 64 queued ones at a time are fetched whole, those whose exponent can reach
 // the skip threshold somewhere on the block (with culling on) are staged in
-// the wave's LDS slice (ballot + mbcnt), and the 64 lanes composite them front to
-// back in groups of eight, what is left of a group waiting for the next batch.
-// The records of a batch are fetched while the one before is composited.  Each
-// pixel's operations (and their rounding) are the same for every tile shape,
-// and the entries culling drops are ones every pixel of the block skips.  A wave
-// leaves as soon as all of its pixels have terminated; there is no barrier
-// between the waves of a tile.
+// LDS (ballot + mbcnt), and the 64 lanes composite them front to back in groups
+// of eight, what is left of a group waiting for the next batch.  Each pixel's
+// operations (and their rounding) are the same for every tile shape, and the
+// entries culling drops are ones every pixel of the block skips.  The wave
+// leaves as soon as all of its pixels have terminated.
 //
 // Bound by vector issue, so what has the form of a product with a constant
 // over the block goes to the matrix cores, which run beside it: the
@@ -2757,8 +2755,9 @@ __device__ __forceinline__ bool below_threshold(float A, float B, float C, float
 // kept the L1 busy (521 -> 426 us; a wave of 16 tiles' lists looks at 15 lists
 // of 64 entries); pairs of words, with exact blocks, cost the placement more
 // than they save (13 us at 3M/1080p).
-// The launch at 3M/1080p, 3M/4K, 1M/720p and over 32 views: 144, 418, 97 us and
-// 2.39 ms; with lists of the same size before, 170, 497, 110 us and 2.87 ms.
+// With a workgroup per tile, the launch at 3M/1080p, 3M/4K, 1M/720p and over 32
+// views took 144, 418, 97 us and 2.39 ms; with the vector form before, 170, 497,
+// 110 us and 2.87 ms.
 // x, from which nothing is formed ahead of this point: addresses and constants
 // that the compiler keeps over a loop for a rare step in it take registers.
 __device__ __forceinline__ uint32_t fresh(uint32_t x) {
@@ -2846,47 +2845,41 @@ __device__ __forceinline__ void blend_groups(const Stage& S, int lane, float pyr
     }
 }
 
-template <int TW, int TH, bool COUNT>
-__device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, int w, Stage& S) {
-    constexpr int BX = TW / 8;
-    int vi = 0;
-    {
-        int lo = 0, hi = A.nviews - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (A.views[mid].btile_base <= tile) lo = mid; else hi = mid - 1;
-        }
-        vi = lo;
-    }
-    const ViewParams& v = A.views[vi];
-    // tiles are numbered list by list, row-major inside a list; those of an
-    // edge list may lie outside the frame and have nothing to do
-    const int ls = v.lx + v.ly;
-    const uint32_t lt = (tile - v.btile_base) >> ls, sub = (tile - v.btile_base) & ((1u << ls) - 1u);
-    const int tx = ((int)(lt % (uint32_t)v.tiles_x) << v.lx) + (int)(sub & ((1u << v.lx) - 1u));
-    const int ty = ((int)(lt / (uint32_t)v.tiles_x) << v.ly) + (int)(sub >> v.lx);
+template <bool COUNT>
+__device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams& v, uint32_t lt, uint32_t block,
+                                            Stage& S) {
+    // the blocks of a list, row-major; those of an edge list may lie outside
+    // the frame and have nothing to do
+    // (scalars for what the whole wave shares, however the compiler loads it)
+    auto scalar = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    const int lw = scalar(v.tw_log + v.lx), lh = scalar(v.th_log + v.ly);
+    const int width = scalar(v.width), height = scalar(v.height);
+    const uint32_t nx = (uint32_t)scalar(v.tiles_x), rec0 = (uint32_t)scalar((int)v.rec_base);
+    const uint32_t ly = lt / nx, lx = lt - ly * nx;
+    const int sx = scalar((int)((lx << lw) + ((block & ((1u << (lw - 3)) - 1u)) << 3)));
+    const int sy = scalar((int)((ly << lh) + ((block >> (lw - 3)) << 3)));
+    if (sx >= width || sy >= height) return;
     const int lane = (int)fresh(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(fresh(~0u), 0u)));
-    const int sx = tx * TW + (w % BX) * 8, sy = ty * TH + (w / BX) * 8;
     const float pxr = (float)(lane & 7) + 0.5f, pyr = (float)(lane >> 3) + 0.5f;
     const float fsx = (float)sx, fsy = (float)sy;
     // the pixels still compositing, as a wave mask: the per-pair decisions are
     // combined in scalar registers and applied with one select
-    uint64_t live = ballot(sx + (lane & 7) < v.width && sy + (lane >> 3) < v.height);
+    uint64_t live = ballot(sx + (lane & 7) < width && sy + (lane >> 3) < height);
     f32x4 acc = {0.0f, 0.0f, 0.0f, 1.0f};  // r, g, b, T
     const f32x4 px4 = {pxr, pxr, pxr, pxr};
     uint32_t n_eval = 0, n_contrib = 0;  // (pixel, Gaussian) evaluations / contributions, COUNT only
     // the wave's block clipped to the image: the only pixels it must cover
-    const int bx1 = min(sx + 7, v.width - 1), by1 = min(sy + 7, v.height - 1);
+    const int bx1 = min(sx + 7, width - 1), by1 = min(sy + 7, height - 1);
     const uint2 rg = A.ranges[v.tile_base + lt];
-    const uint32_t end = live ? rg.y : rg.x;
+    const uint32_t begin = (uint32_t)scalar((int)rg.x);
+    const uint32_t end = (uint32_t)scalar((int)rg.y);
     auto wave_sync = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    uint32_t base = rg.x, queued = 0;
+    uint32_t base = begin, queued = 0;
     // the cells of the list that hold the block
-    const int lw = v.tw_log + v.lx, lh = v.th_log + v.ly;
     const uint32_t need = ((1u << 24) << ((sx & ((1 << lw) - 1)) >> cell_log(lw))) |
                           ((1u << 28) << ((sy & ((1 << lh) - 1)) >> cell_log(lh)));
     // (the lists' buffers have room for a read of 64 entries from any of them)
@@ -2904,7 +2897,7 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
             uint64_t m;
             if (A.cells) {
                 m = in & ballot((en & need) == need);
-                en = (en & 0xffffffu) + v.rec_base;
+                en = (en & 0xffffffu) + rec0;
             } else {
                 bool hit = en < A.nrec && __builtin_amdgcn_inverse_ballot_w64(in);
                 if (hit) {
@@ -2996,11 +2989,11 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
         }
     }
     const int ln = (int)fresh(lane), px = sx + (ln & 7), py = sy + (ln >> 3);
-    if (px < v.width && py < v.height) {
+    if (px < width && py < height) {
         const float r = __builtin_fmaf(acc[3], v.bg[0], acc[0]);
         const float g = __builtin_fmaf(acc[3], v.bg[1], acc[1]);
         const float b = __builtin_fmaf(acc[3], v.bg[2], acc[2]);
-        const size_t pix = (size_t)py * (size_t)v.width + (size_t)px;
+        const size_t pix = (size_t)py * (size_t)width + (size_t)px;
         if (v.fmt == 1) {
             float* out = reinterpret_cast<float*>(v.out_ptr) + pix * 3;
             out[0] = r;
@@ -3015,59 +3008,26 @@ __device__ __forceinline__ void blend_tile(const BlendArgs& A, uint32_t tile, in
     }
 }
 
-// One workgroup per tile, in the dense-first order when one is given (the
-// longest lists first: the launch ends with short tiles instead of a tail of
-// long ones).  Otherwise XCD-aware: consecutive workgroup ids go round-robin
-// to the 8 XCDs; XCD x takes the chunks of BLEND_CHUNK consecutive tiles
-// numbered x, x + 8, x + 16, ..., so neighbouring tiles (which share
-// Gaussians) meet in the same L2 while every XCD gets a share of every part
-// of the image (dense and sparse regions alike).
-constexpr uint32_t BLEND_CHUNK = 16;
-template <int TW, int TH, bool COUNT>
-__global__ __launch_bounds__(TW* TH, COUNT ? 1 : 8) void k_blend(BlendArgs A) {
-    constexpr int NW = TW * TH / 64;
-    __shared__ Stage stage[NW];
-    uint32_t tile;
-    if (A.order) {
-        if (blockIdx.x >= A.n_tiles) return;
-        const int ls = A.views[0].lx + A.views[0].ly;
-        tile = (A.order[blockIdx.x >> ls] << ls) | (blockIdx.x & ((1u << ls) - 1u));
-    } else {
-        const uint32_t j = blockIdx.x >> 3, x = blockIdx.x & 7;
-        tile = ((j / BLEND_CHUNK) * 8u + x) * BLEND_CHUNK + (j % BLEND_CHUNK);
-        if (tile >= A.n_tiles) return;
-    }
-    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    blend_tile<TW, TH, COUNT>(A, tile, w, stage[w]);
-}
-
-// Persistent form for many views of uneven size: a fixed grid of resident
-// workgroups pulls tiles from 8 device work queues, one per band of
-// consecutive tiles; a workgroup starts on the band of its XCD (id mod 8) and
-// moves on to the other bands when its own is drained.  The queue counters are
-// cleared by k_scan_visible each frame; every workgroup exits once all bands
-// are drained.
-template <int TW, int TH>
-__global__ __launch_bounds__(TW* TH, TW* TH == 64 ? 7 : 8) void k_blend_persistent(BlendArgs A, uint32_t* __restrict__ queue) {
-    constexpr int NW = TW * TH / 64;
-    __shared__ Stage stage[NW];
-    __shared__ uint32_t next;
-    const uint32_t per = (A.n_tiles + 7) / 8;
-    const int home = blockIdx.x & 7, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    for (int k = 0; k < 8; ++k) {
-        const int band = (home + k) & 7;
-        const uint32_t first = (uint32_t)band * per;
-        const uint32_t band_end = min(A.n_tiles, first + per);
-        if (first >= band_end) continue;
-        for (;;) {
-            if (w == 0 && lane_id() == 0) next = first + atomicAdd(&queue[band], 1u);
-            __syncthreads();
-            const uint32_t tile = next;
-            __syncthreads();
-            if (tile >= band_end) break;
-            blend_tile<TW, TH, false>(A, (uint32_t)__builtin_amdgcn_readfirstlane((int)tile), w, stage[w]);
-        }
-    }
+// One wave per workgroup: a workgroup of several holds its slots until its
+// longest block is done, and one that pulled its tiles from a queue waited for
+// it at every tile.  Launches of one wave against a workgroup per tile of 16x32:
+// 3M/1080p 131 and 145 us, 3M/4K 378 and 423, 1M/720p 91 and 98, 20k/256x256 33
+// and 39, 32 views 2.07 ms and 2.43 (a queue of four blocks an item 2.89).
+// A workgroup per block (2^block_log for every list, the most of any view):
+// list i of the dispatch order on XCD i mod 8 (consecutive workgroups go
+// round-robin to the XCDs), so that a list's records are fetched into one L2.
+// A single view's lists come dense first: the launch ends with short ones
+// instead of a tail of long ones.
+template <bool COUNT>
+__global__ __launch_bounds__(64, COUNT ? 1 : 8) void k_blend(BlendArgs A) {
+    __shared__ Stage stage;
+    const uint32_t slot = blockIdx.x >> 3, i = ((slot >> A.block_log) << 3) + (blockIdx.x & 7u);
+    if (i >= A.n_lists) return;
+    const uint32_t list = A.order ? A.order[i] : i, block = slot & ((1u << A.block_log) - 1u);
+    const int vi = view_of(list, A.nviews, [&](int k) { return A.views[k].tile_base; });
+    const ViewParams& v = A.views[vi];
+    if (block >> (v.tw_log + v.lx + v.th_log + v.ly - 6)) return;
+    blend_block<COUNT>(A, v, list - v.tile_base, block, stage);
 }
 
 // One view's parameters, passed by value as a kernel argument, stored to
@@ -3271,43 +3231,20 @@ void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_
                      nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
 }
 
-template <int TW, int TH>
-static void blend_launch(const BlendArgs& A, bool count, uint32_t* queue, int persistent_blocks, hipStream_t st) {
-    if (queue) {
-        TIGAS_LAUNCH((k_blend_persistent<TW, TH>), dim3(persistent_blocks), dim3(TW * TH), st, A, queue);
-    } else {
-        const uint32_t per_round = 8 * BLEND_CHUNK;  // one chunk for every XCD
-        const uint32_t tiles = ((A.n_tiles + per_round - 1) / per_round) * per_round;
-        const dim3 grid(tiles);
-        if (count) TIGAS_LAUNCH((k_blend<TW, TH, true>), grid, dim3(TW * TH), st, A);
-        else TIGAS_LAUNCH((k_blend<TW, TH, false>), grid, dim3(TW * TH), st, A);
+void launch_blend(const ViewParams* views_dev, const ViewParams* views_host, int nviews, uint32_t n_lists,
+                  const uint2* ranges, const uint32_t* vals, const PreOut& o, uint32_t nrec, bool cells,
+                  unsigned long long* work, bool cull, const uint32_t* order, hipStream_t st) {
+    if (n_lists == 0) return;
+    int bl = 0;  // log2 of a list's blocks
+    for (int i = 0; i < nviews; ++i) {
+        const ViewParams& v = views_host[i];
+        bl = std::max(bl, v.tw_log + v.lx + v.th_log + v.ly - 6);
     }
-}
-
-void launch_blend(const ViewParams* views_dev, int nviews, uint32_t n_tiles, const uint2* ranges,
-                  const uint32_t* vals, const PreOut& o, uint32_t nrec, int tile_w, int tile_h,
-                  bool cells, unsigned long long* work, uint32_t* queue, int persistent_blocks, bool cull,
-                  const uint32_t* order, hipStream_t st) {
-    if (n_tiles == 0) return;
-    const BlendArgs A{views_dev, nviews, n_tiles, ranges, vals, cells ? 1 : 0, o.rec, nrec, work, cull ? 1 : 0, order};
-    const bool count = work != nullptr;
-    if (count) queue = nullptr;
-    if (tile_w == 8 && tile_h == 8) blend_launch<8, 8>(A, count, queue, persistent_blocks, st);
-    else if (tile_w == 16 && tile_h == 32) blend_launch<16, 32>(A, count, queue, persistent_blocks, st);
-    else if (tile_w == 32 && tile_h == 16) blend_launch<32, 16>(A, count, queue, persistent_blocks, st);
-    else blend_launch<16, 16>(A, count, queue, persistent_blocks, st);
-}
-
-// Resident workgroups per CU of the persistent blend kernel for a tile shape.
-int blend_persistent_occupancy(int tile_w, int tile_h) {
-    int n = 0;
-#define TIGAS_OCC(TW, TH) (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_blend_persistent<TW, TH>, TW * TH, 0)
-    if (tile_w == 8 && tile_h == 8) TIGAS_OCC(8, 8);
-    else if (tile_w == 16 && tile_h == 32) TIGAS_OCC(16, 32);
-    else if (tile_w == 32 && tile_h == 16) TIGAS_OCC(32, 16);
-    else TIGAS_OCC(16, 16);
-#undef TIGAS_OCC
-    return n > 0 ? n : 1;
+    const BlendArgs A{views_dev, nviews, n_lists, bl, ranges, vals, cells ? 1 : 0, o.rec, nrec, work, cull ? 1 : 0,
+                      order};
+    const dim3 grid(((n_lists + 7) / 8 * 8) << bl);
+    if (work) TIGAS_LAUNCH(k_blend<true>, grid, dim3(64), st, A);
+    else TIGAS_LAUNCH(k_blend<false>, grid, dim3(64), st, A);
 }
 
 void launch_wave_scan_selftest(const uint32_t* in, uint32_t* out, int n, hipStream_t st) {

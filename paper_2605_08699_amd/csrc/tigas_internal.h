@@ -74,11 +74,11 @@ struct ViewParams {
     int width, height;
     // Tile lists: 2^lx x 2^ly tiles of 2^tw_log x 2^th_log pixels share one
     // (a single tile unless the placement is by counting); tiles_x, tiles_y
-    // and tile_base number the lists, btile_base the tiles.  Where the lists
-    // are built, a list is what is called a tile.
+    // and tile_base number the lists.  Where the lists are built, a list is what
+    // is called a tile.
     int tw_log, th_log, lx, ly, tiles_x, tiles_y;
     int cells;           // the records' list rectangles carry their end cells
-    uint32_t tile_base, btile_base;
+    uint32_t tile_base;
     int sh_degree;
     int fmt;             // 0 RGB8, 1 RGBF32
     float bg[3];
@@ -195,7 +195,7 @@ struct TileMem {
 
 // Arrays cleared (as u32 words) by the first kernel after preprocess.
 struct ZeroList {
-    static constexpr int N = 4;
+    static constexpr int N = 2;
     uint32_t* p[N];
     uint32_t n[N];
 };
@@ -329,17 +329,12 @@ struct JpegBatch {
     uint32_t* seg_len;      // [intervals] output bytes (stuffing and marker included)
 };
 void launch_jpeg(const JpegBatch& a, uint32_t nseg, hipStream_t st);
-void launch_blend(const ViewParams* views_dev, int nviews, uint32_t n_tiles, const uint2* ranges,
-                  const uint32_t* vals, const PreOut& o, uint32_t nrec, int tile_w, int tile_h,
-                  bool cells, unsigned long long* work, uint32_t* queue, int persistent_blocks, bool cull,
-                  const uint32_t* order, hipStream_t st);
-// order (one workgroup per tile, without queue): the tiles' dispatch order,
-// or null for the XCD-chunked order.
-// With `queue` (8 counters cleared per frame) the blend runs as a persistent
-// kernel of persistent_blocks workgroups pulling tiles from work queues.
-// cull: drop, per wave, the entries whose exponent stays below the skip threshold on the
-// wave's whole pixel block (they would be skipped at every pixel anyway).
-int blend_persistent_occupancy(int tile_w, int tile_h);
+// Composites the lists (n_lists of all views; a single view's in `order`).
+// cull: drop the entries whose exponent stays below the skip threshold on a
+// block's whole pixel block (they would be skipped at every pixel anyway).
+void launch_blend(const ViewParams* views_dev, const ViewParams* views_host, int nviews, uint32_t n_lists,
+                  const uint2* ranges, const uint32_t* vals, const PreOut& o, uint32_t nrec, bool cells,
+                  unsigned long long* work, bool cull, const uint32_t* order, hipStream_t st);
 void launch_wave_scan_selftest(const uint32_t* in, uint32_t* out, int n, hipStream_t st);
 
 // Per-launch timing for profiling: while a timer is installed for the calling
