@@ -2845,9 +2845,9 @@ __device__ __forceinline__ void blend_groups(const Stage& S, int lane, float pyr
     }
 }
 
-template <bool COUNT>
+template <bool COUNT, int PARTS>
 __device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams& v, uint32_t lt, uint32_t block,
-                                            Stage& S) {
+                                            uint32_t part, Stage& S) {
     // the blocks of a list, row-major; those of an edge list may lie outside
     // the frame and have nothing to do
     // (scalars for what the whole wave shares, however the compiler loads it)
@@ -2860,11 +2860,18 @@ __device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams
     const int sy = scalar((int)((ly << lh) + ((block >> (lw - 3)) << 3)));
     if (sx >= width || sy >= height) return;
     const int lane = (int)fresh(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(fresh(~0u), 0u)));
+    // this wave's part of the block: all of it, the upper or lower half, or a
+    // quarter; its lanes, and the rectangle of its pixel centres
+    const int qx = PARTS == 4 ? (int)(part & 1u) * 4 : 0;
+    const int qy = PARTS == 4 ? (int)(part >> 1) * 4 : PARTS == 2 ? (int)part * 4 : 0;
+    const uint64_t own = PARTS == 1 ? ~0ull : (PARTS == 2 ? 0xffffffffull : 0x0f0f0f0full) << (qx + 8 * qy);
+    const float cx0 = 0.5f + (float)qx, cx1 = PARTS == 4 ? cx0 + 3.0f : 7.5f;
+    const float cy0 = 0.5f + (float)qy, cy1 = PARTS > 1 ? cy0 + 3.0f : 7.5f;
     const float pxr = (float)(lane & 7) + 0.5f, pyr = (float)(lane >> 3) + 0.5f;
     const float fsx = (float)sx, fsy = (float)sy;
     // the pixels still compositing, as a wave mask: the per-pair decisions are
     // combined in scalar registers and applied with one select
-    uint64_t live = ballot(sx + (lane & 7) < width && sy + (lane >> 3) < height);
+    uint64_t live = ballot(sx + (lane & 7) < width && sy + (lane >> 3) < height) & own;
     f32x4 acc = {0.0f, 0.0f, 0.0f, 1.0f};  // r, g, b, T
     const f32x4 px4 = {pxr, pxr, pxr, pxr};
     uint32_t n_eval = 0, n_contrib = 0;  // (pixel, Gaussian) evaluations / contributions, COUNT only
@@ -2937,7 +2944,7 @@ __device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams
         // pixel centre relative to the block's origin, hi and lo parts combined here
         const float u = (f0.x - fsx) + f0.z, v0 = (f0.y - fsy) + f0.w;
         bool low;
-        const bool below = below_threshold(f1.x, f1.y, f1.z, f1.w, 0.5f - u, 7.5f - u, 0.5f - v0, 7.5f - v0, &low);
+        const bool below = below_threshold(f1.x, f1.y, f1.z, f1.w, cx0 - u, cx1 - u, cy0 - v0, cy1 - v0, &low);
         const bool hit = (uint32_t)lane < nb && !(A.cull && below);
         const uint64_t m = ballot(hit);
         capped = (left ? capped : 0) | (m & ~ballot(low));
@@ -2989,7 +2996,7 @@ __device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams
         }
     }
     const int ln = (int)fresh(lane), px = sx + (ln & 7), py = sy + (ln >> 3);
-    if (px < width && py < height) {
+    if (px < width && py < height && __builtin_amdgcn_inverse_ballot_w64(own)) {
         const float r = __builtin_fmaf(acc[3], v.bg[0], acc[0]);
         const float g = __builtin_fmaf(acc[3], v.bg[1], acc[1]);
         const float b = __builtin_fmaf(acc[3], v.bg[2], acc[2]);
@@ -3013,21 +3020,22 @@ __device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams
 // it at every tile.  Launches of one wave against a workgroup per tile of 16x32:
 // 3M/1080p 131 and 145 us, 3M/4K 378 and 423, 1M/720p 91 and 98, 20k/256x256 33
 // and 39, 32 views 2.07 ms and 2.43 (a queue of four blocks an item 2.89).
-// A workgroup per block (2^block_log for every list, the most of any view):
+// A workgroup per part of a block (2^block_log blocks for every list, the most of any view):
 // list i of the dispatch order on XCD i mod 8 (consecutive workgroups go
 // round-robin to the XCDs), so that a list's records are fetched into one L2.
 // A single view's lists come dense first: the launch ends with short ones
 // instead of a tail of long ones.
-template <bool COUNT>
+template <bool COUNT, int PARTS>
 __global__ __launch_bounds__(64, COUNT ? 1 : 8) void k_blend(BlendArgs A) {
     __shared__ Stage stage;
-    const uint32_t slot = blockIdx.x >> 3, i = ((slot >> A.block_log) << 3) + (blockIdx.x & 7u);
+    constexpr int PL = PARTS / 2;  // log2 of 1, 2, 4
+    const uint32_t part = (blockIdx.x >> 3) & (PARTS - 1), slot = blockIdx.x >> (3 + PL), i = ((slot >> A.block_log) << 3) + (blockIdx.x & 7u);
     if (i >= A.n_lists) return;
     const uint32_t list = A.order ? A.order[i] : i, block = slot & ((1u << A.block_log) - 1u);
     const int vi = view_of(list, A.nviews, [&](int k) { return A.views[k].tile_base; });
     const ViewParams& v = A.views[vi];
     if (block >> (v.tw_log + v.lx + v.th_log + v.ly - 6)) return;
-    blend_block<COUNT>(A, v, list - v.tile_base, block, stage);
+    blend_block<COUNT, PARTS>(A, v, list - v.tile_base, block, part, stage);
 }
 
 // One view's parameters, passed by value as a kernel argument, stored to
@@ -3231,20 +3239,35 @@ void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_
                      nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
 }
 
+// Up to these numbers of blocks a wave takes a quarter or a half of one.  The
+// chip has 1024 SIMDs: with few blocks the launch lasts as long as the longest
+// block's chain of pairs, and a part of it meets fewer Gaussians (a quarter
+// 55 where the block meets 89, at 20k/256x256); with more of them the work that
+// the parts do again costs more.  Launches of 1, 2 and 4 waves a block, 20k and
+// 100k Gaussians over the frame: 256x256 (1024 blocks) 33 / 28 / 24 and 42 / 35 /
+// 31 us; 320x320 (1600) 28 / 25 / 23 and 36 / 34 / 32; 384x384 (2304) 25.0 / 22.6 /
+// 22.1 and 32.1 / 32.1 / 35.2; 448x448 (3136) 23.7 / 22.1 / 24.2 and 31.8 / 31.9 /
+// 37.9; 512x512 (4096) 22.4 / 21.8 / 27.9 and 31.1 / 34.0 / 43.9.
+constexpr uint64_t BLEND_QUARTERS = 1800, BLEND_HALVES = 3200;
+
 void launch_blend(const ViewParams* views_dev, const ViewParams* views_host, int nviews, uint32_t n_lists,
                   const uint2* ranges, const uint32_t* vals, const PreOut& o, uint32_t nrec, bool cells,
                   unsigned long long* work, bool cull, const uint32_t* order, hipStream_t st) {
     if (n_lists == 0) return;
     int bl = 0;  // log2 of a list's blocks
+    uint64_t blocks = 0;  // inside the frames
     for (int i = 0; i < nviews; ++i) {
         const ViewParams& v = views_host[i];
         bl = std::max(bl, v.tw_log + v.lx + v.th_log + v.ly - 6);
+        blocks += (uint64_t)((v.width + 7) / 8) * (uint64_t)((v.height + 7) / 8);
     }
     const BlendArgs A{views_dev, nviews, n_lists, bl, ranges, vals, cells ? 1 : 0, o.rec, nrec, work, cull ? 1 : 0,
                       order};
     const dim3 grid(((n_lists + 7) / 8 * 8) << bl);
-    if (work) TIGAS_LAUNCH(k_blend<true>, grid, dim3(64), st, A);
-    else TIGAS_LAUNCH(k_blend<false>, grid, dim3(64), st, A);
+    if (work) TIGAS_LAUNCH((k_blend<true, 1>), grid, dim3(64), st, A);
+    else if (blocks <= BLEND_QUARTERS) TIGAS_LAUNCH((k_blend<false, 4>), dim3(grid.x * 4), dim3(64), st, A);
+    else if (blocks <= BLEND_HALVES) TIGAS_LAUNCH((k_blend<false, 2>), dim3(grid.x * 2), dim3(64), st, A);
+    else TIGAS_LAUNCH((k_blend<false, 1>), grid, dim3(64), st, A);
 }
 
 void launch_wave_scan_selftest(const uint32_t* in, uint32_t* out, int n, hipStream_t st) {

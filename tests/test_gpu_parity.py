@@ -308,6 +308,29 @@ def test_tiles_sharing_a_list_give_the_same_frame(ctx, size, tile, kind):
     s.free()
 
 
+@pytest.mark.parametrize("kind", ["small", "mixed", "stack"])
+@pytest.mark.parametrize("size", [(320, 320), (317, 331), (448, 448), (451, 449)])
+def test_blend_by_quarters_halves_and_whole_blocks(ctx, size, kind):
+    """One, two and three views of one frame in a launch: few blocks are
+    composited by quarters, some by halves, many whole, with blocks that hang
+    over the frame's edges; the frame is the same."""
+    W, H = size
+    s = ctx.load_scene(_rect_scene(kind, 6000 if kind != "mixed" else 700))
+    k = intr(max(W, H) / 2.0, W / 2, H / 2)
+    _say("blend parts", size, kind)
+    want = ctx.render(s, eye_pose(), k, W, H, fmt="f32", bg=(0.1, 0.6, 0.3), tile=(16, 16))
+    for n in (2, 3):
+        for got in ctx.render_batch([s] * n, [eye_pose()] * n, [k] * n, [W] * n, [H] * n, fmt="f32",
+                                    bg=(0.1, 0.6, 0.3), tile=(16, 16)):
+            np.testing.assert_array_equal(got, want)
+    small = ctx.render(s, eye_pose(), intr(40.0, 33, 30), 66, 60, fmt="f32", bg=(0.1, 0.6, 0.3), tile=(16, 16))
+    n = 60  # 4320 blocks in all
+    for got in ctx.render_batch([s] * n, [eye_pose()] * n, [intr(40.0, 33, 30)] * n, [66] * n, [60] * n, fmt="f32",
+                                bg=(0.1, 0.6, 0.3), tile=(16, 16)):
+        np.testing.assert_array_equal(got, small)
+    s.free()
+
+
 @pytest.mark.parametrize("opacity", [0.02, 0.6, 0.9999])
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 64, 65, 71, 72, 73, 129, 700])
 def test_blend_groups_and_batches(ctx, n, opacity):
