@@ -472,17 +472,20 @@ def kernel_work(name, w, n, storage, tile_passes):
         # sorted record id and packed tile rectangle per visible Gaussian;
         # tile word + record id per duplicate
         return "hbm", V * 8 + D * 8
-    if "k_sort_downsweep<true, false, " in name:
-        # the depth passes (three of 9-bit digits, else four of 8 bits): key,
-        # record and packed rectangle read and written
+    if "k_sort_downsweep<true, false" in name:
+        # radix depth passes (four of 8 bits; three of 9-bit digits in older
+        # profiles): key, record and packed rectangle read and written
         return "hbm", (3 if "false, 512" in name else 4) * 24 * V
-    if "k_sort_downsweep<false, false, " in name:
+    if "k_bucket_scatter" in name:
+        # depth key and rectangle of every record, one 16-byte element per
+        # visible one
+        return "hbm", n * 12 + V * 16
+    if "k_bucket_sort" in name:
+        # an element read, record and packed rectangle written
+        return "hbm", V * 24
+    if "k_sort_downsweep<false, false" in name:
         # the tile passes: key + value read and written per duplicate
         return "hbm", tile_passes * 16 * D
-    if "k_bin_emit" in name:
-        # depth-ordered record and packed rectangle read per visible Gaussian,
-        # one record id written per entry
-        return "hbm", V * 8 + D * 4
     return None
 
 
@@ -503,7 +506,9 @@ def roofline(v, n, storage):
     """Roofline of the dominant kernel of the FP32 run: algorithmic work per
     launch / average launch duration (HIP events around every launch)."""
     w = v["work"]
-    depth_passes = 3 if any("k_sort_downsweep<true, false, 512" in k for k in v["kernels"]) else 4
+    # the bucketed depth order counts as three passes, the radix one takes four
+    radix = [k for k in v["kernels"] if "k_sort_downsweep<true, false" in k]
+    depth_passes = 4 if radix and not any("false, 512" in k for k in radix) else 3
     tile_passes = v["sort_passes"] - depth_passes
     ranked = sorted(v["kernels"].items(), key=lambda kv: -kv[1]["ms_per_frame"])
     for name, k in ranked:

@@ -483,7 +483,7 @@ struct tigas_context {
     double stage_ms[6] = {0, 0, 0, 0, 0, 0};
     int64_t stage_frames = 0;
     std::mutex tune_mu;
-    std::map<std::string, TileCfg> tuned;  // shape -> best tile / batch depth
+    std::map<std::string, TileCfg> tuned;  // shape -> best tile
     std::string tune_file;
     // asynchronous frames: ticket -> (workspace, slot) while in flight, then its outcome
     struct AsyncDone {
@@ -1232,7 +1232,7 @@ void save_tune_file(tigas_context* ctx) {
     std::rename(tmp.c_str(), ctx->tune_file.c_str());
 }
 
-// Picks the tile shape and batch depth for the plan's shape: each candidate
+// Picks the tile shape for the plan's shape: each candidate
 // is rendered (graph captured, two warm-ups) and timed by the median of seven
 // replays; the fastest is cached per shape (and in the file named by TIGAS_TUNE_CACHE).
 // Frames are identical for every candidate, so tuning changes only speed.
