@@ -205,7 +205,8 @@ struct Plan {
     uint64_t row_words = 0;
     uint32_t nunits = 0, tchunks = 0, max_tiles = 0;  // tile placement (set_tiles)
     TileCfg tc{16, 16, 64, 1};
-    bool batch = false;  // a batch's plan: tuned apart from single frames
+    bool batch = false;   // a batch's plan: tuned apart from single frames
+    bool shared = false;  // tiles may share lists (set_tiles)
     bool allow_graph = true;  // capture/replay (off for one-off shapes such as serving batches)
 };
 
@@ -680,6 +681,7 @@ void list_scale(ViewParams& v, const TileCfg& tc) {
 void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
     plan.tc = tc;
     plan.n_tiles = plan.n_frame_tiles = plan.tchunks = plan.max_tiles = 0;
+    plan.shared = shared;
     bool cells = shared;
     for (const Group& g : plan.groups) cells = cells && g.n_pad <= 1u << CELL_REC_BITS;
     for (ViewParams& v : plan.views) {
@@ -780,8 +782,8 @@ std::string shape_key(const Plan& plan, bool with_tiles) {
         k += buf;
     }
     if (with_tiles) {
-        std::snprintf(buf, sizeof buf, "t%dx%d:%d:%d:%d", plan.tc.tw, plan.tc.th, plan.tc.bd, plan.tc.ppl,
-                      (int)plan.batch);
+        std::snprintf(buf, sizeof buf, "t%dx%d:%d:%d:%d:%d", plan.tc.tw, plan.tc.th, plan.tc.bd, plan.tc.ppl,
+                      (int)plan.batch, (int)plan.shared);
         k += buf;
     }
     return k;
@@ -866,6 +868,14 @@ struct LaunchOptions {
     bool bin = true;          // tile digit placed by counting (else radix passes over the duplicates)
     bool cull_tiles = false;  // duplicates only for tiles the Gaussian can reach (radix passes then)
     bool buckets = true;      // bucketed depth sort when the rectangles pack (else four radix passes)
+    // A plan of shared lists was laid out for the placement by counting: a
+    // switch flipped by another thread since then waits for the next frame.
+    void follow(const Plan& plan) {
+        if (plan.shared) {
+            bin = true;
+            cull_tiles = false;
+        }
+    }
 };
 
 // Whether every view's tile rectangles fit the packed one-word form.
@@ -1010,6 +1020,7 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
     opt.bin = ctx->tile_bin.load();
     opt.cull_tiles = ctx->tile_cull.load();
     opt.buckets = !ctx->depth4.load();
+    opt.follow(plan);
     const bool kprof = ctx->profile_kernels.load();
     const bool graph = ctx->use_graphs.load() && plan.allow_graph && !debug && !work && !prof && !kprof;
     if (kprof) {
@@ -1567,6 +1578,7 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     opt.cull = ctx->blend_cull.load();
     opt.bin = ctx->tile_bin.load();
     opt.cull_tiles = ctx->tile_cull.load();
+    opt.follow(plan);
     (void)enqueue(m, plan, false, false, nullptr, opt);
 }
 
