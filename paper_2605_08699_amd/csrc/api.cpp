@@ -967,7 +967,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     int cur = cd;
     if (bin) {
         // tile digit by counting, straight from the depth-ordered Gaussians
-        launch_tiles(m.tm, m.bk, vdev, plan.views.data(), nv, cnt, !opt.buckets, plan.tchunks, sb.val[cv], sb.ext[cv],
+        launch_tiles(m.tm, m.bk, vdev, plan.views.data(), nv, plan.nrec, cnt, !opt.buckets, plan.tchunks, sb.val[cv], sb.ext[cv],
                      cells, m.ranges, nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
                      debug ? sb.key[cd] : nullptr, debug ? sb.ext[cd] : nullptr, o.zkey, st);
         mark(4);

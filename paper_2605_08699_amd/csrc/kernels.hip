@@ -2340,15 +2340,21 @@ __global__ __launch_bounds__(1024) void k_tile_scan(TileMem m, BucketMem b, cons
 // of 3M/4K 57 (two radix passes with duplicates, ranges and order: 305), that
 // of 32 views 0.83 ms (two radix passes: 2.55).  Gaussians of more than 16
 // tiles are spread over the lanes: from 32 on 75 us instead of 72.
-template <bool DEBUG>
-__global__ __launch_bounds__(TILE_THREADS) void k_tile_emit(
+// Few units leave the chip idle, and each lasts as long as its waves' chains of
+// queues: up to TILE_WIDE_RECORDS records eight waves share a unit's rows instead
+// of four.  Launches with 4 / 8 waves: 20k records 9.8 / 8.9 us, 100k 11.2 / 8.6,
+// 200k 16.1 / 10.5, 400k 14.4 / 11.1, 800k 14.1 / 13.2, 1M 13.8 / 16.1, 3M 29.7 /
+// 32.4, 32 views of 3M 434 / 681 (16 waves: 20k 9.2, 200k 9.2, 400k 11.6, 800k 19.6).
+constexpr uint32_t TILE_WIDE_RECORDS = 800u << 10;
+template <bool DEBUG, int NW>
+__global__ __launch_bounds__(NW * 64) void k_tile_emit(
     TileMem m, BucketMem b, const ViewParams* __restrict__ views, int nviews, const Counters* __restrict__ cnt,
     bool flat, uint32_t nfront, uint32_t nchunks, uint2* __restrict__ ranges, uint32_t* __restrict__ order,
     FrameCounters* host_cnt, const uint32_t* __restrict__ rec, const uint32_t* __restrict__ packed,
     bool cells, uint32_t* __restrict__ val_out, uint32_t* __restrict__ tile_out, uint32_t* __restrict__ depth_out,
     const uint32_t* __restrict__ zkey) {
-    constexpr int NT = TILE_THREADS, NW = TILE_WAVES;
-    static_assert(NW == 4, "rows modulo four");
+    constexpr int NT = NW * 64;
+    static_assert((NW & (NW - 1)) == 0, "rows modulo the waves");
     constexpr int FRONT_CHUNKS = TILE_FRONT_TILES / TILE_CHUNK;
     constexpr uint32_t MANY = 16;  // tiles from which a Gaussian is spread over the lanes
     __shared__ unsigned long long mask[TILE_CELLS];
@@ -3217,7 +3223,7 @@ void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t ca
 }
 
 void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
-                  int nviews, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
+                  int nviews, uint32_t nrec, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
                   const uint32_t* packed, bool cells, uint2* ranges, uint32_t* order,
                   FrameCounters* host_cnt, uint32_t* val_out,
                   uint32_t* tile_out, uint32_t* depth_out, const uint32_t* zkey, hipStream_t st) {
@@ -3232,10 +3238,13 @@ void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_
     if (nchunks) TIGAS_LAUNCH(k_tile_scan, dim3(nchunks), dim3(1024), st, m, b, views_dev, nviews, cnt, flat);
     const uint32_t gx = (nfront + units + 7) / 8 * 8;  // a multiple of the XCDs: a column of the grid stays on one
     if (tile_out)
-        TIGAS_LAUNCH(k_tile_emit<true>, dim3(gx, groups), dim3(TILE_THREADS), st, m, b, views_dev, nviews, cnt, flat,
+        TIGAS_LAUNCH((k_tile_emit<true, 4>), dim3(gx, groups), dim3(256), st, m, b, views_dev, nviews, cnt, flat,
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
+    else if (nrec <= TILE_WIDE_RECORDS)
+        TIGAS_LAUNCH((k_tile_emit<false, 8>), dim3(gx, groups), dim3(512), st, m, b, views_dev, nviews, cnt, flat,
                      nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
     else
-        TIGAS_LAUNCH(k_tile_emit<false>, dim3(gx, groups), dim3(TILE_THREADS), st, m, b, views_dev, nviews, cnt, flat,
+        TIGAS_LAUNCH((k_tile_emit<false, 4>), dim3(gx, groups), dim3(256), st, m, b, views_dev, nviews, cnt, flat,
                      nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
 }
 

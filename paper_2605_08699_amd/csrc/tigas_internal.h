@@ -274,7 +274,7 @@ void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, h
 // nchunks: chunks of TILE_CHUNK tiles over all views.  order (may be null):
 // receives the blend's dense-first dispatch order (a single view).
 void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
-                  int nviews, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
+                  int nviews, uint32_t nrec, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
                   const uint32_t* packed, bool cells, uint2* ranges, uint32_t* order,
                   FrameCounters* host_cnt, uint32_t* val_out, uint32_t* tile_out, uint32_t* depth_out,
                   const uint32_t* zkey, hipStream_t st);
