@@ -1133,14 +1133,20 @@ __device__ __forceinline__ uint32_t key_bucket(uint32_t key, const uint32_t* cdf
 }
 
 // Per segment of a view's records: the records of each bucket (rows) and the
-// smallest and largest visible key.  Every workgroup forms the view's sample
-// distribution itself (the first one of the view also stores it for the
-// scatter): the samples are 1/64 of the keys, and a launch of its own would
-// cost more.  All share the clearing of zl.  64 VGPRs: two workgroups per CU.
+// smallest and largest visible key.  In a plan of one round of workgroups each
+// forms the view's sample distribution itself (the first one of the view also
+// stores it for the scatter): the samples are 1/64 of the keys, and a launch of
+// its own would cost more (FORM).  In larger plans a workgroup per view forms it
+// first (FORM_ONLY), and the segments read it (READ): 32 views of 3M records in
+// 5888 segments 226 us in two launches, 278 formed by all.
+// All share the clearing of zl.  64 VGPRs: two workgroups per CU.
 // Bound by latency (3M records: 512 workgroups of six rounds, 8192 samples
 // each); the preprocess blocks' totals are summed segment by segment: one
 // workgroup for all 11720 blocks of 3M records was the last to end.
 // 3M records: 25 us with that workgroup, 18 without.
+enum SampleMode { FORM, FORM_ONLY, READ };
+constexpr uint32_t BUCKET_FORM_SEGMENTS = 512;  // a round: two workgroups on each of 256 compute units
+template <SampleMode MODE>
 __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, BucketMem b,
                                                                     const ViewParams* __restrict__ views, int nviews,
                                                                     uint32_t nseg, uint32_t seg_len, ZeroList zl) {
@@ -1151,13 +1157,16 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
     __shared__ unsigned long long tot64[2];
     static_assert(NT / 4 >= SEG_MAX / K1_THREADS, "a thread of the first waves per preprocess block");
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (MODE != FORM_ONLY) {
 #pragma unroll
-    for (int k = 0; k < ZeroList::N; ++k)
-        for (uint32_t i = blockIdx.x * NT + t; i < zl.n[k]; i += gridDim.x * NT) zl.p[k][i] = 0u;
-    if (blockIdx.x >= nseg) return;  // no records at all: the clearing only
-    const int vi = view_of(blockIdx.x, nviews, [&](int i) { return views[i].seg_base; });
+        for (int k = 0; k < ZeroList::N; ++k)
+            for (uint32_t i = blockIdx.x * NT + t; i < zl.n[k]; i += gridDim.x * NT) zl.p[k][i] = 0u;
+        if (blockIdx.x >= nseg) return;  // no records at all: the clearing only
+    }
+    const int vi = MODE == FORM_ONLY ? (int)blockIdx.x
+                                     : view_of(blockIdx.x, nviews, [&](int i) { return views[i].seg_base; });
     const ViewParams& v = views[vi];
-    const uint32_t seg = blockIdx.x - v.seg_base, nbkt = v.nbkt;
+    const uint32_t seg = MODE == FORM_ONLY ? 0u : blockIdx.x - v.seg_base, nbkt = v.nbkt;
     const uint32_t r0 = v.rec_base + seg * seg_len, r1 = min(r0 + seg_len, v.rec_base + v.n_pad);
 
     // the first records are on their way while the samples are sorted out
@@ -1171,82 +1180,101 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
             key[k] = i < r1 ? o.zkey[i] : 0u;
         }
     };
-    load(r0);
+    if (MODE != FORM_ONLY) load(r0);
     if (t < 2) {
         tot64[t] = 0ull;
         tot32[t] = 0u;
     }
-    // the samples' distribution
-    // (four samples per bucket: a bucket of twice the mean size is rare, and
-    // one of more than BUCKET_SORT_CAP only costs time)
-    const uint32_t nsamp_all = v.n_pad / 64;
-    const uint32_t nsamp = min(nsamp_all, min((uint32_t)BUCKET_SAMPLES, max(2048u, 4u * nbkt)));
-    const float stride = nsamp ? (float)nsamp_all / (float)nsamp : 0.0f;
-    uint32_t sk[SPT], lo = 0xffffffffu, hi = 0u;
-#pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-        const uint32_t i = (uint32_t)(k * NT + t);
-        sk[k] = 0xffffffffu;
-        if (i < nsamp) sk[k] = o.sample[v.rec_base / 64 + min((uint32_t)((float)i * stride), nsamp_all - 1u)];
-        if (sk[k] != 0xffffffffu) {
-            lo = min(lo, sk[k]);
-            hi = max(hi, sk[k]);
+    // a preprocess block's counts, and their sums over the segment
+    struct BlockCounts {
+        uint32_t d, t, n, f;
+    };
+    auto block_counts = [&] {
+        BlockCounts c{0, 0, 0, 0};
+        if (MODE != FORM_ONLY && (uint32_t)t < (r1 - r0) / K1_THREADS) {
+            const uint32_t i = r0 / K1_THREADS + (uint32_t)t;
+            c = BlockCounts{o.blk_sum[i], o.blk_tiles[i], o.blk_vis[i], o.blk_fb[i]};
         }
-    }
-    for (int i = t; i < BUCKET_BINS; i += NT) cdf[i] = 0u;
-    for (uint32_t i = t; i < nbkt; i += NT) hist[i] = 0u;
-    lo = wave_min(lo);
-    hi = wave_max(hi);
-    if (lane == 0) {
-        red[w] = lo;
-        red2[w] = hi;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NW; ++k) {
-        lo = min(lo, red[k]);
-        hi = max(hi, red2[k]);
-    }
-    KeyMap m;
-    m.lo = lo <= hi ? lo : 0u;
-    m.hi = lo <= hi ? hi : 0u;
-    m.shift = (uint32_t)max(0, bit_length(m.hi - m.lo) - 11);
-    static_assert(BUCKET_BINS == 1 << 11, "eleven bits of the samples' range");
-#pragma unroll
-    for (int k = 0; k < SPT; ++k)
-        if (sk[k] != 0xffffffffu) atomicAdd(&cdf[(sk[k] - m.lo) >> m.shift], 1u);
-    uint32_t bd = 0, bt = 0, bn = 0, bf = 0;  // a preprocess block's counts
-    if ((uint32_t)t < (r1 - r0) / K1_THREADS) {
-        const uint32_t i = r0 / K1_THREADS + (uint32_t)t;
-        bd = o.blk_sum[i];
-        bt = o.blk_tiles[i];
-        bn = o.blk_vis[i];
-        bf = o.blk_fb[i];
-    }
-    __syncthreads();
-    const uint32_t c0 = cdf[2 * t], c1 = cdf[2 * t + 1];
-    uint32_t total;
-    const uint32_t ex = block_excl_scan<NT>(c0 + c1, red, &total);
-    cdf[2 * t] = ex;
-    cdf[2 * t + 1] = ex + c0;
-    if (t == 0) cdf[BUCKET_BINS] = total;
-    m.scale = total ? (nbkt << 16) / total : 0u;
-    if (w < NW / 4) {  // the totals of the segment's preprocess blocks
-        const uint64_t d = wave_sum_u64(bd), tl = wave_sum_u64(bt);
-        const uint32_t n = wave_sum(bn), f = wave_sum(bf);
+        return c;
+    };
+    auto add_totals = [&](const BlockCounts& c) {
+        if (MODE == FORM_ONLY || w >= NW / 4) return;
+        const uint64_t d = wave_sum_u64(c.d), tl = wave_sum_u64(c.t);
+        const uint32_t n = wave_sum(c.n), f = wave_sum(c.f);
         if (lane == 0) {
             atomicAdd(&tot64[0], (unsigned long long)d);
             atomicAdd(&tot64[1], (unsigned long long)tl);
             atomicAdd(&tot32[0], n);
             atomicAdd(&tot32[1], f);
         }
+    };
+    KeyMap m;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    if constexpr (MODE == READ) {
+        const uint32_t* src = b.cdf + (size_t)vi * BUCKET_CDF_WORDS;
+        m = KeyMap{src[BUCKET_BINS + 1], src[BUCKET_BINS + 2], src[BUCKET_BINS + 3], src[BUCKET_BINS + 4]};
+        for (int i = t; i <= BUCKET_BINS; i += NT) cdf[i] = src[i];
+        for (uint32_t i = t; i < nbkt; i += NT) hist[i] = 0u;
+        const BlockCounts bc = block_counts();
+        __syncthreads();
+        add_totals(bc);
+    } else {
+        // the samples' distribution
+        // (four samples per bucket: a bucket of twice the mean size is rare, and
+        // one of more than BUCKET_SORT_CAP only costs time)
+        const uint32_t nsamp_all = v.n_pad / 64;
+        const uint32_t nsamp = min(nsamp_all, min((uint32_t)BUCKET_SAMPLES, max(2048u, 4u * nbkt)));
+        const float stride = nsamp ? (float)nsamp_all / (float)nsamp : 0.0f;
+        uint32_t sk[SPT];
+#pragma unroll
+        for (int k = 0; k < SPT; ++k) {
+            const uint32_t i = (uint32_t)(k * NT + t);
+            sk[k] = 0xffffffffu;
+            if (i < nsamp) sk[k] = o.sample[v.rec_base / 64 + min((uint32_t)((float)i * stride), nsamp_all - 1u)];
+            if (sk[k] != 0xffffffffu) {
+                lo = min(lo, sk[k]);
+                hi = max(hi, sk[k]);
+            }
+        }
+        for (int i = t; i < BUCKET_BINS; i += NT) cdf[i] = 0u;
+        for (uint32_t i = t; i < nbkt; i += NT) hist[i] = 0u;
+        lo = wave_min(lo);
+        hi = wave_max(hi);
+        if (lane == 0) {
+            red[w] = lo;
+            red2[w] = hi;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            lo = min(lo, red[k]);
+            hi = max(hi, red2[k]);
+        }
+        m.lo = lo <= hi ? lo : 0u;
+        m.hi = lo <= hi ? hi : 0u;
+        m.shift = (uint32_t)max(0, bit_length(m.hi - m.lo) - 11);
+        static_assert(BUCKET_BINS == 1 << 11, "eleven bits of the samples' range");
+#pragma unroll
+        for (int k = 0; k < SPT; ++k)
+            if (sk[k] != 0xffffffffu) atomicAdd(&cdf[(sk[k] - m.lo) >> m.shift], 1u);
+        const BlockCounts bc = block_counts();
+        __syncthreads();
+        const uint32_t c0 = cdf[2 * t], c1 = cdf[2 * t + 1];
+        uint32_t total;
+        const uint32_t ex = block_excl_scan<NT>(c0 + c1, red, &total);
+        cdf[2 * t] = ex;
+        cdf[2 * t + 1] = ex + c0;
+        if (t == 0) cdf[BUCKET_BINS] = total;
+        m.scale = total ? (nbkt << 16) / total : 0u;
+        add_totals(bc);
+        __syncthreads();
+        if (MODE == FORM_ONLY || seg == 0) {
+            uint32_t* out = b.cdf + (size_t)vi * BUCKET_CDF_WORDS;
+            for (int i = t; i <= BUCKET_BINS; i += NT) out[i] = cdf[i];
+            if (t < 4) out[BUCKET_BINS + 1 + t] = t == 0 ? m.lo : t == 1 ? m.hi : t == 2 ? m.shift : m.scale;
+        }
     }
-    __syncthreads();
-    if (seg == 0) {
-        uint32_t* out = b.cdf + (size_t)vi * BUCKET_CDF_WORDS;
-        for (int i = t; i <= BUCKET_BINS; i += NT) out[i] = cdf[i];
-        if (t < 4) out[BUCKET_BINS + 1 + t] = t == 0 ? m.lo : t == 1 ? m.hi : t == 2 ? m.shift : m.scale;
-    }
+    if (MODE == FORM_ONLY) return;
 
     // the segment's visible records
     lo = 0xffffffffu;
@@ -3172,8 +3200,15 @@ void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* v
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
                         bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
                         hipStream_t st) {
-    TIGAS_LAUNCH(k_bucket_count, dim3(std::max(nseg, 1u)), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,
-                 seg_len, zl);
+    if (nseg <= BUCKET_FORM_SEGMENTS) {
+        TIGAS_LAUNCH(k_bucket_count<FORM>, dim3(std::max(nseg, 1u)), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews,
+                     nseg, seg_len, zl);
+    } else {
+        TIGAS_LAUNCH(k_bucket_count<FORM_ONLY>, dim3(nviews), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,
+                     seg_len, zl);
+        TIGAS_LAUNCH(k_bucket_count<READ>, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
+                     zl);
+    }
     TIGAS_LAUNCH(k_bucket_scan, dim3(nchunks + 1), dim3(1024), st, b, views_dev, nviews, nseg, nchunks, cnt, cap,
                  flag_wide, nunits);
     if (nseg == 0) return;

@@ -221,6 +221,29 @@ def test_depth_buckets_of_several_views_and_a_culled_one(ctx):
         s.free()
 
 
+@pytest.mark.parametrize("n,views", [(180_000, 46), (180_000, 48)])
+def test_depth_buckets_of_more_segments_than_a_round(ctx, n, views):
+    """About 506 segments, each forming the samples' distribution, and 528,
+    which read it: every view is its single frame."""
+    rng = np.random.default_rng(5)
+    z = rng.uniform(2.0, 30.0, n)
+    xy = rng.uniform(-0.7, 0.7, (n, 2))
+    scene = make_scene(np.column_stack([xy[:, 0] * z, xy[:, 1] * z, z]),
+                       np.repeat(np.log(0.01 * z)[:, None], 3, axis=1), None, rng.normal(-1.0, 1.0, n),
+                       rng.uniform(0.0, 1.0, (n, 3)))
+    s = ctx.load_scene(scene)
+    poses = [synth.Pose(np.eye(3, dtype=np.float32), np.array([0.01 * i, 0, -0.2 * i], np.float32))
+             for i in range(views)]
+    k, W, H = intr(40.0, 33, 30), 66, 60
+    _say("many segments", n, views)
+    got = ctx.render_batch([s] * views, poses, [k] * views, [W] * views, [H] * views, fmt="f32", tile=(16, 16))
+    for i in (0, 1, views // 2, views - 1):
+        want = ctx.render(s, poses[i], k, W, H, fmt="f32", tile=(16, 16))
+        assert want.any()
+        np.testing.assert_array_equal(got[i], want)
+    s.free()
+
+
 def _rect_scene(kind, n):
     """Gaussians whose tile rectangles meet the placement in different forms."""
     rng = np.random.default_rng(n + 1)
