@@ -275,10 +275,12 @@ tigas_status tigas_set_tile_culling(tigas_context* ctx, int enable);
  * depth ranges (counted, scanned, scattered: reported as three passes in
  * tigas_stats.sort_passes) and sorts every bucket on chip, when every view
  * has at most 256 x 256 tiles.  A frame whose visible FP32 depth keys span
- * 2^27 or more (about 16 octaves of depth) is detected on the GPU, rendered
- * again with four radix passes, and the context keeps four passes from then
- * on (counted in tigas_stats.rerenders); tigas_render_noalloc sorts such a
- * frame in buckets too.  passes = 4 always takes four 8-bit radix passes of
+ * 2^27 or more (about 16 octaves of depth), or of which over 16384 keys fall
+ * into one bucket (most of a view at nearly one depth), is detected on the
+ * GPU, rendered again with four radix passes, and the context keeps four
+ * passes from then on (counted in tigas_stats.rerenders);
+ * tigas_render_noalloc, which has no second attempt, sorts such a frame in
+ * its buckets (slower) until the context takes four passes.  passes = 4 always takes four 8-bit radix passes of
  * the whole key (environment TIGAS_DEPTH_PASSES=4 at context creation).  The
  * order, and so every frame, is identical either way.  E_INVALID for another
  * value. */

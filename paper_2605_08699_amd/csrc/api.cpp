@@ -817,8 +817,7 @@ FrameMem frame_mem(Workspace& ws, const Plan& plan) {
     FrameMem m = ws.mem();
     size_t rb, sb;
     m.bk = carve_buckets(plan, ws.bkt_rows.p, ws.bkt_small.p, &rb, &sb);
-    // 16 bytes for each visible record: the duplicate buffers hold at least
-    // four words per record
+    // 16 bytes for each visible record
     m.bk.elem = ws.key[0].as<uint4>();
     m.tm = carve_tiles(plan, ws.tile_rows.p, ws.tile_small.p, &rb, &sb);
     return m;
@@ -839,6 +838,7 @@ void prepare(Workspace& ws, Plan& plan, bool debug) {
     uint64_t est = std::max<uint64_t>((uint64_t)ws.last_D + ws.last_D / 4, (uint64_t)plan.nrec * 4);
     est = std::max<uint64_t>(est, 1u << 20);
     ws.ensure_dups((uint32_t)std::min<uint64_t>(est, 0xfff00000ull));
+    ws.grow(ws.key[0], (size_t)plan.nrec * 16);  // the bucketed sort's elements, also beyond the cap above
     {
         size_t rb, sb;
         (void)carve_buckets(plan, nullptr, nullptr, &rb, &sb);
@@ -938,8 +938,11 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     int cv = 0;
     if (opt.buckets && packed) {
         mark(2);
+        zl.p[2] = &cnt->overflow;
+        zl.n[2] = 1;
+        // (an inspection shows the bucketed order however long it takes)
         launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl, m.flag_wide,
-                           plan.nunits, sb.val[0], sb.ext[0], cells, st);
+                           m.flag_wide && !debug ? BUCKET_CROWD : 0xffffffffu, plan.nunits, sb.val[0], sb.ext[0], cells, st);
     } else {
         launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
         mark(2);
@@ -1084,8 +1087,8 @@ FrameCounters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool d
     std::memcpy(&c, ws.fs().host_counters.p, sizeof(c));
     rerenders = 0;
     if (c.overflow) {
-        // bit 1: the visible depth keys span too much for the bucketed
-        // sort: four radix passes from now on; bit 0: more duplicates than the
+        // bit 1: the visible depth keys span too much for the bucketed sort,
+        // or crowd into one bucket: four radix passes from now on; bit 0: more duplicates than the
         // buffers hold: grow them
         if (c.overflow & 2u) {
             ctx->depth4.store(true);
@@ -1578,6 +1581,7 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     opt.cull = ctx->blend_cull.load();
     opt.bin = ctx->tile_bin.load();
     opt.cull_tiles = ctx->tile_cull.load();
+    opt.buckets = !ctx->depth4.load();
     opt.follow(plan);
     (void)enqueue(m, plan, false, false, nullptr, opt);
 }

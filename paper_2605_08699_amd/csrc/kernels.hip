@@ -1387,7 +1387,7 @@ __device__ __forceinline__ bool depth_wide(uint32_t lo, uint32_t hi) {
 // frame's counters and the views' first positions.
 __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewParams* __restrict__ views, int nviews,
                                                       uint32_t nseg, uint32_t nchunks, Counters* cnt, uint32_t cap,
-                                                      bool flag_wide, uint32_t nunits) {
+                                                      bool flag_wide, uint32_t crowd, uint32_t nunits) {
     __shared__ uint32_t lds[(1024 / COL_CHUNK + 1) * (COL_CHUNK + 1)];
     if (blockIdx.x < nchunks) {
         const uint32_t c0 = blockIdx.x * COL_CHUNK;
@@ -1395,6 +1395,9 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewPar
         const ViewParams& v = views[vi];
         column_scan<COL_CHUNK, 16>(b.rows + v.row_base, v.nseg, v.nbkt, v.nbkt, c0 - v.bkt_base, b.start_in + c0, b.tot + c0,
                     b.chunk + blockIdx.x, lds);
+        // (a thread reads the total that it wrote)
+        if (threadIdx.x < COL_CHUNK && c0 - v.bkt_base + threadIdx.x < v.nbkt && b.tot[c0 + threadIdx.x] > crowd)
+            atomicOr(&cnt->overflow, 2u);
         return;
     }
     uint32_t lo = 0xffffffffu, hi = 0u;
@@ -1473,7 +1476,8 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewPar
         cnt->pairs = P > 0xffffffffull ? 0xffffffffu : (uint32_t)P;
         cnt->visible = V;
         cnt->fallbacks = F;
-        cnt->overflow = (D > (uint64_t)cap ? 1u : 0u) | (flag_wide && depth_wide(lo, hi) ? 2u : 0u);
+        // cleared by the launch before; other workgroups may have set bit 1
+        atomicOr(&cnt->overflow, (D > (uint64_t)cap ? 1u : 0u) | (flag_wide && depth_wide(lo, hi) ? 2u : 0u));
         cnt->fb_listed = cnt->fb_list;
         cnt->fb_list = 0u;  // the next frame appends from zero
     }
@@ -1565,9 +1569,13 @@ __device__ void bitonic_sort(uint64_t* a, uint32_t n2) {
 // bins of equal key ranges (of records, when all keys are equal), placed in
 // LDS bin by bin, and each finds its rank among the few elements of its own
 // bin.  Buckets with a crowded bin (many equal keys) take a bitonic sort
-// instead, and those of more than BUCKET_SORT_CAP elements are sorted window
-// by window: as many of the smallest remaining elements as fit, found by
-// counting over the bins of the remaining range.  The launch also recomputes
+// instead.  Those of more than BUCKET_SORT_CAP elements are first placed bin by
+// bin of their range of (key, record) words in the bucket's part of the
+// outputs, and bins that fit together are sorted in LDS; a bin that does not
+// fit goes window by window: as many of its smallest remaining elements as fit,
+// found by counting over the bins of the remaining range (60000 elements of one
+// depth: a frame of 0.45 ms at 960x540; window by window alone its passes grow
+// with the square of the bucket).  The launch also recomputes
 // the FP64 conics of the near-singular Gaussians, before anything reads the
 // exponent coefficients.
 __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, BucketMem b,
@@ -1736,20 +1744,34 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
         }
         return;
     }
-    // more elements than fit: [lo, hi] is the range of (key, record) words in
-    // which the next window's elements lie
+    // more elements than fit: [lo, top] is the range of (key, record) words in
+    // which they lie; a record's number takes the bits that the view's need,
+    // so that the bins part it early
+    const int rb = bit_length(v.n_pad);
+    const uint32_t rmask = (1u << rb) - 1u;
+    auto join = [&](uint32_t key, uint32_t rec) { return ((uint64_t)key << rb) | (rec - v.rec_base); };
+    auto rec_of = [&](uint64_t x) { return ((uint32_t)x & rmask) + v.rec_base; };
     auto word = [&](uint32_t i) {
         const uint4 x = e[i];
-        return ((uint64_t)x.x << 32) | x.y;
+        return join(x.x, x.y);
+    };
+    auto each = [&](auto&& f) {  // over the elements' words, eight loads in flight
+        for (uint32_t i0 = t; i0 < n; i0 += NT * 8) {
+            uint64_t x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = word(min(i0 + (uint32_t)(k * NT), n - 1));
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i0 + (uint32_t)(k * NT) < n) f(x[k]);
+        }
     };
     uint64_t lo = ~0ull, top = 0ull;
     uint32_t entries = 0;
-    for (uint32_t i = t; i < n; i += NT) {
-        entries += rect_count(e[i].z);
-        const uint64_t x = word(i);
+    for (uint32_t i = t; i < n; i += NT) entries += rect_count(e[i].z);
+    each([&](uint64_t x) {
         lo = x < lo ? x : lo;
         top = x > top ? x : top;
-    }
+    });
     store_cost(entries);
 #pragma unroll
     for (int k = 32; k > 0; k >>= 1) {
@@ -1766,55 +1788,139 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
         lo = redlo[k] < lo ? redlo[k] : lo;
         top = redhi[k] > top ? redhi[k] : top;
     }
-    uint64_t hi = top;
-    for (uint32_t done = 0; done < n;) {
-        const int sh = max(0, 64 - __clzll((long long)(hi - lo)) - 11);
-        __syncthreads();
-        for (int k = t; k < BINS; k += NT) bin[k] = 0u;
-        if (t == 0) picked = fill = 0u;
-        __syncthreads();
-        for (uint32_t i = t; i < n; i += NT) {
-            const uint64_t x = word(i);
-            if (x >= lo && x <= hi) atomicAdd(&bin[(uint32_t)((x - lo) >> sh)], 1u);
-        }
-        __syncthreads();
-        uint32_t sum = 0;
-        for (int k = 0; k < BPT; ++k) sum += bin[t * BPT + k];
-        uint32_t total, acc = block_excl_scan<NT>(sum, red, &total);
-        uint32_t take = 0;  // bins whose inclusive count still fits
+    // placed bin by bin in (val, ext), as (record, key)
+    const int sh0 = max(0, 64 - __clzll((long long)(top - lo)) - 11);
+    __syncthreads();
+    for (int k = t; k < BINS; k += NT) bin[k] = 0u;
+    __syncthreads();
+    each([&](uint64_t x) { atomicAdd(&bin[(uint32_t)((x - lo) >> sh0)], 1u); });
+    __syncthreads();
+    {
+        uint32_t c[BPT], sum = 0, total;
+#pragma unroll
+        for (int k = 0; k < BPT; ++k) sum += c[k] = bin[t * BPT + k];
+        uint32_t ex = block_excl_scan<NT>(sum, red, &total);
+#pragma unroll
         for (int k = 0; k < BPT; ++k) {
-            acc += bin[t * BPT + k];
-            if (acc <= (uint32_t)CAP) take = (uint32_t)(t * BPT + k) + 1u;
+            bin[t * BPT + k] = ex;
+            ex += c[k];
         }
-        atomicMax(&picked, take);
-        __syncthreads();
-        const uint32_t nb = picked;
-        if (nb == 0) {  // uniform: the first bin alone holds too many; look inside it
-            const uint64_t end = lo + (((uint64_t)1 << sh) - 1);
-            hi = end < hi ? end : hi;
-            continue;
-        }
-        uint64_t last = lo + (((uint64_t)nb << sh) - 1);
-        if (nb >= (uint32_t)BINS || last > hi) last = hi;
-        for (uint32_t i = t; i < n; i += NT) {
-            const uint64_t x = word(i);
-            if (x >= lo && x <= last) arr[atomicAdd(&fill, 1u)] = x;
-        }
-        __syncthreads();
-        const uint32_t m = fill;
+    }
+    __syncthreads();
+    each([&](uint64_t x) {
+        const uint32_t pos = atomicAdd(&bin[(uint32_t)((x - lo) >> sh0)], 1u);  // leaves the bin's end
+        val[pos] = rec_of(x);
+        ext[pos] = (uint32_t)(x >> rb);
+    });
+    auto placed = [&](uint32_t i) { return join(ext[i], val[i]); };
+    auto put = [&](uint32_t pos, uint64_t x) {
+        const uint32_t r = rec_of(x);
+        const uint2 rr = o.rect[r];
+        val[pos] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
+        ext[pos] = pack_rect(rr);
+    };
+    // sorts arr[0, m) and writes it to `at`
+    auto sort_out = [&](uint32_t m, uint32_t at) {
         uint32_t n2 = 64;
         while (n2 < m) n2 <<= 1;
         for (uint32_t i = m + t; i < n2; i += NT) arr[i] = ~0ull;
         bitonic_sort<NT>(arr, n2);
-        for (uint32_t i = t; i < m; i += NT) {
-            const uint32_t r = (uint32_t)arr[i];
-            const uint2 rr = o.rect[r];
-            val[done + i] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
-            ext[done + i] = pack_rect(rr);
+        for (uint32_t i = t; i < m; i += NT) put(at + i, arr[i]);
+    };
+    uint64_t* part = reinterpret_cast<uint64_t*>(b.elem + first);  // the elements are read no more
+    for (uint32_t done = 0; done < n;) {
+        __syncthreads();  // the placed words, and the use of arr and picked before
+        if (t == 0) picked = fill = 0u;
+        __syncthreads();
+        uint32_t take = 0;  // bins whose end still fits
+        for (int k = 0; k < BPT; ++k)
+            if (bin[t * BPT + k] <= done + (uint32_t)CAP) take = (uint32_t)(t * BPT + k) + 1u;
+        atomicMax(&picked, take);
+        __syncthreads();
+        const uint32_t nb = picked, end = nb ? bin[nb - 1] : 0u;
+        if (end > done) {  // uniform
+            const uint32_t m = end - done;
+            uint32_t big = 0;
+            for (int k = 0; k < BPT; ++k) {
+                const uint32_t bi = (uint32_t)(t * BPT + k), e1 = bin[bi];
+                if (e1 > done && e1 <= end) big = max(big, e1 - (bi ? bin[bi - 1] : 0u));
+            }
+            atomicMax(&fill, big);
+            uint64_t me[EPT];
+#pragma unroll
+            for (int k = 0; k < EPT; ++k) me[k] = placed(done + min((uint32_t)(k * NT + t), m - 1));
+#pragma unroll
+            for (int k = 0; k < EPT; ++k)
+                if ((uint32_t)(k * NT + t) < m) arr[k * NT + t] = me[k];
+            __syncthreads();
+            if (fill <= 4u * CROWDED) {  // uniform: ranks inside the bins; the bitonic sort is of 4096 here
+#pragma unroll 1
+                for (int k = 0; k < EPT; ++k)
+                    if ((uint32_t)(k * NT + t) < m) {
+                        const uint64_t x = arr[k * NT + t];
+                        const uint32_t r = rec_of(x);
+                        const uint2 rr = o.rect[r];
+                        const uint32_t bi = (uint32_t)((x - lo) >> sh0);
+                        const uint32_t q0 = (bi ? bin[bi - 1] : 0u) - done, q1 = bin[bi] - done;
+                        uint32_t pos = q0;
+#pragma unroll 4
+                        for (uint32_t q = q0; q < q1; ++q) pos += arr[q] < x ? 1u : 0u;
+                        val[done + pos] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
+                        ext[done + pos] = pack_rect(rr);
+                    }
+            } else {
+                sort_out(m, done);
+            }
+            done = end;
+            continue;
         }
-        done += m;
-        lo = last + 1;
-        hi = top;
+        // the next bin alone holds too many: its words out of the way, then
+        // window by window; `bin` keeps the ends, arr also holds the counts
+        uint32_t* cnt2 = reinterpret_cast<uint32_t*>(arr);
+        const uint32_t d0 = done, m0 = bin[nb] - done;
+        for (uint32_t i = t; i < m0; i += NT) part[d0 + i] = placed(d0 + i);
+        uint64_t wlo = lo + ((uint64_t)nb << sh0), whi = wlo + (((uint64_t)1 << sh0) - 1);
+        const uint64_t wtop = whi;
+        while (done < d0 + m0) {
+            const int sh = max(0, 64 - __clzll((long long)(whi - wlo)) - 11);
+            __syncthreads();
+            for (int k = t; k < BINS; k += NT) cnt2[k] = 0u;
+            if (t == 0) picked = fill = 0u;
+            __syncthreads();
+            for (uint32_t i = t; i < m0; i += NT) {
+                const uint64_t x = part[d0 + i];
+                if (x >= wlo && x <= whi) atomicAdd(&cnt2[(uint32_t)((x - wlo) >> sh)], 1u);
+            }
+            __syncthreads();
+            uint32_t sum = 0;
+            for (int k = 0; k < BPT; ++k) sum += cnt2[t * BPT + k];
+            uint32_t total, acc = block_excl_scan<NT>(sum, red, &total);
+            uint32_t fits = 0;  // bins whose inclusive count still fits
+            for (int k = 0; k < BPT; ++k) {
+                acc += cnt2[t * BPT + k];
+                if (acc <= (uint32_t)CAP) fits = (uint32_t)(t * BPT + k) + 1u;
+            }
+            atomicMax(&picked, fits);
+            __syncthreads();
+            const uint32_t wb = picked;
+            if (wb == 0) {  // uniform: the first bin alone holds too many; look inside it
+                const uint64_t last = wlo + (((uint64_t)1 << sh) - 1);
+                whi = last < whi ? last : whi;
+                continue;
+            }
+            uint64_t last = wlo + (((uint64_t)wb << sh) - 1);
+            if (wb >= (uint32_t)BINS || last > whi) last = whi;
+            for (uint32_t i = t; i < m0; i += NT) {
+                const uint64_t x = part[d0 + i];
+                if (x >= wlo && x <= last) arr[atomicAdd(&fill, 1u)] = x;
+            }
+            __syncthreads();
+            const uint32_t m = fill;
+            sort_out(m, done);
+            done += m;
+            wlo = last + 1;
+            whi = wtop;
+        }
     }
 }
 
@@ -3198,7 +3304,7 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
+                        bool flag_wide, uint32_t crowd, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
                         hipStream_t st) {
     if (nseg <= BUCKET_FORM_SEGMENTS) {
         TIGAS_LAUNCH(k_bucket_count<FORM>, dim3(std::max(nseg, 1u)), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews,
@@ -3210,7 +3316,7 @@ void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* v
                      zl);
     }
     TIGAS_LAUNCH(k_bucket_scan, dim3(nchunks + 1), dim3(1024), st, b, views_dev, nviews, nseg, nchunks, cnt, cap,
-                 flag_wide, nunits);
+                 flag_wide, crowd, nunits);
     if (nseg == 0) return;
     TIGAS_LAUNCH(k_bucket_scatter, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
                  (const Counters*)cnt);

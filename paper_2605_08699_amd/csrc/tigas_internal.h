@@ -32,6 +32,12 @@ constexpr int BUCKET_SAMPLES = 16384;
 constexpr int BUCKET_BINS = 2048;
 constexpr int BUCKET_CDF_WORDS = BUCKET_BINS + 8;  // cumulative counts, smallest and largest sample, shift, scale
 constexpr int BUCKET_SORT_CAP = 4096;
+// A frame with more elements in one bucket (most Gaussians of a view at nearly
+// one depth) takes the radix passes: one workgroup sorts a bucket, at about
+// 10 us per 1000 elements of one depth (200k of them at 960x540: 235 us a frame
+// by the radix passes, 2.0 ms in one bucket), and 16384 are a tenfold share of
+// the 1024 to 2048 that a bucket gets.
+constexpr uint32_t BUCKET_CROWD = 16384;
 constexpr int COL_CHUNK = 32;  // columns per workgroup of a column scan
 // A list is divided into at most 4 x 4 cells of whole 8x8 blocks: log2 of a
 // cell's side for that of the list's.  An entry's word holds the cells that its
@@ -199,7 +205,7 @@ struct TileMem {
 
 // Arrays cleared (as u32 words) by the first kernel after preprocess.
 struct ZeroList {
-    static constexpr int N = 2;
+    static constexpr int N = 3;
     uint32_t* p[N];
     uint32_t n[N];
 };
@@ -251,7 +257,7 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 // all views; nunits: of the tile placement that follows.
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
+                        bool flag_wide, uint32_t crowd, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
                         hipStream_t st);
 // Runs LSD passes over the count selected by `which` (0 duplicates, 1 visible)
 // starting in buffer `start`; returns the buffer index holding the result.

@@ -203,6 +203,39 @@ def test_depth_buckets_give_the_stable_order(ctx, kind, n):
     s.free()
 
 
+@pytest.mark.parametrize("kind,n", [("equal", 17_000), ("equal", 200_000), ("steps", 200_000), ("slab", 66_000),
+                                    ("slab", 200_000)])
+def test_crowded_depth_buckets(ctx, kind, n):
+    """More Gaussians at about one depth than a workgroup is given to sort: the
+    frame is rendered again with the radix passes, once; the form without a
+    second attempt sorts them in their bucket, to the same frame."""
+    import torch
+    scene = _depth_scene("thin" if kind == "slab" else kind, n)
+    if kind == "slab":  # 99 % of them in a few buckets: at least 39 % in one
+        scene.means[::97, 2] = 900.0
+    W, H = 160, 112
+    k = intr(150.0, W / 2, H / 2)
+    s = ctx.load_scene(scene)
+    _say("crowded buckets", kind, n)
+    out = torch.zeros((H, W, 3), dtype=torch.float32, device="cuda")
+    ctx.render_noalloc(s, eye_pose(), k, W, H, out, fmt="f32", tile=(16, 16))
+    torch.cuda.synchronize()
+    try:
+        img = ctx.render(s, eye_pose(), k, W, H, fmt="f32", tile=(16, 16))
+        assert img.any() and ctx.stats()["rerenders"] == 1
+        ctx.set_depth_passes(4)
+        ref = ctx.render(s, eye_pose(), k, W, H, fmt="f32", tile=(16, 16))
+        radix = torch.zeros_like(out)
+        ctx.render_noalloc(s, eye_pose(), k, W, H, radix, fmt="f32", tile=(16, 16))
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_depth_passes(3)
+    np.testing.assert_array_equal(img, ref)
+    np.testing.assert_array_equal(radix.cpu().numpy(), ref)
+    np.testing.assert_array_equal(out.cpu().numpy(), ref)
+    s.free()
+
+
 def test_depth_buckets_of_several_views_and_a_culled_one(ctx):
     """Views of scenes of different sizes, one of which shows nothing, in one
     sequence: each frame is the view's own."""
