@@ -1095,7 +1095,9 @@ FrameCounters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool d
             set_tiles(plan, plan.tc, !debug && share_lists(ctx, plan));
             prepare(ws, plan, debug);
         }
-        if (c.overflow & 1u) {
+        // (c.D, the (Gaussian, tile) pairs, bounds the entries in every layout;
+        // a plan laid out again without shared lists has as many)
+        if ((c.overflow & 1u) || c.D > ws.dup_cap) {
             const uint64_t want = (uint64_t)c.D + c.D / 4 + 1024;
             if (want > 0xfff00000ull) fail(TIGAS_E_OOM, "duplicate count exceeds the 32-bit index range");
             ws.ensure_dups((uint32_t)want);

@@ -236,6 +236,39 @@ def test_crowded_depth_buckets(ctx, kind, n):
     s.free()
 
 
+@pytest.mark.parametrize("kind", ["equal", "deep"])
+def test_batch_that_needs_another_depth_order_and_more_room(kind):
+    """Views whose first attempt fits in shared lists but is rendered again
+    with more entries than the first buffers hold (2^20): each frame is the
+    view's own."""
+    rng = np.random.default_rng(41)
+    n, W, H = 30_000, 1920, 1080
+    z = np.full(n, 4.0) if kind == "equal" else np.exp(rng.uniform(math.log(0.5), math.log(2e7), n))
+    means = np.column_stack([rng.uniform(-0.9, 0.9, n) * z, rng.uniform(-0.5, 0.5, n) * z, z])
+    scene = make_scene(means, np.repeat(np.log(0.0125 * z)[:, None], 3, axis=1), None, rng.normal(1.0, 0.3, n),
+                       rng.uniform(0.0, 1.0, (n, 3)))
+    k = intr(960.0, W / 2, H / 2)
+    poses = [eye_pose(), eye_pose((0.05, 0.02, 0.0))]
+    _say("batch rendered again", kind)
+    c = tigas.Context(0)  # buffers and depth order of their own
+    try:
+        s = c.load_scene(scene)
+        got = c.render_batch([s] * 2, poses, [k] * 2, [W] * 2, [H] * 2, fmt="f32", tile=(16, 16))
+        st = c.stats()
+        _say(st)
+        assert st["duplicates"] > max(4 * 2 * n, 1 << 20)
+        again = c.render_batch([s] * 2, poses, [k] * 2, [W] * 2, [H] * 2, fmt="f32", tile=(16, 16))
+        assert c.stats()["rerenders"] == 0 and c.stats()["duplicates"] == st["duplicates"]
+        c.set_depth_passes(4)
+        for i in range(2):
+            want = c.render(s, poses[i], k, W, H, fmt="f32", tile=(16, 16))
+            assert want.any()
+            np.testing.assert_array_equal(got[i], want)
+            np.testing.assert_array_equal(again[i], want)
+    finally:
+        c.close()
+
+
 def test_depth_buckets_of_several_views_and_a_culled_one(ctx):
     """Views of scenes of different sizes, one of which shows nothing, in one
     sequence: each frame is the view's own."""
