@@ -321,7 +321,7 @@ struct Workspace {
     DevBuf recs, rect, srect, zkey;
     DevBuf blk_sum, blk_vis, blk_fb, blk_tiles, blk_view, blk_off, blk_sum2, blk_off2;
     DevBuf fb_list;  // near-singular Gaussians for the FP64 conic kernel
-    DevBuf chunk_vis, chunk_dup, chunk_fb, chunk_dups;  // totals per chunk of block counts
+    DevBuf chunk_vis, chunk_dup, chunk_fb, chunk_tiles, chunk_dups;  // totals per chunk of block counts
     DevBuf counters;
     // per duplicate (also holds the visible Gaussians during the depth passes)
     DevBuf key[2], val[2], ext[2];
@@ -395,6 +395,7 @@ struct Workspace {
         o.chunk_vis = chunk_vis.as<uint32_t>();
         o.chunk_dup = chunk_dup.as<unsigned long long>();
         o.chunk_fb = chunk_fb.as<uint32_t>();
+        o.chunk_tiles = chunk_tiles.as<unsigned long long>();
         o.chunk_dups = chunk_dups.as<uint32_t>();
         o.fb_cap = rec_cap;
         o.cnt = counters.as<Counters>();
@@ -417,7 +418,7 @@ struct Workspace {
         grow(sample, r / 64 * 4);
         const size_t nch = nb / SCAN_CHUNK + 2;
         for (DevBuf* b : {&chunk_vis, &chunk_fb, &chunk_dups}) grow(*b, nch * 4);
-        grow(chunk_dup, nch * 8);
+        for (DevBuf* b : {&chunk_dup, &chunk_tiles}) grow(*b, nch * 8);
         rec_cap = (uint32_t)r;
     }
     void ensure_dups(uint32_t cap) {
@@ -1512,6 +1513,7 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_o
     o.chunk_fb = c.take<uint32_t>(nch * 4);
     o.chunk_dups = c.take<uint32_t>(nch * 4);
     o.chunk_dup = c.take<unsigned long long>(nch * 8);
+    o.chunk_tiles = c.take<unsigned long long>(nch * 8);
     o.cnt = m.cnt;
     m.ranges = c.take<uint2>((size_t)std::max<uint32_t>(n_tiles, 1) * 8);
     m.order = c.take<uint32_t>((size_t)std::max<uint32_t>(n_tiles, 1) * 4);

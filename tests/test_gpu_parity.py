@@ -397,6 +397,38 @@ def test_tiles_sharing_a_list_give_the_same_frame(ctx, size, tile, kind):
     s.free()
 
 
+@pytest.mark.parametrize("size,tile", [((1030, 1030), (16, 16)), ((1933, 1083), (16, 32))])
+def test_shared_lists_with_four_depth_passes(ctx, size, tile):
+    """Tiles that share lists, in the depth order of the radix passes: the
+    frame and the counts, those of the allocation-free form too, are those of
+    the bucketed order."""
+    import torch
+    W, H = size
+    s = ctx.load_scene(_rect_scene("small", 6000))
+    k = intr(max(W, H) / 2.0, W / 2, H / 2)
+    _say("shared lists, four passes", size, tile)
+    got, st, cnt = {}, {}, {}
+    for passes in (3, 4):
+        ctx.set_depth_passes(passes)
+        try:
+            got[passes] = ctx.render(s, eye_pose(), k, W, H, fmt="f32", tile=tile)
+            st[passes] = ctx.stats()
+            out = torch.empty((H, W, 3), dtype=torch.float32, device="cuda")
+            counters = torch.zeros(6, dtype=torch.int32, device="cuda")
+            ctx.render_noalloc(s, eye_pose(), k, W, H, out, counters=counters, fmt="f32", tile=tile)
+            torch.cuda.synchronize()
+            cnt[passes] = counters.cpu().numpy()[:4].tolist()
+        finally:
+            ctx.set_depth_passes(3)
+        np.testing.assert_array_equal(out.cpu().numpy(), got[3])
+    np.testing.assert_array_equal(got[3], got[4])
+    assert (st[3]["sort_passes"], st[4]["sort_passes"]) == (4, 5)
+    for name in ("duplicates", "tiles", "visible", "fallbacks"):
+        assert st[3][name] == st[4][name]
+    assert cnt[3] == cnt[4] == [st[3]["duplicates"], st[3]["visible"], st[3]["fallbacks"], 0]
+    s.free()
+
+
 @pytest.mark.parametrize("kind", ["small", "mixed", "stack"])
 @pytest.mark.parametrize("size", [(320, 320), (317, 331), (448, 448), (451, 449)])
 def test_blend_by_quarters_halves_and_whole_blocks(ctx, size, kind):
