@@ -279,9 +279,9 @@ tigas_status tigas_set_tile_culling(tigas_context* ctx, int enable);
  * into one bucket (most of a view at nearly one depth), is detected on the
  * GPU, rendered again with four radix passes, and the context keeps four
  * passes from then on (counted in tigas_stats.rerenders);
- * tigas_render_noalloc, which has no second attempt, sorts such a frame in
- * its buckets (slower) until the context takes four passes.  passes = 4 always takes four 8-bit radix passes of
- * the whole key (environment TIGAS_DEPTH_PASSES=4 at context creation).  The
+ * tigas_render_noalloc, which has no second attempt, parts the buckets of such
+ * a frame by order statistics of sampled (depth, record) words.  passes = 4
+ * always takes four 8-bit radix passes of the whole key (environment TIGAS_DEPTH_PASSES=4 at context creation).  The
  * order, and so every frame, is identical either way.  E_INVALID for another
  * value. */
 tigas_status tigas_set_depth_passes(tigas_context* ctx, int passes);

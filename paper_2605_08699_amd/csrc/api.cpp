@@ -943,7 +943,8 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         zl.n[2] = 1;
         // (an inspection shows the bucketed order however long it takes)
         launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl, m.flag_wide,
-                           m.flag_wide && !debug ? BUCKET_CROWD : 0xffffffffu, plan.nunits, sb.val[0], sb.ext[0], cells, st);
+                           m.flag_wide && !debug ? BUCKET_CROWD : 0xffffffffu, /*split=*/!m.flag_wide, plan.nunits,
+                           sb.val[0], sb.ext[0], cells, st);
     } else {
         launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
         mark(2);

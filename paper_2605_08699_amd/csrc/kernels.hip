@@ -299,6 +299,14 @@ __device__ __forceinline__ uint32_t sh_finite(const float* k) {
     return (bad & (0u - bad)) - 1u;
 }
 
+// The lane whose record is the sample of a wave's visible ones (mask m, not
+// empty): the first at or after one that varies from wave to wave.
+__device__ __forceinline__ uint32_t sample_lane(uint64_t m, uint32_t wid) {
+    const uint32_t r = (wid * 0x9E3779B1u) >> 26;
+    const uint64_t rot = (m >> r) | (m << ((64u - r) & 63u));
+    return ((uint32_t)__builtin_ctzll(rot) + r) & 63u;
+}
+
 template <int ST, int DEG>
 __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const ViewParams* __restrict__ views,
                                                            int nviews, uint32_t rec_base, uint32_t n_pad,
@@ -517,14 +525,11 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
         }
         o.rect[rec] = tr;  // every record: whole-line, coalesced stores
         {
-            // the wave's visible records, and one of them (the first at or
-            // after a lane that varies from wave to wave) as a sample of the
+            // the wave's visible records, and one of them as a sample of the
             // view's depth distribution
             const uint64_t m = ballot(touched != 0u);
             const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(rec >> 6));
-            const uint32_t r = (wid * 0x9E3779B1u) >> 26;
-            const uint64_t rot = (m >> r) | (m << ((64u - r) & 63u));
-            const uint32_t src = m ? ((uint32_t)__builtin_ctzll(rot) + r) & 63u : 0u;
+            const uint32_t src = m ? sample_lane(m, wid) : 0u;
             const uint32_t key = readlane(__float_as_uint(z32), (int)src);
             if ((threadIdx.x & 63) == 0) {
                 o.vmask[wid] = m;
@@ -1081,7 +1086,8 @@ __global__ __launch_bounds__(K1_THREADS) void k_duplicate_culled(
 // record), which makes the order the stable one.  A bucket is a range of
 // depth keys, every bucket holding about the same number of records: the
 // boundaries come from the distribution of one sample per 64 records (a
-// histogram of the samples' keys, and linear interpolation inside its bins).
+// histogram of the samples' keys, and linear interpolation inside its bins; or,
+// where many depths are nearly equal, order statistics of the samples).
 // What bounds it: at 3M Gaussians the bytes (keys read twice, 16 bytes
 // written and read per visible record) take about a third of the time, the
 // launches and the workgroups' chains the rest; so nothing is ranked but in
@@ -1140,6 +1146,43 @@ __device__ __forceinline__ uint32_t key_bucket(uint32_t key, const uint32_t* cdf
     return min(__umulhi(pos, m.scale), nbkt - 1u);
 }
 
+// Bitonic sort of n 64-bit words in LDS (padded to a power of two with all
+// ones by the caller), by the whole workgroup.
+template <int NT>
+__device__ void bitonic_sort(uint64_t* a, uint32_t n2) {
+    for (uint32_t k = 2; k <= n2; k <<= 1)
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < n2 / 2; i += NT) {
+                const uint32_t x = (i / j) * 2 * j + i % j, y = x + j;
+                const uint64_t p = a[x], q = a[y];
+                if ((p > q) == ((x & k) == 0)) {
+                    a[x] = q;
+                    a[y] = p;
+                }
+            }
+        }
+    __syncthreads();
+}
+
+// A view whose samples crowd (over 2 x the mean + 8 of them in one bucket: a flat
+// model seen face on, say) is parted by order statistics of the samples'
+// (depth key, record) words instead: SPLIT_MAX - 1 of them at most, in the place
+// of the distribution and marked by KeyMap::shift.  Equal depths are then parted
+// by record, and no bucket is long however the depths lie.  Allocation-free
+// frames of 17k / 200k Gaussians of one depth at 960x540 take 82 / 136 us; in one
+// bucket 141 / 1987, by the radix passes 159 / 201 (with spread depths 65 / 107).
+constexpr uint32_t SPLIT_MAX = BUCKET_BINS / 2;
+constexpr uint32_t SPLIT_SAMPLES = 4096;
+constexpr uint32_t KEYMAP_SPLIT = 0xffffffffu;
+__device__ __forceinline__ uint32_t split_bucket(uint32_t key, uint32_t rec, const uint64_t* split) {
+    const uint64_t x = ((uint64_t)key << 32) | rec;
+    uint32_t pos = 0;
+#pragma unroll
+    for (uint32_t s = SPLIT_MAX / 2; s > 0; s >>= 1) pos += split[pos + s - 1] <= x ? s : 0u;
+    return pos;
+}
+
 // Per segment of a view's records: the records of each bucket (rows) and the
 // smallest and largest visible key.  In a plan of one round of workgroups each
 // forms the view's sample distribution itself (the first one of the view also
@@ -1154,15 +1197,21 @@ __device__ __forceinline__ uint32_t key_bucket(uint32_t key, const uint32_t* cdf
 // 3M records: 25 us with that workgroup, 18 without.
 enum SampleMode { FORM, FORM_ONLY, READ };
 constexpr uint32_t BUCKET_FORM_SEGMENTS = 512;  // a round: two workgroups on each of 256 compute units
-template <SampleMode MODE>
+// SPLIT: views whose samples crowd are parted by order statistics.
+template <SampleMode MODE, bool SPLIT>
 __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, BucketMem b,
                                                                     const ViewParams* __restrict__ views, int nviews,
                                                                     uint32_t nseg, uint32_t seg_len, ZeroList zl) {
     constexpr int NT = BUCKET_THREADS, NW = NT / 64, SPT = BUCKET_SAMPLES / NT, RPT = 6;
     static_assert(BUCKET_BINS == 2 * NT, "two bins per thread");
-    __shared__ uint32_t cdf[BUCKET_BINS + 1], hist[BUCKET_MAX];
+    __shared__ __align__(8) uint32_t cdf[BUCKET_BINS + 1];
+    __shared__ uint32_t hist[BUCKET_MAX];
     __shared__ uint32_t red[NW], red2[NW], tot32[2];
     __shared__ unsigned long long tot64[2];
+    __shared__ uint64_t words[SPLIT && MODE != READ ? SPLIT_SAMPLES : 1];
+    __shared__ uint32_t crowd[2], nwords;
+    static_assert(SPLIT_MAX == NT && SPLIT_MAX * 2 <= BUCKET_BINS, "a thread per splitter, in the distribution's place");
+    uint64_t* const split = reinterpret_cast<uint64_t*>(cdf);
     static_assert(NT / 4 >= SEG_MAX / K1_THREADS, "a thread of the first waves per preprocess block");
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     if (MODE != FORM_ONLY) {
@@ -1192,6 +1241,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
     if (t < 2) {
         tot64[t] = 0ull;
         tot32[t] = 0u;
+        crowd[t] = 0u;
     }
     // a preprocess block's counts, and their sums over the segment
     struct BlockCounts {
@@ -1233,12 +1283,14 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
         const uint32_t nsamp_all = v.n_pad / 64;
         const uint32_t nsamp = min(nsamp_all, min((uint32_t)BUCKET_SAMPLES, max(2048u, 4u * nbkt)));
         const float stride = nsamp ? (float)nsamp_all / (float)nsamp : 0.0f;
+        // (the 64 records that sample i stands for)
+        auto wave_of = [&](uint32_t i) { return v.rec_base / 64 + min((uint32_t)((float)i * stride), nsamp_all - 1u); };
         uint32_t sk[SPT];
 #pragma unroll
         for (int k = 0; k < SPT; ++k) {
             const uint32_t i = (uint32_t)(k * NT + t);
             sk[k] = 0xffffffffu;
-            if (i < nsamp) sk[k] = o.sample[v.rec_base / 64 + min((uint32_t)((float)i * stride), nsamp_all - 1u)];
+            if (i < nsamp) sk[k] = o.sample[wave_of(i)];
             if (sk[k] != 0xffffffffu) {
                 lo = min(lo, sk[k]);
                 hi = max(hi, sk[k]);
@@ -1274,8 +1326,50 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
         cdf[2 * t + 1] = ex + c0;
         if (t == 0) cdf[BUCKET_BINS] = total;
         m.scale = total ? (nbkt << 16) / total : 0u;
+        const uint32_t mean = nbkt ? total / nbkt : 0u;
+        // a bucket holds its share and parts of two bins at most
+        if (SPLIT && max(c0, c1) > (mean + 8u) / 2u) crowd[0] = 1u;
         add_totals(bc);
         __syncthreads();
+        if constexpr (SPLIT) {
+            if (crowd[0]) {  // uniform
+                for (uint32_t i = t; i < nsamp; i += NT) {
+                    const uint32_t key = o.sample[wave_of(i)];
+                    if (key != 0xffffffffu) atomicAdd(&hist[key_bucket(key, cdf, m, nbkt)], 1u);
+                }
+                __syncthreads();
+                for (uint32_t i = t; i < nbkt; i += NT) {
+                    if (hist[i] > 2u * mean + 8u) crowd[1] = 1u;
+                    hist[i] = 0u;
+                }
+                __syncthreads();
+            }
+            if (crowd[1]) {  // uniform
+                const uint32_t every = (nsamp + SPLIT_SAMPLES - 1u) / SPLIT_SAMPLES, ns = (nsamp + every - 1u) / every;
+                uint32_t n2 = 64, have = 0;
+                while (n2 < ns) n2 <<= 1;
+                if (t == 0) nwords = 0u;
+                __syncthreads();
+                for (uint32_t k = t; k < n2; k += NT) {
+                    uint64_t x = ~0ull;
+                    if (k < ns) {
+                        const uint32_t wid = wave_of(k * every), key = o.sample[wid];
+                        if (key != 0xffffffffu) {
+                            x = ((uint64_t)key << 32) | (wid * 64u + sample_lane(o.vmask[wid], wid));
+                            ++have;
+                        }
+                    }
+                    words[k] = x;
+                }
+                have = wave_sum(have);
+                if (lane == 0) atomicAdd(&nwords, have);
+                bitonic_sort<NT>(words, n2);
+                const uint32_t parts = min(nbkt, SPLIT_MAX);
+                split[t] = (uint32_t)t + 1u < parts && nwords ? words[((uint32_t)t + 1u) * nwords / parts] : ~0ull;
+                m.shift = KEYMAP_SPLIT;
+                __syncthreads();
+            }
+        }
         if (MODE == FORM_ONLY || seg == 0) {
             uint32_t* out = b.cdf + (size_t)vi * BUCKET_CDF_WORDS;
             for (int i = t; i <= BUCKET_BINS; i += NT) out[i] = cdf[i];
@@ -1292,7 +1386,10 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
 #pragma unroll
         for (int k = 0; k < RPT; ++k)
             if (vis[k]) {
-                atomicAdd(&hist[key_bucket(key[k], cdf, m, nbkt)], 1u);
+                const uint32_t b = SPLIT && m.shift == KEYMAP_SPLIT
+                                       ? split_bucket(key[k], i0 + (uint32_t)(k * NT + t), split)
+                                       : key_bucket(key[k], cdf, m, nbkt);
+                atomicAdd(&hist[b], 1u);
                 lo = min(lo, key[k]);
                 hi = max(hi, key[k]);
             }
@@ -1499,12 +1596,14 @@ __device__ __forceinline__ uint32_t chunks_before(const uint32_t* __restrict__ c
 }
 
 // Every visible record of a segment to the next free place of its bucket.
+template <bool SPLIT>
 __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, BucketMem b,
                                                                       const ViewParams* __restrict__ views, int nviews,
                                                                       uint32_t nseg, uint32_t seg_len,
                                                                       const Counters* __restrict__ cnt) {
     constexpr int NT = BUCKET_THREADS, RPT = 6;
-    __shared__ uint32_t cdf[BUCKET_BINS + 1], next[BUCKET_MAX], cpre[BUCKET_MAX / COL_CHUNK];
+    __shared__ __align__(8) uint32_t cdf[BUCKET_BINS + 1];
+    __shared__ uint32_t next[BUCKET_MAX], cpre[BUCKET_MAX / COL_CHUNK];
     if (cnt->overflow & 2u) return;  // uniform: rendered again
     const int t = threadIdx.x, lane = t & 63;
     const int wg = xcd_segment((int)blockIdx.x, (int)nseg);  // neighbouring segments, whose elements meet, in one L2
@@ -1548,29 +1647,13 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, 
         for (int k = 0; k < RPT; ++k)
             if (vis[k]) {
                 const uint32_t i = i0 + (uint32_t)(k * NT + t);
-                const uint32_t pos = atomicAdd(&next[key_bucket(key[k], cdf, m, nbkt)], 1u);
+                const uint32_t bk = SPLIT && m.shift == KEYMAP_SPLIT
+                                        ? split_bucket(key[k], i, reinterpret_cast<const uint64_t*>(cdf))
+                                        : key_bucket(key[k], cdf, m, nbkt);
+                const uint32_t pos = atomicAdd(&next[bk], 1u);
                 b.elem[pos] = make_uint4(key[k], i, pack_rect(rect[k]), rect_cells(rect[k]) << 24);
             }
     }
-}
-
-// Bitonic sort of n 64-bit words in LDS (padded to a power of two with all
-// ones by the caller), by the whole workgroup.
-template <int NT>
-__device__ void bitonic_sort(uint64_t* a, uint32_t n2) {
-    for (uint32_t k = 2; k <= n2; k <<= 1)
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < n2 / 2; i += NT) {
-                const uint32_t x = (i / j) * 2 * j + i % j, y = x + j;
-                const uint64_t p = a[x], q = a[y];
-                if ((p > q) == ((x & k) == 0)) {
-                    a[x] = q;
-                    a[y] = p;
-                }
-            }
-        }
-    __syncthreads();
 }
 
 // One bucket sorted by (depth key, record).  Its elements are counted into
@@ -3313,22 +3396,33 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t crowd, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
-                        hipStream_t st) {
+                        bool flag_wide, uint32_t crowd, bool split, uint32_t nunits, uint32_t* val, uint32_t* ext,
+                        bool cells, hipStream_t st) {
+#define TIGAS_COUNT(M, GRID)                                                                                          \
+    do {                                                                                                              \
+        if (split)                                                                                                    \
+            TIGAS_LAUNCH((k_bucket_count<M, true>), dim3(GRID), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews,    \
+                         nseg, seg_len, zl);                                                                          \
+        else                                                                                                          \
+            TIGAS_LAUNCH((k_bucket_count<M, false>), dim3(GRID), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews,   \
+                         nseg, seg_len, zl);                                                                          \
+    } while (0)
     if (nseg <= BUCKET_FORM_SEGMENTS) {
-        TIGAS_LAUNCH(k_bucket_count<FORM>, dim3(std::max(nseg, 1u)), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews,
-                     nseg, seg_len, zl);
+        TIGAS_COUNT(FORM, std::max(nseg, 1u));
     } else {
-        TIGAS_LAUNCH(k_bucket_count<FORM_ONLY>, dim3(nviews), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,
-                     seg_len, zl);
-        TIGAS_LAUNCH(k_bucket_count<READ>, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
-                     zl);
+        TIGAS_COUNT(FORM_ONLY, nviews);
+        TIGAS_COUNT(READ, nseg);
     }
+#undef TIGAS_COUNT
     TIGAS_LAUNCH(k_bucket_scan, dim3(nchunks + 1), dim3(1024), st, b, views_dev, nviews, nseg, nchunks, cnt, cap,
                  flag_wide, crowd, nunits);
     if (nseg == 0) return;
-    TIGAS_LAUNCH(k_bucket_scatter, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg, seg_len,
-                 (const Counters*)cnt);
+    if (split)
+        TIGAS_LAUNCH(k_bucket_scatter<true>, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,
+                     seg_len, (const Counters*)cnt);
+    else
+        TIGAS_LAUNCH(k_bucket_scatter<false>, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,
+                     seg_len, (const Counters*)cnt);
     TIGAS_LAUNCH(k_bucket_sort, dim3(nchunks * COL_CHUNK), dim3(BUCKET_SORT_THREADS), st, o, b, views_dev,
                  nviews, (const Counters*)cnt, val, ext, cells);
 }

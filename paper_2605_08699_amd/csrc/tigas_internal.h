@@ -253,13 +253,15 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 // launches set the frame's counters, clear zl and recompute, in FP64, the
 // conic of every Gaussian preprocess listed as near-singular.  flag_wide: a
 // frame whose depth keys span 2^27 or more sets overflow bit 1 and is left
-// unsorted (the caller renders it again with the four-pass radix sort).
+// unsorted (the caller renders it again with the four-pass radix sort), and so
+// is one with over `crowd` elements in a bucket.  split: views whose samples crowd
+// are parted so that no bucket is long.
 // seg_len: records per segment; nseg, nchunks: segments and bucket chunks of
 // all views; nunits: of the tile placement that follows.
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t crowd, uint32_t nunits, uint32_t* val, uint32_t* ext, bool cells,
-                        hipStream_t st);
+                        bool flag_wide, uint32_t crowd, bool split, uint32_t nunits, uint32_t* val, uint32_t* ext,
+                        bool cells, hipStream_t st);
 // Runs LSD passes over the count selected by `which` (0 duplicates, 1 visible)
 // starting in buffer `start`; returns the buffer index holding the result.
 // With `rect_src`, the last pass also writes rect_src[value] to rect_dst in

@@ -236,6 +236,61 @@ def test_crowded_depth_buckets(ctx, kind, n):
     s.free()
 
 
+def _noalloc_frame(ctx, s, k, W, H):
+    import torch
+    out = torch.zeros((H, W, 3), dtype=torch.float32, device="cuda")
+    ctx.render_noalloc(s, eye_pose(), k, W, H, out, fmt="f32", tile=(16, 16))
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("kind,n", [("equal", n) for n in (2047, 2049, 4095, 4097, 8191, 16_385, 131_073, 300_000)] +
+                         [(k, n) for k in ("two", "lattice", "thin", "steps") for n in (4097, 17_000, 200_000)])
+def test_crowded_depths_are_parted_by_order_statistics(ctx, kind, n):
+    """Depths that crowd, in the form that parts them on the spot: the frame of
+    the four-pass radix sort."""
+    scene = _depth_scene(kind, n)
+    W, H = 160, 112
+    k = intr(150.0, W / 2, H / 2)
+    s = ctx.load_scene(scene)
+    _say("parted by order statistics", kind, n)
+    got = _noalloc_frame(ctx, s, k, W, H)
+    ctx.set_depth_passes(4)
+    try:
+        want = ctx.render(s, eye_pose(), k, W, H, fmt="f32", tile=(16, 16))
+    finally:
+        ctx.set_depth_passes(3)
+    assert want.any()
+    np.testing.assert_array_equal(got, want)
+    s.free()
+
+
+def test_frame_of_one_depth_takes_about_as_long_as_any_other(ctx):
+    """200k Gaussians of one depth, in the form without a second attempt: within
+    four times the frame of as many at spread depths (in one bucket it was 18)."""
+    import time
+
+    import torch
+    W, H, n = 960, 540, 200_000
+    k = intr(480.0, W / 2, H / 2)
+    out = torch.zeros((H, W, 3), dtype=torch.uint8, device="cuda")
+    us = {}
+    for kind in ("spread", "equal", "steps"):
+        s = ctx.load_scene(_depth_scene(kind, n))
+        times = []
+        for _ in range(9):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(10):
+                ctx.render_noalloc(s, eye_pose(), k, W, H, out, tile=(16, 16))
+            torch.cuda.synchronize()
+            times.append((time.perf_counter() - t0) * 1e5)
+        us[kind] = sorted(times)[4]
+        s.free()
+    _say("us a frame", us)
+    assert max(us["equal"], us["steps"]) < 4 * us["spread"]
+
+
 @pytest.mark.parametrize("kind", ["equal", "deep"])
 def test_batch_that_needs_another_depth_order_and_more_room(kind):
     """Views whose first attempt fits in shared lists but is rendered again
