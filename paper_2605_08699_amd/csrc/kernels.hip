@@ -76,6 +76,13 @@ __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
     return v;
 }
 
+// x, from which nothing is formed ahead of this point: addresses and constants
+// that the compiler keeps over a loop for a rare step in it take registers.
+__device__ __forceinline__ uint32_t fresh(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // Exclusive scan over a workgroup of NT threads; *total receives the sum.
 template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds, uint32_t* total) {
@@ -1146,22 +1153,102 @@ __device__ __forceinline__ uint32_t key_bucket(uint32_t key, const uint32_t* cdf
     return min(__umulhi(pos, m.scale), nbkt - 1u);
 }
 
-// Bitonic sort of n 64-bit words in LDS (padded to a power of two with all
-// ones by the caller), by the whole workgroup.
+// Bitonic sort of n2 64-bit words in LDS (a power of two from sort_min to SORT_MAX,
+// padded with all ones by the caller) by the whole workgroup: a wave sorts
+// sort_min of them in its registers (neighbours in a lane, lanes met by
+// permutes), and the waves meet through LDS, where a word's place is its (wave,
+// register, lane).  Of the 78 steps of 4096 words 6 (512 threads) or 10 (1024) are
+// in LDS behind barriers.  A frame of 17k Gaussians at 960x540, 3500 of them at one
+// depth, takes 131 us; with every step in LDS 155, by the radix passes 151, without
+// a crowded bucket 86.
+constexpr int SORT_MAX = 4096;
+template <int NT>
+__device__ constexpr uint32_t sort_min() {
+    return 64 * (SORT_MAX / NT);
+}
 template <int NT>
 __device__ void bitonic_sort(uint64_t* a, uint32_t n2) {
-    for (uint32_t k = 2; k <= n2; k <<= 1)
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+    constexpr int E = SORT_MAX / NT;  // words a lane
+    constexpr uint32_t PER_WAVE = sort_min<NT>();
+    const uint32_t lane = fresh(threadIdx.x) & 63u;
+    const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool on = c * PER_WAVE < n2;  // uniform over the wave
+    const uint32_t i0 = c * PER_WAVE + lane * E;  // number of the lane's first word
+    uint64_t* const mine = a + c * PER_WAVE + lane;
+    uint64_t x[E];
+    auto lanes_step = [&](uint32_t j, bool up) {  // words j >= E apart in the wave
+        const bool least = up == ((i0 & j) == 0u);
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            const uint64_t y = __shfl_xor((unsigned long long)x[r], (int)(j / E), 64);
+            x[r] = (y < x[r]) == least ? y : x[r];
+        }
+    };
+    auto lane_step = [&](int j, int r, bool up) {  // words r and r + j of the lane
+        const uint64_t p = x[r], q = x[r + j];
+        const bool swap = (p > q) == up;
+        x[r] = swap ? q : p;
+        x[r + j] = swap ? p : q;
+    };
+    auto lane_steps = [&](bool up) {
+#pragma unroll
+        for (int j = E / 2; j > 0; j >>= 1)
+#pragma unroll
+            for (int r = 0; r < E; ++r)
+                if ((r & j) == 0) lane_step(j, r, up);
+    };
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int r = 0; r < E; ++r) x[r] = mine[r * 64];  // any word to any place at first
+#pragma unroll
+        for (int k = 2; k < E; k <<= 1)
+#pragma unroll
+            for (int j = k / 2; j > 0; j >>= 1)
+#pragma unroll
+                for (int r = 0; r < E; ++r)
+                    if ((r & j) == 0) lane_step(j, r, (r & k) == 0);
+        lane_steps((i0 & E) == 0u);
+#pragma unroll 1
+        for (uint32_t k = 2 * E; k <= PER_WAVE; k <<= 1) {
+            const bool up = (i0 & k) == 0u;
+#pragma unroll 1
+            for (uint32_t j = k / 2; j >= (uint32_t)E; j >>= 1) lanes_step(j, up);
+            lane_steps(up);
+        }
+    }
+#pragma unroll 1
+    for (uint32_t k = 2 * PER_WAVE; k <= n2; k <<= 1) {
+        const bool up = (i0 & k) == 0u;
+#pragma unroll 1
+        for (uint32_t j = k / 2; j >= PER_WAVE; j >>= 1) {
             __syncthreads();
-            for (uint32_t i = threadIdx.x; i < n2 / 2; i += NT) {
-                const uint32_t x = (i / j) * 2 * j + i % j, y = x + j;
-                const uint64_t p = a[x], q = a[y];
-                if ((p > q) == ((x & k) == 0)) {
-                    a[x] = q;
-                    a[y] = p;
+            if (on) {
+#pragma unroll
+                for (int r = 0; r < E; ++r) mine[r * 64] = x[r];
+            }
+            __syncthreads();
+            if (on) {
+                const uint64_t* other = a + (c ^ (j / PER_WAVE)) * PER_WAVE + lane;
+                const bool least = up == ((i0 & j) == 0u);
+#pragma unroll
+                for (int r = 0; r < E; ++r) {
+                    const uint64_t y = other[r * 64];
+                    x[r] = (y < x[r]) == least ? y : x[r];
                 }
             }
         }
+        if (on) {
+#pragma unroll 1
+            for (uint32_t j = PER_WAVE / 2; j >= (uint32_t)E; j >>= 1) lanes_step(j, up);
+            lane_steps(up);
+        }
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int r = 0; r < E; ++r) a[i0 + r] = x[r];
+    }
     __syncthreads();
 }
 
@@ -1170,8 +1257,8 @@ __device__ void bitonic_sort(uint64_t* a, uint32_t n2) {
 // (depth key, record) words instead: SPLIT_MAX - 1 of them at most, in the place
 // of the distribution and marked by KeyMap::shift.  Equal depths are then parted
 // by record, and no bucket is long however the depths lie.  Allocation-free
-// frames of 17k / 200k Gaussians of one depth at 960x540 take 82 / 136 us; in one
-// bucket 141 / 1987, by the radix passes 159 / 201 (with spread depths 65 / 107).
+// frames of 17k / 200k Gaussians of one depth at 960x540 take 78 / 126 us; in one
+// bucket 141 / 1987, by the radix passes 160 / 202 (with spread depths 66 / 106).
 constexpr uint32_t SPLIT_MAX = BUCKET_BINS / 2;
 constexpr uint32_t SPLIT_SAMPLES = 4096;
 constexpr uint32_t KEYMAP_SPLIT = 0xffffffffu;
@@ -1210,6 +1297,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
     __shared__ unsigned long long tot64[2];
     __shared__ uint64_t words[SPLIT && MODE != READ ? SPLIT_SAMPLES : 1];
     __shared__ uint32_t crowd[2], nwords;
+    static_assert(SPLIT_SAMPLES <= SORT_MAX, "sorted at once");
     static_assert(SPLIT_MAX == NT && SPLIT_MAX * 2 <= BUCKET_BINS, "a thread per splitter, in the distribution's place");
     uint64_t* const split = reinterpret_cast<uint64_t*>(cdf);
     static_assert(NT / 4 >= SEG_MAX / K1_THREADS, "a thread of the first waves per preprocess block");
@@ -1346,7 +1434,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
             }
             if (crowd[1]) {  // uniform
                 const uint32_t every = (nsamp + SPLIT_SAMPLES - 1u) / SPLIT_SAMPLES, ns = (nsamp + every - 1u) / every;
-                uint32_t n2 = 64, have = 0;
+                uint32_t n2 = sort_min<NT>(), have = 0;
                 while (n2 < ns) n2 <<= 1;
                 if (t == 0) nwords = 0u;
                 __syncthreads();
@@ -1372,7 +1460,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
         }
         if (MODE == FORM_ONLY || seg == 0) {
             uint32_t* out = b.cdf + (size_t)vi * BUCKET_CDF_WORDS;
-            for (int i = t; i <= BUCKET_BINS; i += NT) out[i] = cdf[i];
+            for (uint32_t i = fresh(t); i <= BUCKET_BINS; i += NT) out[i] = cdf[i];
             if (t < 4) out[BUCKET_BINS + 1 + t] = t == 0 ? m.lo : t == 1 ? m.hi : t == 2 ? m.shift : m.scale;
         }
     }
@@ -1410,7 +1498,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
         b.seg[blockIdx.x] = SegTotals{tot64[0], tot64[1], tot32[0], tot32[1], lo, hi};
     }
     uint32_t* row = b.rows + v.row_base + (size_t)seg * nbkt;
-    for (uint32_t i = t; i < nbkt; i += NT) row[i] = hist[i];
+    for (uint32_t i = fresh(t); i < nbkt; i += NT) row[i] = hist[i];
 }
 
 // Exclusive prefixes down the columns of a row-major nrows x ncols array
@@ -1669,14 +1757,15 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, 
 // with the square of the bucket).  The launch also recomputes
 // the FP64 conics of the near-singular Gaussians, before anything reads the
 // exponent coefficients.
-__global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, BucketMem b,
+__global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o, BucketMem b,
                                                                      const ViewParams* __restrict__ views, int nviews,
                                                                      const Counters* __restrict__ cnt,
                                                                      uint32_t* __restrict__ val,
                                                                      uint32_t* __restrict__ ext, bool cells) {
     constexpr int NT = BUCKET_SORT_THREADS, NW = NT / 64, CAP = BUCKET_SORT_CAP, EPT = CAP / NT;
     constexpr int BINS = 2048, BPT = BINS / NT;
-    constexpr uint32_t CROWDED = 48;  // a pass over a bin of this size costs about as much as the bitonic sort
+    static_assert(CAP <= SORT_MAX, "sorted at once");
+    constexpr uint32_t CROWDED = 48;  // larger bins are left to the bitonic sort
     __shared__ uint64_t arr[CAP];
     __shared__ uint32_t bin[BINS + 1];
     __shared__ uint32_t red[NW], red2[NW];
@@ -1698,8 +1787,9 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
         if (t == 0) b.cost[blockIdx.x] = 0u;
         return;
     }
-    const uint32_t first = b.vc[vi].start + chunks_before(b.chunk + v.bkt_base / COL_CHUNK, lb / COL_CHUNK) +
-                           b.start_in[blockIdx.x];
+    // (scalar: the addresses formed from it are kept over the sort)
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)(b.vc[vi].start + chunks_before(b.chunk + v.bkt_base / COL_CHUNK, lb / COL_CHUNK) + b.start_in[blockIdx.x]));
     const uint4* e = b.elem + first;
     // the bucket's placement cost, for the units of the tile placement
     auto store_cost = [&](uint32_t entries) {
@@ -1823,7 +1913,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
             }
             return;
         }
-        uint32_t n2 = 64;
+        uint32_t n2 = sort_min<NT>();
         while (n2 < n) n2 <<= 1;
         for (uint32_t i = n + t; i < n2; i += NT) arr[i] = ~0ull;
         bitonic_sort<NT>(arr, n2);
@@ -1912,7 +2002,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS) void k_bucket_sort(PreOut o, B
     };
     // sorts arr[0, m) and writes it to `at`
     auto sort_out = [&](uint32_t m, uint32_t at) {
-        uint32_t n2 = 64;
+        uint32_t n2 = sort_min<NT>();
         while (n2 < m) n2 <<= 1;
         for (uint32_t i = m + t; i < n2; i += NT) arr[i] = ~0ull;
         bitonic_sort<NT>(arr, n2);
@@ -2989,13 +3079,6 @@ __device__ __forceinline__ bool below_threshold(float A, float B, float C, float
 // With a workgroup per tile, the launch at 3M/1080p, 3M/4K, 1M/720p and over 32
 // views took 144, 418, 97 us and 2.39 ms; with the vector form before, 170, 497,
 // 110 us and 2.87 ms.
-// x, from which nothing is formed ahead of this point: addresses and constants
-// that the compiler keeps over a loop for a rare step in it take registers.
-__device__ __forceinline__ uint32_t fresh(uint32_t x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // The staged entries 0 .. whole - 1 of a wave, in groups of eight, on its
