@@ -274,16 +274,18 @@ tigas_status tigas_set_tile_culling(tigas_context* ctx, int enable);
  * Sections 4.1 and 5.1): passes = 3 (the default) scatters them to buckets of
  * depth ranges (counted, scanned, scattered: reported as three passes in
  * tigas_stats.sort_passes) and sorts every bucket on chip, when every view
- * has at most 256 x 256 tiles.  A frame whose visible FP32 depth keys span
- * 2^27 or more (about 16 octaves of depth), or of which over 16384 keys fall
- * into one bucket (most of a view at nearly one depth), is detected on the
- * GPU, rendered again with four radix passes, and the context keeps four
- * passes from then on (counted in tigas_stats.rerenders);
- * tigas_render_noalloc, which has no second attempt, parts the buckets of such
- * a frame by order statistics of sampled (depth, record) words.  passes = 4
- * always takes four 8-bit radix passes of the whole key (environment TIGAS_DEPTH_PASSES=4 at context creation).  The
- * order, and so every frame, is identical either way.  E_INVALID for another
- * value. */
+ * has at most 256 x 256 tiles.  Two kinds of frames are detected on the GPU
+ * and rendered again (counted in tigas_stats.rerenders): a single view whose
+ * visible FP32 depth keys span 2^27 or more (about 16 octaves of depth), with four
+ * radix passes; and any frame with over 4096 keys, and over four times the mean,
+ * in one bucket (much of a view at nearly one depth), with buckets parted by order
+ * statistics of sampled (depth, record) words.  Later frames of the same scene
+ * take that order at once, frames of other scenes are not affected, and the next
+ * call of this function forgets it.  tigas_render_noalloc, which has no second
+ * attempt, chooses the buckets' parting on the GPU and takes keys of any span.
+ * passes = 4 always takes four 8-bit radix passes of the whole key (environment
+ * TIGAS_DEPTH_PASSES=4 at context creation).  The order, and so every frame, is
+ * identical either way.  E_INVALID for another value. */
 tigas_status tigas_set_depth_passes(tigas_context* ctx, int passes);
 tigas_status tigas_stage_times(tigas_context* ctx, tigas_stage_ms* out);
 

@@ -196,6 +196,17 @@ struct Group {
     uint32_t rec_base, n_pad;
 };
 
+// What changes a plan's launch sequence (not its results), as it stood when the
+// plan was laid out: a switch flipped by another thread since then waits for the
+// next frame.
+struct LaunchOptions {
+    bool cull = true;         // blend: per-block threshold culling of list entries
+    bool bin = true;          // tile digit placed by counting (else radix passes over the duplicates)
+    bool cull_tiles = false;  // duplicates only for tiles the Gaussian can reach (radix passes then)
+    bool buckets = true;      // bucketed depth sort when the rectangles pack (else four radix passes)
+    uint32_t split = 0;       // shares of a bucket's samples from which order statistics part a view's buckets (0: never)
+};
+
 struct Plan {
     std::vector<ViewParams> views;
     std::vector<Group> groups;
@@ -207,6 +218,8 @@ struct Plan {
     TileCfg tc{16, 16, 64, 1};
     bool batch = false;   // a batch's plan: tuned apart from single frames
     bool shared = false;  // tiles may share lists (set_tiles)
+    LaunchOptions opt;    // lay_out
+    uint32_t found = 0;   // FLAG_WIDE, FLAG_CROWDED: met by an attempt of this plan
     bool allow_graph = true;  // capture/replay (off for one-off shapes such as serving batches)
 };
 
@@ -300,7 +313,7 @@ struct FrameMem {
     uint32_t* hist = nullptr;      // digit counts per sort segment
     uint32_t* hist_tot = nullptr;  // per-digit totals
     BucketMem bk{};                // bucketed depth sort
-    bool flag_wide = true;         // flag frames too deep for it (the caller renders them again)
+    bool retry = true;             // flag frames that it does not suit (the caller renders them again)
     uint2* ranges = nullptr;
     uint32_t* order = nullptr;     // the blend's dispatch order of the tiles
     TileMem tm{};                  // tile placement by counting
@@ -481,7 +494,8 @@ struct tigas_context {
     std::atomic<bool> blend_cull{true};     // blend: per-block threshold culling
     std::atomic<bool> tile_bin{true};       // tile digit placed by counting
     std::atomic<bool> tile_cull{false};     // duplicates only for tiles each Gaussian can reach
-    std::atomic<bool> depth4{false};        // four-pass depth sort (requested, or after a frame too deep for three)
+    std::atomic<bool> depth4{false};        // four-pass depth sort requested
+    std::atomic<uint32_t> depth_epoch{1};   // requests so far: one forgets what the scenes' frames were found to be
     double stage_ms[6] = {0, 0, 0, 0, 0, 0};
     int64_t stage_frames = 0;
     std::mutex tune_mu;
@@ -519,6 +533,9 @@ struct tigas_scene {
     DevBuf mean, attr, sh;
     size_t bytes = 0;
     std::atomic<int> refs{0};
+    // the context's depth_epoch in which a frame of the scene was last found to
+    // have depths too wide, or too crowded, for the buckets of depth ranges
+    std::atomic<uint32_t> wide{0}, crowded{0};
 };
 
 namespace {
@@ -863,22 +880,6 @@ void prepare(Workspace& ws, Plan& plan, bool debug) {
 //   preprocess -> depth order of the visible Gaussians (buckets; or scan
 //   visible -> compact -> radix passes) -> tile placement (counting; or
 //   duplicate in depth order -> tile passes -> ranges) -> blend
-// Per-context switches that change the launch sequence (not its results).
-struct LaunchOptions {
-    bool cull = true;         // blend: per-block threshold culling of list entries
-    bool bin = true;          // tile digit placed by counting (else radix passes over the duplicates)
-    bool cull_tiles = false;  // duplicates only for tiles the Gaussian can reach (radix passes then)
-    bool buckets = true;      // bucketed depth sort when the rectangles pack (else four radix passes)
-    // A plan of shared lists was laid out for the placement by counting: a
-    // switch flipped by another thread since then waits for the next frame.
-    void follow(const Plan& plan) {
-        if (plan.shared) {
-            bin = true;
-            cull_tiles = false;
-        }
-    }
-};
-
 // Whether every view's tile rectangles fit the packed one-word form.
 bool packed_rects(const Plan& plan) {
     bool packed = true;
@@ -886,13 +887,36 @@ bool packed_rects(const Plan& plan) {
     return packed;
 }
 
-// Whether the plan's tile digit is placed by counting.
-bool use_bin(const Plan& plan, const LaunchOptions& opt) {
-    return opt.bin && !opt.cull_tiles && packed_rects(plan) && (opt.buckets || plan.views.size() == 1);
+// Whether the tiles of a plan may share lists: where they are placed by counting.
+bool share_lists(const Plan& plan) {
+    const LaunchOptions& opt = plan.opt;
+    return opt.bin && !opt.cull_tiles && (opt.buckets || plan.views.size() == 1);
 }
 
-int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned long long* work,
-            const LaunchOptions& opt) {
+// Whether the plan's tile digit is placed by counting.
+bool use_bin(const Plan& plan) { return share_lists(plan) && packed_rects(plan); }
+
+// Lays a plan out for a tile configuration by the context's switches and by what
+// earlier frames of its scenes, or an attempt of its own, were found to be.  A
+// single view of wide depths takes the radix passes; several views stay in
+// buckets, which take keys of any span, because without them the lists are not
+// placed by counting.
+void lay_out(tigas_context* ctx, Plan& plan, const TileCfg& tc, bool debug) {
+    uint32_t found = plan.found;
+    const uint32_t epoch = ctx->depth_epoch.load();
+    for (const Group& g : plan.groups)
+        found |= (g.scene->wide.load() == epoch ? FLAG_WIDE : 0u) | (g.scene->crowded.load() == epoch ? FLAG_CROWDED : 0u);
+    LaunchOptions& opt = plan.opt;
+    opt.cull = ctx->blend_cull.load();
+    opt.bin = ctx->tile_bin.load();
+    opt.cull_tiles = ctx->tile_cull.load();
+    opt.buckets = !ctx->depth4.load() && !((found & FLAG_WIDE) && plan.views.size() == 1);
+    opt.split = found & FLAG_CROWDED ? SPLIT_SHARES : 0u;
+    set_tiles(plan, tc, !debug && share_lists(plan));
+}
+
+int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned long long* work) {
+    const LaunchOptions& opt = plan.opt;
     hipStream_t st = m.stream;
     auto mark = [&](int i) {
         if (prof) HIPCHK(hipEventRecord(m.ev[i], st));
@@ -934,7 +958,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     // is the same); the tile rectangles travel packed with them when every
     // view has at most 256 x 256 tiles, else the last radix pass gathers them
     const bool packed = packed_rects(plan);
-    const bool bin = use_bin(plan, opt);
+    const bool bin = use_bin(plan);
     const bool cells = bin && opt.buckets && !debug && plan.views[0].cells;  // in the entries
     int cv = 0;
     if (opt.buckets && packed) {
@@ -942,9 +966,9 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         zl.p[2] = &cnt->overflow;
         zl.n[2] = 1;
         // (an inspection shows the bucketed order however long it takes)
-        launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl, m.flag_wide,
-                           m.flag_wide && !debug ? BUCKET_CROWD : 0xffffffffu, /*split=*/!m.flag_wide, plan.nunits,
-                           sb.val[0], sb.ext[0], cells, st);
+        launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl,
+                           /*flag_wide=*/m.retry && nv == 1, /*flag_crowd=*/m.retry && !debug && !opt.split, opt.split,
+                           plan.nunits, sb.val[0], sb.ext[0], cells, st);
     } else {
         launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
         mark(2);
@@ -994,23 +1018,8 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     return cur;
 }
 
-// Whether the tiles of a plan of the context may share lists.
-bool share_lists(tigas_context* ctx, const Plan& plan) {
-    return ctx->tile_bin.load() && !ctx->tile_cull.load() && (!ctx->depth4.load() || plan.views.size() == 1);
-}
-
-bool plan_binned(tigas_context* ctx, const Plan& plan) {
-    LaunchOptions opt;
-    opt.bin = ctx->tile_bin.load();
-    opt.cull_tiles = ctx->tile_cull.load();
-    opt.buckets = !ctx->depth4.load();
-    return use_bin(plan, opt);
-}
-
-// Depth passes of the context's frames of this plan (after a frame settled).
-int depth_passes(tigas_context* ctx, const Plan& plan) {
-    return !ctx->depth4.load() && packed_rects(plan) ? 3 : 4;
-}
+// Depth passes of a plan's frames, as the statistics count them.
+int depth_passes(const Plan& plan) { return plan.opt.buckets && packed_rects(plan) ? 3 : 4; }
 
 // Launch the plan once: from a captured graph when allowed (captured on the
 // first use of its shape, re-captured after any workspace reallocation), else
@@ -1020,22 +1029,17 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
     std::memcpy(ws.fs().host_views.p, plan.views.data(), sizeof(ViewParams) * plan.views.size());
     if (prof) ws.ensure_events();
     // stage timing needs events between the launches: that runs uncaptured
-    LaunchOptions opt;
-    opt.cull = ctx->blend_cull.load();
-    opt.bin = ctx->tile_bin.load();
-    opt.cull_tiles = ctx->tile_cull.load();
-    opt.buckets = !ctx->depth4.load();
-    opt.follow(plan);
+    const LaunchOptions& opt = plan.opt;
     const bool kprof = ctx->profile_kernels.load();
     const bool graph = ctx->use_graphs.load() && plan.allow_graph && !debug && !work && !prof && !kprof;
     if (kprof) {
         ws.ktimer.reset();
         TimerScope ts(&ws.ktimer);
-        return enqueue(frame_mem(ws, plan), plan, debug, prof, work, opt);
+        return enqueue(frame_mem(ws, plan), plan, debug, prof, work);
     }
-    if (!graph) return enqueue(frame_mem(ws, plan), plan, debug, prof, work, opt);
+    if (!graph) return enqueue(frame_mem(ws, plan), plan, debug, prof, work);
     const std::string key = shape_key(plan, true) + (opt.cull ? "c1" : "c0") + (opt.bin ? "b1" : "b0") + (opt.cull_tiles ? "t1" : "t0") +
-                            (opt.buckets ? "d3" : "d4") + (ws.active ? "f1" : "f0");
+                            (opt.buckets ? "d3" : "d4") + (opt.split ? "s1" : "s0") + (ws.active ? "f1" : "f0");
     GraphEntry& g = ws.graphs[key];
     if (!g.exec || g.gen != ws.gen) {
         if (g.exec) HIPCHK(hipGraphExecDestroy(g.exec));
@@ -1048,7 +1052,7 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
         HIPCHK(hipStreamBeginCapture(ws.stream, hipStreamCaptureModeThreadLocal));
         int cur = 0;
         try {
-            cur = enqueue(frame_mem(ws, plan), plan, debug, prof, work, opt);
+            cur = enqueue(frame_mem(ws, plan), plan, debug, prof, work);
         } catch (...) {
             (void)hipStreamEndCapture(ws.stream, &graph_t);
             if (graph_t) (void)hipGraphDestroy(graph_t);
@@ -1089,17 +1093,22 @@ FrameCounters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool d
     std::memcpy(&c, ws.fs().host_counters.p, sizeof(c));
     rerenders = 0;
     if (c.overflow) {
-        // bit 1: the visible depth keys span too much for the bucketed sort,
-        // or crowd into one bucket: four radix passes from now on; bit 0: more duplicates than the
-        // buffers hold: grow them
-        if (c.overflow & 2u) {
-            ctx->depth4.store(true);
-            set_tiles(plan, plan.tc, !debug && share_lists(ctx, plan));
+        // depths that the buckets of depth ranges do not suit: another order,
+        // which later frames of the plan's scenes take at once
+        plan.found |= c.overflow & (FLAG_WIDE | FLAG_CROWDED);
+        if (c.overflow & (FLAG_WIDE | FLAG_CROWDED)) {
+            const uint32_t epoch = ctx->depth_epoch.load();
+            for (const Group& g : plan.groups) {
+                if (c.overflow & FLAG_WIDE) g.scene->wide.store(epoch);
+                if (c.overflow & FLAG_CROWDED) g.scene->crowded.store(epoch);
+            }
+            lay_out(ctx, plan, plan.tc, debug);
             prepare(ws, plan, debug);
         }
+        // more entries than the buffers hold: larger ones
         // (c.D, the (Gaussian, tile) pairs, bounds the entries in every layout;
         // a plan laid out again without shared lists has as many)
-        if ((c.overflow & 1u) || c.D > ws.dup_cap) {
+        if ((c.overflow & FLAG_FULL) || c.D > ws.dup_cap) {
             const uint64_t want = (uint64_t)c.D + c.D / 4 + 1024;
             if (want > 0xfff00000ull) fail(TIGAS_E_OOM, "duplicate count exceeds the 32-bit index range");
             ws.ensure_dups((uint32_t)want);
@@ -1109,20 +1118,20 @@ FrameCounters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool d
         cur = launch_plan(ctx, ws, plan, debug, prof, work);
         wait_stream(ws.stream);
         std::memcpy(&c, ws.fs().host_counters.p, sizeof(c));
-        if (c.overflow) fail(TIGAS_E_DEVICE, "duplicate buffer overflow after regrowth or four-pass depth sort");
+        if (c.overflow) fail(TIGAS_E_DEVICE, "duplicate buffer overflow after regrowth or in another depth order");
         rerenders += 1;
     }
     ws.last_D = c.D;
     return c;
 }
 
-tigas_stats frame_stats(const Plan& plan, const FrameCounters& c, int rerenders, bool binned, int depth_passes) {
+tigas_stats frame_stats(const Plan& plan, const FrameCounters& c, int rerenders) {
     tigas_stats st{};
     st.visible = c.visible;
     st.duplicates = c.D;
     st.fallbacks = c.fallbacks;
     st.tiles = plan.n_frame_tiles;
-    st.sort_passes = depth_passes + (binned ? 1 : (int64_t)tile_passes(plan.n_tiles).size());
+    st.sort_passes = depth_passes(plan) + (use_bin(plan) ? 1 : (int64_t)tile_passes(plan.n_tiles).size());
     st.rerenders = rerenders;
     st.tile_w = plan.tc.tw;
     st.tile_h = plan.tc.th;
@@ -1187,7 +1196,7 @@ void finish_async(tigas_context* ctx, Workspace& ws, int si) {
         ws.active = si;
         int cur = f.cur, rerenders = 0;
         const FrameCounters c = settle_frame(ctx, ws, f.plan, false, false, nullptr, cur, rerenders);
-        d.stats = frame_stats(f.plan, c, rerenders, plan_binned(ctx, f.plan), depth_passes(ctx, f.plan));
+        d.stats = frame_stats(f.plan, c, rerenders);
         record_stats(ctx, ws, d.stats, false);
     } catch (const Error& e) {
         d.status = e.st;
@@ -1220,7 +1229,7 @@ int run_plan(tigas_context* ctx, Workspace& ws, Plan& plan, bool debug, unsigned
     wait_stream(ws.stream);
     int rerenders = 0;
     const FrameCounters c = settle_frame(ctx, ws, plan, debug, prof, work, cur, rerenders);
-    record_stats(ctx, ws, frame_stats(plan, c, rerenders, plan_binned(ctx, plan), depth_passes(ctx, plan)), prof);
+    record_stats(ctx, ws, frame_stats(plan, c, rerenders), prof);
     return cur;
 }
 
@@ -1265,7 +1274,7 @@ TileCfg autotune(tigas_context* ctx, Workspace& ws, Plan& plan) {
     TileCfg best = kTileCandidates[1];
     double best_ms = 1e30;
     for (const TileCfg& tc : kTileCandidates) {
-        set_tiles(plan, tc, share_lists(ctx, plan));
+        lay_out(ctx, plan, tc, false);
         run_plan(ctx, ws, plan, false);  // capture + warm
         run_plan(ctx, ws, plan, false);
         double ts[7];
@@ -1339,7 +1348,7 @@ void render_views(tigas_context* ctx, Workspace& ws, Plan& plan, const tigas_qua
         if (q && q->batch_depth != 0) tc.bd = req.bd;
         if (q && q->pixels_per_lane != 0 && tc.th >= 16) tc.ppl = req.ppl;
     }
-    set_tiles(plan, tc, !dbg && share_lists(ctx, plan));
+    lay_out(ctx, plan, tc, dbg != nullptr);
     unsigned long long* work = nullptr;
     if (work_out) {
         ws.work.ensure(16);
@@ -1398,7 +1407,7 @@ void render_submit(tigas_scene* scene, const tigas_pose* pose, const tigas_intri
         if (q && q->batch_depth != 0) tc.bd = req.bd;
         if (q && q->pixels_per_lane != 0 && tc.th >= 16) tc.ppl = req.ppl;
     }
-    set_tiles(plan, tc, share_lists(ctx, plan));
+    lay_out(ctx, plan, tc, false);
     const int si = ws.next_async;
     FrameSlot& f = ws.slot[si];
     if (f.pending) finish_async(ctx, ws, si);  // two frames in flight at most
@@ -1537,7 +1546,7 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_o
     rows_bytes = (rows_bytes + 255) / 256 * 256;
     o.vmask = reinterpret_cast<unsigned long long*>(hist + rows_bytes + small_bytes);
     o.sample = reinterpret_cast<uint32_t*>(hist + rows_bytes + small_bytes + mask_bytes);
-    m.flag_wide = false;  // no second attempt here
+    m.retry = false;  // no second attempt here
     // six duplicate arrays of dup_cap words (keys, values, extra; two each)
     const size_t left = c.cap > c.off + 6 * 256 ? c.cap - c.off - 6 * 256 : 0;
     const uint64_t dup_cap = std::min<uint64_t>(left / 24 / 256 * 256, 16u << 20);
@@ -1574,21 +1583,18 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     out->out_h = v.height;
     if (!out->data || out->capacity < frame_bytes(v)) fail(TIGAS_E_BUFFER, "output frame buffer too small");
     v.out_ptr = (uint64_t)(uintptr_t)out->data;
-    // as requested, else 16x16 tiles: no autotuner here
-    set_tiles(plan, tile_cfg(q), ctx->tile_bin.load() && !ctx->tile_cull.load());
+    // as requested, else 16x16 tiles: no autotuner here; no second attempt either,
+    // so the buckets meet crowded depths on the spot, and wide ones as they are
+    lay_out(ctx, plan, tile_cfg(q), false);
+    plan.opt.buckets = !ctx->depth4.load();
+    plan.opt.split = CROWD_SHARES;
     set_buckets(plan);
     // fewer units than with a workspace: their rows come out of the array
     plan.nunits = std::min<uint32_t>(plan.nunits, (plan.nrec + 2047) / 2048 + 20);
     const hipStream_t st = pick_stream(ctx, hip_stream);
     const FrameMem m =
         carve_scratch(scratch_dev, plan, reinterpret_cast<FrameCounters*>(counters), st);
-    LaunchOptions opt;
-    opt.cull = ctx->blend_cull.load();
-    opt.bin = ctx->tile_bin.load();
-    opt.cull_tiles = ctx->tile_cull.load();
-    opt.buckets = !ctx->depth4.load();
-    opt.follow(plan);
-    (void)enqueue(m, plan, false, false, nullptr, opt);
+    (void)enqueue(m, plan, false, false, nullptr);
 }
 
 void debug_copy(Workspace& ws, const Plan& plan, int cur, int64_t n, uint32_t n_pad, tigas_debug_out* dbg) {
@@ -2532,6 +2538,7 @@ tigas_status tigas_set_depth_passes(tigas_context* ctx, int passes) {
         if (!ctx) fail(TIGAS_E_INVALID, "null context");
         if (passes != 3 && passes != 4) fail(TIGAS_E_INVALID, "depth passes must be 3 or 4");
         ctx->depth4.store(passes == 4);
+        ctx->depth_epoch.fetch_add(1);
     });
 }
 

@@ -1252,8 +1252,7 @@ __device__ void bitonic_sort(uint64_t* a, uint32_t n2) {
     __syncthreads();
 }
 
-// A view whose samples crowd (over 2 x the mean + 8 of them in one bucket: a flat
-// model seen face on, say) is parted by order statistics of the samples'
+// A view whose samples crowd (over `shares` times the mean + 8 of them in one bucket: a flat model seen face on, say) is parted by order statistics of the samples'
 // (depth key, record) words instead: SPLIT_MAX - 1 of them at most, in the place
 // of the distribution and marked by KeyMap::shift.  Equal depths are then parted
 // by record, and no bucket is long however the depths lie.  Allocation-free
@@ -1284,11 +1283,13 @@ __device__ __forceinline__ uint32_t split_bucket(uint32_t key, uint32_t rec, con
 // 3M records: 25 us with that workgroup, 18 without.
 enum SampleMode { FORM, FORM_ONLY, READ };
 constexpr uint32_t BUCKET_FORM_SEGMENTS = 512;  // a round: two workgroups on each of 256 compute units
-// SPLIT: views whose samples crowd are parted by order statistics.
+// SPLIT: views with over `shares` times the mean + 8 samples in a bucket are parted
+// by order statistics.
 template <SampleMode MODE, bool SPLIT>
 __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, BucketMem b,
                                                                     const ViewParams* __restrict__ views, int nviews,
-                                                                    uint32_t nseg, uint32_t seg_len, ZeroList zl) {
+                                                                    uint32_t nseg, uint32_t seg_len, uint32_t shares,
+                                                                    ZeroList zl) {
     constexpr int NT = BUCKET_THREADS, NW = NT / 64, SPT = BUCKET_SAMPLES / NT, RPT = 6;
     static_assert(BUCKET_BINS == 2 * NT, "two bins per thread");
     __shared__ __align__(8) uint32_t cdf[BUCKET_BINS + 1];
@@ -1415,8 +1416,9 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
         if (t == 0) cdf[BUCKET_BINS] = total;
         m.scale = total ? (nbkt << 16) / total : 0u;
         const uint32_t mean = nbkt ? total / nbkt : 0u;
+        const uint32_t most = shares * mean + 8u;
         // a bucket holds its share and parts of two bins at most
-        if (SPLIT && max(c0, c1) > (mean + 8u) / 2u) crowd[0] = 1u;
+        if (SPLIT && max(c0, c1) > (most - mean) / 2u) crowd[0] = 1u;
         add_totals(bc);
         __syncthreads();
         if constexpr (SPLIT) {
@@ -1427,7 +1429,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
                 }
                 __syncthreads();
                 for (uint32_t i = t; i < nbkt; i += NT) {
-                    if (hist[i] > 2u * mean + 8u) crowd[1] = 1u;
+                    if (hist[i] > most) crowd[1] = 1u;
                     hist[i] = 0u;
                 }
                 __syncthreads();
@@ -1580,7 +1582,7 @@ __device__ __forceinline__ bool depth_wide(uint32_t lo, uint32_t hi) {
 // frame's counters and the views' first positions.
 __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewParams* __restrict__ views, int nviews,
                                                       uint32_t nseg, uint32_t nchunks, Counters* cnt, uint32_t cap,
-                                                      bool flag_wide, uint32_t crowd, uint32_t nunits) {
+                                                      bool flag_wide, bool flag_crowd, uint32_t nunits) {
     __shared__ uint32_t lds[(1024 / COL_CHUNK + 1) * (COL_CHUNK + 1)];
     if (blockIdx.x < nchunks) {
         const uint32_t c0 = blockIdx.x * COL_CHUNK;
@@ -1589,8 +1591,9 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewPar
         column_scan<COL_CHUNK, 16>(b.rows + v.row_base, v.nseg, v.nbkt, v.nbkt, c0 - v.bkt_base, b.start_in + c0, b.tot + c0,
                     b.chunk + blockIdx.x, lds);
         // (a thread reads the total that it wrote)
-        if (threadIdx.x < COL_CHUNK && c0 - v.bkt_base + threadIdx.x < v.nbkt && b.tot[c0 + threadIdx.x] > crowd)
-            atomicOr(&cnt->overflow, 2u);
+        if (flag_crowd && threadIdx.x < COL_CHUNK && c0 - v.bkt_base + threadIdx.x < v.nbkt &&
+            b.tot[c0 + threadIdx.x] > max((uint32_t)BUCKET_SORT_CAP, v.n_pad / v.nbkt * CROWD_SHARES))
+            atomicOr(&cnt->overflow, FLAG_CROWDED);
         return;
     }
     uint32_t lo = 0xffffffffu, hi = 0u;
@@ -1669,8 +1672,8 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketMem b, const ViewPar
         cnt->pairs = P > 0xffffffffull ? 0xffffffffu : (uint32_t)P;
         cnt->visible = V;
         cnt->fallbacks = F;
-        // cleared by the launch before; other workgroups may have set bit 1
-        atomicOr(&cnt->overflow, (D > (uint64_t)cap ? 1u : 0u) | (flag_wide && depth_wide(lo, hi) ? 2u : 0u));
+        // cleared by the launch before; other workgroups may have set FLAG_CROWDED
+        atomicOr(&cnt->overflow, (D > (uint64_t)cap ? 1u : 0u) | (flag_wide && depth_wide(lo, hi) ? FLAG_WIDE : 0u));
         cnt->fb_listed = cnt->fb_list;
         cnt->fb_list = 0u;  // the next frame appends from zero
     }
@@ -1692,7 +1695,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, 
     constexpr int NT = BUCKET_THREADS, RPT = 6;
     __shared__ __align__(8) uint32_t cdf[BUCKET_BINS + 1];
     __shared__ uint32_t next[BUCKET_MAX], cpre[BUCKET_MAX / COL_CHUNK];
-    if (cnt->overflow & 2u) return;  // uniform: rendered again
+    if (cnt->overflow & (FLAG_WIDE | FLAG_CROWDED)) return;  // uniform: rendered again
     const int t = threadIdx.x, lane = t & 63;
     const int wg = xcd_segment((int)blockIdx.x, (int)nseg);  // neighbouring segments, whose elements meet, in one L2
     const int vi = view_of((uint32_t)wg, nviews, [&](int i) { return views[i].seg_base; });
@@ -1771,7 +1774,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o
     __shared__ uint32_t red[NW], red2[NW];
     __shared__ uint64_t redlo[NW], redhi[NW];
     __shared__ uint32_t picked, fill;
-    if (cnt->overflow & 2u) return;  // uniform: rendered again
+    if (cnt->overflow & (FLAG_WIDE | FLAG_CROWDED)) return;  // uniform: rendered again
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     {
         const uint32_t nfb = min(cnt->fb_listed, o.fb_cap);
@@ -3479,16 +3482,16 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t crowd, bool split, uint32_t nunits, uint32_t* val, uint32_t* ext,
+                        bool flag_wide, bool flag_crowd, uint32_t split, uint32_t nunits, uint32_t* val, uint32_t* ext,
                         bool cells, hipStream_t st) {
 #define TIGAS_COUNT(M, GRID)                                                                                          \
     do {                                                                                                              \
         if (split)                                                                                                    \
             TIGAS_LAUNCH((k_bucket_count<M, true>), dim3(GRID), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews,    \
-                         nseg, seg_len, zl);                                                                          \
+                         nseg, seg_len, split, zl);                                                                          \
         else                                                                                                          \
             TIGAS_LAUNCH((k_bucket_count<M, false>), dim3(GRID), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews,   \
-                         nseg, seg_len, zl);                                                                          \
+                         nseg, seg_len, split, zl);                                                                          \
     } while (0)
     if (nseg <= BUCKET_FORM_SEGMENTS) {
         TIGAS_COUNT(FORM, std::max(nseg, 1u));
@@ -3498,7 +3501,7 @@ void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* v
     }
 #undef TIGAS_COUNT
     TIGAS_LAUNCH(k_bucket_scan, dim3(nchunks + 1), dim3(1024), st, b, views_dev, nviews, nseg, nchunks, cnt, cap,
-                 flag_wide, crowd, nunits);
+                 flag_wide, flag_crowd, nunits);
     if (nseg == 0) return;
     if (split)
         TIGAS_LAUNCH(k_bucket_scatter<true>, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,

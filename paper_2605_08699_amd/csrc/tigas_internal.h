@@ -32,12 +32,15 @@ constexpr int BUCKET_SAMPLES = 16384;
 constexpr int BUCKET_BINS = 2048;
 constexpr int BUCKET_CDF_WORDS = BUCKET_BINS + 8;  // cumulative counts, smallest and largest sample, shift, scale
 constexpr int BUCKET_SORT_CAP = 4096;
-// A frame with more elements in one bucket (most Gaussians of a view at nearly
-// one depth) takes the radix passes: one workgroup sorts a bucket, at about
-// 10 us per 1000 elements of one depth (200k of them at 960x540: 235 us a frame
-// by the radix passes, 2.0 ms in one bucket), and 16384 are a tenfold share of
-// the 1024 to 2048 that a bucket gets.
-constexpr uint32_t BUCKET_CROWD = 16384;
+// A bucket with more than CROWD_SHARES times its share of a view's records (and
+// over BUCKET_SORT_CAP) is crowded: the frame is rendered again with the buckets of
+// views that have one parted by order statistics, from SPLIT_SHARES of the samples
+// on (fewer, as samples scatter).  Where there is no second attempt, the samples
+// tell from CROWD_SHARES on.  200k Gaussians at 960x540, 5500 / 7000 / 12000 of them at one
+// depth (3.5, 4.5 and 7.7 shares of 1564): 197 / 224 / 281 us a frame by depth
+// ranges, about 163 / 152 / 152 by order statistics, which cost 12 us to form; 150k over
+// 40 depths (3.2 shares of 1172 each, which a workgroup sorts fast) 124 and 147.
+constexpr uint32_t CROWD_SHARES = 4, SPLIT_SHARES = 2;
 constexpr int COL_CHUNK = 32;  // columns per workgroup of a column scan
 // A list is divided into at most 4 x 4 cells of whole 8x8 blocks: log2 of a
 // cell's side for that of the list's.  An entry's word holds the cells that its
@@ -104,11 +107,14 @@ struct ViewParams {
     uint32_t tchunk_base;  // tile placement: chunks of TILE_CHUNK tiles of the views before
 };
 
+// Why a frame has to be rendered again: more entries than the buffers hold; depth
+// keys that span too much, or crowd in one bucket (only where the caller asked).
+constexpr uint32_t FLAG_FULL = 1, FLAG_WIDE = 2, FLAG_CROWDED = 4;
 struct FrameCounters {  // as the caller sees them
     uint32_t D;         // duplicates (clamped to 2^32-1)
     uint32_t visible;
     uint32_t fallbacks;
-    uint32_t overflow;  // D exceeded the duplicate capacity: nothing was emitted
+    uint32_t overflow;  // FLAG_*: nothing was emitted
     uint32_t fb_list;   // append cursor of the FP64-fallback list (cleared once counted)
     uint32_t fb_listed; // entries in the FP64-fallback list this frame
 };
@@ -252,15 +258,16 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 // depths in record order (views of at most 256 x 256 tiles).  The same
 // launches set the frame's counters, clear zl and recompute, in FP64, the
 // conic of every Gaussian preprocess listed as near-singular.  flag_wide: a
-// frame whose depth keys span 2^27 or more sets overflow bit 1 and is left
-// unsorted (the caller renders it again with the four-pass radix sort), and so
-// is one with over `crowd` elements in a bucket.  split: views whose samples crowd
-// are parted so that no bucket is long.
+// frame whose depth keys span 2^27 or more is flagged and left unsorted (the
+// caller renders it again with the four-pass radix sort); flag_crowd: so is one with
+// a crowded bucket (the caller renders it again with split).  split (0: off): views
+// with more than this many shares of the samples in a bucket are parted so that
+// no bucket is long.
 // seg_len: records per segment; nseg, nchunks: segments and bucket chunks of
 // all views; nunits: of the tile placement that follows.
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
-                        bool flag_wide, uint32_t crowd, bool split, uint32_t nunits, uint32_t* val, uint32_t* ext,
+                        bool flag_wide, bool flag_crowd, uint32_t split, uint32_t nunits, uint32_t* val, uint32_t* ext,
                         bool cells, hipStream_t st);
 // Runs LSD passes over the count selected by `which` (0 duplicates, 1 visible)
 // starting in buffer `start`; returns the buffer index holding the result.

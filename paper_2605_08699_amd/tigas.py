@@ -305,8 +305,8 @@ class Context:
         _check(lib().tigas_set_tile_culling(self.handle, int(bool(enable))))
 
     def set_depth_passes(self, passes: int):
-        """Depth sort in three 9-bit passes with a four-pass fallback for
-        frames too deep (3, the default) or always four 8-bit passes (4);
+        """Depth order in buckets, with another form for frames that do not suit
+        them (3, the default), or always by four 8-bit radix passes (4);
         identical frames either way."""
         _check(lib().tigas_set_depth_passes(self.handle, int(passes)))
 

@@ -291,6 +291,83 @@ def test_frame_of_one_depth_takes_about_as_long_as_any_other(ctx):
     assert max(us["equal"], us["steps"]) < 4 * us["spread"]
 
 
+def test_a_frame_that_needs_another_depth_order_changes_only_its_own_scene():
+    """After a crowded frame and a too deep one, frames of other scenes, alone
+    and in a batch with those, are in buckets and placed by counting as before;
+    the two scenes' own next frames are rendered once; a new request for three
+    passes starts afresh."""
+    W, H = 160, 112
+    k = intr(150.0, W / 2, H / 2)
+    rng = np.random.default_rng(8)
+    z = np.exp(rng.uniform(math.log(0.5), math.log(2e7), 600))
+    deep = make_scene(np.column_stack([rng.uniform(-0.3, 0.3, 600) * z, rng.uniform(-0.2, 0.2, 600) * z, z]),
+                      np.repeat(np.log(0.02 * z)[:, None], 3, axis=1), None, rng.normal(1.0, 1.0, 600),
+                      rng.uniform(0.0, 1.0, (600, 3)))
+    c = tigas.Context(0)
+
+    def render(*scenes):
+        n = len(scenes)
+        out = c.render_batch(scenes, [eye_pose()] * n, [k] * n, [W] * n, [H] * n, fmt="f32", tile=(16, 16)) \
+            if n > 1 else [c.render(scenes[0], eye_pose(), k, W, H, fmt="f32", tile=(16, 16))]
+        st = c.stats()
+        return out, (st["rerenders"], st["sort_passes"])
+
+    try:
+        plain, flat, far = (c.load_scene(x) for x in (_depth_scene("spread", 6000), _depth_scene("equal", 20_000), deep))
+        own = {}
+        for s, first, later in ((plain, (0, 4), (0, 4)), (flat, (1, 4), (0, 4)), (far, (1, 5), (0, 5))):
+            (own[s],), how = render(s)
+            assert how == first
+            (again,), how = render(s)
+            assert how == later
+            np.testing.assert_array_equal(again, own[s])
+        assert render(plain)[1] == (0, 4)
+        for batch in ((plain, plain), (plain, flat), (flat, far, plain)):
+            got, how = render(*batch)
+            assert how == (0, 4), how
+            for s, img in zip(batch, got):
+                np.testing.assert_array_equal(img, own[s])
+        c.set_depth_passes(4)
+        for s in (plain, flat, far):
+            (ref,), how = render(s)
+            assert how == (0, 5)
+            np.testing.assert_array_equal(ref, own[s])
+        c.set_depth_passes(3)
+        assert render(flat)[1] == (1, 4) and render(far)[1] == (1, 5) and render(plain)[1] == (0, 4)
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("n,views", [(2_100_000, 1), (180_000, 48)])
+def test_crowded_depths_of_large_plans(n, views):
+    """Crowded depths in a view of 2048 buckets, of whose samples every second is
+    sorted, and in 528 segments, which read the views' order statistics: the
+    frames of the four-pass radix sort."""
+    scene = _depth_scene("steps", n)
+    W, H = (640, 400) if views == 1 else (66, 60)
+    k = intr(600.0 if views == 1 else 40.0, W / 2, H / 2)
+    poses = [eye_pose((0.01 * i, 0.0, -0.02 * i)) for i in range(views)]
+    _say("crowded large plan", n, views)
+    c = tigas.Context(0)
+    try:
+        s = c.load_scene(scene)
+        for attempt in range(2):  # flagged and rendered again, then at once
+            got = c.render_batch([s] * views, poses, [k] * views, [W] * views, [H] * views, fmt="f32", tile=(16, 16)) \
+                if views > 1 else [c.render(s, poses[0], k, W, H, fmt="f32", tile=(16, 16))]
+            st = c.stats()
+            assert (st["rerenders"], st["sort_passes"]) == (1 - attempt, 4)
+            if attempt == 0:
+                first = got
+        c.set_depth_passes(4)
+        for i in (0, views // 2, views - 1):
+            want = c.render(s, poses[i], k, W, H, fmt="f32", tile=(16, 16))
+            assert want.any()
+            np.testing.assert_array_equal(first[i], want)
+            np.testing.assert_array_equal(got[i], want)
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("kind", ["equal", "deep"])
 def test_batch_that_needs_another_depth_order_and_more_room(kind):
     """Views whose first attempt fits in shared lists but is rendered again
