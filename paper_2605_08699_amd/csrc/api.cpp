@@ -340,12 +340,12 @@ struct Workspace {
     DevBuf key[2], val[2], ext[2];
     DevBuf hist;
     DevBuf vmask, sample;        // per 64 records
-    DevBuf bkt_rows, bkt_small;  // bucketed depth sort: counts, everything else
+    DevBuf bkt_small;            // bucketed depth sort, but for its elements and counts
     // emission-order copies for the inspection entry point
     DevBuf dbg_key, dbg_val, dbg_ext;
     // per tile / per view
     DevBuf ranges;
-    DevBuf tile_rows, tile_small;  // tile placement: counts, everything else
+    DevBuf tile_rows, tile_small;  // tile placement: counts that `key` has no room for; everything else
     DevBuf frame_staging;
     static constexpr int NSLOT = 2;
     FrameSlot slot[NSLOT];
@@ -724,9 +724,10 @@ void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
         }
     }
     // units of the tile placement: each has a row of the largest view's tiles
-    // (at most 256 MB of them), and costs a pass over it
+    // (at most 256 MB of them: 1024 rows of the 65536 that it takes at most), and
+    // costs a pass over it
     const uint64_t want = std::min<uint64_t>(TILE_UNITS_MAX, (uint64_t)TILE_UNITS * plan.views.size());
-    plan.nunits = (uint32_t)std::max<uint64_t>(256, std::min<uint64_t>(want, (64u << 20) / std::max(plan.max_tiles, 1u)));
+    plan.nunits = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, (64u << 20) / std::max(plan.max_tiles, 1u)));
 }
 
 // Lays out the bucketed depth sort of a plan: each view's records in segments
@@ -756,11 +757,11 @@ void set_buckets(Plan& plan) {
 }
 
 // Lays the bucketed depth sort's scratch, except the element array, out from
-// `rows` and `small` (null: only the sizes).
-BucketMem carve_buckets(const Plan& plan, void* rows, void* small, size_t* rows_bytes, size_t* small_bytes) {
+// `rows` and `small` (null: only
+// the size of `small`).
+BucketMem carve_buckets(const Plan& plan, void* rows, void* small, size_t* small_bytes) {
     BucketMem b{};
     b.rows = static_cast<uint32_t*>(rows);
-    *rows_bytes = std::max<size_t>(plan.row_words, 1) * 4;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char* p = small ? static_cast<char*>(small) + off : nullptr;
@@ -808,14 +809,13 @@ std::string shape_key(const Plan& plan, bool with_tiles) {
 }
 
 // Lays the tile placement's scratch out from `rows` and `small` (null: only
-// the sizes).
-TileMem carve_tiles(const Plan& plan, void* rows, void* small, size_t* rows_bytes, size_t* small_bytes) {
+// the size of `small`).
+TileMem carve_tiles(const Plan& plan, void* rows, void* small, size_t* small_bytes) {
     TileMem m{};
     m.nunits = plan.nunits;
     m.stride = std::max(plan.max_tiles, 1u);
     m.rows = static_cast<uint32_t*>(rows);
     const size_t units = (size_t)plan.nunits + plan.views.size();
-    *rows_bytes = units * m.stride * 4;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char* p = small ? static_cast<char*>(small) + off : nullptr;
@@ -828,50 +828,6 @@ TileMem carve_tiles(const Plan& plan, void* rows, void* small, size_t* rows_byte
     m.chunk = reinterpret_cast<uint32_t*>(take((size_t)plan.tchunks * 4));
     *small_bytes = std::max<size_t>(off, 256);
     return m;
-}
-
-// The plan's frame memory in the workspace's active slot.
-FrameMem frame_mem(Workspace& ws, const Plan& plan) {
-    FrameMem m = ws.mem();
-    size_t rb, sb;
-    m.bk = carve_buckets(plan, ws.bkt_rows.p, ws.bkt_small.p, &rb, &sb);
-    // 16 bytes for each visible record
-    m.bk.elem = ws.key[0].as<uint4>();
-    m.tm = carve_tiles(plan, ws.tile_rows.p, ws.tile_small.p, &rb, &sb);
-    return m;
-}
-
-void prepare(Workspace& ws, Plan& plan, bool debug) {
-    set_buckets(plan);
-    if (ws.counters.ensure(sizeof(Counters))) {
-        // the FP64-list count is cleared by each frame after use; start at zero
-        HIPCHK(hipMemset(ws.counters.p, 0, sizeof(Counters)));
-        ++ws.gen;
-    }
-    ws.ensure_views((int)plan.views.size());
-    ws.ensure_records(plan.nrec);
-    ws.ensure_tiles(plan.n_tiles);
-    // never below 4x the record count: the depth passes keep the visible
-    // Gaussians in the same buffers
-    uint64_t est = std::max<uint64_t>((uint64_t)ws.last_D + ws.last_D / 4, (uint64_t)plan.nrec * 4);
-    est = std::max<uint64_t>(est, 1u << 20);
-    ws.ensure_dups((uint32_t)std::min<uint64_t>(est, 0xfff00000ull));
-    ws.grow(ws.key[0], (size_t)plan.nrec * 16);  // the bucketed sort's elements, also beyond the cap above
-    {
-        size_t rb, sb;
-        (void)carve_buckets(plan, nullptr, nullptr, &rb, &sb);
-        ws.grow(ws.bkt_rows, rb);
-        ws.grow(ws.bkt_small, sb);
-        (void)carve_tiles(plan, nullptr, nullptr, &rb, &sb);
-        ws.grow(ws.tile_rows, rb);
-        ws.grow(ws.tile_small, sb);
-    }
-    if (debug) {
-        const size_t bytes = (size_t)ws.dup_cap * 4;
-        ws.dbg_key.ensure(bytes);
-        ws.dbg_val.ensure(bytes);
-        ws.dbg_ext.ensure(bytes);
-    }
 }
 
 // Enqueue the whole launch sequence of a plan on ws.stream (no allocation, no
@@ -893,8 +849,72 @@ bool share_lists(const Plan& plan) {
     return opt.bin && !opt.cull_tiles && (opt.buckets || plan.views.size() == 1);
 }
 
-// Whether the plan's tile digit is placed by counting.
+// Whether the plan's tile digit is placed by counting, and its depth order formed
+// in buckets.
 bool use_bin(const Plan& plan) { return share_lists(plan) && packed_rects(plan); }
+bool use_buckets(const Plan& plan) { return plan.opt.buckets && packed_rects(plan); }
+
+size_t bucket_row_bytes(const Plan& plan) { return std::max<size_t>(plan.row_words, 1) * 4; }
+size_t tile_row_bytes(const Plan& plan) {
+    return ((size_t)plan.nunits + plan.views.size()) * std::max(plan.max_tiles, 1u) * 4;
+}
+
+// Whether the placement's counts lie in key[1]: that holds tile words, which the
+// placement by counting writes only for inspection.
+bool tile_rows_in_key(const Workspace& ws, const Plan& plan, bool debug) {
+    return !debug && tile_row_bytes(plan) <= ws.key[1].bytes;
+}
+
+// The plan's frame memory in the workspace's active slot.
+FrameMem frame_mem(Workspace& ws, const Plan& plan, bool debug) {
+    FrameMem m = ws.mem();
+    size_t sb;
+    if (use_buckets(plan)) {
+        // the counts in ext[1], which is written after the last of them was read
+        m.bk = carve_buckets(plan, ws.ext[1].p, ws.bkt_small.p, &sb);
+        // 16 bytes for each visible record
+        m.bk.elem = ws.key[0].as<uint4>();
+    }
+    if (use_bin(plan))
+        m.tm = carve_tiles(plan, tile_rows_in_key(ws, plan, debug) ? ws.key[1].p : ws.tile_rows.p, ws.tile_small.p, &sb);
+    return m;
+}
+
+void prepare(Workspace& ws, Plan& plan, bool debug) {
+    set_buckets(plan);
+    if (ws.counters.ensure(sizeof(Counters))) {
+        // the FP64-list count is cleared by each frame after use; start at zero
+        HIPCHK(hipMemset(ws.counters.p, 0, sizeof(Counters)));
+        ++ws.gen;
+    }
+    ws.ensure_views((int)plan.views.size());
+    ws.ensure_records(plan.nrec);
+    ws.ensure_tiles(plan.n_tiles);
+    // never below 4x the record count: the depth passes keep the visible
+    // Gaussians in the same buffers
+    uint64_t est = std::max<uint64_t>((uint64_t)ws.last_D + ws.last_D / 4, (uint64_t)plan.nrec * 4);
+    est = std::max<uint64_t>(est, 1u << 20);
+    ws.ensure_dups((uint32_t)std::min<uint64_t>(est, 0xfff00000ull));
+    ws.grow(ws.key[0], (size_t)plan.nrec * 16);  // the bucketed sort's elements, also beyond the cap above
+    size_t sb;
+    if (use_buckets(plan)) {
+        // (less than a word per record: segments of 4096 records and more, buckets of 1024)
+        if (bucket_row_bytes(plan) > ws.ext[1].bytes) fail(TIGAS_E_DEVICE, "bucket counts exceed their buffer");
+        (void)carve_buckets(plan, nullptr, nullptr, &sb);
+        ws.grow(ws.bkt_small, sb);
+    }
+    if (use_bin(plan)) {
+        (void)carve_tiles(plan, nullptr, nullptr, &sb);
+        ws.grow(ws.tile_small, sb);
+        if (!tile_rows_in_key(ws, plan, debug)) ws.grow(ws.tile_rows, tile_row_bytes(plan));
+    }
+    if (debug) {
+        const size_t bytes = (size_t)ws.dup_cap * 4;
+        ws.dbg_key.ensure(bytes);
+        ws.dbg_val.ensure(bytes);
+        ws.dbg_ext.ensure(bytes);
+    }
+}
 
 // Lays a plan out for a tile configuration by the context's switches and by what
 // earlier frames of its scenes, or an attempt of its own, were found to be.  A
@@ -943,8 +963,6 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     ZeroList zl{};
     zl.p[0] = reinterpret_cast<uint32_t*>(m.ranges);
     zl.n[0] = 2 * plan.n_tiles;
-    zl.p[1] = reinterpret_cast<uint32_t*>(m.bk.ccost);
-    zl.n[1] = 2 * plan.nchunks;
     SortBuffers sb;
     for (int i = 0; i < 2; ++i) {
         sb.key[i] = m.key[i];
@@ -961,8 +979,10 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     const bool bin = use_bin(plan);
     const bool cells = bin && opt.buckets && !debug && plan.views[0].cells;  // in the entries
     int cv = 0;
-    if (opt.buckets && packed) {
+    if (use_buckets(plan)) {
         mark(2);
+        zl.p[1] = reinterpret_cast<uint32_t*>(m.bk.ccost);
+        zl.n[1] = 2 * plan.nchunks;
         zl.p[2] = &cnt->overflow;
         zl.n[2] = 1;
         // (an inspection shows the bucketed order however long it takes)
@@ -1019,7 +1039,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
 }
 
 // Depth passes of a plan's frames, as the statistics count them.
-int depth_passes(const Plan& plan) { return plan.opt.buckets && packed_rects(plan) ? 3 : 4; }
+int depth_passes(const Plan& plan) { return use_buckets(plan) ? 3 : 4; }
 
 // Launch the plan once: from a captured graph when allowed (captured on the
 // first use of its shape, re-captured after any workspace reallocation), else
@@ -1035,9 +1055,9 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
     if (kprof) {
         ws.ktimer.reset();
         TimerScope ts(&ws.ktimer);
-        return enqueue(frame_mem(ws, plan), plan, debug, prof, work);
+        return enqueue(frame_mem(ws, plan, debug), plan, debug, prof, work);
     }
-    if (!graph) return enqueue(frame_mem(ws, plan), plan, debug, prof, work);
+    if (!graph) return enqueue(frame_mem(ws, plan, debug), plan, debug, prof, work);
     const std::string key = shape_key(plan, true) + (opt.cull ? "c1" : "c0") + (opt.bin ? "b1" : "b0") + (opt.cull_tiles ? "t1" : "t0") +
                             (opt.buckets ? "d3" : "d4") + (opt.split ? "s1" : "s0") + (ws.active ? "f1" : "f0");
     GraphEntry& g = ws.graphs[key];
@@ -1052,7 +1072,7 @@ int launch_plan(tigas_context* ctx, Workspace& ws, const Plan& plan, bool debug,
         HIPCHK(hipStreamBeginCapture(ws.stream, hipStreamCaptureModeThreadLocal));
         int cur = 0;
         try {
-            cur = enqueue(frame_mem(ws, plan), plan, debug, prof, work);
+            cur = enqueue(frame_mem(ws, plan, debug), plan, debug, prof, work);
         } catch (...) {
             (void)hipStreamEndCapture(ws.stream, &graph_t);
             if (graph_t) (void)hipGraphDestroy(graph_t);
@@ -1493,7 +1513,7 @@ struct Carver {
 
 // Lays out a single-view launch sequence of nrec records and n_tiles tiles
 // in the scratch array; the duplicate buffers take what is left.
-FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_out, hipStream_t st) {
+FrameMem carve_scratch(void* scratch_dev, Plan& plan, FrameCounters* cnt_out, hipStream_t st) {
     const uint32_t nrec = plan.nrec, n_tiles = plan.n_tiles;
     Carver c{static_cast<char*>(scratch_dev), (size_t)TIGAS_NOALLOC_SCRATCH_BYTES};
     FrameMem m;
@@ -1527,23 +1547,19 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_o
     o.cnt = m.cnt;
     m.ranges = c.take<uint2>((size_t)std::max<uint32_t>(n_tiles, 1) * 8);
     m.order = c.take<uint32_t>((size_t)std::max<uint32_t>(n_tiles, 1) * 4);
-    size_t tr, ts;
-    (void)carve_tiles(plan, nullptr, nullptr, &tr, &ts);
-    char* tile_rows = c.take<char>(tr);
-    char* tile_small = c.take<char>(ts);
-    m.tm = carve_tiles(plan, tile_rows, tile_small, &tr, &ts);
+    size_t small_bytes = 0;
+    if (use_bin(plan)) (void)carve_tiles(plan, nullptr, nullptr, &small_bytes);
+    char* tile_small = c.take<char>(small_bytes);
     // sort passes over at most 16M keys use at most 1024 segments; the
     // bucketed sort, which runs instead of them, has its scratch in the same place
-    size_t rows_bytes, small_bytes;
-    (void)carve_buckets(plan, nullptr, nullptr, &rows_bytes, &small_bytes);
-    rows_bytes = (rows_bytes + 255) / 256 * 256;
+    (void)carve_buckets(plan, nullptr, nullptr, &small_bytes);
+    const size_t rows_bytes = (bucket_row_bytes(plan) + 255) / 256 * 256;
     const size_t mask_bytes = ((size_t)nrec / 64 * 8 + 255) / 256 * 256;
     const size_t bkt_bytes = rows_bytes + small_bytes + mask_bytes + (size_t)nrec / 64 * 4;
     char* hist = c.take<char>(std::max((size_t)256 * 1024 * 4, bkt_bytes));
     m.hist = reinterpret_cast<uint32_t*>(hist);
     m.hist_tot = c.take<uint32_t>((size_t)512 * 4);
-    m.bk = carve_buckets(plan, hist, hist + rows_bytes, &rows_bytes, &small_bytes);
-    rows_bytes = (rows_bytes + 255) / 256 * 256;
+    m.bk = carve_buckets(plan, hist, hist + rows_bytes, &small_bytes);
     o.vmask = reinterpret_cast<unsigned long long*>(hist + rows_bytes + small_bytes);
     o.sample = reinterpret_cast<uint32_t*>(hist + rows_bytes + small_bytes + mask_bytes);
     m.retry = false;  // no second attempt here
@@ -1560,6 +1576,13 @@ FrameMem carve_scratch(void* scratch_dev, const Plan& plan, FrameCounters* cnt_o
     for (uint32_t** p : {&m.key[0], &m.key[1], &m.val[1], &m.ext[1], &m.val[0], &m.ext[0]})
         *p = c.take<uint32_t>(dup_cap * 4);
     m.bk.elem = reinterpret_cast<uint4*>(m.key[0]);
+    // the placement's counts where the keys and the elements were
+    if (use_bin(plan)) {
+        const uint64_t rows = 2 * dup_cap / std::max(plan.max_tiles, 1u);
+        if (rows < 2) fail(TIGAS_E_INVALID, "too many tiles for the allocation-free render of this scene");
+        plan.nunits = (uint32_t)std::min<uint64_t>(plan.nunits, rows - 1);
+        m.tm = carve_tiles(plan, m.key[0], tile_small, &small_bytes);
+    }
     if (c.off > c.cap) fail(TIGAS_E_DEVICE, "scratch layout exceeds the array");
     m.dup_cap = (uint32_t)dup_cap;
     return m;
@@ -1589,7 +1612,7 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     plan.opt.buckets = !ctx->depth4.load();
     plan.opt.split = CROWD_SHARES;
     set_buckets(plan);
-    // fewer units than with a workspace: their rows come out of the array
+    // fewer units than with a workspace: a row of each in the array
     plan.nunits = std::min<uint32_t>(plan.nunits, (plan.nrec + 2047) / 2048 + 20);
     const hipStream_t st = pick_stream(ctx, hip_stream);
     const FrameMem m =

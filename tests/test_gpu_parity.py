@@ -561,6 +561,34 @@ def test_shared_lists_with_four_depth_passes(ctx, size, tile):
     s.free()
 
 
+@pytest.mark.parametrize("how", ["culled", "radix", "counted"])
+def test_scratch_of_the_placement_is_kept_only_where_it_is_used(how):
+    """A large frame of small tiles: its buffers take what its records, its 2^20
+    entries (six words each) and its tiles need, not a row of all tiles per unit
+    (1 MB a row for 512 x 512 tiles) where the lists are not placed by counting,
+    nor beside the keys where they are."""
+    import torch
+    W = H = 4096
+    out = torch.zeros((H, W, 3), dtype=torch.uint8, device="cuda")
+    c = tigas.Context(0)
+    try:
+        s = c.load_scene(_rect_scene("small", 6000))
+        c.set_tile_culling(how == "culled")
+        c.set_tile_binning(how != "radix")
+        tile = (16, 32) if how == "counted" else (8, 8)
+        k = intr(W / 2.0, W / 2, H / 2)
+        c.render(s, eye_pose(), intr(20.0, 16, 16), 32, 32, tile=(8, 8))  # the kernels are loaded
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        c.render(s, eye_pose(), k, W, H, out=out, tile=tile)
+        torch.cuda.synchronize()
+        used = before - torch.cuda.mem_get_info()[0]
+        _say("placement scratch", how, used >> 20, "MiB")
+        assert out.any() and used < 64 << 20
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("kind", ["small", "mixed", "stack"])
 @pytest.mark.parametrize("size", [(320, 320), (317, 331), (448, 448), (451, 449)])
 def test_blend_by_quarters_halves_and_whole_blocks(ctx, size, kind):
