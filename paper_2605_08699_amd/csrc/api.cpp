@@ -123,6 +123,8 @@ struct HostPinned {
     }
 };
 
+constexpr uint32_t MIN_DUPS = 1u << 20;  // entries that the duplicate buffers hold at least
+
 uint32_t round_up(uint64_t x, uint64_t m) { return (uint32_t)((x + m - 1) / m * m); }
 
 int ceil_log2(uint64_t x) {
@@ -361,6 +363,7 @@ struct Workspace {
     EventTimer ktimer;      // per-launch events when kernel timing is on
     uint32_t rec_cap = 0, dup_cap = 0, tile_cap = 0;
     uint32_t last_D = 0;
+    bool reserved = false;  // for a server's budget: the placement has the units that fit in `key`
     uint64_t gen = 1;  // bumped whenever a buffer is reallocated (captured graphs hold its pointers)
     std::map<std::string, GraphEntry> graphs;
 
@@ -893,7 +896,7 @@ void prepare(Workspace& ws, Plan& plan, bool debug) {
     // never below 4x the record count: the depth passes keep the visible
     // Gaussians in the same buffers
     uint64_t est = std::max<uint64_t>((uint64_t)ws.last_D + ws.last_D / 4, (uint64_t)plan.nrec * 4);
-    est = std::max<uint64_t>(est, 1u << 20);
+    est = std::max<uint64_t>(est, MIN_DUPS);
     ws.ensure_dups((uint32_t)std::min<uint64_t>(est, 0xfff00000ull));
     ws.grow(ws.key[0], (size_t)plan.nrec * 16);  // the bucketed sort's elements, also beyond the cap above
     size_t sb;
@@ -904,6 +907,9 @@ void prepare(Workspace& ws, Plan& plan, bool debug) {
         ws.grow(ws.bkt_small, sb);
     }
     if (use_bin(plan)) {
+        const uint64_t rows = ws.key[1].bytes / 4 / std::max(plan.max_tiles, 1u);
+        if (ws.reserved && rows > plan.views.size())
+            plan.nunits = (uint32_t)std::min<uint64_t>(plan.nunits, rows - plan.views.size());
         (void)carve_tiles(plan, nullptr, nullptr, &sb);
         ws.grow(ws.tile_small, sb);
         if (!tile_rows_in_key(ws, plan, debug)) ws.grow(ws.tile_rows, tile_row_bytes(plan));
@@ -2711,9 +2717,20 @@ tigas_status tigas_server_create(tigas_context* ctx, const tigas_server_config* 
                 std::lock_guard<std::mutex> lk(ws.mu);
                 ws.counters.ensure(sizeof(Counters));
                 ws.ensure_records((uint32_t)std::min<uint64_t>(recs, 0x7f000000ull));
-                ws.ensure_dups((uint32_t)std::min<uint64_t>(recs * 5, 0xfff00000ull));
+                // (no fewer than a frame asks for)
+                ws.ensure_dups((uint32_t)std::min<uint64_t>(std::max<uint64_t>(recs * 5, MIN_DUPS), 0xfff00000ull));
                 ws.ensure_views(sv->cfg.max_batch);
-                ws.ensure_tiles((uint32_t)std::min<uint64_t>((uint64_t)sv->cfg.max_batch * 16384, 1u << 26));
+                const uint64_t nv = (uint64_t)sv->cfg.max_batch, tiles = std::min<uint64_t>(nv * 16384, 1u << 26);
+                ws.ensure_tiles((uint32_t)tiles);
+                // the scratch besides the rows of counts, which lie in the
+                // buffers above, at most: a view has 32 buckets or one per 1024
+                // records, a segment or one per 4096, and each array is rounded
+                // up to 256 bytes
+                const uint64_t bkts = nv * 32 + recs / BUCKET_RECORDS, segs = nv + recs / 4096;
+                ws.grow(ws.bkt_small, nv * (sizeof(ViewCount) + BUCKET_CDF_WORDS * 4) + bkts * 13 + segs * sizeof(SegTotals) +
+                                          8 * 256);
+                ws.grow(ws.tile_small, (std::min<uint64_t>(TILE_UNITS_MAX, nv * TILE_UNITS) + nv) * 8 + tiles * 9 + 4 * 256);
+                ws.reserved = true;
             }
         }
         for (auto& sl : sv->slots) sl->th = std::thread(slot_main, sv.get(), sl.get());

@@ -146,6 +146,50 @@ def test_small_budget_defers_requests_but_renders_them_all(ctx, scenes):
         np.testing.assert_array_equal(outs[i], _alone(ctx, meta[i]), err_msg=f"request {i}")
 
 
+@pytest.mark.parametrize("budget_mb,max_batch", [(128, 4), (1024, 32)])
+def test_serving_within_a_budget_allocates_nothing(ctx, scenes, budget_mb, max_batch):
+    """With a budget the slots' workspaces are whole from the start: mixed
+    scenes, sizes and batches leave the free device memory as it was."""
+    W2, H2 = 1920, 1080
+    k = synth.fov_intrinsics(W2, H2)
+    traj = synth.trajectory(seed=26, n_poses=96)
+    rng = np.random.default_rng(26)
+    reqs, outs, meta = [], [], []
+    if budget_mb < 512:  # of the others, few Gaussians in many tiles raise the admission's estimate for all
+        scenes = scenes[:1]
+    for i in range(96):
+        rung = float(rng.choice(synth.RUNG_SCALES))
+        ow, oh = tigas.output_size(W2, H2, rung)
+        sc = scenes[int(rng.integers(0, len(scenes)))]
+        outs.append(torch.zeros((oh, ow, 3), dtype=torch.uint8, device="cuda"))
+        reqs.append(tigas.request_c(sc, traj[i], k, W2, H2, outs[-1], client=i, res_scale=rung))
+        meta.append((sc, traj[i], rung))
+
+    def serve(sv, some):
+        for r in some:
+            sv.submit(r)
+        sv.drain()
+        done = sv.poll()
+        assert len(done) == len(some) and all(d["status"] == 0 for d in done)
+
+    with tigas.Server(ctx, slots=2, max_batch=max_batch) as sv:  # every kernel of the load is loaded
+        serve(sv, reqs)
+    with tigas.Server(ctx, slots=2, max_batch=max_batch, hbm_budget=budget_mb << 20) as sv:
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        for some in (reqs[:1], reqs[1:8], reqs):
+            serve(sv, some)
+        torch.cuda.synchronize()
+        after = torch.cuda.mem_get_info()[0]
+        st = sv.stats()
+    _say("budget", budget_mb, "MiB:", (before - after) >> 10, "KiB more in use", st)
+    assert st["max_batch_seen"] > 1 and after == before
+    for i in (0, 1, 50, 95):
+        sc, pose, rung = meta[i]
+        want = ctx.render(sc, pose, k, W2, H2, res_scale=rung, tile=(16, 32))
+        np.testing.assert_array_equal(outs[i].cpu().numpy(), want)
+
+
 def test_request_over_the_whole_budget_is_refused(ctx, scenes):
     reqs, outs, meta = _requests(scenes[:1], 1, seed=23)
     with tigas.Server(ctx, slots=1, hbm_budget=1 << 20) as sv:
