@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
@@ -22,6 +23,28 @@ FLAGS = [
 ]
 
 
+# the compiler's report of each kernel's registers, spills and scratch memory
+REPORT = ["-Rpass-analysis=kernel-resource-usage"]
+
+
+def spilling_kernels(report: str):
+    """(kernel, scratch bytes a lane, spilled vector registers) of every kernel
+    in the compiler's report that has either, and the number of kernels in it.
+
+    No kernel may: a vector register spilled ahead of the point where the lanes
+    of a divergent block rejoin was lost for the other lanes, and pixels were
+    wrong.  (Scalar registers spill to lanes of a vector register, whatever lanes
+    are active.)"""
+    bad, n = [], 0
+    for part in re.split(r"remark:\s+Function Name: ", report)[1:]:
+        n += 1
+        scratch, spilled = (int(re.search(what + r"\D*: (\d+)", part).group(1))
+                            for what in (r"ScratchSize \[bytes/lane\]", r"VGPRs Spill"))
+        if scratch or spilled:
+            bad.append((part.split()[0], scratch, spilled))
+    return bad, n
+
+
 def build(verbose: bool = False) -> str:
     objs = []
     for src in SOURCES:
@@ -31,7 +54,19 @@ def build(verbose: bool = False) -> str:
             cmd[1:1] = ["-x", "hip"]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd, stderr=subprocess.STDOUT if verbose else None)
+        if src.endswith(".hip"):
+            cmd[1:1] = REPORT
+        r = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+        if r.returncode or verbose:
+            print(r.stderr, file=sys.stderr, flush=True)
+        else:  # without the report, and without the host pass's note on the feature flag
+            print(*(x for x in r.stderr.splitlines() if "warning:" in x), sep="\n", end="", file=sys.stderr, flush=True)
+        r.check_returncode()
+        if src.endswith(".hip"):
+            bad, n = spilling_kernels(r.stderr)
+            if bad or n == 0:
+                raise RuntimeError(f"{src}: kernels with spills or scratch memory: {bad}" if bad
+                                   else f"{src}: no kernel in the compiler's report")
         objs.append(obj)
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
