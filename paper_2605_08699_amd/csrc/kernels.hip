@@ -2991,7 +2991,7 @@ __device__ __forceinline__ uint8_t to_u8(float x) {
 struct BlendArgs {
     const ViewParams* views;
     int nviews;
-    uint32_t n_lists;
+    uint32_t n_lists, first;  // lists; the first one of the launch (a multiple of 8)
     int block_log;
     const uint2* ranges;
     const uint32_t* vals;  // the lists: records, or with cells the view's records below masks of cells
@@ -3346,7 +3346,8 @@ template <bool COUNT, int PARTS>
 __global__ __launch_bounds__(64, COUNT ? 1 : 8) void k_blend(BlendArgs A) {
     __shared__ Stage stage;
     constexpr int PL = PARTS / 2;  // log2 of 1, 2, 4
-    const uint32_t part = (blockIdx.x >> 3) & (PARTS - 1), slot = blockIdx.x >> (3 + PL), i = ((slot >> A.block_log) << 3) + (blockIdx.x & 7u);
+    const uint32_t part = (blockIdx.x >> 3) & (PARTS - 1), slot = blockIdx.x >> (3 + PL);
+    const uint32_t i = A.first + ((slot >> A.block_log) << 3) + (blockIdx.x & 7u);
     if (i >= A.n_lists) return;
     const uint32_t list = A.order ? A.order[i] : i, block = slot & ((1u << A.block_log) - 1u);
     const int vi = view_of(list, A.nviews, [&](int k) { return A.views[k].tile_base; });
@@ -3600,13 +3601,20 @@ void launch_blend(const ViewParams* views_dev, const ViewParams* views_host, int
         bl = std::max(bl, v.tw_log + v.lx + v.th_log + v.ly - 6);
         blocks += (uint64_t)((v.width + 7) / 8) * (uint64_t)((v.height + 7) / 8);
     }
-    const BlendArgs A{views_dev, nviews, n_lists, bl, ranges, vals, cells ? 1 : 0, o.rec, nrec, work, cull ? 1 : 0,
-                      order};
-    const dim3 grid(((n_lists + 7) / 8 * 8) << bl);
-    if (work) TIGAS_LAUNCH((k_blend<true, 1>), grid, dim3(64), st, A);
-    else if (blocks <= BLEND_QUARTERS) TIGAS_LAUNCH((k_blend<false, 4>), dim3(grid.x * 4), dim3(64), st, A);
-    else if (blocks <= BLEND_HALVES) TIGAS_LAUNCH((k_blend<false, 2>), dim3(grid.x * 2), dim3(64), st, A);
-    else TIGAS_LAUNCH((k_blend<false, 1>), grid, dim3(64), st, A);
+    BlendArgs A{views_dev, nviews, n_lists, 0, bl, ranges, vals, cells ? 1 : 0, o.rec, nrec, work, cull ? 1 : 0,
+                order};
+    const int pl = work || blocks > BLEND_HALVES ? 0 : blocks > BLEND_QUARTERS ? 1 : 2;
+    // a launch has fewer than 2^32 threads: 2^26 blocks' waves, past which a batch of
+    // 16 frames of 16384x16384 goes, or one of many lists beside a view with lists
+    // of 128 blocks
+    const uint32_t per = 1u << (25 - bl - pl);  // lists a launch at most
+    for (; A.first < n_lists; A.first += per) {
+        const dim3 grid((std::min(per, n_lists - A.first) + 7) / 8 * 8 << (bl + pl));
+        if (work) TIGAS_LAUNCH((k_blend<true, 1>), grid, dim3(64), st, A);
+        else if (pl == 2) TIGAS_LAUNCH((k_blend<false, 4>), grid, dim3(64), st, A);
+        else if (pl == 1) TIGAS_LAUNCH((k_blend<false, 2>), grid, dim3(64), st, A);
+        else TIGAS_LAUNCH((k_blend<false, 1>), grid, dim3(64), st, A);
+    }
 }
 
 void launch_wave_scan_selftest(const uint32_t* in, uint32_t* out, int n, hipStream_t st) {

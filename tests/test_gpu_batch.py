@@ -196,3 +196,37 @@ def test_scene_reloaded_after_free_renders_its_own_data(ctx, c2small):
             assert not np.array_equal(a, b)
     finally:
         fresh.close()
+
+
+def test_batch_of_more_blocks_than_one_launch_has_waves(ctx):
+    """Over 2^26 workgroups of the blend (512 lists of one row of tiles in each of
+    1024 wide views, beside a view whose lists have 128 blocks): every frame is
+    its own."""
+    import math
+
+    import torch
+
+    from tests.handmade import eye_pose, intr, make_scene
+    rng = np.random.default_rng(31)
+    n = 50
+    z = rng.uniform(2.0, 6.0, n)
+    xy = rng.uniform(-0.9, 0.9, (n, 2))
+    scene = make_scene(np.column_stack([xy[:, 0] * z, xy[:, 1] * z, z]), np.full((n, 3), math.log(0.5)), None,
+                       rng.normal(1.0, 1.0, n), rng.uniform(0.0, 1.0, (n, 3)))
+    s = ctx.load_scene(scene)
+    views = 1024
+    sizes = [(8192, 1)] * views + [(4096, 4096)]
+    ks = [intr(4096.0, w / 2, h / 2) for w, h in sizes]
+    poses = [eye_pose((0.001 * i, 0.0003 * i, 0.0)) for i in range(views + 1)]
+    assert (views * 512 + (4096 // 64) * (4096 // 128)) * 128 > 1 << 26
+    _say("blend in two launches")
+    outs = [torch.full((h, w, 3), 9, dtype=torch.uint8, device="cuda") for w, h in sizes]
+    ctx.render_batch([s] * len(sizes), poses, ks, [w for w, _ in sizes], [h for _, h in sizes], tile=(16, 32),
+                     outs=outs)
+    torch.cuda.synchronize()
+    for i in (0, 1, 511, 512, 1000, views - 1, views):
+        w, h = sizes[i]
+        want = ctx.render(s, poses[i], ks[i], w, h, tile=(16, 32))
+        assert want.any()
+        np.testing.assert_array_equal(outs[i].cpu().numpy(), want)
+    s.free()
