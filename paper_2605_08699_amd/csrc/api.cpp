@@ -6,7 +6,8 @@
 // render is a fixed sequence of launches with no host round trip inside it.
 // The duplicate buffers are sized from the previous frame with headroom; if a
 // frame needs more, its duplicate kernel emits nothing, the overflow flag is
-// seen after the frame and the frame is rendered again with larger buffers.
+// seen after the frame and the frame is rendered again with larger buffers (so is
+// a frame whose depths need another order than the buckets of depth ranges).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -680,9 +681,11 @@ int sort_blocks(uint64_t n) {
 // 2048 / 4096 lists a view: 1M/720p 207 / 203 / 205 / 215 / 212 us; 3M/1080p
 // 405 / 391 / 398 / 414 / 450 us; 3M/4K (16 tiles a list at most: 1020 lists)
 // 652 / 644 / 653 / 642 / 671 us; 32 views at 1080p 6.73 / 6.63 / 6.72 / 6.96 /
-// 7.42 ms; 20k/256x256 has 128 tiles, and lists of two cost 1 us.  Tall lists of
-// an even doubling: 32x64 instead of 64x32 costs the counting 2 us less at
-// 3M/1080p.  Frames are the same.
+// 7.42 ms; 20k/256x256 has 128 tiles, and lists of two cost 1 us.  At 1080p that
+// makes lists of 64x64 pixels from every tile shape of 16 and more; where the
+// doublings leave a list of two to one, it is the taller one (at most 1024 lists:
+// 32x64 instead of 64x32 cost the counting 2 us less at 3M/1080p).  Frames are the
+// same.
 void list_scale(ViewParams& v, const TileCfg& tc) {
     v.lx = v.ly = 0;
     auto lists = [&] {
@@ -804,8 +807,7 @@ std::string shape_key(const Plan& plan, bool with_tiles) {
         k += buf;
     }
     if (with_tiles) {
-        std::snprintf(buf, sizeof buf, "t%dx%d:%d:%d:%d:%d", plan.tc.tw, plan.tc.th, plan.tc.bd, plan.tc.ppl,
-                      (int)plan.batch, (int)plan.shared);
+        std::snprintf(buf, sizeof buf, "t%dx%d:%d:%d", plan.tc.tw, plan.tc.th, (int)plan.batch, (int)plan.shared);
         k += buf;
     }
     return k;
@@ -1033,7 +1035,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         cur = launch_sort(sb, tp.data(), (int)tp.size(), /*which=*/0, m.dup_cap, sort_blocks(m.dup_cap), cd, debug,
                           cnt, nullptr, nullptr, st);
         mark(4);
-        launch_ranges(sb.key[cur], cnt, m.dup_cap, m.ranges, m.cnt_out, o, vdev, st);
+        launch_ranges(sb.key[cur], cnt, m.dup_cap, m.ranges, m.cnt_out, st);
         if (nv == 1) launch_tile_order(m.ranges, plan.n_tiles, m.order, st);
         mark(5);
     }

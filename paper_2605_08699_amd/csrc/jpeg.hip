@@ -308,7 +308,7 @@ __global__ __launch_bounds__(JPEG_SEG_THREADS, 6) void k_jpeg_seg(JpegBatch a) {
             total += eob[q] >> 16;
         }
         s_len[b * 8 + j] = total;
-        __builtin_amdgcn_sched_barrier(0);  // one task's temporaries at a time: 64 VGPRs, four workgroups per CU
+        __builtin_amdgcn_sched_barrier(0);  // one task's temporaries at a time: within the 80 VGPRs of three workgroups per CU
     }
     __syncthreads();
     // the eighths' bit offsets: a scan in stream order, in place

@@ -574,7 +574,8 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
 // Conic of a listed near-singular Gaussian, recomputed in FP64 from the
 // FP32 inputs: Sigma2D, its determinant and its inverse; the exponent
 // coefficients of the record are overwritten (log2 opacity kept).  Run by
-// k_ranges: nothing between preprocess and the blend reads the coefficients.
+// k_bucket_sort or, before the radix passes, by k_compact: ahead of the tighter tile
+// culling and the blend, which read the coefficients.
 __device__ void conic_fp64(const uint2 e, const ViewParams* __restrict__ views, const uint32_t* __restrict__ blk_view,
                            Rec* __restrict__ recs) {
     {
@@ -865,7 +866,7 @@ __global__ __launch_bounds__(K1_THREADS) void k_sorted_sums(const uint2* __restr
 // id, value = record, and (when asked) the depth word, so that the entry's
 // 64-bit key is (tile id << 32) | depth bits.  Load-balanced: the threads of a
 // workgroup write consecutive entries of their 256 Gaussians' output range,
-// each finding its Gaussian by binary search over the LDS prefix sums.
+// each finding its Gaussian by marks at the first slots and a prefix maximum.
 template <bool DEPTH>
 __global__ __launch_bounds__(K1_THREADS) void k_duplicate(const uint32_t* __restrict__ sorted_rec,
                                                           const uint2* __restrict__ sorted_rect,
@@ -3545,7 +3546,7 @@ void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, h
 }
 
 void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t cap, uint2* ranges, FrameCounters* host_cnt,
-                   const PreOut& o, const ViewParams* views_dev, hipStream_t st) {
+                   hipStream_t st) {
     // one 1024-word step per workgroup at capacity, but no more workgroups
     // than a large frame needs (the capacity may have been sized by a much
     // larger frame)

@@ -279,7 +279,7 @@ int launch_sort(const SortBuffers& b, const SortPass* passes, int npasses, int w
 // Tile ranges of the sorted list.  host_cnt: pinned host memory (or device
 // memory) that receives a copy of the counters.
 void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t cap, uint2* ranges, FrameCounters* host_cnt,
-                   const PreOut& o, const ViewParams* views_dev, hipStream_t st);
+                   hipStream_t st);
 // The blend's dense-first dispatch order of n_tiles tiles (longest lists
 // first) from their ranges: order receives a permutation of 0 .. n_tiles-1.
 void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, hipStream_t st);
