@@ -337,7 +337,7 @@ struct Workspace {
     DevBuf recs, rect, srect, zkey;
     DevBuf blk_sum, blk_vis, blk_fb, blk_tiles, blk_view, blk_off, blk_sum2, blk_off2;
     DevBuf fb_list;  // near-singular Gaussians for the FP64 conic kernel
-    DevBuf chunk_vis, chunk_dup, chunk_fb, chunk_tiles, chunk_dups;  // totals per chunk of block counts
+    DevBuf chunk_vis, chunk_dup, chunk_fb, chunk_dups;  // totals per chunk of block counts
     DevBuf counters;
     // per duplicate (also holds the visible Gaussians during the depth passes)
     DevBuf key[2], val[2], ext[2];
@@ -412,7 +412,6 @@ struct Workspace {
         o.chunk_vis = chunk_vis.as<uint32_t>();
         o.chunk_dup = chunk_dup.as<unsigned long long>();
         o.chunk_fb = chunk_fb.as<uint32_t>();
-        o.chunk_tiles = chunk_tiles.as<unsigned long long>();
         o.chunk_dups = chunk_dups.as<uint32_t>();
         o.fb_cap = rec_cap;
         o.cnt = counters.as<Counters>();
@@ -435,7 +434,7 @@ struct Workspace {
         grow(sample, r / 64 * 4);
         const size_t nch = nb / SCAN_CHUNK + 2;
         for (DevBuf* b : {&chunk_vis, &chunk_fb, &chunk_dups}) grow(*b, nch * 4);
-        for (DevBuf* b : {&chunk_dup, &chunk_tiles}) grow(*b, nch * 8);
+        grow(chunk_dup, nch * 8);
         rec_cap = (uint32_t)r;
     }
     void ensure_dups(uint32_t cap) {
@@ -699,19 +698,17 @@ void list_scale(ViewParams& v, const TileCfg& tc) {
 }
 
 // Tile layout of a plan for a tile configuration (list ids are global: view
-// list offset + row-major local id).  shared: lists of several tiles (only
-// for the placement by counting, and not for inspection, which shows the
-// tiles' own lists).
+// list offset + row-major local id).  shared: lists of several tiles, whose
+// entries carry cells (share_lists; not for inspection, which shows the tiles' own
+// lists).
 void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
     plan.tc = tc;
     plan.n_tiles = plan.n_frame_tiles = plan.tchunks = plan.max_tiles = 0;
     plan.shared = shared;
-    bool cells = shared;
-    for (const Group& g : plan.groups) cells = cells && g.n_pad <= 1u << CELL_REC_BITS;
     for (ViewParams& v : plan.views) {
         v.lx = v.ly = 0;
         if (shared) list_scale(v, tc);
-        v.cells = cells ? 1 : 0;
+        v.cells = shared ? 1 : 0;
         v.tw_log = ceil_log2((uint64_t)tc.tw);
         v.th_log = ceil_log2((uint64_t)tc.th);
         const int lw = tc.tw << v.lx, lh = tc.th << v.ly;
@@ -848,16 +845,25 @@ bool packed_rects(const Plan& plan) {
     return packed;
 }
 
-// Whether the tiles of a plan may share lists: where they are placed by counting.
-bool share_lists(const Plan& plan) {
+// Whether the plan's depth order is formed in buckets, and its tile digit placed by
+// counting.
+bool use_buckets(const Plan& plan) { return plan.opt.buckets && packed_rects(plan); }
+bool use_bin(const Plan& plan) {
     const LaunchOptions& opt = plan.opt;
-    return opt.bin && !opt.cull_tiles && (opt.buckets || plan.views.size() == 1);
+    return opt.bin && !opt.cull_tiles && (opt.buckets || plan.views.size() == 1) && packed_rects(plan);
 }
 
-// Whether the plan's tile digit is placed by counting, and its depth order formed
-// in buckets.
-bool use_bin(const Plan& plan) { return share_lists(plan) && packed_rects(plan); }
-bool use_buckets(const Plan& plan) { return plan.opt.buckets && packed_rects(plan); }
+// Whether the tiles of a plan may share lists: where the lists are placed by
+// counting and their entries have room for the cells, in the bucketed order and
+// up to 2^24 records a view.  A shared list without cells has every block of the
+// blend fetch the box of every entry: 17M Gaussians at 1080p 12.7 ms a frame, 4.1 with
+// a list per tile; 3M in the radix order 1.31 and 0.71.
+bool share_lists(const Plan& plan) {
+    const LaunchOptions& opt = plan.opt;
+    bool fits = opt.bin && !opt.cull_tiles && opt.buckets;
+    for (const Group& g : plan.groups) fits = fits && g.n_pad <= 1u << CELL_REC_BITS;
+    return fits;
+}
 
 size_t bucket_row_bytes(const Plan& plan) { return std::max<size_t>(plan.row_words, 1) * 4; }
 size_t tile_row_bytes(const Plan& plan) {
@@ -928,8 +934,9 @@ void prepare(Workspace& ws, Plan& plan, bool debug) {
 // earlier frames of its scenes, or an attempt of its own, were found to be.  A
 // single view of wide depths takes the radix passes; several views stay in
 // buckets, which take keys of any span, because without them the lists are not
-// placed by counting.
-void lay_out(tigas_context* ctx, Plan& plan, const TileCfg& tc, bool debug) {
+// placed by counting, and so does a frame without a second attempt (retry), which
+// meets crowded depths on the spot.
+void lay_out(tigas_context* ctx, Plan& plan, const TileCfg& tc, bool debug, bool retry = true) {
     uint32_t found = plan.found;
     const uint32_t epoch = ctx->depth_epoch.load();
     for (const Group& g : plan.groups)
@@ -938,8 +945,8 @@ void lay_out(tigas_context* ctx, Plan& plan, const TileCfg& tc, bool debug) {
     opt.cull = ctx->blend_cull.load();
     opt.bin = ctx->tile_bin.load();
     opt.cull_tiles = ctx->tile_cull.load();
-    opt.buckets = !ctx->depth4.load() && !((found & FLAG_WIDE) && plan.views.size() == 1);
-    opt.split = found & FLAG_CROWDED ? SPLIT_SHARES : 0u;
+    opt.buckets = !ctx->depth4.load() && !(retry && (found & FLAG_WIDE) && plan.views.size() == 1);
+    opt.split = !retry ? CROWD_SHARES : found & FLAG_CROWDED ? SPLIT_SHARES : 0u;
     set_tiles(plan, tc, !debug && share_lists(plan));
 }
 
@@ -985,7 +992,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     // view has at most 256 x 256 tiles, else the last radix pass gathers them
     const bool packed = packed_rects(plan);
     const bool bin = use_bin(plan);
-    const bool cells = bin && opt.buckets && !debug && plan.views[0].cells;  // in the entries
+    const bool cells = plan.shared;  // in the entries
     int cv = 0;
     if (use_buckets(plan)) {
         mark(2);
@@ -1551,7 +1558,6 @@ FrameMem carve_scratch(void* scratch_dev, Plan& plan, FrameCounters* cnt_out, hi
     o.chunk_fb = c.take<uint32_t>(nch * 4);
     o.chunk_dups = c.take<uint32_t>(nch * 4);
     o.chunk_dup = c.take<unsigned long long>(nch * 8);
-    o.chunk_tiles = c.take<unsigned long long>(nch * 8);
     o.cnt = m.cnt;
     m.ranges = c.take<uint2>((size_t)std::max<uint32_t>(n_tiles, 1) * 8);
     m.order = c.take<uint32_t>((size_t)std::max<uint32_t>(n_tiles, 1) * 4);
@@ -1570,7 +1576,7 @@ FrameMem carve_scratch(void* scratch_dev, Plan& plan, FrameCounters* cnt_out, hi
     m.bk = carve_buckets(plan, hist, hist + rows_bytes, &small_bytes);
     o.vmask = reinterpret_cast<unsigned long long*>(hist + rows_bytes + small_bytes);
     o.sample = reinterpret_cast<uint32_t*>(hist + rows_bytes + small_bytes + mask_bytes);
-    m.retry = false;  // no second attempt here
+    m.retry = false;
     // six duplicate arrays of dup_cap words (keys, values, extra; two each)
     const size_t left = c.cap > c.off + 6 * 256 ? c.cap - c.off - 6 * 256 : 0;
     const uint64_t dup_cap = std::min<uint64_t>(left / 24 / 256 * 256, 16u << 20);
@@ -1614,11 +1620,8 @@ void render_noalloc(tigas_scene* scene, const tigas_pose* pose, const tigas_intr
     out->out_h = v.height;
     if (!out->data || out->capacity < frame_bytes(v)) fail(TIGAS_E_BUFFER, "output frame buffer too small");
     v.out_ptr = (uint64_t)(uintptr_t)out->data;
-    // as requested, else 16x16 tiles: no autotuner here; no second attempt either,
-    // so the buckets meet crowded depths on the spot, and wide ones as they are
-    lay_out(ctx, plan, tile_cfg(q), false);
-    plan.opt.buckets = !ctx->depth4.load();
-    plan.opt.split = CROWD_SHARES;
+    // as requested, else 16x16 tiles: no autotuner here
+    lay_out(ctx, plan, tile_cfg(q), false, /*retry=*/false);
     set_buckets(plan);
     // fewer units than with a workspace: a row of each in the array
     plan.nunits = std::min<uint32_t>(plan.nunits, (plan.nrec + 2047) / 2048 + 20);

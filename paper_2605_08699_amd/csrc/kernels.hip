@@ -635,18 +635,16 @@ __device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, unsigned long long
 // (SCAN_CHUNK counts per workgroup), in two kernels: chunk totals, then each
 // chunk scanned from the sum of the totals before it.
 
-// Totals of chunk blockIdx.x of `in` (and optionally of three more count arrays).
+// Totals of chunk blockIdx.x of `in` (and optionally of two more count arrays).
 __global__ __launch_bounds__(SCAN_THREADS) void k_chunk_totals(const uint32_t* __restrict__ in, int n,
                                                                const uint32_t* __restrict__ in_a,
                                                                const uint32_t* __restrict__ in_b,
-                                                               const uint32_t* __restrict__ in_c,
                                                                uint32_t* __restrict__ tot,
                                                                unsigned long long* __restrict__ tot_a,
-                                                               uint32_t* __restrict__ tot_b,
-                                                               unsigned long long* __restrict__ tot_c) {
+                                                               uint32_t* __restrict__ tot_b) {
     __shared__ unsigned long long red64[SCAN_THREADS / 64];
     const int base = (int)blockIdx.x * SCAN_CHUNK;
-    uint64_t s = 0, sa = 0, sb = 0, sc = 0;
+    uint64_t s = 0, sa = 0, sb = 0;
 #pragma unroll
     for (int r = 0; r < SCAN_ITEMS; ++r) {
         const int i = base + r * SCAN_THREADS + (int)threadIdx.x;
@@ -654,18 +652,15 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_chunk_totals(const uint32_t* _
             s += in[i];
             if (in_a) sa += in_a[i];
             if (in_b) sb += in_b[i];
-            if (in_c) sc += in_c[i];
         }
     }
     s = block_sum_u64(s, red64);
     if (in_a) sa = block_sum_u64(sa, red64);
     if (in_b) sb = block_sum_u64(sb, red64);
-    if (in_c) sc = block_sum_u64(sc, red64);
     if (threadIdx.x == 0) {
         tot[blockIdx.x] = (uint32_t)s;
         if (tot_a) tot_a[blockIdx.x] = sa;
         if (tot_b) tot_b[blockIdx.x] = (uint32_t)sb;
-        if (tot_c) tot_c[blockIdx.x] = sc;
     }
 }
 
@@ -703,35 +698,32 @@ __device__ void scan_chunk(const uint32_t* __restrict__ in, int n, const uint32_
 }
 
 // After preprocess (second kernel of the chunked scan): compaction offsets of
-// the visible records; workgroup 0 also sets the totals V, D, the (Gaussian,
-// tile) pairs and the FP64-fallback count and the overflow flag; every workgroup clears part of the per-frame
+// the visible records; workgroup 0 also sets the totals V, D and FP64-fallback
+// count and the overflow flag; every workgroup clears part of the per-frame
 // accumulators of later kernels (digit totals, tile ranges).
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_visible(const uint32_t* __restrict__ blk_vis, int nblk,
                                                                const uint32_t* __restrict__ tot_vis,
                                                                const unsigned long long* __restrict__ tot_dup,
-                                                               const uint32_t* __restrict__ tot_fb,
-                                                               const unsigned long long* __restrict__ tot_tiles,
-                                                               int nchunks, uint32_t* __restrict__ blk_off,
-                                                               Counters* cnt, uint32_t cap, ZeroList zl) {
+                                                               const uint32_t* __restrict__ tot_fb, int nchunks,
+                                                               uint32_t* __restrict__ blk_off, Counters* cnt,
+                                                               uint32_t cap, ZeroList zl) {
     __shared__ uint32_t red[SCAN_THREADS / 64];
     __shared__ unsigned long long red64[SCAN_THREADS / 64];
     __shared__ uint32_t stage[SCAN_STAGE];
     scan_chunk(blk_vis, nblk, tot_vis, blk_off, red, red64, stage);
     if (blockIdx.x == 0) {
-        uint64_t V = 0, D = 0, F = 0, P = 0;
+        uint64_t V = 0, D = 0, F = 0;
         for (int c = (int)threadIdx.x; c < nchunks; c += SCAN_THREADS) {
             V += tot_vis[c];
             D += tot_dup[c];
             F += tot_fb[c];
-            P += tot_tiles[c];
         }
         V = block_sum_u64(V, red64);
         D = block_sum_u64(D, red64);
         F = block_sum_u64(F, red64);
-        P = block_sum_u64(P, red64);
         if (threadIdx.x == 0) {
             cnt->D = D > 0xffffffffull ? 0xffffffffu : (uint32_t)D;
-            cnt->pairs = P > 0xffffffffull ? 0xffffffffu : (uint32_t)P;
+            cnt->pairs = cnt->D;  // one tile per list: only bucketed plans share lists
             cnt->visible = (uint32_t)V;
             cnt->fallbacks = (uint32_t)F;
             cnt->overflow = D > (uint64_t)cap ? 1u : 0u;
@@ -3419,11 +3411,10 @@ void launch_scan_visible(const PreOut& o, int nblk, uint32_t* blk_off, Counters*
                          const ZeroList& zl, hipStream_t st) {
     const int nchunks = std::max(1, (nblk + SCAN_CHUNK - 1) / SCAN_CHUNK);
     TIGAS_LAUNCH(k_chunk_totals, dim3(nchunks), dim3(SCAN_THREADS), st, (const uint32_t*)o.blk_vis, nblk,
-                 (const uint32_t*)o.blk_sum, (const uint32_t*)o.blk_fb, (const uint32_t*)o.blk_tiles, o.chunk_vis,
-                 o.chunk_dup, o.chunk_fb, o.chunk_tiles);
+                 (const uint32_t*)o.blk_sum, (const uint32_t*)o.blk_fb, o.chunk_vis, o.chunk_dup, o.chunk_fb);
     TIGAS_LAUNCH(k_scan_visible, dim3(nchunks), dim3(SCAN_THREADS), st, (const uint32_t*)o.blk_vis, nblk,
                  (const uint32_t*)o.chunk_vis, (const unsigned long long*)o.chunk_dup, (const uint32_t*)o.chunk_fb,
-                 (const unsigned long long*)o.chunk_tiles, nchunks, blk_off, cnt, cap, zl);
+                 nchunks, blk_off, cnt, cap, zl);
 }
 
 void launch_compact(const PreOut& o, int nblk, const uint32_t* blk_off, uint32_t* key, uint32_t* val, uint32_t* ext,
@@ -3444,8 +3435,8 @@ void launch_duplicate(const PreOut& o, int nblk, const uint32_t* sorted_rec, con
                  blk_sum2);
     const int nchunks = std::max(1, (nblk + SCAN_CHUNK - 1) / SCAN_CHUNK);
     TIGAS_LAUNCH(k_chunk_totals, dim3(nchunks), dim3(SCAN_THREADS), st, (const uint32_t*)blk_sum2, nblk,
-                 (const uint32_t*)nullptr, (const uint32_t*)nullptr, (const uint32_t*)nullptr, o.chunk_dups,
-                 (unsigned long long*)nullptr, (uint32_t*)nullptr, (unsigned long long*)nullptr);
+                 (const uint32_t*)nullptr, (const uint32_t*)nullptr, o.chunk_dups, (unsigned long long*)nullptr,
+                 (uint32_t*)nullptr);
     TIGAS_LAUNCH(k_scan_dups, dim3(nchunks), dim3(SCAN_THREADS), st, (const uint32_t*)blk_sum2, nblk,
                  (const uint32_t*)o.chunk_dups, blk_off2, nchunks, (Counters*)nullptr);
     if (depth_out)
@@ -3467,8 +3458,8 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
                  (uint32_t*)nullptr);
     const int nchunks = std::max(1, (nblk + SCAN_CHUNK - 1) / SCAN_CHUNK);
     TIGAS_LAUNCH(k_chunk_totals, dim3(nchunks), dim3(SCAN_THREADS), st, (const uint32_t*)blk_cnt, nblk,
-                 (const uint32_t*)nullptr, (const uint32_t*)nullptr, (const uint32_t*)nullptr, o.chunk_dups,
-                 (unsigned long long*)nullptr, (uint32_t*)nullptr, (unsigned long long*)nullptr);
+                 (const uint32_t*)nullptr, (const uint32_t*)nullptr, o.chunk_dups, (unsigned long long*)nullptr,
+                 (uint32_t*)nullptr);
     // the kept count becomes the frame's duplicate count D
     TIGAS_LAUNCH(k_scan_dups, dim3(nchunks), dim3(SCAN_THREADS), st, (const uint32_t*)blk_cnt, nblk,
                  (const uint32_t*)o.chunk_dups, blk_off, nchunks, cnt);

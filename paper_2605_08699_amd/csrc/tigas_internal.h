@@ -154,7 +154,6 @@ struct PreOut {
     uint32_t* chunk_vis;            // per SCAN_CHUNK block counts: visible records,
     unsigned long long* chunk_dup;  // duplicates,
     uint32_t* chunk_fb;             // FP64 fallbacks,
-    unsigned long long* chunk_tiles;  // (Gaussian, tile) pairs,
     uint32_t* chunk_dups;           // and (later) depth-ordered duplicate counts
     uint2* fb_list;     // (record, Gaussian) pairs whose conic is recomputed in FP64
     uint32_t fb_cap;

@@ -181,3 +181,48 @@ def test_reduced_precision_decode_matches_oracle_of_rounded_scene(ctx, storage):
     res = gc.check_frame_pixels(img.reshape(-1, 3), br.reshape(-1, br.shape[2], 4), nb.reshape(-1))
     _say(storage, res)
     assert res["n_bad"] == 0 and res["n_unresolved"] == 0, res
+
+
+def test_views_of_more_records_than_a_list_word_numbers(ctx):
+    """2^24 records and more, all in view: the frame of the radix passes, and
+    no jump in time where a list word has no room for the cells any more (with
+    the lists still shared there, 5 times)."""
+    import time
+    n = (1 << 24) + 70_000
+    rng = np.random.default_rng(24)
+    z = rng.uniform(2.0, 30.0, n).astype(np.float32)
+    means = np.empty((n, 3), np.float32)
+    means[:, 0] = rng.uniform(-0.98, 0.98, n).astype(np.float32) * z
+    means[:, 1] = rng.uniform(-0.55, 0.55, n).astype(np.float32) * z
+    means[:, 2] = z
+    sh = np.zeros((n, 16, 3), np.float32)
+    sh[:, 0] = rng.uniform(-1.0, 1.0, (n, 3)).astype(np.float32)
+    scene = synth.Scene(means, np.repeat(np.log(0.0006 * z)[:, None], 3, axis=1),
+                        np.tile(np.array([1, 0, 0, 0], np.float32), (n, 1)), np.full(n, -1.0, np.float32), sh, 0)
+    W, H = 1920, 1080
+    k = synth.Intrinsics(960.0, 960.0, W / 2, H / 2)
+    pose = synth.Pose(np.eye(3, dtype=np.float32), np.zeros(3, np.float32))
+    ms = {}
+    for records in (1 << 24, n):
+        s = ctx.load_scene(scene.subset(slice(0, records)))
+        out = torch.empty((H, W, 3), dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(7):
+            t0 = time.perf_counter()
+            ctx.render(s, pose, k, W, H, out=out, tile=(16, 32))
+            times.append((time.perf_counter() - t0) * 1e3)
+        ms[records] = sorted(times)[3]
+        st = ctx.stats()
+        got = out.cpu().numpy()
+        ctx.set_tile_binning(False)
+        ctx.set_depth_passes(4)
+        try:
+            want = ctx.render(s, pose, k, W, H, tile=(16, 32))
+            assert ctx.stats()["duplicates"] == st["duplicates"] and st["visible"] == records
+        finally:
+            ctx.set_tile_binning(True)
+            ctx.set_depth_passes(3)
+        np.testing.assert_array_equal(got, want)
+        s.free()
+    _say("ms a frame", ms)
+    assert ms[n] < 2 * ms[1 << 24]
