@@ -220,7 +220,7 @@ struct Plan {
     uint32_t nunits = 0, tchunks = 0, max_tiles = 0;  // tile placement (set_tiles)
     TileCfg tc{16, 16, 64, 1};
     bool batch = false;   // a batch's plan: tuned apart from single frames
-    bool shared = false;  // tiles may share lists (set_tiles)
+    bool cells = false;   // the lists' entries carry cells, and tiles may share lists (set_tiles)
     LaunchOptions opt;    // lay_out
     uint32_t found = 0;   // FLAG_WIDE, FLAG_CROWDED: met by an attempt of this plan
     bool allow_graph = true;  // capture/replay (off for one-off shapes such as serving batches)
@@ -697,35 +697,51 @@ void list_scale(ViewParams& v, const TileCfg& tc) {
     }
 }
 
+// Whether a view's lists are placed by counting: their rectangles pack into a word,
+// and, with a list per tile, there are at most COUNT_LISTS_MAX.  With more, every
+// group of rows of a unit walks the unit's Gaussians again for few entries: 3M in the
+// radix order at 4K with 16x16 tiles (32400 lists) 1291 us a frame, by radix tile
+// passes 802; 1280x720 with 8x8 (14400) 842 and 674, 1920x1080 with 16x16 (8160)
+// 734 and 808.  Shared lists are fewer entries: 3M at 8192x8192 (16384 lists of 64x64)
+// 1602 us and 1783, at 16384x16384 (32768 of 64x128) 3745 and 4244.
+bool countable(const ViewParams& v) {
+    return v.tiles_x <= 256 && v.tiles_y <= 256 && (v.lx + v.ly > 0 || v.tiles_x * v.tiles_y <= COUNT_LISTS_MAX);
+}
+
 // Tile layout of a plan for a tile configuration (list ids are global: view
-// list offset + row-major local id).  shared: lists of several tiles, whose
-// entries carry cells (share_lists; not for inspection, which shows the tiles' own
-// lists).
-void set_tiles(Plan& plan, const TileCfg& tc, bool shared) {
+// list offset + row-major local id).  cells: where a list word has room for them
+// (28 bits of record number at most), the lists' entries carry cells; of views up to
+// 2^24 records, where it has room for 4 x 4, tiles share lists.  (A shared list
+// without cells has every block of the blend fetch the box of every entry: 17M
+// Gaussians at 1080p 12.7 ms a frame, 4.1 with a list per tile, 3.0 with cells as
+// well; 3M in the radix order 1.31 and 0.71.)
+void set_tiles(Plan& plan, const TileCfg& tc, bool cells) {
     plan.tc = tc;
     plan.n_tiles = plan.n_frame_tiles = plan.tchunks = plan.max_tiles = 0;
-    plan.shared = shared;
-    for (ViewParams& v : plan.views) {
-        v.lx = v.ly = 0;
-        if (shared) list_scale(v, tc);
-        v.cells = shared ? 1 : 0;
-        v.tw_log = ceil_log2((uint64_t)tc.tw);
-        v.th_log = ceil_log2((uint64_t)tc.th);
-        const int lw = tc.tw << v.lx, lh = tc.th << v.ly;
-        v.tiles_x = (v.width + lw - 1) / lw;
-        v.tiles_y = (v.height + lh - 1) / lh;
-        v.tile_base = plan.n_tiles;
-        v.tchunk_base = plan.tchunks;
-        const uint32_t n = (uint32_t)(v.tiles_x * v.tiles_y);
-        plan.n_tiles += n;
-        plan.n_frame_tiles += (uint32_t)(((v.width + tc.tw - 1) / tc.tw) * ((v.height + tc.th - 1) / tc.th));
-        plan.tchunks += (n + TILE_CHUNK - 1) / TILE_CHUNK;
-        plan.max_tiles = std::max(plan.max_tiles, n);
-        if (shared && (v.tiles_x > 256 || v.tiles_y > 256)) {  // too many even so: not placed by counting
-            set_tiles(plan, tc, false);
-            return;
+    plan.cells = cells;
+    for (const Group& g : plan.groups)
+        for (int k = 0; k < g.nviews; ++k) {
+            ViewParams& v = plan.views[g.first_view + k];
+            v.cells = !cells ? 0 : g.n_pad <= 1u << cell_rec_bits(2) ? 2 : g.n_pad <= 1u << cell_rec_bits(1) ? 1 : 0;
+            v.lx = v.ly = 0;
+            if (v.cells == 2) list_scale(v, tc);
+            v.tw_log = ceil_log2((uint64_t)tc.tw);
+            v.th_log = ceil_log2((uint64_t)tc.th);
+            const int lw = tc.tw << v.lx, lh = tc.th << v.ly;
+            v.tiles_x = (v.width + lw - 1) / lw;
+            v.tiles_y = (v.height + lh - 1) / lh;
+            v.tile_base = plan.n_tiles;
+            v.tchunk_base = plan.tchunks;
+            const uint32_t n = (uint32_t)(v.tiles_x * v.tiles_y);
+            plan.n_tiles += n;
+            plan.n_frame_tiles += (uint32_t)(((v.width + tc.tw - 1) / tc.tw) * ((v.height + tc.th - 1) / tc.th));
+            plan.tchunks += (n + TILE_CHUNK - 1) / TILE_CHUNK;
+            plan.max_tiles = std::max(plan.max_tiles, n);
+            if (cells && !countable(v)) {  // even so: not placed by counting
+                set_tiles(plan, tc, false);
+                return;
+            }
         }
-    }
     // units of the tile placement: each has a row of the largest view's tiles
     // (at most 256 MB of them: 1024 rows of the 65536 that it takes at most), and
     // costs a pass over it
@@ -804,7 +820,7 @@ std::string shape_key(const Plan& plan, bool with_tiles) {
         k += buf;
     }
     if (with_tiles) {
-        std::snprintf(buf, sizeof buf, "t%dx%d:%d:%d", plan.tc.tw, plan.tc.th, (int)plan.batch, (int)plan.shared);
+        std::snprintf(buf, sizeof buf, "t%dx%d:%d:%d", plan.tc.tw, plan.tc.th, (int)plan.batch, (int)plan.cells);
         k += buf;
     }
     return k;
@@ -850,18 +866,8 @@ bool packed_rects(const Plan& plan) {
 bool use_buckets(const Plan& plan) { return plan.opt.buckets && packed_rects(plan); }
 bool use_bin(const Plan& plan) {
     const LaunchOptions& opt = plan.opt;
-    return opt.bin && !opt.cull_tiles && (opt.buckets || plan.views.size() == 1) && packed_rects(plan);
-}
-
-// Whether the tiles of a plan may share lists: where the lists are placed by
-// counting and their entries have room for the cells, in the bucketed order and
-// up to 2^24 records a view.  A shared list without cells has every block of the
-// blend fetch the box of every entry: 17M Gaussians at 1080p 12.7 ms a frame, 4.1 with
-// a list per tile; 3M in the radix order 1.31 and 0.71.
-bool share_lists(const Plan& plan) {
-    const LaunchOptions& opt = plan.opt;
-    bool fits = opt.bin && !opt.cull_tiles && opt.buckets;
-    for (const Group& g : plan.groups) fits = fits && g.n_pad <= 1u << CELL_REC_BITS;
+    bool fits = opt.bin && !opt.cull_tiles && (opt.buckets || plan.views.size() == 1);
+    for (const ViewParams& v : plan.views) fits = fits && countable(v);
     return fits;
 }
 
@@ -947,7 +953,8 @@ void lay_out(tigas_context* ctx, Plan& plan, const TileCfg& tc, bool debug, bool
     opt.cull_tiles = ctx->tile_cull.load();
     opt.buckets = !ctx->depth4.load() && !(retry && (found & FLAG_WIDE) && plan.views.size() == 1);
     opt.split = !retry ? CROWD_SHARES : found & FLAG_CROWDED ? SPLIT_SHARES : 0u;
-    set_tiles(plan, tc, !debug && share_lists(plan));
+    // (the entries of the radix order, and those that an inspection shows, are plain)
+    set_tiles(plan, tc, !debug && opt.bin && !opt.cull_tiles && opt.buckets);
 }
 
 int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned long long* work) {
@@ -992,7 +999,6 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     // view has at most 256 x 256 tiles, else the last radix pass gathers them
     const bool packed = packed_rects(plan);
     const bool bin = use_bin(plan);
-    const bool cells = plan.shared;  // in the entries
     int cv = 0;
     if (use_buckets(plan)) {
         mark(2);
@@ -1003,7 +1009,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         // (an inspection shows the bucketed order however long it takes)
         launch_bucket_sort(o, m.bk, vdev, nv, plan.nseg, plan.nchunks, plan.seg_len, cnt, m.dup_cap, zl,
                            /*flag_wide=*/m.retry && nv == 1, /*flag_crowd=*/m.retry && !debug && !opt.split, opt.split,
-                           plan.nunits, sb.val[0], sb.ext[0], cells, st);
+                           plan.nunits, sb.val[0], sb.ext[0], st);
     } else {
         launch_scan_visible(o, nblk, m.blk_off, cnt, m.dup_cap, zl, st);
         mark(2);
@@ -1032,7 +1038,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
     if (bin) {
         // tile digit by counting, straight from the depth-ordered Gaussians
         launch_tiles(m.tm, m.bk, vdev, plan.views.data(), nv, plan.nrec, cnt, !opt.buckets, plan.tchunks, sb.val[cv], sb.ext[cv],
-                     cells, m.ranges, nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
+                     m.ranges, nv > 1 ? nullptr : m.order, m.cnt_out, sb.val[cd],
                      debug ? sb.key[cd] : nullptr, debug ? sb.ext[cd] : nullptr, o.zkey, st);
         mark(4);
         mark(5);
@@ -1046,7 +1052,7 @@ int enqueue(const FrameMem& m, const Plan& plan, bool debug, bool prof, unsigned
         if (nv == 1) launch_tile_order(m.ranges, plan.n_tiles, m.order, st);
         mark(5);
     }
-    launch_blend(vdev, plan.views.data(), nv, plan.n_tiles, m.ranges, sb.val[cur], o, plan.nrec, cells, work, opt.cull,
+    launch_blend(vdev, plan.views.data(), nv, plan.n_tiles, m.ranges, sb.val[cur], o, plan.nrec, work, opt.cull,
                  nv > 1 ? nullptr : m.order, st);
     mark(6);
     HIPCHK(hipGetLastError());
@@ -1142,7 +1148,7 @@ FrameCounters settle_frame(tigas_context* ctx, Workspace& ws, Plan& plan, bool d
         }
         // more entries than the buffers hold: larger ones
         // (c.D, the (Gaussian, tile) pairs, bounds the entries in every layout;
-        // a plan laid out again without shared lists has as many)
+        // one laid out again without shared lists has as many)
         if ((c.overflow & FLAG_FULL) || c.D > ws.dup_cap) {
             const uint64_t want = (uint64_t)c.D + c.D / 4 + 1024;
             if (want > 0xfff00000ull) fail(TIGAS_E_OOM, "duplicate count exceeds the 32-bit index range");

@@ -471,7 +471,7 @@ __global__ __launch_bounds__(K1_THREADS) void k_preprocess(SceneView s, const Vi
                                     (uint32_t)(tx1 - tx0 + 1) | ((uint32_t)(ty1 - ty0 + 1) << 16));
                     if (v.cells) {
                         // the cells of the pixel box's ends inside its first and last list
-                        const int cw = cell_log(v.tw_log + v.lx), ch = cell_log(v.th_log + v.ly);
+                        const int cw = cell_log(v.tw_log + v.lx, v.cells), ch = cell_log(v.th_log + v.ly, v.cells);
                         const int mx = (1 << (v.tw_log + v.lx - cw)) - 1, my = (1 << (v.th_log + v.ly - ch)) - 1;
                         tr.x |= ((uint32_t)((x0 >> cw) & mx) << 12) | ((uint32_t)((y0 >> ch) & my) << 28);
                         tr.y |= ((uint32_t)((x1 >> cw) & mx) << 12) | ((uint32_t)((y1 >> ch) & my) << 28);
@@ -766,10 +766,13 @@ __device__ __forceinline__ uint32_t pack_rect(uint2 r) {
     const uint32_t tx0 = r.x & 0xfffu, ty0 = (r.x >> 16) & 0xfffu;
     return tx0 | (ty0 << 8) | ((tx0 + (r.y & 0xfffu) - 1u) << 16) | ((ty0 + ((r.y >> 16) & 0xfffu) - 1u) << 24);
 }
-// The cells of the ends of a rectangle of lists, as a byte of 2-bit fields:
+// The cells of the ends of a rectangle of lists, in the bits above a record's number:
 // first column and row (in the first list), last column and row (in the last).
-__device__ __forceinline__ uint32_t rect_cells(uint2 r) {
-    return ((r.x >> 12) & 3u) | (((r.x >> 28) & 3u) << 2) | (((r.y >> 12) & 3u) << 4) | (((r.y >> 28) & 3u) << 6);
+__device__ __forceinline__ uint32_t rect_cells(uint2 r, int cells) {
+    const int c = cells;
+    return (((r.x >> 12) & 3u) | (((r.x >> 28) & 3u) << c) | (((r.y >> 12) & 3u) << (2 * c)) |
+            (((r.y >> 28) & 3u) << (3 * c)))
+           << (cell_rec_bits(c) & 31);
 }
 __device__ __forceinline__ uint2 unpack_rect(uint32_t p) {
     const uint32_t tx0 = p & 0xffu, ty0 = (p >> 8) & 0xffu, tx1 = (p >> 16) & 0xffu, ty1 = p >> 24;
@@ -1694,6 +1697,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, 
     const int vi = view_of((uint32_t)wg, nviews, [&](int i) { return views[i].seg_base; });
     const ViewParams& v = views[vi];
     const uint32_t seg = (uint32_t)wg - v.seg_base, nbkt = v.nbkt;
+    const int cells = v.cells;
     const uint32_t r0 = v.rec_base + seg * seg_len, r1 = min(r0 + seg_len, v.rec_base + v.n_pad);
     // the first records are on their way while the buckets' positions are
     // formed (all records' rectangles: waiting for the mask would cost more)
@@ -1735,7 +1739,7 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, 
                                         ? split_bucket(key[k], i, reinterpret_cast<const uint64_t*>(cdf))
                                         : key_bucket(key[k], cdf, m, nbkt);
                 const uint32_t pos = atomicAdd(&next[bk], 1u);
-                b.elem[pos] = make_uint4(key[k], i, pack_rect(rect[k]), rect_cells(rect[k]) << 24);
+                b.elem[pos] = make_uint4(key[k], i, pack_rect(rect[k]), rect_cells(rect[k], cells));
             }
     }
 }
@@ -1757,7 +1761,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o
                                                                      const ViewParams* __restrict__ views, int nviews,
                                                                      const Counters* __restrict__ cnt,
                                                                      uint32_t* __restrict__ val,
-                                                                     uint32_t* __restrict__ ext, bool cells) {
+                                                                     uint32_t* __restrict__ ext) {
     constexpr int NT = BUCKET_SORT_THREADS, NW = NT / 64, CAP = BUCKET_SORT_CAP, EPT = CAP / NT;
     constexpr int BINS = 2048, BPT = BINS / NT;
     static_assert(CAP <= SORT_MAX, "sorted at once");
@@ -1799,7 +1803,8 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o
     val += first;
     ext += first;
     // with cells, a record is numbered inside its view, below the rectangle's cells
-    const uint32_t rec0 = cells ? v.rec_base : 0u, cmask = cells ? 0xff000000u : 0u;
+    const int cells = v.cells;
+    const uint32_t rec0 = cells ? v.rec_base : 0u;
     if (n <= (uint32_t)CAP) {
         uint32_t key[EPT], rec[EPT], rc[EPT], be[EPT];
         uint32_t klo = 0xffffffffu, khi = 0u, rlo = 0xffffffffu, rhi = 0u;
@@ -1903,7 +1908,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o
                     const uint32_t q0 = bin[at[k] >> 16], q1 = bin[(at[k] >> 16) + 1];
                     uint32_t pos = q0;
                     for (uint32_t q = q0; q < q1; ++q) pos += arr[q] < me ? 1u : 0u;
-                    val[pos] = (rec[k] - rec0) | (be[k] & cmask);
+                    val[pos] = (rec[k] - rec0) | be[k];
                     ext[pos] = rc[k];
                 }
             }
@@ -1916,7 +1921,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o
         for (uint32_t i = t; i < n; i += NT) {
             const uint32_t r = (uint32_t)arr[i];
             const uint2 rr = o.rect[r];
-            val[i] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
+            val[i] = (r - rec0) | rect_cells(rr, cells);
             ext[i] = pack_rect(rr);
         }
         return;
@@ -1993,7 +1998,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o
     auto put = [&](uint32_t pos, uint64_t x) {
         const uint32_t r = rec_of(x);
         const uint2 rr = o.rect[r];
-        val[pos] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
+        val[pos] = (r - rec0) | rect_cells(rr, cells);
         ext[pos] = pack_rect(rr);
     };
     // sorts arr[0, m) and writes it to `at`
@@ -2042,7 +2047,7 @@ __global__ __launch_bounds__(BUCKET_SORT_THREADS, 6) void k_bucket_sort(PreOut o
                         uint32_t pos = q0;
 #pragma unroll 4
                         for (uint32_t q = q0; q < q1; ++q) pos += arr[q] < x ? 1u : 0u;
-                        val[done + pos] = (r - rec0) | ((rect_cells(rr) << 24) & cmask);
+                        val[done + pos] = (r - rec0) | rect_cells(rr, cells);
                         ext[done + pos] = pack_rect(rr);
                     }
             } else {
@@ -2662,7 +2667,7 @@ __global__ __launch_bounds__(NW * 64) void k_tile_emit(
     TileMem m, BucketMem b, const ViewParams* __restrict__ views, int nviews, const Counters* __restrict__ cnt,
     bool flat, uint32_t nfront, uint32_t nchunks, uint2* __restrict__ ranges, uint32_t* __restrict__ order,
     FrameCounters* host_cnt, const uint32_t* __restrict__ rec, const uint32_t* __restrict__ packed,
-    bool cells, uint32_t* __restrict__ val_out, uint32_t* __restrict__ tile_out, uint32_t* __restrict__ depth_out,
+    uint32_t* __restrict__ val_out, uint32_t* __restrict__ tile_out, uint32_t* __restrict__ depth_out,
     const uint32_t* __restrict__ zkey) {
     constexpr int NT = NW * 64;
     static_assert((NW & (NW - 1)) == 0, "rows modulo the waves");
@@ -2784,6 +2789,9 @@ __global__ __launch_bounds__(NW * 64) void k_tile_emit(
         *last = min((int)(p >> 24) - y0g, nr - 1);
     };
     const uint32_t D = cnt->D;
+    // with cells, of the view's lists: bits of a record's number, cells a side
+    const int cells = v.cells, rb = cell_rec_bits(cells) & 31, side = 1 << cells;
+    const uint32_t all = (1u << side) - 1u;
     auto put = [&](uint32_t cell, uint32_t pos, uint32_t r) {
         if (pos >= D) return;
         val_out[pos] = r;
@@ -2796,18 +2804,20 @@ __global__ __launch_bounds__(NW * 64) void k_tile_emit(
         const bool on = (uint32_t)lane < n;
         const uint32_t p = on ? qp[w][lane] : 0u, r = on ? qr[w][lane] : 0u;
         const int x0 = (int)(p & 0xffu), nx = (int)((p >> 16) & 0xffu) - x0 + 1;
-        // with cells: masks of the rectangle's columns (bits 0-3 in its first
-        // list, 8-11 in its last) and rows (4-7, 12-15), all four elsewhere
-        const uint32_t rec = cells ? r & 0xffffffu : r;
-        const uint32_t cm = cells ? ((15u << ((r >> 24) & 3u)) & 15u) | (((15u << ((r >> 26) & 3u)) & 15u) << 4) |
-                                        (((2u << ((r >> 28) & 3u)) - 1u) << 8) | (((2u << (r >> 30)) - 1u) << 12)
+        // with cells: masks of the rectangle's columns (from bit 0 in its first
+        // list, 8 in its last) and rows (from 4 and 12), all elsewhere
+        const uint32_t rec = cells ? r & ((1u << rb) - 1u) : r, ends = r >> rb, last_cell = (uint32_t)side - 1u;
+        const uint32_t cm = cells ? ((all << (ends & last_cell)) & all) |
+                                        (((all << ((ends >> cells) & last_cell)) & all) << 4) |
+                                        (((2u << ((ends >> (2 * cells)) & last_cell)) - 1u) << 8) |
+                                        (((2u << (ends >> (3 * cells))) - 1u) << 12)
                                   : 0u;
         const int yt = (int)((p >> 8) & 0xffu) - y0g, yb = (int)(p >> 24) - y0g;
-        auto row_cells = [cells](uint32_t m, int y, int top, int bottom) {
-            return !cells ? 0u : ((y == top ? m >> 4 : 15u) & (y == bottom ? m >> 12 : 15u)) << 28;
+        auto row_cells = [=](uint32_t m, int y, int top, int bottom) {
+            return !cells ? 0u : ((y == top ? m >> 4 : all) & (y == bottom ? m >> 12 : all)) << (rb + side);
         };
-        auto col_cells = [cells](uint32_t m, int x, int n) {
-            return !cells ? 0u : ((x == 0 ? m : 15u) & (x + 1 == n ? m >> 8 : 15u) & 15u) << 24;
+        auto col_cells = [=](uint32_t m, int x, int n) {
+            return !cells ? 0u : ((x == 0 ? m : all) & (x + 1 == n ? m >> 8 : all) & all) << rb;
         };
         int f, last;
         rows_of(p, &f, &last);
@@ -2987,8 +2997,7 @@ struct BlendArgs {
     uint32_t n_lists, first;  // lists; the first one of the launch (a multiple of 8)
     int block_log;
     const uint2* ranges;
-    const uint32_t* vals;  // the lists: records, or with cells the view's records below masks of cells
-    int cells;
+    const uint32_t* vals;  // the lists: records, or in a view with cells its records below masks of cells
     const Rec* rec;
     uint32_t nrec;
     unsigned long long* work;
@@ -3197,8 +3206,9 @@ __device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams
     };
     uint32_t base = begin, queued = 0;
     // the cells of the list that hold the block
-    const uint32_t need = ((1u << 24) << ((sx & ((1 << lw) - 1)) >> cell_log(lw))) |
-                          ((1u << 28) << ((sy & ((1 << lh) - 1)) >> cell_log(lh)));
+    const int cells = scalar(v.cells), rb = cell_rec_bits(cells) & 31;
+    const uint32_t need = (1u << (rb + ((sx & ((1 << lw) - 1)) >> cell_log(lw, cells)))) |
+                          (1u << ((rb + (1 << cells) + ((sy & ((1 << lh) - 1)) >> cell_log(lh, cells))) & 31));
     // (the lists' buffers have room for a read of 64 entries from any of them)
     uint32_t ahead = 0u;
     auto read = [&] {  // scalar base, 32-bit lane offset
@@ -3212,9 +3222,9 @@ __device__ __forceinline__ void blend_block(const BlendArgs& A, const ViewParams
             base += 64;
             if (base < end) read();
             uint64_t m;
-            if (A.cells) {
+            if (cells) {
                 m = in & ballot((en & need) == need);
-                en = (en & 0xffffffu) + rec0;
+                en = (en & ((1u << rb) - 1u)) + rec0;
             } else {
                 bool hit = en < A.nrec && __builtin_amdgcn_inverse_ballot_w64(in);
                 if (hit) {
@@ -3476,7 +3486,7 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
                         bool flag_wide, bool flag_crowd, uint32_t split, uint32_t nunits, uint32_t* val, uint32_t* ext,
-                        bool cells, hipStream_t st) {
+                        hipStream_t st) {
 #define TIGAS_COUNT(M, GRID)                                                                                          \
     do {                                                                                                              \
         if (split)                                                                                                    \
@@ -3503,7 +3513,7 @@ void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* v
         TIGAS_LAUNCH(k_bucket_scatter<false>, dim3(nseg), dim3(BUCKET_THREADS), st, o, b, views_dev, nviews, nseg,
                      seg_len, (const Counters*)cnt);
     TIGAS_LAUNCH(k_bucket_sort, dim3(nchunks * COL_CHUNK), dim3(BUCKET_SORT_THREADS), st, o, b, views_dev,
-                 nviews, (const Counters*)cnt, val, ext, cells);
+                 nviews, (const Counters*)cnt, val, ext);
 }
 
 int launch_sort(const SortBuffers& b, const SortPass* passes, int npasses, int which, uint32_t cap, int nblocks,
@@ -3547,7 +3557,7 @@ void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t ca
 
 void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
                   int nviews, uint32_t nrec, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
-                  const uint32_t* packed, bool cells, uint2* ranges, uint32_t* order,
+                  const uint32_t* packed, uint2* ranges, uint32_t* order,
                   FrameCounters* host_cnt, uint32_t* val_out,
                   uint32_t* tile_out, uint32_t* depth_out, const uint32_t* zkey, hipStream_t st) {
     int groups = 1;
@@ -3562,13 +3572,13 @@ void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_
     const uint32_t gx = (nfront + units + 7) / 8 * 8;  // a multiple of the XCDs: a column of the grid stays on one
     if (tile_out)
         TIGAS_LAUNCH((k_tile_emit<true, 4>), dim3(gx, groups), dim3(256), st, m, b, views_dev, nviews, cnt, flat,
-                     nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, val_out, tile_out, depth_out, zkey);
     else if (nrec <= TILE_WIDE_RECORDS)
         TIGAS_LAUNCH((k_tile_emit<false, 8>), dim3(gx, groups), dim3(512), st, m, b, views_dev, nviews, cnt, flat,
-                     nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, val_out, tile_out, depth_out, zkey);
     else
         TIGAS_LAUNCH((k_tile_emit<false, 4>), dim3(gx, groups), dim3(256), st, m, b, views_dev, nviews, cnt, flat,
-                     nfront, nchunks, ranges, order, host_cnt, rec, packed, cells, val_out, tile_out, depth_out, zkey);
+                     nfront, nchunks, ranges, order, host_cnt, rec, packed, val_out, tile_out, depth_out, zkey);
 }
 
 // Up to these numbers of blocks a wave takes a quarter or a half of one.  The
@@ -3583,7 +3593,7 @@ void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_
 constexpr uint64_t BLEND_QUARTERS = 1800, BLEND_HALVES = 3200;
 
 void launch_blend(const ViewParams* views_dev, const ViewParams* views_host, int nviews, uint32_t n_lists,
-                  const uint2* ranges, const uint32_t* vals, const PreOut& o, uint32_t nrec, bool cells,
+                  const uint2* ranges, const uint32_t* vals, const PreOut& o, uint32_t nrec,
                   unsigned long long* work, bool cull, const uint32_t* order, hipStream_t st) {
     if (n_lists == 0) return;
     int bl = 0;  // log2 of a list's blocks
@@ -3593,7 +3603,7 @@ void launch_blend(const ViewParams* views_dev, const ViewParams* views_host, int
         bl = std::max(bl, v.tw_log + v.lx + v.th_log + v.ly - 6);
         blocks += (uint64_t)((v.width + 7) / 8) * (uint64_t)((v.height + 7) / 8);
     }
-    BlendArgs A{views_dev, nviews, n_lists, 0, bl, ranges, vals, cells ? 1 : 0, o.rec, nrec, work, cull ? 1 : 0,
+    BlendArgs A{views_dev, nviews, n_lists, 0, bl, ranges, vals, o.rec, nrec, work, cull ? 1 : 0,
                 order};
     const int pl = work || blocks > BLEND_HALVES ? 0 : blocks > BLEND_QUARTERS ? 1 : 2;
     // a launch has fewer than 2^32 threads: 2^26 blocks' waves, past which a batch of

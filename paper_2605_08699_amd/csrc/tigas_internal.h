@@ -42,16 +42,19 @@ constexpr int BUCKET_SORT_CAP = 4096;
 // 40 depths (3.2 shares of 1172 each, which a workgroup sorts fast) 124 and 147.
 constexpr uint32_t CROWD_SHARES = 4, SPLIT_SHARES = 2;
 constexpr int COL_CHUNK = 32;  // columns per workgroup of a column scan
-// A list is divided into at most 4 x 4 cells of whole 8x8 blocks: log2 of a
-// cell's side for that of the list's.  An entry's word holds the cells that its
-// pixel box meets, as a mask of columns and one of rows, above the record's
-// number in its view (in CELL_REC_BITS bits), so a block of the blend tells
-// from the word whether to fetch the record.
-constexpr int CELL_REC_BITS = 24;
-constexpr __host__ __device__ int cell_log(int list_log) { return list_log < 5 ? 3 : list_log - 2; }
+// A list is divided into at most 2^cells x 2^cells cells of whole 8x8 blocks (cells 2
+// or 1; 0: none): log2 of a cell's side for that of the list's.  An entry's word
+// holds the cells that its pixel box meets, as a mask of columns and one of rows,
+// above the record's number in its view (in cell_rec_bits bits, 24 or 28), so a
+// block of the blend tells from the word whether to fetch the record.
+constexpr __host__ __device__ int cell_rec_bits(int cells) { return 32 - 4 * cells; }
+constexpr __host__ __device__ int cell_log(int list_log, int cells) {
+    return list_log - cells < 3 ? 3 : list_log - cells;
+}
 // Tile placement: cells of the tile grid per workgroup, the units of the depth
 // order per view and at most in all, their smallest cost, a Gaussian's cost
 // besides its entries, tiles per workgroup of the ranges.
+constexpr int COUNT_LISTS_MAX = 8192;  // lists of a view that are placed by counting although no tiles share them
 constexpr int TILE_CELLS = 1024;
 constexpr int TILE_UNITS = 1536;
 constexpr int TILE_UNITS_MAX = 49152;
@@ -90,7 +93,7 @@ struct ViewParams {
     // and tile_base number the lists.  Where the lists are built, a list is what
     // is called a tile.
     int tw_log, th_log, lx, ly, tiles_x, tiles_y;
-    int cells;           // the records' list rectangles carry their end cells
+    int cells;           // log2 of a list's cells a side; the records' list rectangles carry their end cells
     uint32_t tile_base;
     int sh_degree;
     int fmt;             // 0 RGB8, 1 RGBF32
@@ -252,7 +255,7 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
                              int tile_w, int tile_h, uint32_t* tile_out, uint32_t* val_out, uint32_t* depth_out,
                              hipStream_t st);
 // Bucketed depth sort of every view's visible records: val / ext receive the
-// record ids (with cells, the record's number in its view and its rectangle's
+// record ids (in a view with cells, the record's number in it and its rectangle's
 // end cells) and packed list rectangles view by view in depth order, equal
 // depths in record order (views of at most 256 x 256 tiles).  The same
 // launches set the frame's counters, clear zl and recompute, in FP64, the
@@ -267,7 +270,7 @@ void launch_duplicate_culled(const PreOut& o, int nblk, const uint32_t* sorted_r
 void launch_bucket_sort(const PreOut& o, const BucketMem& b, const ViewParams* views_dev, int nviews, uint32_t nseg,
                         uint32_t nchunks, uint32_t seg_len, Counters* cnt, uint32_t cap, const ZeroList& zl,
                         bool flag_wide, bool flag_crowd, uint32_t split, uint32_t nunits, uint32_t* val, uint32_t* ext,
-                        bool cells, hipStream_t st);
+                        hipStream_t st);
 // Runs LSD passes over the count selected by `which` (0 duplicates, 1 visible)
 // starting in buffer `start`; returns the buffer index holding the result.
 // With `rect_src`, the last pass also writes rect_src[value] to rect_dst in
@@ -284,8 +287,8 @@ void launch_ranges(const uint32_t* tile_sorted, const Counters* cnt, uint32_t ca
 void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, hipStream_t st);
 // Tile placement by counting (packed rectangles): from the depth-ordered
 // records and packed rectangles, writes each (Gaussian, tile) entry's record
-// id to its sorted position in val_out (with cells, the record's number in its
-// view and the cells of the list that the entry covers; with
+// id to its sorted position in val_out (in a view with cells, the record's number
+// in it and the cells of the list that the entry covers; with
 // tile_out/depth_out, also its tile
 // id and depth word), the tile ranges and the counters to host_cnt.  The
 // depth order is the bucketed one (view by view, b filled in by
@@ -294,7 +297,7 @@ void launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* order, h
 // receives the blend's dense-first dispatch order (a single view).
 void launch_tiles(const TileMem& m, const BucketMem& b, const ViewParams* views_dev, const ViewParams* views_host,
                   int nviews, uint32_t nrec, const Counters* cnt, bool flat, uint32_t nchunks, const uint32_t* rec,
-                  const uint32_t* packed, bool cells, uint2* ranges, uint32_t* order,
+                  const uint32_t* packed, uint2* ranges, uint32_t* order,
                   FrameCounters* host_cnt, uint32_t* val_out, uint32_t* tile_out, uint32_t* depth_out,
                   const uint32_t* zkey, hipStream_t st);
 // Baseline JPEGs of RGB8 frames: one workgroup per restart interval of
@@ -352,7 +355,7 @@ void launch_jpeg(const JpegBatch& a, uint32_t nseg, hipStream_t st);
 // cull: drop the entries whose exponent stays below the skip threshold on a
 // block's whole pixel block (they would be skipped at every pixel anyway).
 void launch_blend(const ViewParams* views_dev, const ViewParams* views_host, int nviews, uint32_t n_lists,
-                  const uint2* ranges, const uint32_t* vals, const PreOut& o, uint32_t nrec, bool cells,
+                  const uint2* ranges, const uint32_t* vals, const PreOut& o, uint32_t nrec,
                   unsigned long long* work, bool cull, const uint32_t* order, hipStream_t st);
 void launch_wave_scan_selftest(const uint32_t* in, uint32_t* out, int n, hipStream_t st);
 

@@ -226,3 +226,40 @@ def test_views_of_more_records_than_a_list_word_numbers(ctx):
         s.free()
     _say("ms a frame", ms)
     assert ms[n] < 2 * ms[1 << 24]
+
+
+@pytest.mark.parametrize("size,tile", [((1280, 720), (8, 8)), ((1301, 733), (16, 16)), ((1920, 1080), (32, 16)),
+                                       ((640, 400), (16, 32))])
+def test_coarse_cells_of_large_views(ctx, size, tile):
+    """2^24 records and more, most of them behind the camera, with Gaussians of
+    many tiles among those in view: the frame of the radix passes with every tile
+    shape."""
+    n = (1 << 24) + 512
+    rng = np.random.default_rng(25)
+    z = np.full(n, -1.0, np.float32)
+    seen = rng.permutation(n)[:20_000]
+    seen[:2] = 0, n - 1
+    z[seen] = rng.uniform(2.0, 30.0, 20_000).astype(np.float32)
+    means = np.column_stack([rng.uniform(-1.0, 1.0, n).astype(np.float32) * z,
+                             rng.uniform(-0.6, 0.6, n).astype(np.float32) * z, z])
+    ls = np.repeat(np.log(0.01 * np.abs(z))[:, None], 3, axis=1)
+    ls[seen[:200]] += 3.0
+    sh = np.zeros((n, 16, 3), np.float32)
+    sh[:, 0] = rng.uniform(-1.0, 1.0, (n, 3)).astype(np.float32)
+    s = ctx.load_scene(synth.Scene(means, ls, np.tile(np.array([1, 0, 0, 0], np.float32), (n, 1)),
+                                   rng.normal(0.0, 1.0, n).astype(np.float32), sh, 0))
+    W, H = size
+    k = synth.Intrinsics(W / 2.0, W / 2.0, W / 2, H / 2)
+    pose = synth.Pose(np.eye(3, dtype=np.float32), np.zeros(3, np.float32))
+    got = ctx.render(s, pose, k, W, H, fmt="f32", tile=tile)
+    st = ctx.stats()
+    ctx.set_tile_binning(False)
+    ctx.set_depth_passes(4)
+    try:
+        want = ctx.render(s, pose, k, W, H, fmt="f32", tile=tile)
+        assert ctx.stats()["duplicates"] == st["duplicates"] > st["visible"] > 10_000
+    finally:
+        ctx.set_tile_binning(True)
+        ctx.set_depth_passes(3)
+    np.testing.assert_array_equal(got, want)
+    s.free()
