@@ -1467,19 +1467,20 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_count(PreOut o, Bu
     // the segment's visible records
     lo = 0xffffffffu;
     hi = 0u;
-    for (uint32_t i0 = r0; i0 < r1; i0 += NT * RPT) {
-        if (i0 != r0) load(i0);
+    auto count = [&](auto&& bucket) {
+        for (uint32_t i0 = r0; i0 < r1; i0 += NT * RPT) {
+            if (i0 != r0) load(i0);
 #pragma unroll
-        for (int k = 0; k < RPT; ++k)
-            if (vis[k]) {
-                const uint32_t b = SPLIT && m.shift == KEYMAP_SPLIT
-                                       ? split_bucket(key[k], i0 + (uint32_t)(k * NT + t), split)
-                                       : key_bucket(key[k], cdf, m, nbkt);
-                atomicAdd(&hist[b], 1u);
-                lo = min(lo, key[k]);
-                hi = max(hi, key[k]);
-            }
-    }
+            for (int k = 0; k < RPT; ++k)
+                if (vis[k]) {
+                    atomicAdd(&hist[bucket(key[k], i0 + (uint32_t)(k * NT + t))], 1u);
+                    lo = min(lo, key[k]);
+                    hi = max(hi, key[k]);
+                }
+        }
+    };
+    if (SPLIT && m.shift == KEYMAP_SPLIT) count([&](uint32_t k, uint32_t i) { return split_bucket(k, i, split); });
+    else count([&](uint32_t k, uint32_t) { return key_bucket(k, cdf, m, nbkt); });
     lo = wave_min(lo);
     hi = wave_max(hi);
     __syncthreads();
@@ -1729,19 +1730,22 @@ __global__ __launch_bounds__(BUCKET_THREADS, 8) void k_bucket_scatter(PreOut o, 
     const uint32_t* row = b.rows + v.row_base + (size_t)seg * nbkt;
     for (uint32_t i = t; i < nbkt; i += NT) next[i] = cpre[i / COL_CHUNK] + b.start_in[v.bkt_base + i] + row[i];
     __syncthreads();
-    for (uint32_t i0 = r0; i0 < r1; i0 += NT * RPT) {
-        if (i0 != r0) load(i0);
+    auto scatter = [&](auto&& bucket) {
+        for (uint32_t i0 = r0; i0 < r1; i0 += NT * RPT) {
+            if (i0 != r0) load(i0);
 #pragma unroll
-        for (int k = 0; k < RPT; ++k)
-            if (vis[k]) {
-                const uint32_t i = i0 + (uint32_t)(k * NT + t);
-                const uint32_t bk = SPLIT && m.shift == KEYMAP_SPLIT
-                                        ? split_bucket(key[k], i, reinterpret_cast<const uint64_t*>(cdf))
-                                        : key_bucket(key[k], cdf, m, nbkt);
-                const uint32_t pos = atomicAdd(&next[bk], 1u);
-                b.elem[pos] = make_uint4(key[k], i, pack_rect(rect[k]), rect_cells(rect[k], cells));
-            }
-    }
+            for (int k = 0; k < RPT; ++k)
+                if (vis[k]) {
+                    const uint32_t i = i0 + (uint32_t)(k * NT + t);
+                    const uint32_t pos = atomicAdd(&next[bucket(key[k], i)], 1u);
+                    b.elem[pos] = make_uint4(key[k], i, pack_rect(rect[k]), rect_cells(rect[k], cells));
+                }
+        }
+    };
+    if (SPLIT && m.shift == KEYMAP_SPLIT)
+        scatter([&](uint32_t k, uint32_t i) { return split_bucket(k, i, reinterpret_cast<const uint64_t*>(cdf)); });
+    else
+        scatter([&](uint32_t k, uint32_t) { return key_bucket(k, cdf, m, nbkt); });
 }
 
 // One bucket sorted by (depth key, record).  Its elements are counted into
