@@ -338,6 +338,49 @@ def test_a_frame_that_needs_another_depth_order_changes_only_its_own_scene():
         c.close()
 
 
+def test_switches_flipped_by_another_thread_change_no_frame():
+    """The depth order, the placement and the culling switched by one thread
+    while another renders single views and batches, crowded, deep and plain:
+    every frame is the one of fixed switches."""
+    import threading
+    W, H = 700, 500
+    k = intr(500.0, W / 2, H / 2)
+    rng = np.random.default_rng(12)
+    z = np.exp(rng.uniform(math.log(0.5), math.log(2e7), 600))
+    deep = make_scene(np.column_stack([rng.uniform(-0.3, 0.3, 600) * z, rng.uniform(-0.2, 0.2, 600) * z, z]),
+                      np.repeat(np.log(0.02 * z)[:, None], 3, axis=1), None, rng.normal(1.0, 1.0, 600),
+                      rng.uniform(0.0, 1.0, (600, 3)))
+    c = tigas.Context(0)
+    try:
+        ss = [c.load_scene(x) for x in (_depth_scene("spread", 6000), _depth_scene("equal", 20_000), deep)]
+        want = [c.render(s, eye_pose(), k, W, H, fmt="f32", tile=(16, 16)) for s in ss]
+        stop = threading.Event()
+
+        def flip():
+            i = 0
+            while not stop.is_set():
+                c.set_depth_passes(3 + i % 2)
+                c.set_tile_binning(i % 3 != 0)
+                c.set_tile_culling(i % 5 == 0)
+                i += 1
+
+        t = threading.Thread(target=flip)
+        t.start()
+        try:
+            for i in range(150):
+                if i % 3 == 2:
+                    got = c.render_batch(ss, [eye_pose()] * 3, [k] * 3, [W] * 3, [H] * 3, fmt="f32", tile=(16, 16))
+                else:
+                    got = [c.render(s, eye_pose(), k, W, H, fmt="f32", tile=(16, 16)) for s in ss]
+                for j in range(3):
+                    np.testing.assert_array_equal(got[j], want[j], err_msg=f"pass {i}, scene {j}")
+        finally:
+            stop.set()
+            t.join()
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("n,views", [(2_100_000, 1), (180_000, 48)])
 def test_crowded_depths_of_large_plans(n, views):
     """Crowded depths in a view of 2048 buckets, of whose samples every second is
